@@ -779,9 +779,11 @@ __device__ __attribute__((always_inline)) inline void solve_x_fwd_body(const Sol
   for (int q = 0; q < kMaxRhs; ++q) {
     if (q < nrhs) {
       const T v = lane_group_sum<RB::LPR>(lin.dot(sm.rhs[q]));
-      if (RB::base() == 0 && RB::out_index() < n) {
-        yx[q * n + RB::out_index()] = v;
-        sm.vbuf[0][q][RB::out_index()] = v;
+      if (RB::base() == 0) {
+        // the padding too: the products below run over all NMAX entries, and LDS that no
+        // pull has written (N = 1) may hold anything
+        sm.vbuf[0][q][RB::out_index()] = RB::out_index() < n ? v : T(0);
+        if (RB::out_index() < n) yx[q * n + RB::out_index()] = v;
       }
     }
   }
