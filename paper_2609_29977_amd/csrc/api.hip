@@ -328,7 +328,6 @@ ResidualArgs residual_args(bmpc_plan p, int c, const double* D, const double* E,
   ra.n = p->d.n;
   ra.nrhs = chunk_rhs(p, c);
   ra.vsys = (size_t)p->d.nrhs * vec_len(p);
-  ra.chunk = 16;
   ra.D = D;
   ra.E = E;
   ra.C = C;
@@ -338,9 +337,13 @@ ResidualArgs residual_args(bmpc_plan p, int c, const double* D, const double* E,
   ra.r = r + off;
   ra.w = p->w;
   ra.done = p->flags;
+  ra.kper = p->kper;
+  ra.rpart = p->rpart;
+  ra.rnorm = p->rnorm + c * p->chunk;
+  ra.seg_sys = p->d.nrhs;
   if (knorm) {
     ra.knorm_part = p->kpart;
-    ra.knorm_root = p->kroot;
+    ra.knorm_root = p->knorm;
     ra.crow = p->crow;
   }
   return ra;
@@ -464,7 +467,8 @@ bmpc_status last_error_status() {
   return hipGetLastError() == hipSuccess ? BMPC_OK : BMPC_ERR_DEVICE;
 }
 
-// Whether the refinement's stop test already holds, read on the host.  Outside stream
+// Whether the refinement's last stop test held, read on the host from the pinned flag that
+// the test writes (no copy behind it).  Outside stream
 // capture the loop stops issuing launches once it holds (the device-side flag would
 // make them return at once, but each still costs a launch); under capture the launch
 // sequence stays fixed and the flag alone decides.
@@ -475,13 +479,11 @@ bool stop_reached(bmpc_plan p) {
     return false;
   }
   if (cs != hipStreamCaptureStatusNone) return false;
-  if (hipMemcpyAsync(p->hflag, p->flags, sizeof(int), hipMemcpyDeviceToHost, p->stream) !=
-          hipSuccess ||
-      hipStreamSynchronize(p->stream) != hipSuccess) {
+  if (hipStreamSynchronize(p->stream) != hipSuccess) {
     (void)hipGetLastError();
     return false;
   }
-  return p->hflag[0] != 0;
+  return *static_cast<volatile int*>(p->hflag) != 0;
 }
 
 // Analysis and workspaces of a plan (bmpc_analyze_ex after its argument checks).  A
@@ -510,8 +512,7 @@ bmpc_status init_plan(bmpc_plan p, const bmpc_dims* dims, bmpc_precision prec, v
   const size_t nn = (size_t)n * n, tb = p->fp64 ? 8 : 4;
   const size_t len = ((size_t)dims->S * N + 1) * n;
   const size_t segs = (size_t)B * nrhs;  // (system, right-hand side) vectors
-  const int res_chunks = (N + 15) / 16;   // tail residual workgroups per chain
-  p->kper = dims->S * res_chunks;
+  p->kper = dims->S * residual_walks(N, n);  // tail residual workgroups per system
   const int npass = (int)p->costs.passes.size();
   p->stride = (npass > 1 ? p->costs.passes[0].windows : 1) + 1;
   const size_t gblocks = g_chain_blocks(N);
@@ -530,14 +531,14 @@ bmpc_status init_plan(bmpc_plan p, const bmpc_dims* dims, bmpc_precision prec, v
             dalloc(p, (void**)&p->w, S * cq * n * 8) &&
             dalloc(p, (void**)&p->x0, (size_t)B * cq * n * 8) &&
             (p->parent || dalloc(p, (void**)&p->rbuf, segs * len * 8)) &&
-            dalloc(p, (void**)&p->norms, 3 * segs * 8) &&
-            dalloc(p, (void**)&p->npart, 2 * segs * kNormBlocks * 8) &&
+            (p->parent || dalloc(p, (void**)&p->rnorm, segs * 8)) &&
+            dalloc(p, (void**)&p->rpart, (size_t)B * p->kper * cq * 8) &&
+            (p->parent || dalloc(p, (void**)&p->npart, 2 * segs * kNormBlocks * 8)) &&
             (p->parent || dalloc(p, (void**)&p->flags, 2 * sizeof(int))) &&
             dalloc(p, (void**)&p->relcorr, sizeof(double)) &&
             dalloc(p, (void**)&p->bnorm, segs * 8) &&
-            dalloc(p, (void**)&p->knorm, (size_t)B * 8) &&
-            dalloc(p, (void**)&p->kpart, S * res_chunks * 8) &&
-            dalloc(p, (void**)&p->kroot, (size_t)B * 8) &&
+            (p->parent || dalloc(p, (void**)&p->knorm, (size_t)B * 8)) &&
+            dalloc(p, (void**)&p->kpart, (size_t)B * p->kper * 8) &&
             dalloc(p, (void**)&p->crow, S * n * 8);
   if (ok && !p->parent && !p->measure &&
       hipHostMalloc((void**)&p->hflag, 2 * sizeof(int), hipHostMallocDefault) != hipSuccess) {
@@ -709,9 +710,7 @@ static bmpc_status refine_impl(bmpc_plan p, const double* D, const double* E, co
   const int segs = p->B * nrhs;  // norms per (system, right-hand side)
   const size_t len = vec_len(p);
   const bool be = p->refine_stop == BMPC_STOP_BACKWARD_ERROR;
-  double* rnorm = p->norms;
-  double* dnorm = p->norms + segs;
-  double* xnorm = p->norms + 2 * segs;
+  double* rnorm = p->rnorm;
   timed(p, KC_REFINE_MISC, [&] { launch_refine_reset(p->flags, st); });
   if (fused) {
     if (p->fp64)
@@ -727,7 +726,7 @@ static bmpc_status refine_impl(bmpc_plan p, const double* D, const double* E, co
       enqueue_solve<float>(p, b, x);
   }
   if (be && max_iters >= 0)
-    timed(p, KC_REFINE_MISC, [&] { launch_maxabs(b, segs, len, p->npart, p->bnorm, nullptr, st); });
+    timed(p, KC_REFINE_MISC, [&] { launch_maxabs(b, segs, len, p->npart, p->bnorm, st); });
   // r = b - K x for every chunk; the first residual of a backward-error loop also takes
   // the row sums of |K|
   auto residual = [&](bool knorm) {
@@ -756,25 +755,20 @@ static bmpc_status refine_impl(bmpc_plan p, const double* D, const double* E, co
     if (be) {
       // stop before the correction when x is already backward stable
       timed(p, KC_REFINE_MISC, [&] {
-        launch_refine_be_check(p->rbuf, x, p->B, nrhs, len, p->npart, it == 0 ? p->kpart : nullptr,
-                               p->kper, p->kroot, p->knorm, p->bnorm, tol, 1, p->flags,
-                               p->relcorr, rnorm, st);
+        launch_refine_be_check(x, p->B, nrhs, len, p->npart, rnorm, p->knorm, p->bnorm, tol, 1,
+                               p->flags, p->hflag, p->relcorr, st);
       });
       // The first solve of an FP32 plan cannot meet a tolerance far below FP32's
       // rounding, so the host does not wait for that check (the device still applies it:
       // the later launches of a converged loop return at once).
       const bool hopeless = it == 0 && !p->fp64 && tol < 0x1p-30;
       if (!hopeless && (stopped = stop_reached(p))) break;
-    } else {
-      timed(p, KC_REFINE_MISC, [&] {
-        launch_maxabs(p->rbuf, segs, len, p->npart, rnorm, p->flags, st);
-      });
     }
     correction();
     if (!be) {
       timed(p, KC_REFINE_MISC, [&] {
-        launch_refine_check(p->rbuf, x, segs, len, p->npart, tol, p->flags, p->relcorr, dnorm,
-                            xnorm, st);
+        launch_refine_check(p->rbuf, x, segs, len, p->npart, tol, p->flags, p->hflag, p->relcorr,
+                            st);
       });
       if (it + 1 < max_iters && (stopped = stop_reached(p))) break;
     }
@@ -783,9 +777,8 @@ static bmpc_status refine_impl(bmpc_plan p, const double* D, const double* E, co
     // the returned x is certified by its own residual
     residual(max_iters == 0);
     timed(p, KC_REFINE_MISC, [&] {
-      launch_refine_be_check(p->rbuf, x, p->B, nrhs, len, p->npart,
-                             max_iters == 0 ? p->kpart : nullptr, p->kper, p->kroot, p->knorm,
-                             p->bnorm, tol, 0, p->flags, p->relcorr, rnorm, st);
+      launch_refine_be_check(x, p->B, nrhs, len, p->npart, rnorm, p->knorm, p->bnorm, tol, 0,
+                             p->flags, p->hflag, p->relcorr, st);
     });
   }
   p->last_max_iters = be ? std::max(max_iters, 1) : max_iters;

@@ -140,7 +140,6 @@ struct ResidualArgs {
   int S, N, n, nrhs;     // S = scenarios per system, nrhs of this chunk
   int B;                 // systems in the batch
   size_t vsys;           // vector elements per system (all right-hand sides)
-  int chunk;             // stages per work item of the tail residual
   const double* D;
   const double* E;
   const double* C;
@@ -150,9 +149,13 @@ struct ResidualArgs {
   double* r;             // [B][nrhs][len]
   double* w;             // [S][nrhs][n] products C_s x_{s,0}
   const int* done;
+  int kper;              // tail workgroups per system
+  double* rpart;         // [B * kper][nrhs] largest |r| of each tail workgroup
+  double* rnorm;         // largest |r| of system sys, right-hand side q: [sys * seg_sys + q]
+  int seg_sys;
   // Row sums of |K| (backward-error stop): per workgroup of the tail residual the
-  // maximum over its rows (knorm_part[blockIdx]), per system the maximum over the
-  // root rows (knorm_root[sys]) and the per-chain |C_s| row sums (crow [B*S][n]).
+  // maximum over its rows (knorm_part), the per-chain |C_s| row sums (crow
+  // [B*S][n]), and from these and the root rows |K| of each system (knorm_root[sys]).
   // Null: not computed.
   double* knorm_part;
   double* knorm_root;
@@ -212,32 +215,33 @@ void launch_solve64_level(const SolveArgs& a, int level, bool fwd, hipStream_t s
 template <typename T>
 void launch_solve64_x(const SolveArgs& a, bool fwd, hipStream_t st);
 
+// Workgroups of the tail residual per chain of N stages with blocks of n.
+int residual_walks(int N, int n);
 void launch_residual(const ResidualArgs& a, int nmax, hipStream_t st);
 void launch_grad_blocks(const GradArgs& a, hipStream_t st);
 void launch_residual_root(const ResidualArgs& a, hipStream_t st);
 void launch_refine_reset(int* flags, hipStream_t st);
-// Infinity norms by a two-stage maximum (kNormBlocks block partials, then one wave),
-// deterministic and NaN-propagating; skipped when *done is set.
+// Infinity norms by a two-stage maximum (at most kNormBlocks block partials per vector,
+// then one wave), deterministic and NaN-propagating.
 constexpr int kNormBlocks = 1024;
-// out[q] = max_i |v[q][i]|, through partial[nrhs][kNormBlocks]
-void launch_maxabs(const double* v, int nrhs, size_t len, double* partial, double* out,
-                   const int* done, hipStream_t st);
-// dnorm[q] = |d_q|_inf, xnorm[q] = |x_q|_inf (partials in partial[2][nrhs][kNormBlocks]),
-// then the stop test: flags[0] = 1 if dnorm <= tol * xnorm for every q; flags[1] counts
-// the corrections; relcorr = max_q dnorm / xnorm.
-void launch_refine_check(const double* d, const double* x, int nrhs, size_t len,
-                         double* partial, double tol, int* flags, double* relcorr,
-                         double* dnorm, double* xnorm, hipStream_t st);
+// out[k] = max_i |v[k][i]| of segs vectors, through partial[segs][kNormBlocks]
+void launch_maxabs(const double* v, int segs, size_t len, double* partial, double* out,
+                   hipStream_t st);
+// The stop test |d_k|_inf <= tol |x_k|_inf for every segment k (partials in
+// partial[2][segs][kNormBlocks]): flags[0] = 1 if it holds, flags[1] counts the
+// corrections, *hflag (pinned host memory) = whether it holds; relcorr = max_k |d_k| /
+// |x_k|.  Skipped when flags[0] is set.
+void launch_refine_check(const double* d, const double* x, int segs, size_t len,
+                         double* partial, double tol, int* flags, int* hflag, double* relcorr,
+                         hipStream_t st);
 
 // Backward-error stop test after a residual r = b - K x of B systems with nrhs
-// right-hand sides each (see refine_be_check_kernel): |r| and |x| by block partials,
-// |K| per system reduced from the residual's row-sum partials when kpart is not null
-// (kper partials per system), |b| from bnorm.  Sets flags[0] when every normwise
-// backward error is <= tol, else counts a correction (flags[1]) if count; |r| into rnorm.
-void launch_refine_be_check(const double* r, const double* x, int B, int nrhs, size_t len,
-                            double* partial, const double* kpart, int kper,
-                            const double* kroot, double* knorm, const double* bnorm,
-                            double tol, int count, int* flags, double* relcorr, double* rnorm,
+// right-hand sides each (see refine_be_check_kernel): |r| (rnorm) and |K| (knorm, per
+// system) from the residual, |x| by block partials, |b| from bnorm.  Sets flags[0] when
+// every normwise backward error is <= tol, else counts a correction (flags[1]) if count.
+void launch_refine_be_check(const double* x, int B, int nrhs, size_t len, double* partial,
+                            const double* rnorm, const double* knorm, const double* bnorm,
+                            double tol, int count, int* flags, int* hflag, double* relcorr,
                             hipStream_t st);
 
 // number of chain positions eliminated at level l (1-based) of a chain of length m

@@ -91,8 +91,10 @@ struct RootArgs {
   unsigned long long sys_rows, root_row;
 };
 
-// One (system, right-hand side) vector of a ragged batch: its element offset in the
-// concatenated vectors and its length.
+// A slice of a (system, right-hand side) vector of a ragged batch: its element offset in
+// the concatenated vectors and its length (at most kNormSlice: 32 elements per thread of
+// a workgroup, thousands of slices on a batch that fills the GPU).
+constexpr size_t kNormSlice = 8192;
 struct SegRec {
   size_t off;
   size_t len;
@@ -155,20 +157,20 @@ void launch_residual_multi(int nmax, bool full, const MultiItem<ResidualArgs>* i
 void launch_residual_root_multi(const MultiItem<ResidualArgs>* items, int nitems,
                                 unsigned blocks, const Reloc& r, hipStream_t st);
 
-// Ragged refinement bookkeeping over the (system, right-hand side) segments.
-// out[k] = max |v[seg k]| (and out2[k] = max |v2[seg k]| if v2), one workgroup per
-// segment; skipped when *done is set (done may be null).
-void launch_seg_maxabs(const double* v, const double* v2, const SegRec* segs, int nseg,
-                       double* out, double* out2, const int* done, hipStream_t st);
-// Stop tests of a ragged batch (flags[0] = done, flags[1] = corrections, relcorr = the
-// largest test quantity), after launch_seg_maxabs:
-//   correction size: dn[k] <= tol * xn[k] for every segment;
-//   backward error: rn[k] <= tol * (knorm[sys(k)] * xn[k] + bn[k]), knorm[sys] reduced
-//   here from kpart[kp_off[sys] .. kp_off[sys + 1]) and kroot[sys] when kpart is set.
-void launch_ragged_check(int mode, const double* dn_or_rn, const double* xn, const double* bn,
-                         const int* seg_sys, int nseg, int B, const double* kpart,
-                         const int* kp_off, const double* kroot, double* knorm, double tol,
-                         int count, int* flags, double* relcorr, int* sys_ok,
-                         double* sys_worst, hipStream_t st);
+// Ragged refinement bookkeeping: part[i] = max |v| over slice i (and part[nslice + i] of
+// v2, if set); skipped when *done is set (done may be null).
+void launch_seg_maxabs(const double* v, const double* v2, const SegRec* slices, int nslice,
+                       double* part, const int* done, hipStream_t st);
+// out[k] = max over the slices slice0[k] .. slice0[k + 1] - 1 of segment k
+void launch_seg_final(const double* part, const int* slice0, int nseg, double* out,
+                      hipStream_t st);
+// Stop tests of a ragged batch (flags[0] = done, flags[1] = corrections, *hflag the
+// host's copy of flags[0], relcorr = the largest test quantity), after launch_seg_maxabs:
+//   mode 0, correction size (part of d and x): |d_k| <= tol * |x_k| for every segment;
+//   mode 1, backward error (part of x): rnorm[k] <= tol * (knorm[sys(k)] * |x_k| + bnorm[k]).
+void launch_ragged_check(int mode, const double* part, const int* slice0, int nslice, int B,
+                         int nrhs, const double* rnorm, const double* knorm,
+                         const double* bnorm, double tol, int count, int* flags, int* hflag,
+                         double* relcorr, int* sys_ok, double* sys_worst, hipStream_t st);
 
 }  // namespace bmpc

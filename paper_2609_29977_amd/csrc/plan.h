@@ -70,19 +70,19 @@ struct bmpc_plan_s {
   double* w = nullptr;
   double* x0 = nullptr;
   double* rbuf = nullptr;
-  double* norms = nullptr;  // rnorm, dnorm, xnorm: 3 * nrhs
+  double* rnorm = nullptr;  // |r| per segment
+  double* rpart = nullptr;  // largest |r| of each tail residual workgroup
   double* npart = nullptr;  // partial maxima: 2 * nrhs * kNormBlocks
   int* flags = nullptr;     // done, iterations
   double* relcorr = nullptr;
   // backward-error stop: |b| per segment, |K| per system, the residual's row-sum
-  // partials (per tail workgroup), root-row maxima and per-chain |C_s| row sums
+  // partials (per tail workgroup) and per-chain |C_s| row sums
   double* bnorm = nullptr;
   double* knorm = nullptr;
   double* kpart = nullptr;
-  double* kroot = nullptr;
   double* crow = nullptr;
   int kper = 0;  // residual workgroups per system
-  int* hflag = nullptr;  // pinned host copy of the refinement's stop flag
+  int* hflag = nullptr;  // the refinement's stop flag in pinned memory, written by the test
   // Workspace placement: measure (only add up the sizes), or carve from an arena owned
   // by a ragged parent; otherwise each buffer is its own allocation.
   bool measure = false;

@@ -57,12 +57,11 @@ struct RaggedState {
   std::vector<Seq> resid[2];   // per chunk [with the row sums of |K|]
   unsigned long long* info = nullptr;  // per system
   double* rbuf = nullptr;      // residual / correction vectors, the callers' vector layout
-  int nseg = 0;
-  SegRec* segs = nullptr;
-  int* seg_sys = nullptr;
-  int* kp_off = nullptr;
-  double *rnorm = nullptr, *dnorm = nullptr, *xnorm = nullptr, *bnorm = nullptr;
-  double *knorm = nullptr, *kpart = nullptr, *kroot = nullptr, *worst = nullptr;
+  int nseg = 0, nslice = 0;
+  SegRec* slices = nullptr;    // the segments (system, right-hand side) cut into slices
+  int* slice0 = nullptr;       // first slice of each segment (nseg + 1)
+  double *rnorm = nullptr, *bnorm = nullptr, *npart = nullptr;
+  double *knorm = nullptr, *worst = nullptr;
   int* ok = nullptr;
   std::vector<void*> allocs;
 };
@@ -103,8 +102,6 @@ void emit(RaggedState& R, Seq& seq, LaunchRec rec, std::vector<Pending<Args>> it
   rec.blocks = start;
   if (start > 0) seq.push_back(rec);
 }
-
-int nclass(int n) { return n <= 8 ? 8 : (n <= 16 ? 16 : 32); }
 
 const double* fake(size_t el) { return rel_field<const double>(el); }
 double* fake_w(size_t el) { return rel_field<double>(el); }
@@ -347,7 +344,7 @@ void build_residual(bmpc_plan p, Seq& seq, int c, bool knorm) {
                                     fake(R.offR[i]), fake(R.offV[i]), fake(R.offV[i]),
                                     fake_w(R.offV[i]), knorm && c == 0);
     ra.done = p->flags;
-    const int chunks = (s->d.N + ra.chunk - 1) / ra.chunk;
+    const int chunks = residual_walks(s->d.N, s->d.n);
     const auto key = std::make_tuple(s->nmax, s->d.n == s->nmax);
     groups[key].push_back({i, ra, chunks, 0, (unsigned)(s->d.S * chunks), 1u, 1u});
     LaunchRec& rec = recs[key];
@@ -531,41 +528,37 @@ bmpc_status ragged_refine(bmpc_plan p, const double* D, const double* E, const d
         run<float>(p, R.corr[c], rc);
     }
   };
-  auto check = [&](int mode, const double* v1, bool knorm, int count) {
+  auto check = [&](int mode, int count) {
     timed(p, KC_REFINE_MISC, [&] {
-      launch_seg_maxabs(mode == 1 ? R.rbuf : v1, x, R.segs, R.nseg,
-                        mode == 1 ? R.rnorm : R.dnorm, R.xnorm, p->flags, st);
-      launch_ragged_check(mode, mode == 1 ? R.rnorm : R.dnorm, R.xnorm, R.bnorm, R.seg_sys,
-                          R.nseg, B, knorm ? R.kpart : nullptr, R.kp_off, R.kroot, R.knorm, tol,
-                          count, p->flags, p->relcorr, R.ok, R.worst, st);
+      launch_seg_maxabs(mode == 1 ? x : R.rbuf, mode == 1 ? nullptr : x, R.slices, R.nslice,
+                        R.npart, p->flags, st);
+      launch_ragged_check(mode, R.npart, R.slice0, R.nslice, B, R.nrhs, R.rnorm, R.knorm,
+                          R.bnorm, tol, count, p->flags, p->hflag, p->relcorr, R.ok, R.worst, st);
     });
   };
   if (be)
     timed(p, KC_REFINE_MISC, [&] {
-      launch_seg_maxabs(b, nullptr, R.segs, R.nseg, R.bnorm, nullptr, nullptr, st);
+      launch_seg_maxabs(b, nullptr, R.slices, R.nslice, R.npart, nullptr, st);
+      launch_seg_final(R.npart, R.slice0, R.nseg, R.bnorm, st);
     });
   bool stopped = false;
   for (int it = 0; it < max_iters; ++it) {
     residual(be && it == 0);
     if (be) {
-      check(1, nullptr, it == 0, 1);
+      check(1, 1);
       // as in the one-system loop: no host wait on an FP32 first solve's check
       const bool hopeless = it == 0 && !p->fp64 && tol < 0x1p-30;
       if (!hopeless && (stopped = stop_reached(p))) break;
-    } else {
-      timed(p, KC_REFINE_MISC, [&] {
-        launch_seg_maxabs(R.rbuf, nullptr, R.segs, R.nseg, R.rnorm, nullptr, p->flags, st);
-      });
     }
     correction();
     if (!be) {
-      check(0, R.rbuf, false, 2);
+      check(0, 2);
       if (it + 1 < max_iters && (stopped = stop_reached(p))) break;
     }
   }
   if (be && !stopped) {
     residual(max_iters == 0);
-    check(1, nullptr, max_iters == 0, 0);
+    check(1, 0);
   }
   p->last_max_iters = be ? std::max(max_iters, 1) : max_iters;
   return last_error_status();
@@ -648,7 +641,6 @@ bmpc_status bmpc_analyze_ragged(int32_t B, const bmpc_dims* dims, bmpc_precision
   R.offR.assign(B + 1, 0);
   R.offV.assign(B + 1, 0);
   R.rows.assign(B + 1, 0);
-  std::vector<int> kp(B + 1, 0);
   R.chunk = kMaxRhs;
   R.chunks = (R.nrhs + R.chunk - 1) / R.chunk;
   for (int i = 0; i < B; ++i) {
@@ -660,30 +652,28 @@ bmpc_status bmpc_analyze_ragged(int32_t B, const bmpc_dims* dims, bmpc_precision
     R.offR[i + 1] = R.offR[i] + nn;
     R.rows[i + 1] = R.rows[i] + ((size_t)d.S * d.N + 1) * d.n;
     R.offV[i + 1] = R.offV[i] + (size_t)R.nrhs * ((size_t)d.S * d.N + 1) * d.n;
-    kp[i + 1] = kp[i] + R.subs[i]->kper;
   }
   R.nseg = B * R.nrhs;
-  std::vector<SegRec> segs(R.nseg);
-  std::vector<int> seg_sys(R.nseg);
+  std::vector<SegRec> slices;
+  std::vector<int> slice0(1, 0);
   for (int i = 0; i < B; ++i)
     for (int q = 0; q < R.nrhs; ++q) {
-      const size_t len = R.rows[i + 1] - R.rows[i];
-      segs[i * R.nrhs + q] = {R.offV[i] + (size_t)q * len, len};
-      seg_sys[i * R.nrhs + q] = i;
+      const size_t len = R.rows[i + 1] - R.rows[i], off = R.offV[i] + (size_t)q * len;
+      for (size_t o = 0; o < len; o += kNormSlice)
+        slices.push_back({off + o, std::min(kNormSlice, len - o)});
+      slice0.push_back((int)slices.size());
     }
+  R.nslice = (int)slices.size();
   const size_t ns = (size_t)R.nseg;
   bool ok = ralloc(R, (void**)&R.info, (size_t)B * 8) &&
             ralloc(R, (void**)&R.rbuf, R.offV[B] * 8) &&
             ralloc(R, (void**)&p->flags, 2 * sizeof(int)) &&
             ralloc(R, (void**)&p->relcorr, sizeof(double)) &&
-            ralloc(R, (void**)&R.segs, ns * sizeof(SegRec)) &&
-            ralloc(R, (void**)&R.seg_sys, ns * sizeof(int)) &&
-            ralloc(R, (void**)&R.kp_off, (size_t)(B + 1) * sizeof(int)) &&
-            ralloc(R, (void**)&R.rnorm, ns * 8) && ralloc(R, (void**)&R.dnorm, ns * 8) &&
-            ralloc(R, (void**)&R.xnorm, ns * 8) && ralloc(R, (void**)&R.bnorm, ns * 8) &&
+            ralloc(R, (void**)&R.slices, slices.size() * sizeof(SegRec)) &&
+            ralloc(R, (void**)&R.slice0, slice0.size() * sizeof(int)) &&
+            ralloc(R, (void**)&R.rnorm, ns * 8) && ralloc(R, (void**)&R.bnorm, ns * 8) &&
+            ralloc(R, (void**)&R.npart, 2 * slices.size() * 8) &&
             ralloc(R, (void**)&R.knorm, (size_t)B * 8) &&
-            ralloc(R, (void**)&R.kpart, (size_t)kp[B] * 8) &&
-            ralloc(R, (void**)&R.kroot, (size_t)B * 8) &&
             ralloc(R, (void**)&R.worst, (size_t)B * 8) &&
             ralloc(R, (void**)&R.ok, (size_t)B * sizeof(int));
   if (!ok) return fail(BMPC_ERR_ALLOC);
@@ -697,8 +687,8 @@ bmpc_status bmpc_analyze_ragged(int32_t B, const bmpc_dims* dims, bmpc_precision
     s->flags = p->flags;
     s->rbuf = R.rbuf + R.offV[i];
     s->d_info = R.info + i;
-    s->kpart = R.kpart + kp[i];
-    s->kroot = R.kroot + i;
+    s->rnorm = R.rnorm + (size_t)i * R.nrhs;
+    s->knorm = R.knorm + i;
     s->stream = p->stream;
   }
   // item order: largest work (tail blocks x block volume) first
@@ -730,10 +720,9 @@ bmpc_status bmpc_analyze_ragged(int32_t B, const bmpc_dims* dims, bmpc_precision
   }
   if (!ralloc(R, (void**)&R.dtab, R.htab.size())) return fail(BMPC_ERR_ALLOC);
   if (hipMemcpy(R.dtab, R.htab.data(), R.htab.size(), hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(R.segs, segs.data(), ns * sizeof(SegRec), hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(R.seg_sys, seg_sys.data(), ns * sizeof(int), hipMemcpyHostToDevice) !=
-          hipSuccess ||
-      hipMemcpy(R.kp_off, kp.data(), (size_t)(B + 1) * sizeof(int), hipMemcpyHostToDevice) !=
+      hipMemcpy(R.slices, slices.data(), slices.size() * sizeof(SegRec),
+                hipMemcpyHostToDevice) != hipSuccess ||
+      hipMemcpy(R.slice0, slice0.data(), slice0.size() * sizeof(int), hipMemcpyHostToDevice) !=
           hipSuccess) {
     (void)hipGetLastError();
     return fail(BMPC_ERR_DEVICE);

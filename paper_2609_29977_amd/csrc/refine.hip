@@ -4,11 +4,11 @@
 // eq. (root_coupled_matrix) / eq. (tail_block_tridiagonal): row block (s,k) of a
 // tail is D_{s,k} x_{s,k} + E_{s,k-1} x_{s,k-1} + E_{s,k}^T x_{s,k+1} (+ C_s^T x_0
 // for k = 0); the root row block is R x_0 + sum_s C_s x_{s,0}, with the sum over s
-// taken in scenario order.  One wave walks a chunk of consecutive stages of one tail,
-// so each E block is fetched from HBM once and used for both rows it touches; the
-// blocks of the next stage are loaded while the current one is applied.  Infinity
-// norms are maxima taken by a two-stage reduction (per-block partial maxima, then
-// one block), so they are deterministic and need no atomics.
+// taken in scenario order.  Infinity norms are maxima taken by a two-stage reduction
+// (per-block partial maxima, then one block), so they are deterministic and need no
+// atomics.
+#include <algorithm>
+
 #include "bmpc_internal.h"
 #include "multi.h"
 #include "regblock.h"
@@ -17,16 +17,34 @@ namespace bmpc {
 
 namespace {
 
-// One 256-thread workgroup walks a chunk of consecutive stages of one tail.  The
+// Maximum that propagates NaN (so a NaN residual or correction fails the stop test).
+__device__ inline double nan_max(double a, double b) { return (a != a || a > b) ? a : b; }
+
+__device__ inline double wave_max(double v) {
+  for (int off = 32; off > 0; off >>= 1) v = nan_max(v, __shfl_xor(v, off));
+  return v;
+}
+
+// One workgroup walks res_stages consecutive stages of one tail: four waves for blocks of
+// more than 16 rows, one wave for smaller ones, whose stages are too little work for four
+// (a stage of a 16 x 16 block has one entry per thread there, and both barriers of a step
+// are between waves).  The
 // blocks of a stage (the lower triangle of D, all of E) are read with coalesced 8-byte
 // loads into registers two stages ahead, together with the x of the next stage and the
 // b of the stage, then staged in double-buffered LDS, where the symmetric product with
 // D and the product with E^T read them transposed; so each E block leaves HBM once and
 // serves both rows it touches.  Nothing fetched ahead is used before the step that
 // needs it, so the loads of two stages stay in flight while a stage is applied.  Row o
-// of the stage's result is summed by RT = min(256 / NMAX, NMAX) threads, each over
-// NMAX / RT columns (at NMAX = 8 only the first 64 threads have a row).
-constexpr int RES_T = 256;
+// of the stage's result is summed by RT = RES_T / NMAX threads, each over
+// NMAX / RT columns.
+// On 64 systems of 2 K to 65 K stages: n = 8 405 -> 144 us, n = 16 584 -> 471 us
+// (n = 32 keeps four waves); S = 256, N = 128, n = 16, one right-hand side 36 -> 31 us.
+// Eight stages per walk there: four right-hand sides 58 -> 48 us against sixteen.
+constexpr int res_stages(int n) { return n > 16 ? 16 : 8; }
+template <int NMAX>
+constexpr int res_threads() {
+  return NMAX > 16 ? 256 : 64;
+}
 
 // LDS of a residual workgroup: Ds[2][NMAX][NMAX+1] (D of stage k in Ds[k & 1]),
 // Es[2][NMAX][NMAX+1] (E of stage k in Es[k & 1]; C in Es[1] at stage 0), then
@@ -45,6 +63,7 @@ inline size_t residual_lds_bytes(int nrhs) {
 // never holds stale values.
 template <int NMAX, bool FULL>
 struct StageFetch {
+  static constexpr int RES_T = res_threads<NMAX>();
   static constexpr int PER = (NMAX * NMAX + RES_T - 1) / RES_T;
   static constexpr int VPER = (rhs_chunk(NMAX) * NMAX + RES_T - 1) / RES_T;
   double d[PER], e[PER], xv[VPER], bv[VPER];
@@ -108,17 +127,20 @@ struct StageFetch {
   // past k1 (the end of the chunk) fetch nothing from the blocks and clamped vectors.
   __device__ void issue(const ResidualArgs& a, const double* Dc, const double* Ec, size_t xk,
                         size_t len, int k, int k1) {
-    static_assert(VPER == 1, "one vector element per thread");
     const int n = a.n, N = a.N, nrhs = a.nrhs;
     const size_t nn = (size_t)n * n;
     const int kc = min(k, N - 1);
     block<true>(d, Dc + (size_t)kc * nn, n, k < k1);
     block<false>(e, Ec + (size_t)min(kc, N - 2 < 0 ? 0 : N - 2) * nn, n, k < k1 && k + 1 < N);
-    const int idx = threadIdx.x;
-    const int q = min(idx / NMAX, nrhs - 1), i = min(idx % NMAX, n - 1);
-    const size_t base = xk + (size_t)q * len + i;
-    xv[0] = a.x[base + (size_t)min(k + 1, N - 1) * n];
-    bv[0] = a.b[base + (size_t)kc * n];
+#pragma unroll
+    for (int u = 0; u < VPER; ++u) {
+      if (u > 0 && u * RES_T >= nrhs * NMAX) continue;  // uniform
+      const int idx = threadIdx.x + u * RES_T;
+      const int q = min(idx / NMAX, nrhs - 1), i = min(idx % NMAX, n - 1);
+      const size_t base = xk + (size_t)q * len + i;
+      xv[u] = a.x[base + (size_t)min(k + 1, N - 1) * n];
+      bv[u] = a.b[base + (size_t)kc * n];
+    }
   }
   // stage k into D/E slots, x_{k+1} into xslot, b_k into bslot
   __device__ void commit(const ResidualArgs& a, int k, double* Dsl, double* Esl, double* xslot,
@@ -126,11 +148,14 @@ struct StageFetch {
     const int n = a.n, N = a.N, nrhs = a.nrhs;
     put(Dsl, d);
     if (k + 1 < N) put(Esl, e);
-    const int idx = threadIdx.x;
-    if (idx < nrhs * NMAX) {
-      const bool ok = idx % NMAX < n;
-      xslot[idx] = ok && k + 1 < N ? xv[0] : 0.0;
-      bslot[idx] = ok ? bv[0] : 0.0;
+#pragma unroll
+    for (int u = 0; u < VPER; ++u) {
+      const int idx = threadIdx.x + u * RES_T;
+      if (idx < nrhs * NMAX) {
+        const bool ok = idx % NMAX < n;
+        xslot[idx] = ok && k + 1 < N ? xv[u] : 0.0;
+        bslot[idx] = ok ? bv[u] : 0.0;
+      }
     }
   }
 };
@@ -141,7 +166,8 @@ __device__ __attribute__((always_inline)) inline void residual_body(const Residu
   if (a.done && *a.done) return;
   constexpr int LD = NMAX + 1;
   constexpr int BS = NMAX * LD;
-  constexpr int RT = RES_T / NMAX < NMAX ? RES_T / NMAX : NMAX;  // threads per row
+  constexpr int RES_T = res_threads<NMAX>();
+  constexpr int RT = RES_T / NMAX;  // threads per row
   constexpr int CPT = NMAX / RT;                                 // columns per thread
   static_assert(CPT >= 1 && RT * CPT == NMAX, "row split");
   typedef StageFetch<NMAX, FULL> SF;
@@ -162,12 +188,13 @@ __device__ __attribute__((always_inline)) inline void residual_body(const Residu
   const int sys = s / S, sl = s - sys * S;
   const size_t vbase = (size_t)sys * a.vsys;
   const size_t xk = vbase + (size_t)sl * N * n;  // stage 0 of this chain, q = 0
-  const int k0 = ch * a.chunk, k1 = min(N, k0 + a.chunk);
+  const int k0 = ch * res_stages(NMAX), k1 = min(N, k0 + res_stages(NMAX));
   const double* Dc = a.D + (size_t)s * N * nn;
   const double* Ec = a.E + (size_t)s * (N > 1 ? N - 1 : 0) * nn;
   const int t = threadIdx.x, orow = t / RT, p = t - orow * RT;
-  const int o = orow < NMAX ? orow : 0;  // rows past NMAX (NMAX = 8) compute row 0, unused
+  const int o = orow;
   double kmax = 0.0;  // largest row sum of |K| over this workgroup's rows (knorm_part)
+  double rmax[SF::VPER] = {};  // largest |r| of the right-hand sides this thread stores
 
   // Prologue: stage k0 with x_{k0+1} and b_{k0}, E_{k0-1} (or C_s at k0 = 0), x_{k0-1},
   // x_{k0} and (k0 = 0) the root x, all straight into LDS.
@@ -210,26 +237,44 @@ __device__ __attribute__((always_inline)) inline void residual_body(const Residu
       const double* xp = xs + ((k + 1) % 3) * VS;
       const double* bk = bs + (k & 1) * VS;
       const bool has_prev = k > 0, has_next = k + 1 < N;
-#pragma unroll 1
-      for (int q = 0; q < nrhs; ++q) {
-        double acc = 0.0, accw = 0.0;
+      // This thread's entries of the row, the same for every right-hand side: D, E_{k-1}
+      // (or C^T at k = 0), E_k^T.  Blocks up to 16 keep them in registers (four right-hand
+      // sides 54 -> 48 us, one as fast); at 32 the registers cost a wave per SIMD (5%).
+      auto ld = [&](int u) { const int c = p * CPT + u; return c <= o ? D[o * LD + c] : D[c * LD + o]; };
+      auto lp = [&](int u) { const int c = p * CPT + u; return has_prev ? Ep[o * LD + c] : Ep[c * LD + o]; };
+      auto ln = [&](int u) { return has_next ? Ek[(p * CPT + u) * LD + o] : 0.0; };
+      constexpr bool KEEP = NMAX <= 16;
+      double md[KEEP ? CPT : 1], mp[KEEP ? CPT : 1], mn[KEEP ? CPT : 1];
+      if constexpr (KEEP) {
 #pragma unroll
         for (int u = 0; u < CPT; ++u) {
-          const int c = p * CPT + u;
-          const double dv = c <= o ? D[o * LD + c] : D[c * LD + o];
-          acc += dv * xkk[q * NMAX + c];
-          if (has_prev) acc += Ep[o * LD + c] * xm[q * NMAX + c];  // E_{k-1} x_{k-1}
-          if (has_next) acc += Ek[c * LD + o] * xp[q * NMAX + c];  // E_k^T x_{k+1}
-          if (!has_prev) {                                        // k = 0: C^T x_0, C x_{s,0}
-            acc += Ep[c * LD + o] * x0s[q * NMAX + c];
-            accw += Ep[o * LD + c] * xkk[q * NMAX + c];
-          }
+          md[u] = ld(u);
+          mp[u] = lp(u);
+          mn[u] = ln(u);
+        }
+      }
+      const double* xq0 = has_prev ? xm : x0s;
+#pragma unroll 1
+      for (int q = 0; q < nrhs; ++q) {
+        double acc = 0.0;
+#pragma unroll
+        for (int u = 0; u < CPT; ++u) {
+          const int c = q * NMAX + p * CPT + u;
+          acc += (KEEP ? md[KEEP ? u : 0] : ld(u)) * xkk[c];
+          acc += (KEEP ? mp[KEEP ? u : 0] : lp(u)) * xq0[c];
+          if (has_next) acc += (KEEP ? mn[KEEP ? u : 0] : ln(u)) * xp[c];
         }
         acc = lane_group_sum_dpp<RT>(acc);
-        if (p == 0 && orow < NMAX) rs[q * NMAX + o] = bk[q * NMAX + o] - acc;
-        if (!has_prev) {
+        if (p == 0) rs[q * NMAX + o] = bk[q * NMAX + o] - acc;
+        if (!has_prev) {  // k = 0: C x_{s,0} for the root rows
+          double accw = 0.0;
+#pragma unroll
+          for (int u = 0; u < CPT; ++u) {
+            const int c = p * CPT + u;
+            accw += Ep[o * LD + c] * xkk[q * NMAX + c];
+          }
           accw = lane_group_sum_dpp<RT>(accw);
-          if (p == 0 && orow < NMAX) ws[q * NMAX + o] = accw;
+          if (p == 0) ws[q * NMAX + o] = accw;
         }
       }
       if (a.knorm_part) {
@@ -239,14 +284,10 @@ __device__ __attribute__((always_inline)) inline void residual_body(const Residu
         double ab = 0.0, abc = 0.0;
 #pragma unroll
         for (int u = 0; u < CPT; ++u) {
-          const int c = p * CPT + u;
-          ab += fabs(c <= o ? D[o * LD + c] : D[c * LD + o]);
-          if (has_prev) ab += fabs(Ep[o * LD + c]);
-          if (has_next) ab += fabs(Ek[c * LD + o]);
-          if (!has_prev) {
-            ab += fabs(Ep[c * LD + o]);
-            abc += fabs(Ep[o * LD + c]);
-          }
+          ab += fabs(ld(u));
+          ab += fabs(lp(u));
+          if (has_next) ab += fabs(ln(u));
+          if (!has_prev) abc += fabs(Ep[o * LD + p * CPT + u]);
         }
         ab = lane_group_sum_dpp<RT>(ab);
         kmax = fmax(kmax, ab);
@@ -260,15 +301,27 @@ __device__ __attribute__((always_inline)) inline void residual_body(const Residu
     f.commit(a, k + 1, Ds + ((k + 1) & 1) * BS, Es + ((k + 1) & 1) * BS,
              xs + ((k + 2) % 3) * VS, bs + ((k + 1) & 1) * VS);
     f.issue(a, Dc, Ec, xk, len, k + 3, k1);
-    if (k < k1 && t < VS && t % NMAX < n) {
-      const int q = t / NMAX, i = t % NMAX;
-      a.r[xk + (size_t)q * len + (size_t)k * n + i] = rs[t];
-      if (k == 0) a.w[((size_t)s * nrhs + q) * n + i] = ws[t];
+#pragma unroll
+    for (int u = 0; u < SF::VPER; ++u) {
+      const int idx = t + u * RES_T;
+      if (k < k1 && idx < VS && idx % NMAX < n) {
+        const int q = idx / NMAX, i = idx % NMAX;
+        a.r[xk + (size_t)q * len + (size_t)k * n + i] = rs[idx];
+        rmax[u] = nan_max(fabs(rs[idx]), rmax[u]);
+        if (k == 0) a.w[((size_t)s * nrhs + q) * n + i] = ws[idx];
+      }
     }
   };
   for (int k = k0; k < k1; k += 2) {
     step(k, fa);
     step(k + 1, fb);
+  }
+#pragma unroll
+  for (int u = 0; u < SF::VPER; ++u) {
+    const int idx = t + u * RES_T;
+    double m = rmax[u];  // over the NMAX lanes of a right-hand side (a group of one wave)
+    for (int off = NMAX / 2; off > 0; off >>= 1) m = nan_max(m, __shfl_xor(m, off));
+    if (idx < VS && idx % NMAX == 0) a.rpart[(size_t)bx * nrhs + idx / NMAX] = m;
   }
   if (a.knorm_part) {
     __shared__ double wmax[RES_T / 64];
@@ -284,84 +337,146 @@ __device__ __attribute__((always_inline)) inline void residual_body(const Residu
 }
 
 template <int NMAX, bool FULL>
-__global__ void __launch_bounds__(RES_T) residual_kernel(ResidualArgs a, int chunks) {
+__global__ void __launch_bounds__(res_threads<NMAX>()) residual_kernel(ResidualArgs a, int chunks) {
   residual_body<NMAX, FULL>(a, chunks, blockIdx.x);
 }
 
-// One workgroup per system; thread (g, i) sums element i of the products C_s x_{s,0}
-// over the scenarios s = g mod G (G = 1024 / NMAX groups), the groups in order.
+// max of the non-negative (or NaN) p[i * st] over i = t0, t0 + step, .. < cnt, 0 if none.
+// U loads are issued together per round (indices clamped into range, the extra ones
+// not counted), so that a thread waits once per round rather than once per load.
+template <int U>
+__device__ inline double strided_max(const double* p, int cnt, int t0, int step, int st = 1) {
+  double m = 0.0;
+  for (int i0 = t0; i0 < cnt; i0 += U * step) {
+    double t[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) t[u] = p[(size_t)min(i0 + u * step, cnt - 1) * st];
+#pragma unroll
+    for (int u = 0; u < U; ++u) m = i0 + u * step < cnt ? nan_max(t[u], m) : m;
+  }
+  return m;
+}
+
+// Sum of v[s][q][i] over the scenarios s = g, g + G, .. < S for the QB right-hand sides
+// q0 .. of nv (n elements each), B scenarios' loads in flight; then over the lanes of the
+// wave that hold element i.
+template <int NMAX, int QB, int B>
+__device__ inline void scenario_sums(const double* __restrict__ v, int S, int n, int nv, int q0,
+                                     double (&acc)[QB]) {
+  constexpr int G = 1024 / NMAX;
+  const int i = threadIdx.x % NMAX, g = threadIdx.x / NMAX;
+#pragma unroll
+  for (int q = 0; q < QB; ++q) acc[q] = 0.0;
+  if (i < n) {
+    for (int s0 = g; s0 < S; s0 += G * B) {
+      double w[QB][B];
+#pragma unroll
+      for (int u = 0; u < B; ++u) {
+        const double* p = v + ((size_t)min(s0 + G * u, S - 1) * nv) * n + i;
+#pragma unroll
+        for (int q = 0; q < QB; ++q) w[q][u] = p[(size_t)min(q0 + q, nv - 1) * n];
+      }
+#pragma unroll
+      for (int q = 0; q < QB; ++q)
+#pragma unroll
+        for (int u = 0; u < B; ++u) acc[q] += s0 + G * u < S ? w[q][u] : 0.0;
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < QB; ++q)
+    for (int off = NMAX; off < 64; off <<= 1) acc[q] += __shfl_xor(acc[q], off);
+}
+
+// One workgroup per system: the root rows of r, and the largest |r| of each right-hand
+// side (rnorm), from the tail workgroups' maxima and the root rows.  Thread (g, i) sums
+// element i of the products C_s x_{s,0} over the scenarios s = g mod G (G = 1024 / NMAX
+// groups), four right-hand sides at a time; the lanes of a wave are added by shuffles, the
+// waves in order from LDS.  Latency-bound (one workgroup per system).
 template <int NMAX>
 __device__ __attribute__((always_inline)) inline void residual_root_body(const ResidualArgs& a,
                                                                          unsigned bx) {
   if (a.done && *a.done) return;
-  constexpr int G = 1024 / NMAX;
-  __shared__ double part[G][NMAX + 1];
+  constexpr int W = 16, QB = 4;
+  __shared__ double part[QB][W][NMAX];
+  __shared__ double xr[16][NMAX];
+  __shared__ double wm[17][W];  // per wave: largest |r| (per right-hand side), |K| row
   const int n = a.n, N = a.N, S = a.S, nrhs = a.nrhs;
-  const int sys = bx;  // one workgroup per system
+  const int sys = bx;
   const size_t len = ((size_t)S * N + 1) * n;
   const size_t root = (size_t)sys * a.vsys + (size_t)S * N * n;
-  const double* w = a.w + (size_t)sys * S * nrhs * n;
   const double* R = a.R + (size_t)sys * n * n;
-  const int t = threadIdx.x, i = t % NMAX, g = t / NMAX;
-  for (int q = 0; q < nrhs; ++q) {
-    double acc = 0.0;
-    if (i < n) {
-      constexpr int B = 8;
-      for (int s0 = g; s0 < S; s0 += G * B) {
-        double v[B];
+  const int t = threadIdx.x, i = t % NMAX, q = t / NMAX, wv = t >> 6;
+  const bool mine = q < nrhs && i < n;  // this thread's root row and right-hand side
+  const size_t o = root + (size_t)q * len + i;
+  if (q < nrhs) xr[q][i] = i < n ? a.x[o] : 0.0;
+  const double bv = mine ? a.b[o] : 0.0;
+  // the tail workgroups' largest |r|, a.kper of them per system
+  const double* rp = a.rpart + (size_t)sys * a.kper * nrhs;
+  for (int k = 0; k < nrhs; ++k) {
+    const double m = wave_max(strided_max<4>(rp + k, a.kper, t, 1024, nrhs));
+    if ((t & 63) == 0) wm[k][wv] = m;
+  }
+  const double* w = a.w + (size_t)sys * S * nrhs * n;
+  double sum = 0.0;
+  for (int q0 = 0; q0 < nrhs; q0 += QB) {
+    if (q0) __syncthreads();
+    if (nrhs == 1) {
+      double acc[1];
+      scenario_sums<NMAX, 1, 16>(w, S, n, 1, 0, acc);
+      if ((t & 63) < NMAX) part[0][wv][i] = acc[0];
+    } else {
+      double acc[QB];
+      scenario_sums<NMAX, QB, 4>(w, S, n, nrhs, q0, acc);
+      if ((t & 63) < NMAX)
 #pragma unroll
-        for (int u = 0; u < B; ++u) {
-          const int sc = s0 + G * u;
-          v[u] = sc < S ? w[((size_t)sc * nrhs + q) * n + i] : 0.0;
-        }
-#pragma unroll
-        for (int u = 0; u < B; ++u) acc += v[u];
-      }
-    }
-    part[g][i] = acc;
-    __syncthreads();
-    if (t < n) {
-      const int row = t;
-      double sum = 0.0;
-      for (int gg = 0; gg < G; ++gg) sum += part[gg][row];
-      double rx = 0.0;
-      for (int c = 0; c < n; ++c) {
-        const double rv = (row >= c) ? R[row * n + c] : R[c * n + row];
-        rx += rv * a.x[(size_t)q * len + root + c];
-      }
-      a.r[(size_t)q * len + root + row] = a.b[(size_t)q * len + root + row] - rx - sum;
+        for (int u = 0; u < QB; ++u) part[u][wv][i] = acc[u];
     }
     __syncthreads();
+    if (mine && q >= q0 && q < q0 + QB) {
+#pragma unroll
+      for (int v = 0; v < W; ++v) sum += part[q - q0][v][i];
+    }
+  }
+  double rabs = 0.0;
+  if (mine) {
+    double rx = 0.0;
+    for (int c = 0; c < n; ++c) rx += (i >= c ? R[i * n + c] : R[c * n + i]) * xr[q][c];
+    const double r = bv - rx - sum;
+    a.r[o] = r;
+    rabs = fabs(r);
+  }
+  if (q < nrhs) {  // whole NMAX-lane groups
+    for (int off = NMAX / 2; off > 0; off >>= 1) rabs = nan_max(rabs, __shfl_xor(rabs, off));
+    if (i == 0) {
+      double m = rabs;
+#pragma unroll
+      for (int v = 0; v < W; ++v) m = nan_max(wm[q][v], m);
+      a.rnorm[(size_t)sys * a.seg_sys + q] = m;
+    }
   }
   if (a.knorm_root) {
-    // root rows of |K|: the |C_s| row sums of the scenarios (G interleaved groups, each
-    // in scenario order, then the groups in order, as the sum of w above), plus |R|
-    const double* cr = a.crow + (size_t)sys * S * n;
-    double acc = 0.0;
-    if (i < n) {
-      constexpr int B = 8;
-      for (int s0 = g; s0 < S; s0 += G * B) {
-        double v[B];
-#pragma unroll
-        for (int u = 0; u < B; ++u) {
-          const int sc = s0 + G * u;
-          v[u] = sc < S ? cr[(size_t)sc * n + i] : 0.0;
-        }
-#pragma unroll
-        for (int u = 0; u < B; ++u) acc += v[u];
-      }
-    }
-    part[g][i] = acc;
+    // |K| of the system: the tail workgroups' largest row sums, and the root rows' (the
+    // |C_s| row sums of the scenarios plus |R|)
     __syncthreads();
-    double m = 0.0;
+    double acc[1];
+    scenario_sums<NMAX, 1, 16>(a.crow + (size_t)sys * S * n, S, n, 1, 0, acc);
+    if ((t & 63) < NMAX) part[0][wv][i] = acc[0];
+    const double m =
+        wave_max(strided_max<4>(a.knorm_part + (size_t)sys * a.kper, a.kper, t, 1024));
+    if ((t & 63) == 0) wm[16][wv] = m;
+    __syncthreads();
+    double k = 0.0;
     if (t < n) {
-      double sum = 0.0;
-      for (int gg = 0; gg < G; ++gg) sum += part[gg][t];
-      for (int c = 0; c < n; ++c) sum += fabs(t >= c ? R[t * n + c] : R[c * n + t]);
-      m = sum;
+#pragma unroll
+      for (int v = 0; v < W; ++v) k += part[0][v][t];
+      for (int c = 0; c < n; ++c) k += fabs(t >= c ? R[t * n + c] : R[c * n + t]);
     }
-    for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off));
-    if (t == 0) a.knorm_root[sys] = m;  // n <= 64: the rows sit in wave 0
+    k = wave_max(k);  // n <= 64: the rows sit in wave 0
+    if (t == 0) {
+#pragma unroll
+      for (int v = 0; v < W; ++v) k = nan_max(wm[16][v], k);
+      a.knorm_root[sys] = k;
+    }
   }
 }
 
@@ -370,11 +485,8 @@ __global__ void __launch_bounds__(1024) residual_root_kernel(ResidualArgs a) {
   residual_root_body<NMAX>(a, blockIdx.x);
 }
 
-// Maximum that propagates NaN (so a NaN residual or correction fails the stop test).
-__device__ inline double nan_max(double a, double b) { return (a != a || a > b) ? a : b; }
-
 __device__ inline double block_max(double v, double* sh) {
-  for (int off = 32; off > 0; off >>= 1) v = nan_max(v, __shfl_xor(v, off));
+  v = wave_max(v);
   const int wv = threadIdx.x >> 6;
   if ((threadIdx.x & 63) == 0) sh[wv] = v;
   __syncthreads();
@@ -385,66 +497,51 @@ __device__ inline double block_max(double v, double* sh) {
   return m;
 }
 
-// partial[t][q][blk] = max over this block's slice of |v_t[q][.]| (t = 0: v, 1: v2).
-// Each thread keeps four independent loads in flight per iteration.
-__global__ void __launch_bounds__(256) maxabs_partial_kernel(const double* v, const double* v2,
-                                                             int nrhs, size_t len,
-                                                             double* partial, const int* done) {
-  if (done && *done) return;
-  __shared__ double sh[4];
-  const size_t stride = (size_t)gridDim.x * blockDim.x;
-  const size_t t0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  for (int t = 0; t < (v2 ? 2 : 1); ++t) {
-    const double* src = t == 0 ? v : v2;
-    for (int q = 0; q < nrhs; ++q) {
-      const double* p = src + (size_t)q * len;
-      double m0 = 0.0, m1 = 0.0, m2 = 0.0, m3 = 0.0;
-      size_t i = t0;
-      for (; i + 3 * stride < len; i += 4 * stride) {
-        const double a0 = p[i], a1 = p[i + stride], a2 = p[i + 2 * stride], a3 = p[i + 3 * stride];
-        m0 = nan_max(fabs(a0), m0);
-        m1 = nan_max(fabs(a1), m1);
-        m2 = nan_max(fabs(a2), m2);
-        m3 = nan_max(fabs(a3), m3);
-      }
-      for (; i < len; i += stride) m0 = nan_max(fabs(p[i]), m0);
-      double mx = block_max(nan_max(nan_max(m0, m1), nan_max(m2, m3)), sh);
-      if (threadIdx.x == 0) partial[((size_t)t * nrhs + q) * gridDim.x + blockIdx.x] = mx;
-    }
+// max |p[i]| over i = t0, t0 + stride, .. < len, eight independent loads in flight
+__device__ inline double stream_maxabs(const double* __restrict__ p, size_t len, size_t t0,
+                                       size_t stride) {
+  constexpr int U = 8;
+  double m[U] = {};
+  size_t i = t0;
+  for (; i + (U - 1) * stride < len; i += U * stride) {
+    double v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = p[i + u * stride];
+#pragma unroll
+    for (int u = 0; u < U; ++u) m[u] = nan_max(fabs(v[u]), m[u]);
   }
+  for (; i < len; i += stride) m[0] = nan_max(fabs(p[i]), m[0]);
+#pragma unroll
+  for (int u = 1; u < U; ++u) m[0] = nan_max(m[u], m[0]);
+  return m[0];
 }
 
-// max of the non-negative (or NaN) p[i] over i = t0, t0 + step, .. < cnt, 0 if none.
-// U loads are issued together per round (indices clamped into range, the extra ones
-// not counted), so that a thread waits once per round rather than once per load.
-template <int U>
-__device__ inline double strided_max(const double* p, int cnt, int t0, int step) {
-  double m = 0.0;
-  for (int i0 = t0; i0 < cnt; i0 += U * step) {
-    double t[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) t[u] = p[min(i0 + u * step, cnt - 1)];
-#pragma unroll
-    for (int u = 0; u < U; ++u) m = i0 + u * step < cnt ? nan_max(t[u], m) : m;
-  }
-  return m;
+// partial[t][q][blk] = max over block blk's slice of |v_t[q][.]| (t = 0: v, 1: v2); grid
+// (blk, q, t).  Streams its vectors once; the blocks per vector follow its length
+// (norm_blocks), so that short vectors take one wait per block and long ones fill the
+// GPU, and every right-hand side has blocks of its own.
+__global__ void __launch_bounds__(256) maxabs_partial_kernel(const double* v, const double* v2,
+                                                             size_t len, double* partial,
+                                                             const int* done) {
+  if (done && *done) return;
+  __shared__ double sh[4];
+  const size_t q = blockIdx.y, t = blockIdx.z;
+  const double mx = block_max(
+      stream_maxabs((t == 0 ? v : v2) + q * len, len,
+                    (size_t)blockIdx.x * blockDim.x + threadIdx.x,
+                    (size_t)gridDim.x * blockDim.x), sh);
+  if (threadIdx.x == 0) partial[(t * gridDim.y + q) * gridDim.x + blockIdx.x] = mx;
 }
 
 // max over the block partials of one vector and right-hand side, on one wave
 __device__ inline double wave_reduce_partials(const double* part, int blocks) {
-  double mx = strided_max<16>(part, blocks, (int)threadIdx.x, 64);
-  for (int off = 32; off > 0; off >>= 1) mx = nan_max(mx, __shfl_xor(mx, off));
-  return mx;
+  return wave_max(strided_max<16>(part, blocks, (int)threadIdx.x & 63, 64));
 }
 
 __global__ void __launch_bounds__(64) maxabs_final_kernel(const double* partial, int blocks,
-                                                          int nrhs, double* out,
-                                                          const int* done) {
-  if (done && *done) return;
-  for (int q = 0; q < nrhs; ++q) {
-    const double mx = wave_reduce_partials(partial + (size_t)q * blocks, blocks);
-    if (threadIdx.x == 0) out[q] = mx;
-  }
+                                                          double* out) {
+  const double mx = wave_reduce_partials(partial + (size_t)blockIdx.x * blocks, blocks);
+  if (threadIdx.x == 0) out[blockIdx.x] = mx;
 }
 
 // flags[0] = done, flags[1] = corrections applied
@@ -455,83 +552,72 @@ __global__ void refine_reset_kernel(int* flags) {
   }
 }
 
-// |d|_inf and |x|_inf from the block partials, then the stop test
-// |d_q|_inf <= tol |x_q|_inf for every right-hand side.
-__global__ void __launch_bounds__(64) refine_check_kernel(const double* partial, int blocks,
-                                                          int nrhs, double tol, int* flags,
-                                                          double* relcorr, double* dnorm,
-                                                          double* xnorm) {
-  if (flags[0]) return;
+// Stop test over all segments (one workgroup; segment k = system, right-hand side, on
+// wave k mod 16): quantity(k) from the block partials, the largest into relcorr, and
+// flags[0] = 1 (and the host's copy hflag) when every one passes.  count: corrections
+// are counted always (1) or when the test fails (2) or not at all (0).
+template <typename Q>
+__device__ inline void stop_test(int segs, int count, int* flags, int* hflag, double* relcorr,
+                                 Q quantity) {
+  __shared__ double sworst[16];
+  __shared__ int sok[16];
+  const int wv = threadIdx.x >> 6, W = blockDim.x >> 6;
   bool ok = true;
   double worst = 0.0;
-  for (int q = 0; q < nrhs; ++q) {
-    const double d = wave_reduce_partials(partial + (size_t)q * blocks, blocks);
-    const double xv = wave_reduce_partials(partial + ((size_t)nrhs + q) * blocks, blocks);
-    const double rel = xv > 0.0 ? d / xv : d;
-    worst = nan_max(worst, rel);
-    if (!(d <= tol * xv)) ok = false;
-    if (threadIdx.x == 0) {
-      dnorm[q] = d;
-      xnorm[q] = xv;
-    }
+  for (int k = wv; k < segs; k += W) {
+    bool pass;
+    const double v = quantity(k, pass);
+    worst = nan_max(v, worst);
+    ok = ok && pass;
   }
+  if ((threadIdx.x & 63) == 0) {
+    sworst[wv] = worst;
+    sok[wv] = ok;
+  }
+  __syncthreads();
   if (threadIdx.x == 0) {
-    flags[1] += 1;
+    for (int w = 1; w < W; ++w) {
+      worst = nan_max(sworst[w], worst);
+      ok = ok && sok[w];
+    }
     *relcorr = worst;
+    if (count == 1 || (count == 2 && !ok)) flags[1] += 1;
     if (ok) flags[0] = 1;
+    *hflag = ok;
   }
 }
 
-// Backward-error stop test (one workgroup).  For every system sys and right-hand side q
-// (segment sys * nrhs + q): |r|_inf and |x|_inf from the block partials of
-// maxabs_partial_kernel (partial[0] over r, partial[1] over x), |b|_inf from bnorm and
-// |K|_inf of the system (reduced here from the residual's per-workgroup row-sum maxima
-// and its root rows when kpart is not null, kept in knorm); then
-// eta = |r| / (|K| |x| + |b|), the normwise backward error of x.  The loop is done
-// (flags[0] = 1) when eta <= tol for every segment; otherwise flags[1] counts one more
-// correction if count is set.  rnorm receives |r| for the correction solve, relcorr the
-// largest eta.
-__global__ void __launch_bounds__(256) refine_be_check_kernel(
-    const double* partial, int blocks, int B, int nrhs, const double* kpart, int kper,
-    const double* kroot, double* knorm, const double* bnorm, double tol, int count, int* flags,
-    double* relcorr, double* rnorm) {
+// |d|_inf and |x|_inf from the block partials, then the stop test
+// |d_q|_inf <= tol |x_q|_inf for every right-hand side.
+__global__ void __launch_bounds__(1024) refine_check_kernel(const double* partial, int blocks,
+                                                            int segs, double tol, int* flags,
+                                                            int* hflag, double* relcorr) {
   if (flags[0]) return;
-  __shared__ double sh[4];
-  const int segs = B * nrhs;
-  bool ok = true;
-  double worst = 0.0;
-  for (int sys = 0; sys < B; ++sys) {
-    if (kpart) {
-      double m = strided_max<8>(kpart + (size_t)sys * kper, kper, (int)threadIdx.x, (int)blockDim.x);
-      m = block_max(m, sh);
-      if (threadIdx.x == 0) knorm[sys] = nan_max(m, kroot[sys]);
-      __syncthreads();
-    }
-    const double kn = knorm[sys];
-    for (int q = 0; q < nrhs; ++q) {
-      const int seg = sys * nrhs + q;
-      double mr = strided_max<4>(partial + (size_t)seg * blocks, blocks, (int)threadIdx.x,
-                                 (int)blockDim.x);
-      double mx = strided_max<4>(partial + ((size_t)segs + seg) * blocks, blocks,
-                                 (int)threadIdx.x, (int)blockDim.x);
-      mr = block_max(mr, sh);
-      mx = block_max(mx, sh);
-      if (threadIdx.x == 0) {
-        const double den = kn * mx + bnorm[seg];
-        const double eta = den > 0.0 ? mr / den : (mr > 0.0 ? HUGE_VAL : 0.0);
-        worst = nan_max(worst, eta);
-        if (!(eta <= tol)) ok = false;
-        rnorm[seg] = mr;
-      }
-    }
-  }
-  if (threadIdx.x == 0) {
-    *relcorr = worst;
-    if (ok)
-      flags[0] = 1;
-    else if (count)
-      flags[1] += 1;
-  }
+  stop_test(segs, 1, flags, hflag, relcorr, [&](int q, bool& pass) {
+    const double d = wave_reduce_partials(partial + (size_t)q * blocks, blocks);
+    const double xv = wave_reduce_partials(partial + ((size_t)segs + q) * blocks, blocks);
+    pass = d <= tol * xv;
+    return xv > 0.0 ? d / xv : d;
+  });
+}
+
+// Backward-error stop test.  For every segment (system sys, right-hand side): |r|_inf from
+// the residual (rnorm), |x|_inf from the block partials, |b|_inf from bnorm and |K|_inf of
+// the system from knorm; eta = |r| / (|K| |x| + |b|), the normwise backward error of x.
+// The loop is done (flags[0] = 1) when eta <= tol for every segment; otherwise flags[1]
+// counts one more correction if count is set.
+__global__ void __launch_bounds__(1024) refine_be_check_kernel(
+    const double* partial, int blocks, int segs, int nrhs, const double* rnorm,
+    const double* knorm, const double* bnorm, double tol, int count, int* flags, int* hflag,
+    double* relcorr) {
+  if (flags[0]) return;
+  stop_test(segs, count ? 2 : 0, flags, hflag, relcorr, [&](int seg, bool& pass) {
+    const double mx = wave_reduce_partials(partial + (size_t)seg * blocks, blocks);
+    const double den = knorm[seg / nrhs] * mx + bnorm[seg], mr = rnorm[seg];
+    const double eta = den > 0.0 ? mr / den : (mr > 0.0 ? HUGE_VAL : mr);
+    pass = eta <= tol;
+    return eta;
+  });
 }
 
 // ---- ragged batches (see multi.h) ----
@@ -549,8 +635,8 @@ __device__ inline ResidualArgs relocate_residual(const ResidualArgs& t, const Re
 }
 
 template <int NMAX, bool FULL>
-__global__ void __launch_bounds__(RES_T) residual_multi(const MultiItem<ResidualArgs>* items,
-                                                        int nitems, Reloc r) {
+__global__ void __launch_bounds__(res_threads<NMAX>()) residual_multi(
+    const MultiItem<ResidualArgs>* items, int nitems, Reloc r) {
   const MultiItem<ResidualArgs>& it = items[multi_find(items, nitems, blockIdx.x)];
   residual_body<NMAX, FULL>(relocate_residual(it.a, r), it.p0, multi_local(it).x);
 }
@@ -562,68 +648,76 @@ __global__ void __launch_bounds__(1024) residual_root_multi(const MultiItem<Resi
   residual_root_body<NMAX>(relocate_residual(it.a, r), multi_local(it).x);
 }
 
+// part[slice] = max |v| over slice blockIdx.x of the concatenated vectors (and part[slices
+// + slice] of v2, if set).  A segment is cut into slices of kNormSlice elements, so that
+// the long systems of a batch are streamed by many workgroups: on 64 systems of 0.02 to
+// 2.1 M elements, 2480 us with one workgroup per segment.
 __global__ void __launch_bounds__(256) seg_maxabs_kernel(const double* v, const double* v2,
-                                                         const SegRec* segs, double* out,
-                                                         double* out2, const int* done) {
+                                                         const SegRec* slices, double* part,
+                                                         const int* done) {
   if (done && *done) return;
   __shared__ double sh[4];
-  const SegRec sg = segs[blockIdx.x];
+  const SegRec sg = slices[blockIdx.x];
   for (int t = 0; t < (v2 ? 2 : 1); ++t) {
-    const double* p = (t == 0 ? v : v2) + sg.off;
-    double m0 = 0.0, m1 = 0.0;
-    size_t i = threadIdx.x;
-    for (; i + 256 < sg.len; i += 512) {
-      m0 = nan_max(fabs(p[i]), m0);
-      m1 = nan_max(fabs(p[i + 256]), m1);
-    }
-    for (; i < sg.len; i += 256) m0 = nan_max(fabs(p[i]), m0);
-    const double mx = block_max(nan_max(m0, m1), sh);
-    if (threadIdx.x == 0) (t == 0 ? out : out2)[blockIdx.x] = mx;
+    const double mx =
+        block_max(stream_maxabs((t == 0 ? v : v2) + sg.off, sg.len, threadIdx.x, 256), sh);
+    if (threadIdx.x == 0) part[t * gridDim.x + blockIdx.x] = mx;
   }
 }
 
-// Per system (one workgroup each): its |K| (backward-error mode, when kpart is set) and
-// whether all its segments pass; sys_worst = the largest test quantity.
+// out[k] = max over the slices of segment k
+__global__ void __launch_bounds__(64) seg_final_kernel(const double* part, const int* slice0,
+                                                       double* out) {
+  const int k = blockIdx.x, s0 = slice0[k];
+  const double mx = wave_reduce_partials(part + s0, slice0[k + 1] - s0);
+  if (threadIdx.x == 0) out[k] = mx;
+}
+
+// Per system (one workgroup each, a wave per segment in turn): whether all its segments
+// pass; sys_worst = the largest test quantity.  part: slice maxima of d and x (mode 0), of
+// x (mode 1, backward error).
 __global__ void __launch_bounds__(256) ragged_sys_check_kernel(
-    int mode, const double* dr, const double* xn, const double* bn, const int* seg_sys,
-    int nseg, const double* kpart, const int* kp_off, const double* kroot, double* knorm,
-    double tol, const int* flags, int* sys_ok, double* sys_worst) {
+    int mode, const double* part, const int* slice0, int nslice, int nrhs, const double* rnorm,
+    const double* knorm, const double* bnorm, double tol, const int* flags, int* sys_ok,
+    double* sys_worst) {
   if (flags[0]) return;
-  __shared__ double sh[4];
-  const int sys = blockIdx.x;
-  if (mode == 1 && kpart) {
-    double m = strided_max<8>(kpart + kp_off[sys], kp_off[sys + 1] - kp_off[sys],
-                              (int)threadIdx.x, (int)blockDim.x);
-    m = block_max(m, sh);
-    if (threadIdx.x == 0) knorm[sys] = nan_max(m, kroot[sys]);
-    __syncthreads();
-  }
-  if (threadIdx.x != 0) return;
+  __shared__ double sworst[4];
+  __shared__ int sok[4];
+  const int sys = blockIdx.x, wv = threadIdx.x >> 6;
   bool ok = true;
   double worst = 0.0;
-  // the segments of a system are consecutive; find them by a scan of seg_sys
-  int lo = 0, hi = nseg;
-  while (lo < hi) {  // first segment of sys
-    const int mid = (lo + hi) >> 1;
-    if (seg_sys[mid] < sys) lo = mid + 1; else hi = mid;
-  }
-  for (int k = lo; k < nseg && seg_sys[k] == sys; ++k) {
+  for (int k = sys * nrhs + wv; k < (sys + 1) * nrhs; k += 4) {
+    const int s0 = slice0[k], cnt = slice0[k + 1] - s0;
     double q;
     if (mode == 1) {
-      const double den = knorm[sys] * xn[k] + bn[k];
-      q = den > 0.0 ? dr[k] / den : (dr[k] > 0.0 ? HUGE_VAL : 0.0);
+      const double den = knorm[sys] * wave_reduce_partials(part + s0, cnt) + bnorm[k];
+      const double mr = rnorm[k];
+      q = den > 0.0 ? mr / den : (mr > 0.0 ? HUGE_VAL : mr);
     } else {
-      q = xn[k] > 0.0 ? dr[k] / xn[k] : dr[k];
+      const double d = wave_reduce_partials(part + s0, cnt);
+      const double xv = wave_reduce_partials(part + nslice + s0, cnt);
+      q = xv > 0.0 ? d / xv : d;
     }
-    worst = nan_max(worst, q);
+    worst = nan_max(q, worst);
     if (!(q <= tol)) ok = false;
   }
-  sys_ok[sys] = ok ? 1 : 0;
-  sys_worst[sys] = worst;
+  if ((threadIdx.x & 63) == 0) {
+    sworst[wv] = worst;
+    sok[wv] = ok;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < 4; ++w) {
+      worst = nan_max(sworst[w], worst);
+      ok = ok && sok[w];
+    }
+    sys_ok[sys] = ok;
+    sys_worst[sys] = worst;
+  }
 }
 
 __global__ void __launch_bounds__(256) ragged_final_check_kernel(int B, int count, int* flags,
-                                                                 double* relcorr,
+                                                                 int* hflag, double* relcorr,
                                                                  const int* sys_ok,
                                                                  const double* sys_worst) {
   if (flags[0]) return;
@@ -641,10 +735,13 @@ __global__ void __launch_bounds__(256) ragged_final_check_kernel(int B, int coun
     // 1 = one is applied after it unless the test holds (backward error), 0 = none
     if (count == 2 || (count == 1 && bad != 0.0)) flags[1] += 1;
     if (bad == 0.0) flags[0] = 1;
+    *hflag = bad == 0.0;
   }
 }
 
 }  // namespace
+
+int residual_walks(int N, int n) { return (N + res_stages(n) - 1) / res_stages(n); }
 
 size_t residual_lds(int nmax, int nrhs) {
   return nmax <= 8 ? residual_lds_bytes<8>(nrhs)
@@ -653,7 +750,7 @@ size_t residual_lds(int nmax, int nrhs) {
 
 void launch_residual_multi(int nmax, bool full, const MultiItem<ResidualArgs>* items, int nitems,
                            unsigned blocks, size_t lds, const Reloc& r, hipStream_t st) {
-  const dim3 g(blocks), b(RES_T);
+  const dim3 g(blocks), b(nmax > 16 ? res_threads<32>() : res_threads<16>());
 #define BMPC_RES_MULTI(NM)                                                             \
   if (full)                                                                            \
     hipLaunchKernelGGL((residual_multi<NM, true>), g, b, lds, st, items, nitems, r);     \
@@ -674,34 +771,59 @@ void launch_residual_root_multi(const MultiItem<ResidualArgs>* items, int nitems
   hipLaunchKernelGGL(residual_root_multi<32>, dim3(blocks), dim3(1024), 0, st, items, nitems, r);
 }
 
-void launch_seg_maxabs(const double* v, const double* v2, const SegRec* segs, int nseg,
-                       double* out, double* out2, const int* done, hipStream_t st) {
-  hipLaunchKernelGGL(seg_maxabs_kernel, dim3(nseg), dim3(256), 0, st, v, v2, segs, out, out2,
-                     done);
+void launch_seg_maxabs(const double* v, const double* v2, const SegRec* slices, int nslice,
+                       double* part, const int* done, hipStream_t st) {
+  hipLaunchKernelGGL(seg_maxabs_kernel, dim3(nslice), dim3(256), 0, st, v, v2, slices, part, done);
 }
 
-void launch_ragged_check(int mode, const double* dn_or_rn, const double* xn, const double* bn,
-                         const int* seg_sys, int nseg, int B, const double* kpart,
-                         const int* kp_off, const double* kroot, double* knorm, double tol,
-                         int count, int* flags, double* relcorr, int* sys_ok,
-                         double* sys_worst, hipStream_t st) {
-  hipLaunchKernelGGL(ragged_sys_check_kernel, dim3(B), dim3(256), 0, st, mode, dn_or_rn, xn, bn,
-                     seg_sys, nseg, kpart, kp_off, kroot, knorm, tol, (const int*)flags, sys_ok,
+void launch_seg_final(const double* part, const int* slice0, int nseg, double* out,
+                      hipStream_t st) {
+  hipLaunchKernelGGL(seg_final_kernel, dim3(nseg), dim3(64), 0, st, part, slice0, out);
+}
+
+void launch_ragged_check(int mode, const double* part, const int* slice0, int nslice, int B,
+                         int nrhs, const double* rnorm, const double* knorm,
+                         const double* bnorm, double tol, int count, int* flags, int* hflag,
+                         double* relcorr, int* sys_ok, double* sys_worst, hipStream_t st) {
+  hipLaunchKernelGGL(ragged_sys_check_kernel, dim3(B), dim3(256), 0, st, mode, part, slice0,
+                     nslice, nrhs, rnorm, knorm, bnorm, tol, (const int*)flags, sys_ok,
                      sys_worst);
   hipLaunchKernelGGL(ragged_final_check_kernel, dim3(1), dim3(256), 0, st, B, count, flags,
-                     relcorr, (const int*)sys_ok, (const double*)sys_worst);
+                     hflag, relcorr, (const int*)sys_ok, (const double*)sys_worst);
 }
 
-void launch_refine_be_check(const double* r, const double* x, int B, int nrhs, size_t len,
-                            double* partial, const double* kpart, int kper,
-                            const double* kroot, double* knorm, const double* bnorm,
-                            double tol, int count, int* flags, double* relcorr, double* rnorm,
+// Blocks per vector of maxabs_partial_kernel: 2048 elements each (a round of eight loads
+// per thread), at most kNormBlocks.
+static int norm_blocks(size_t len) {
+  return (int)std::min<size_t>(kNormBlocks, (len + 2047) / 2048);
+}
+static int check_threads(int segs) { return 64 * std::min(16, segs); }
+
+// The launches take the segments in the y dimension of the grid; beyond its limit they go
+// in rounds of 65535.
+static void maxabs_partials(const double* v, const double* v2, int segs, size_t len,
+                            double* partial, const int* done, hipStream_t st) {
+  const int nb = norm_blocks(len);
+  if (segs <= 65535) {
+    hipLaunchKernelGGL(maxabs_partial_kernel, dim3(nb, segs, v2 ? 2 : 1), dim3(256), 0, st, v, v2,
+                       len, partial, done);
+    return;
+  }
+  for (int t = 0; t < (v2 ? 2 : 1); ++t)
+    for (int k0 = 0; k0 < segs; k0 += 65535)
+      hipLaunchKernelGGL(maxabs_partial_kernel, dim3(nb, std::min(65535, segs - k0), 1), dim3(256),
+                         0, st, (t ? v2 : v) + (size_t)k0 * len, (const double*)nullptr, len,
+                         partial + ((size_t)t * segs + k0) * nb, done);
+}
+
+void launch_refine_be_check(const double* x, int B, int nrhs, size_t len, double* partial,
+                            const double* rnorm, const double* knorm, const double* bnorm,
+                            double tol, int count, int* flags, int* hflag, double* relcorr,
                             hipStream_t st) {
-  hipLaunchKernelGGL(maxabs_partial_kernel, dim3(kNormBlocks), dim3(256), 0, st, r, x, B * nrhs,
-                     len, partial, (const int*)flags);
-  hipLaunchKernelGGL(refine_be_check_kernel, dim3(1), dim3(256), 0, st, (const double*)partial,
-                     kNormBlocks, B, nrhs, kpart, kper, kroot, knorm, bnorm, tol, count, flags,
-                     relcorr, rnorm);
+  maxabs_partials(x, nullptr, B * nrhs, len, partial, flags, st);
+  hipLaunchKernelGGL(refine_be_check_kernel, dim3(1), dim3(check_threads(B * nrhs)), 0, st,
+                     (const double*)partial, norm_blocks(len), B * nrhs, nrhs, rnorm, knorm,
+                     bnorm, tol, count, flags, hflag, relcorr);
 }
 
 template <int NMAX>
@@ -720,13 +842,13 @@ static void launch_residual_t(const ResidualArgs& a, dim3 grid, int chunks, hipS
     }
   }
   if (a.n == NMAX)
-    hipLaunchKernelGGL((residual_kernel<NMAX, true>), grid, dim3(RES_T), lds, st, a, chunks);
+    hipLaunchKernelGGL((residual_kernel<NMAX, true>), grid, dim3(res_threads<NMAX>()), lds, st, a, chunks);
   else
-    hipLaunchKernelGGL((residual_kernel<NMAX, false>), grid, dim3(RES_T), lds, st, a, chunks);
+    hipLaunchKernelGGL((residual_kernel<NMAX, false>), grid, dim3(res_threads<NMAX>()), lds, st, a, chunks);
 }
 
 void launch_residual(const ResidualArgs& a, int nmax, hipStream_t st) {
-  const int chunks = (a.N + a.chunk - 1) / a.chunk;
+  const int chunks = residual_walks(a.N, a.n);
   const dim3 grid((unsigned)(a.B * a.S) * (unsigned)chunks);
   if (nmax <= 8)
     launch_residual_t<8>(a, grid, chunks, st);
@@ -745,25 +867,23 @@ void launch_residual_root(const ResidualArgs& a, hipStream_t st) {
     hipLaunchKernelGGL(residual_root_kernel<32>, dim3(a.B), dim3(1024), 0, st, a);
 }
 
-void launch_maxabs(const double* v, int nrhs, size_t len, double* partial, double* out,
-                   const int* done, hipStream_t st) {
-  hipLaunchKernelGGL(maxabs_partial_kernel, dim3(kNormBlocks), dim3(256), 0, st, v,
-                     (const double*)nullptr, nrhs, len, partial, done);
-  hipLaunchKernelGGL(maxabs_final_kernel, dim3(1), dim3(64), 0, st, partial, kNormBlocks, nrhs,
-                     out, done);
+void launch_maxabs(const double* v, int segs, size_t len, double* partial, double* out,
+                   hipStream_t st) {
+  maxabs_partials(v, nullptr, segs, len, partial, nullptr, st);
+  hipLaunchKernelGGL(maxabs_final_kernel, dim3(segs), dim3(64), 0, st, partial, norm_blocks(len),
+                     out);
 }
 
 void launch_refine_reset(int* flags, hipStream_t st) {
   hipLaunchKernelGGL(refine_reset_kernel, dim3(1), dim3(64), 0, st, flags);
 }
 
-void launch_refine_check(const double* d, const double* x, int nrhs, size_t len,
-                         double* partial, double tol, int* flags, double* relcorr,
-                         double* dnorm, double* xnorm, hipStream_t st) {
-  hipLaunchKernelGGL(maxabs_partial_kernel, dim3(kNormBlocks), dim3(256), 0, st, d, x, nrhs, len,
-                     partial, (const int*)flags);
-  hipLaunchKernelGGL(refine_check_kernel, dim3(1), dim3(64), 0, st, (const double*)partial,
-                     kNormBlocks, nrhs, tol, flags, relcorr, dnorm, xnorm);
+void launch_refine_check(const double* d, const double* x, int segs, size_t len,
+                         double* partial, double tol, int* flags, int* hflag, double* relcorr,
+                         hipStream_t st) {
+  maxabs_partials(d, x, segs, len, partial, flags, st);
+  hipLaunchKernelGGL(refine_check_kernel, dim3(1), dim3(check_threads(segs)), 0, st,
+                     (const double*)partial, norm_blocks(len), segs, tol, flags, hflag, relcorr);
 }
 
 }  // namespace bmpc
