@@ -25,16 +25,16 @@ double trsm_flops(double n) { return n * n * n; }
 double syrk_flops(double n) { return n * n * n + n * n; }
 double gemm_flops(double n) { return 2.0 * n * n * n; }
 
-// Levels per factor pass.  Measured on n = 16 and n = 32 workloads (S up to 512, N up
-// to 256): deeper windows save pass launches and boundary traffic but lengthen the
-// serial walk of each window, which sets the pass time once the chains are short or
-// few; 3 (FP64) and 4 (FP32) were fastest or within a few percent of it throughout.
-// Levels per pass, measured on the paper-grid and c2/c3 shapes: four for FP32 blocks
-// up to 16, three otherwise (FP64, whose slots are twice as large; FP32 32 x 32 blocks,
-// where three levels let four workgroups share a CU).
-int default_window_depth(bool fp64, int nmax) {
+// Levels of the first factor pass.  n > 16 (the serial walk of factor.hip): three, so that
+// four workgroups (FP32) share a CU; deeper windows save passes and boundary traffic but
+// lengthen the walk.  n <= 16 (tree.hip): deeper windows save passes, but leave more waves
+// idle at their upper levels once the GPU is full and take more LDS.  16 x 16: three (FP64,
+// 8192 chains of 64 stages: factor 1475 us with three, 1787 with four; 100 chains of 160:
+// 91 and 85).  8 x 8: four (FP64 / FP32, 8192 chains of 136: 1126 / 615 us with four, 1117 /
+// 617 with three and one wave; 4 chains of 16: 15 us, 19 with three).
+int default_window_depth(int nmax) {
   if (nmax > 32) return 1;  // blocks of 33..64: one level per pass (factor64.hip)
-  return (fp64 || nmax == 32) ? 3 : 4;
+  return nmax <= 8 ? 4 : 3;
 }
 
 int ctz_host(unsigned v) { return __builtin_ctz(v); }
@@ -68,14 +68,16 @@ Costs make_costs(const bmpc_dims& d, bool fp64, int Tw1, int Tw2, int B, bool no
   const double len = ((double)S * N + 1) * n;
   int mk = m, shift = 0;
   double nG = 0;  // off-diagonal factor blocks per tail
-  // the odd positions' inverses of the first pass come from their own kernel (n <= 32)
-  const bool level1 = n <= 32 && m >= 1;
+  // the odd positions' inverses of the first pass come from their own kernel (n 17..32)
+  const bool level1 = n > 16 && n <= 32 && m >= 1;
   double l1_fl = 0, l1_by = 0;
   for (;;) {
     PassPlan p{};
     const int Tw = shift == 0 ? Tw1 : Tw2;
     p.tw = Tw;
     p.is_final = mk < (1 << Tw);
+    // the last pass takes the levels that are left (less LDS, fewer waves)
+    if (p.is_final && mk > 0) p.tw = std::min(Tw, chain_levels(mk));
     p.windows = p.is_final ? 1 : (mk >> Tw) + 1;
     p.mk = mk;
     p.shift = shift;
@@ -239,22 +241,23 @@ bool dalloc(bmpc_plan p, void** ptr, size_t bytes) {
 // substitution for one chunk of the plan's right-hand sides, so that path always fits.
 int pick_window_depth(bool fp64, int nmax, int nrhs, const bmpc_options* o) {
   if (nmax > 32) return 1;
-  int Tw = (o && o->window_depth > 0) ? o->window_depth : default_window_depth(fp64, nmax);
+  int Tw = (o && o->window_depth > 0) ? o->window_depth : default_window_depth(nmax);
   Tw = std::min(Tw, kMaxWindowDepth);
   const int q = std::min(nrhs, rhs_chunk(nmax));
-  while (Tw > 1 && factor_pass_lds_bytes(fp64, nmax, Tw, q) > (size_t)kLdsBudget) --Tw;
+  while (Tw > 1 && factor_pass_lds_bytes(fp64, nmax, Tw, 1 << Tw, q) > (size_t)kLdsBudget) --Tw;
   return Tw;
 }
 
-// Levels of the passes after the first: the option, else the first pass's depth.  A
-// smaller depth gives the later passes more workgroups per chain and the final pass a
-// shorter walk, but adds passes; on the c2 and c3 shapes the extra passes cost more
-// than the shorter walks save.
-int pick_later_depth(bool fp64, int nmax, int nrhs, int Tw, const bmpc_options* o) {
+// Levels of the passes after the first: the option, else the first pass's depth, or four at
+// 16 x 16 where that makes the second pass the last one (256 chains of 128 stages, FP32:
+// 84 us instead of 91).
+int pick_later_depth(bool fp64, int nmax, int N, int nrhs, int Tw, const bmpc_options* o) {
   if (nmax > 32) return 1;
   bmpc_options lo{};
   if (o) lo = *o;
-  lo.window_depth = std::min((o && o->later_depth > 0) ? o->later_depth : Tw, kMaxWindowDepth);
+  const int mk = (N - 1) >> Tw;
+  const int dflt = nmax == 16 && !(o && o->window_depth > 0) && mk >= 8 && mk < 16 ? 4 : Tw;
+  lo.window_depth = std::min((o && o->later_depth > 0) ? o->later_depth : dflt, kMaxWindowDepth);
   return pick_window_depth(fp64, nmax, nrhs, &lo);
 }
 
@@ -356,7 +359,7 @@ void enqueue_factor(bmpc_plan p, const double* D, const double* E, const double*
   hipStream_t st = p->stream;
   timed(p, KC_FACTOR_INIT, [&] { launch_factor_init(p->d_info, st); });
   const int npass = (int)p->costs.passes.size();
-  if (p->nmax <= 32 && d.N > 1) {
+  if (p->nmax == 32 && d.N > 1) {
     const FactorPassArgs a0 = factor_pass_args(p, 0, D, E, C, nullptr, 0);
     timed(p, KC_FACTOR_L1INV, [&] { launch_level1_inverse<T>(a0, p->nmax, st); });
   }
@@ -497,7 +500,7 @@ bmpc_status init_plan(bmpc_plan p, const bmpc_dims* dims, bmpc_precision prec, v
   p->m = dims->N - 1;
   p->nmax = nmax_for(dims->n);
   p->Tw = pick_window_depth(p->fp64, p->nmax, dims->nrhs, opts);
-  p->Tw2 = pick_later_depth(p->fp64, p->nmax, dims->nrhs, p->Tw, opts);
+  p->Tw2 = pick_later_depth(p->fp64, p->nmax, dims->N, dims->nrhs, p->Tw, opts);
   p->B = systems_of(opts);
   p->opt_flags = flags_of(opts);
   p->chunk = rhs_chunk(p->nmax);
@@ -620,7 +623,7 @@ bmpc_status bmpc_cost_model(const bmpc_dims* dims, bmpc_precision prec,
     return BMPC_ERR_INVALID;
   const bool fp64 = prec == BMPC_FP64;
   const int Tw = pick_window_depth(fp64, nmax_for(dims->n), dims->nrhs, opts);
-  const int Tw2 = pick_later_depth(fp64, nmax_for(dims->n), dims->nrhs, Tw, opts);
+  const int Tw2 = pick_later_depth(fp64, nmax_for(dims->n), dims->N, dims->nrhs, Tw, opts);
   Costs c = make_costs(*dims, fp64, Tw, Tw2, systems_of(opts), no_top_merge_of(opts));
   std::memset(cost, 0, sizeof(*cost));
   cost->factor_flops = c.factor_flops;

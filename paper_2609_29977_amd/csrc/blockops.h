@@ -158,6 +158,19 @@ __device__ inline void rows_both(double y, double& lo, double& hi) {
   hi = __hiloint2double((int)ph[1], (int)pl[1]);
 }
 
+// Lane K of each 16-lane row to every lane of the row (DPP row_newbcast).
+template <int K>
+__device__ inline float row_bcast(float x) {
+  return __int_as_float(
+      __builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x150 + K, 0xf, 0xf, false));
+}
+template <int K>
+__device__ inline double row_bcast(double x) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), 0x150 + K, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), 0x150 + K, 0xf, 0xf, false);
+  return __hiloint2double(hi, lo);
+}
+
 // Lane K of rows 0 and 2 to every lane of rows 0-1 and 2-3: a row broadcast (DPP
 // row_newbcast) and the even-to-odd row copy.  The pivot broadcast of a leaf that
 // factors one block in each 32-lane half of the wave.
@@ -298,14 +311,16 @@ constexpr int kPacked32 = 32 * 33 / 2;  // entries of a packed 32 x 32 lower tri
 // per-lane branches: row lanes also update entries above the diagonal, which are
 // never read.  Blocks smaller than NMAX must be padded with an identity block.
 // Returns (on every lane) the 0-based row of the first non-positive pivot, or -1.
-// PAIR: two independent blocks, one per 32-lane half of the wave (A is the lane's own
-// block; lanes 32-63 repeat the layout of lanes 0-31), each half's pivot broadcast to
-// its half only; the return value is per half.  The instructions are the same as for
-// one block, so the pair costs one block's issue slots.
-template <typename T, int NMAX, typename Ix = RowMajor<Lay<NMAX>::LD>, bool PAIR = false>
+// GROUP: that many independent blocks, one per 64 / GROUP lanes of the wave (A is the
+// lane's own block; every group of lanes repeats the layout of the first), each group's
+// pivot broadcast to its lanes only; the return value is per group.  Two at most at NMAX =
+// 16, four at NMAX = 8, whose row and column lanes share one 16-lane row.  The instructions
+// are those of one block, so a group costs one block's issue slots.
+template <typename T, int NMAX, typename Ix = RowMajor<Lay<NMAX>::LD>, int GROUP = 1>
 __device__ __attribute__((always_inline)) inline int wave_potrf_inv_leaf(T* A) {
   static_assert(NMAX == 8 || NMAX == 16, "row and column lanes in the first 32 lanes");
-  const int lane = threadIdx.x & (PAIR ? 31 : 63);
+  static_assert(GROUP == 1 || (GROUP == 2 && NMAX == 16) || (GROUP == 4 && NMAX == 8), "lanes");
+  const int lane = threadIdx.x & (64 / GROUP - 1);
   const bool rowl = lane < NMAX;
   const int j = lane - NMAX;
   const int idx = rowl ? lane : (j < NMAX ? j : NMAX - 1);
@@ -324,13 +339,19 @@ __device__ __attribute__((always_inline)) inline int wave_potrf_inv_leaf(T* A) {
     // it would not change (the entries above a column's diagonal stay zero, so every
     // earlier step subtracts zero from it), and a per-lane constant per column would
     // otherwise be kept in a register across the caller's loop.
-    v[k] = wave_set_lane<NMAX + k>(v[k], T(1));
-    if constexpr (PAIR) v[k] = wave_set_lane<32 + NMAX + k>(v[k], T(1));
     T piv;
-    if constexpr (PAIR)
-      piv = half_bcast<k>(v[k]);
-    else
-      piv = wave_bcast(v[k], k);
+    if constexpr (GROUP == 4) {
+      v[k] = lane == NMAX + k ? T(1) : v[k];
+      piv = row_bcast<k>(v[k]);
+    } else {
+      v[k] = wave_set_lane<NMAX + k>(v[k], T(1));
+      if constexpr (GROUP == 2) {
+        v[k] = wave_set_lane<32 + NMAX + k>(v[k], T(1));
+        piv = half_bcast<k>(v[k]);
+      } else {
+        piv = wave_bcast(v[k], k);
+      }
+    }
     if (fail < 0 && !(piv > T(0))) fail = k;
     const T inv = pivot_rsqrt(piv);
     const T y = v[k] * inv;  // L[i][k] on row lane i (>= k); Z[k][j] / L[k][k] on column lane j
@@ -392,7 +413,7 @@ struct TileCfg {
   static constexpr int KSTEPS = NMAX / 4;            // MFMA k-steps (4 k per step)
 };
 
-// This wave's 16x16 tile of op(X) Y^T (NMAX x NMAX blocks in LDS, zero padded beyond
+// acc + this wave's 16x16 tile of op(X) Y^T (NMAX x NMAX blocks in LDS, zero padded beyond
 // the used size) in MFMA accumulator layout, op(X)[r][k] = X[k][r] if transX.  The
 // contraction index is distributed as k = KSTEPS*(lane/16) + s over the MFMA steps s,
 // identically for both operands.  Blocks smaller than a tile (NMAX = 8) are masked.
@@ -404,11 +425,11 @@ constexpr bool kValu8 = true;
 
 template <typename T, int NMAX, bool TRANSX>
 __device__ __attribute__((always_inline)) inline typename Mfma<T>::acc_t mfma_tile_nt(
-    const T* X, const T* Y) {
+    const T* X, const T* Y, typename Mfma<T>::acc_t acc = {0, 0, 0, 0}) {
   constexpr int LD = Lay<NMAX>::LD;
   if constexpr (NMAX == 8 && kValu8) {
     const int l = threadIdx.x & 63, r = l >> 3, c = l & 7;
-    T a = T(0);
+    T a = acc[0];
 #pragma unroll
     for (int k = 0; k < 8; ++k) a += (TRANSX ? X[k * LD + r] : X[r * LD + k]) * Y[c * LD + k];
     return {a, T(0), T(0), T(0)};
@@ -421,7 +442,6 @@ __device__ __attribute__((always_inline)) inline typename Mfma<T>::acc_t mfma_ti
   const int r = ti * 16 + i, c = tj * 16 + i;
   const bool rin = NMAX >= 16 || r < NMAX, cin = NMAX >= 16 || c < NMAX;
   const int rr = rin ? r : 0, cc = cin ? c : 0;
-  typename Mfma<T>::acc_t acc = {0, 0, 0, 0};
 #pragma unroll
   for (int s = 0; s < KS; ++s) {
     const int k = KS * g + s;
@@ -664,7 +684,7 @@ __device__ __attribute__((always_inline)) inline int wave_potrf_inv_packed_pair(
   const int l = threadIdx.x & 63, g = l >> 4, i = l & 15;
   T* const Ab[2] = {A0, A1};
   T* const Ah = (l & 32) ? A1 : A0;
-  int fail = wave_potrf_inv_leaf<T, 16, PackedLower<0>, true>(Ah);  // A11 := L11^{-1}
+  int fail = wave_potrf_inv_leaf<T, 16, PackedLower<0>, 2>(Ah);  // A11 := L11^{-1}
   wave_lds_fence();
   // L21 = A21 L11^{-T}: out[r][c] = sum_k A21[r][k] Linv11[c][k]
   acc_t t[2];
@@ -711,7 +731,7 @@ __device__ __attribute__((always_inline)) inline int wave_potrf_inv_packed_pair(
       if (i <= r) Ab[b][P::at(16 + r, 16 + i)] = t[b][v];
     }
   wave_lds_fence();
-  const int fail2 = wave_potrf_inv_leaf<T, 16, PackedLower<16>, true>(Ah);  // A22 := L22^{-1}
+  const int fail2 = wave_potrf_inv_leaf<T, 16, PackedLower<16>, 2>(Ah);  // A22 := L22^{-1}
   wave_lds_fence();
   // W = L21 L11^{-1}: out[r][c] = sum_k L21[r][k] Linv11[k][c]
 #pragma unroll

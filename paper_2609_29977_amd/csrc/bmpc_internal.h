@@ -177,9 +177,14 @@ struct GradArgs {
 template <typename T>
 void launch_factor_pass(const FactorPassArgs& a, int nmax, hipStream_t st);
 // L^{-1} of the odd chain positions' diagonal blocks (D only), before the first pass
-// (whose arguments a are).
+// (whose arguments a are); block sizes 17..32 only.
 template <typename T>
 void launch_level1_inverse(const FactorPassArgs& a, int nmax, hipStream_t st);
+// block sizes up to 16 (tree.hip): window LDS and threads of a pass of Tw levels
+template <typename T>
+void launch_tree_pass(const FactorPassArgs& a, int nmax, hipStream_t st);
+// over mk chain positions
+size_t tree_pass_lds(bool fp64, int nmax, int Tw, int mk, int nrhs_fused, bool final);
 // block sizes 33..64: window depth 1, no fused forward substitution (factor64.hip)
 template <typename T>
 void launch_factor_pass64(const FactorPassArgs& a, hipStream_t st);

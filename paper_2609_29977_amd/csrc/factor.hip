@@ -1,4 +1,5 @@
-// Factorization kernels (Algorithm 1) for gfx950.
+// Factorization kernels (Algorithm 1) for gfx950: blocks of 17..32 (smaller ones: tree.hip,
+// larger ones: factor64.hip), and the root.
 //
 // Tail factorization, L_i = chol(Pi_i K_i Pi_i^T).  Any schedule that eliminates the
 // chain positions with their Gamma levels (position j at level tz(j)+1, Section II)
@@ -594,30 +595,21 @@ __device__ __attribute__((always_inline)) inline void eliminate(T* Aj, T* Cj, T*
   typedef typename Mfma<T>::acc_t acc_t;
   if (!have_inverse) factor_diag<T, NMAX>(Aj, perm_row0, n, info);
   const bool left = Cl != nullptr;
-  if constexpr (NMAX == 32) {
-    // G products: wave w forms row tile w % 2 of G_r (w < 2) or of G_l (w >= 2), both
-    // column tiles, skipping the zero upper quadrant of L^{-1}: 12 MFMA steps per wave
-    // instead of 16.  Without a left neighbour waves 2 and 3 have nothing to do here.
-    const int w = wave_id();
-    const int ti = w & 1;
-    acc_t g0, g1;
-    if (w < 2)
-      mfma_rowtile_lower<T, false>(Cj, Aj, ti, g0, g1);
-    else if (left)
-      mfma_rowtile_lower<T, true>(Cl, Aj, ti, g0, g1);
-    __syncthreads();
-    if (w < 2 || left) {
-      T* G = w < 2 ? Cj : Cl;
-      mfma_tile_store_at<T, false>(G, g0, T(1), ti, 0);
-      mfma_tile_store_at<T, false>(G, g1, T(1), ti, 1);
-    }
-  } else {
-    acc_t gr = mfma_tile_nt<T, NMAX, false>(Cj, Aj);
-    acc_t gl = {0, 0, 0, 0};
-    if (left) gl = mfma_tile_nt<T, NMAX, true>(Cl, Aj);
-    __syncthreads();
-    mfma_tile_store<T, NMAX, false>(Cj, gr, T(1));
-    if (left) mfma_tile_store<T, NMAX, false>(Cl, gl, T(1));
+  // G products: wave w forms row tile w % 2 of G_r (w < 2) or of G_l (w >= 2), both
+  // column tiles, skipping the zero upper quadrant of L^{-1}: 12 MFMA steps per wave
+  // instead of 16.  Without a left neighbour waves 2 and 3 have nothing to do here.
+  const int w = wave_id();
+  const int ti = w & 1;
+  acc_t g0, g1;
+  if (w < 2)
+    mfma_rowtile_lower<T, false>(Cj, Aj, ti, g0, g1);
+  else if (left)
+    mfma_rowtile_lower<T, true>(Cl, Aj, ti, g0, g1);
+  __syncthreads();
+  if (w < 2 || left) {
+    T* G = w < 2 ? Cj : Cl;
+    mfma_tile_store_at<T, false>(G, g0, T(1), ti, 0);
+    mfma_tile_store_at<T, false>(G, g1, T(1), ti, 1);
   }
   if constexpr (FWD)  // y_j = L_jj^{-1} V_j (Aj and Vj are not written in this phase)
     block_matvec<T, NMAX>(Aj, Vj, nrhs, [&](int q, int o, T v) {
@@ -631,7 +623,7 @@ __device__ __attribute__((always_inline)) inline void eliminate(T* Aj, T* Cj, T*
   // The diagonal blocks' updates are symmetric and only their lower triangles are ever
   // read (the factorization, and the lower-triangle loads of the next pass), so the
   // wave of the upper-right tile skips them.
-  const bool upper = TileCfg<NMAX>::TILES == 2 && wave_id() == 1;
+  const bool upper = w == 1;
   acc_t ur = {0, 0, 0, 0}, ul = {0, 0, 0, 0}, uf = {0, 0, 0, 0};
   if (!upper) ur = mfma_tile_nt<T, NMAX, false>(Cj, Cj);
   if (left) {
@@ -1000,12 +992,6 @@ __global__ void __launch_bounds__(TileCfg<NMAX>::NT,
   factor_pass_body<T, NMAX, FIRST, FINAL, FWD, FULL>(a, blockIdx.x);
 }
 
-// LDS entries per block of the level-1 inverse kernels.
-template <int NMAX>
-constexpr int level1_slot_entries() {
-  return NMAX == 32 ? kPacked32 : Lay<NMAX>::SZ;
-}
-
 // Level-1 inverses of the first pass.  The odd chain positions (level 1 of Gamma's
 // order) take no Schur update from the rest of the chain, so L_jj^{-1} of their
 // diagonal blocks depends on D alone (Algorithm 1's diagonal factorizations at the
@@ -1020,15 +1006,12 @@ __device__ __attribute__((always_inline)) inline void level1_inverse_body(
   FactorPassArgs a = a_in;
   if constexpr (FULL) a.n = NMAX;
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  // 32 x 32 blocks are held as their packed lower triangles (half the LDS of a padded
-  // slot, so that more waves fit on a CU), in FP64 two per wave (the diagonal leaves
-  // use 32 lanes, so one wave factors both for the issue slots of one); smaller ones in
-  // padded slots; one block per wave but for the FP64 pairs
-  constexpr bool PK = NMAX == 32;
-  constexpr int BPW = level1_blocks_per_wave(NMAX, sizeof(T) == 8);
-  constexpr int E = level1_slot_entries<NMAX>();
-  constexpr int LD = Lay<NMAX>::LD;
-  typedef typename std::conditional<PK, PackedLower<0>, RowMajor<LD>>::type Ix;
+  // blocks are held as their packed lower triangles (half the LDS of a padded slot, so that
+  // more waves fit on a CU), in FP64 two per wave (the diagonal leaves use 32 lanes, so one
+  // wave factors both for the issue slots of one)
+  constexpr int BPW = level1_blocks_per_wave(sizeof(T) == 8);
+  constexpr int E = kPacked32;
+  typedef PackedLower<0> Ix;
   const unsigned b0 = wi * BPW;
   if (b0 >= total) return;  // the whole wave leaves; no workgroup barrier follows
   T* const slot0 = reinterpret_cast<T*>(smem_raw) + wave_id() * BPW * E;
@@ -1064,7 +1047,7 @@ __device__ __attribute__((always_inline)) inline void level1_inverse_body(
 #pragma unroll
       for (int u = 0; u < NMAX * NMAX / 64; ++u) {
         const int e = 2 * (lane + 64 * (u >> 1)) + (u & 1), r = e / NMAX, c = e % NMAX;
-        if (!Ix::kLowerOnly || c <= r) slot[Ix::at(r, c)] = static_cast<T>(dv[u]);
+        if (c <= r) slot[Ix::at(r, c)] = static_cast<T>(dv[u]);
       }
     } else {
       // D's lower triangle, identity padded (zeros above the diagonal)
@@ -1076,18 +1059,16 @@ __device__ __attribute__((always_inline)) inline void level1_inverse_body(
 #pragma unroll
       for (int u = 0; u < NMAX * NMAX / 64; ++u) {
         const int e = lane + 64 * u, r = e / NMAX, c = e % NMAX;
-        if (!Ix::kLowerOnly || c <= r) slot[Ix::at(r, c)] = static_cast<T>(dv[u]);
+        if (c <= r) slot[Ix::at(r, c)] = static_cast<T>(dv[u]);
       }
     }
   }
   wave_lds_fence();
   int fail;  // pairs: per 32-lane half, that half's block
-  if constexpr (PK && BPW == 2)
+  if constexpr (BPW == 2)
     fail = wave_potrf_inv_packed_pair<T>(slot0, slot0 + E);
-  else if constexpr (PK)
-    fail = wave_potrf_inv_packed<T>(slot0);
   else
-    fail = wave_potrf_inv<T, NMAX>(slot0);
+    fail = wave_potrf_inv_packed<T>(slot0);
   {
     const int h = lane >> 5;
     if (h < BPW && (lane & 31) == 0 && b0 + h < total && fail >= 0 && fail < n) {
@@ -1111,14 +1092,7 @@ __device__ __attribute__((always_inline)) inline void level1_inverse_body(
 #pragma unroll
     for (int p0 = 0; p0 < NMAX * (NMAX + 1) / 2; p0 += 64) {
       const int p = p0 + lane;
-      if constexpr (PK) {
-        if (p < np) Li[p] = slot[p];
-      } else {
-        int r = (int)((__fsqrt_rn(8.0f * (float)p + 1.0f) - 1.0f) * 0.5f);
-        r = (r * (r + 1) / 2 > p) ? r - 1 : r;
-        r = ((r + 1) * (r + 2) / 2 <= p) ? r + 1 : r;
-        if (p < np) Li[p] = slot[r * LD + (p - r * (r + 1) / 2)];
-      }
+      if (p < np) Li[p] = slot[p];
     }
   }
 }
@@ -1361,24 +1335,17 @@ void launch_pass_t(const FactorPassArgs& a, hipStream_t st) {
 
 }  // namespace
 
-size_t factor_pass_lds_bytes(bool fp64, int nmax, int Tw, int nrhs_fused) {
+size_t factor_pass_lds_bytes(bool fp64, int nmax, int Tw, int mk, int nrhs_fused) {
   if (nmax > 32) return Tw == 1 && nrhs_fused == 0 ? factor64_lds_bytes(fp64) : ~(size_t)0;
-  if (fp64) {
-    if (nmax <= 8) return pass_lds_bytes<double, 8>(Tw, nrhs_fused);
-    if (nmax <= 16) return pass_lds_bytes<double, 16>(Tw, nrhs_fused);
-    return pass_lds_bytes<double, 32>(Tw, nrhs_fused);
-  }
-  if (nmax <= 8) return pass_lds_bytes<float, 8>(Tw, nrhs_fused);
-  if (nmax <= 16) return pass_lds_bytes<float, 16>(Tw, nrhs_fused);
-  return pass_lds_bytes<float, 32>(Tw, nrhs_fused);
+  if (nmax <= 16) return tree_pass_lds(fp64, nmax, Tw, mk, nrhs_fused, mk < (1 << Tw));
+  return fp64 ? pass_lds_bytes<double, 32>(Tw, nrhs_fused)
+              : pass_lds_bytes<float, 32>(Tw, nrhs_fused);
 }
 
 template <typename T>
 void launch_factor_pass(const FactorPassArgs& a, int nmax, hipStream_t st) {
-  if (nmax <= 8)
-    launch_pass_t<T, 8>(a, st);
-  else if (nmax <= 16)
-    launch_pass_t<T, 16>(a, st);
+  if (nmax <= 16)
+    launch_tree_pass<T>(a, nmax, st);
   else if (nmax <= 32)
     launch_pass_t<T, 32>(a, st);
   else
@@ -1393,8 +1360,8 @@ void launch_l1inv_t(const FactorPassArgs& a, hipStream_t st) {
   const int nodd = (a.m + 1) / 2;
   const unsigned total = (unsigned)a.S * (unsigned)nodd;
   if (total == 0) return;
-  constexpr unsigned PER_WG = 4 * level1_blocks_per_wave(NMAX, sizeof(T) == 8);
-  const size_t lds = PER_WG * (size_t)level1_slot_entries<NMAX>() * sizeof(T);
+  constexpr unsigned PER_WG = 4 * level1_blocks_per_wave(sizeof(T) == 8);
+  const size_t lds = PER_WG * (size_t)kPacked32 * sizeof(T);
   const dim3 grid((total + PER_WG - 1) / PER_WG);
   if (a.n == NMAX)
     hipLaunchKernelGGL((level1_inverse_kernel<T, NMAX, true>), grid, dim3(256), lds, st, a, nodd,
@@ -1407,7 +1374,7 @@ template <typename T, int NMAX>
 void launch_l1inv_multi_t(const MultiItem<FactorPassArgs>* items, int nitems, unsigned blocks,
                           bool full, const Reloc& r, hipStream_t st) {
   const size_t lds =
-      4 * (size_t)level1_blocks_per_wave(NMAX, sizeof(T) == 8) * level1_slot_entries<NMAX>() *
+      4 * (size_t)level1_blocks_per_wave(sizeof(T) == 8) * kPacked32 *
       sizeof(T);
   if (full)
     hipLaunchKernelGGL((level1_inverse_multi<T, NMAX, true>), dim3(blocks), dim3(256), lds, st,
@@ -1420,12 +1387,7 @@ void launch_l1inv_multi_t(const MultiItem<FactorPassArgs>* items, int nitems, un
 
 template <typename T>
 void launch_level1_inverse(const FactorPassArgs& a, int nmax, hipStream_t st) {
-  if (nmax <= 8)
-    launch_l1inv_t<T, 8>(a, st);
-  else if (nmax <= 16)
-    launch_l1inv_t<T, 16>(a, st);
-  else
-    launch_l1inv_t<T, 32>(a, st);
+  if (nmax == 32) launch_l1inv_t<T, 32>(a, st);
 }
 template void launch_level1_inverse<double>(const FactorPassArgs&, int, hipStream_t);
 template void launch_level1_inverse<float>(const FactorPassArgs&, int, hipStream_t);
@@ -1434,12 +1396,7 @@ template <typename T>
 void launch_level1_inverse_multi(const MultiItem<FactorPassArgs>* items, int nitems,
                                  unsigned blocks, int nmax, bool full, const Reloc& r,
                                  hipStream_t st) {
-  if (nmax <= 8)
-    launch_l1inv_multi_t<T, 8>(items, nitems, blocks, full, r, st);
-  else if (nmax <= 16)
-    launch_l1inv_multi_t<T, 16>(items, nitems, blocks, full, r, st);
-  else
-    launch_l1inv_multi_t<T, 32>(items, nitems, blocks, full, r, st);
+  if (nmax == 32) launch_l1inv_multi_t<T, 32>(items, nitems, blocks, full, r, st);
 }
 template void launch_level1_inverse_multi<double>(const MultiItem<FactorPassArgs>*, int,
                                                   unsigned, int, bool, const Reloc&,
@@ -1450,20 +1407,18 @@ template void launch_level1_inverse_multi<float>(const MultiItem<FactorPassArgs>
 template <typename T>
 void launch_factor_pass_multi(const MultiItem<FactorPassArgs>* items, int nitems,
                               unsigned blocks, int nmax, bool first, bool final, bool fwd,
-                              bool full, size_t lds, const Reloc& r, hipStream_t st) {
-  if (nmax <= 8)
-    launch_multi_pass_t<T, 8>(items, nitems, blocks, first, final, fwd, full, lds, r, st);
-  else if (nmax <= 16)
-    launch_multi_pass_t<T, 16>(items, nitems, blocks, first, final, fwd, full, lds, r, st);
+                              bool full, int W, size_t lds, const Reloc& r, hipStream_t st) {
+  if (nmax <= 16)
+    launch_tree_pass_multi<T>(items, nitems, blocks, nmax, first, final, fwd, full, W, lds, r, st);
   else
     launch_multi_pass_t<T, 32>(items, nitems, blocks, first, final, fwd, full, lds, r, st);
 }
 template void launch_factor_pass_multi<double>(const MultiItem<FactorPassArgs>*, int, unsigned,
-                                               int, bool, bool, bool, bool, size_t,
+                                               int, bool, bool, bool, bool, int, size_t,
                                                const Reloc&, hipStream_t);
 template void launch_factor_pass_multi<float>(const MultiItem<FactorPassArgs>*, int, unsigned,
-                                              int, bool, bool, bool, bool, size_t, const Reloc&,
-                                              hipStream_t);
+                                              int, bool, bool, bool, bool, int, size_t,
+                                              const Reloc&, hipStream_t);
 
 void launch_root_reduce_multi(const MultiItem<RootArgs>* items, int nitems, unsigned blocks,
                               hipStream_t st) {

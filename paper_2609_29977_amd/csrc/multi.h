@@ -106,11 +106,16 @@ struct SegRec {
 template <typename T>
 void launch_factor_pass_multi(const MultiItem<FactorPassArgs>* items, int nitems,
                               unsigned blocks, int nmax, bool first, bool final, bool fwd,
-                              bool full, size_t lds, const Reloc& r, hipStream_t st);
-// Blocks per wave of the level-1 inverse kernels for tile size nmax: FP64 32 x 32 blocks
-// in pairs (one per 32-lane half of the wave in the diagonal leaves), the others alone
-// (in FP32 a pair measured no faster).  A workgroup holds four waves.
-constexpr int level1_blocks_per_wave(int nmax, bool fp64) { return fp64 && nmax > 16 ? 2 : 1; }
+                              bool full, int W, size_t lds, const Reloc& r, hipStream_t st);
+// n <= 16 (tree.hip): W, the most positions per window of any item
+template <typename T>
+void launch_tree_pass_multi(const MultiItem<FactorPassArgs>* items, int nitems, unsigned blocks,
+                            int nmax, bool first, bool final, bool fwd, bool full, int W,
+                            size_t lds, const Reloc& r, hipStream_t st);
+// Blocks per wave of the level-1 inverse kernels (block sizes 17..32): FP64 in pairs (one per
+// 32-lane half of the wave in the diagonal leaves), FP32 alone (a pair measured no faster).
+// A workgroup holds four waves.
+constexpr int level1_blocks_per_wave(bool fp64) { return fp64 ? 2 : 1; }
 // Level-1 inverses of a ragged batch: item p0 = odd positions per chain, p1 = blocks
 // (level1_blocks_per_wave per wave, four waves per workgroup) of the system.
 template <typename T>

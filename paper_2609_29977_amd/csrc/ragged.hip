@@ -253,12 +253,12 @@ void build_factor(bmpc_plan p, Seq& seq, bool fused) {
     for (int i = 0; i < B; ++i) {
       bmpc_plan s = R.subs[i];
       const int nodd = s->d.N / 2;  // odd positions 1, 3, .. of the N - 1 chain positions
-      if (nodd == 0) continue;
+      if (nodd == 0 || s->nmax != 32) continue;
       const FactorPassArgs a = factor_pass_args(s, 0, fake(R.offD[i]), fake(R.offE[i]),
                                                 fake(R.offC[i]), nullptr, 0);
       const unsigned total = (unsigned)(s->B * s->d.S) * (unsigned)nodd;
       const unsigned per_wg =
-          4u * (unsigned)level1_blocks_per_wave(s->nmax, p->prec == BMPC_FP64);
+          4u * (unsigned)level1_blocks_per_wave(p->prec == BMPC_FP64);
       groups[std::make_tuple(s->nmax, s->d.n == s->nmax)].push_back(
           {i, a, nodd, (int)total, (total + per_wg - 1) / per_wg, 1u, 1u});
     }
@@ -296,8 +296,10 @@ void build_factor(bmpc_plan p, Seq& seq, bool fused) {
       rec.first = k == 0;
       rec.final = fin;
       rec.fwd = fused;
+      rec.kind = std::max(rec.kind, std::min(1 << s->costs.passes[k].tw, s->costs.passes[k].mk + 1));
       rec.lds = std::max(rec.lds,
-                         factor_pass_lds_bytes(s->fp64, s->nmax, s->costs.passes[k].tw, nq));
+                         factor_pass_lds_bytes(s->fp64, s->nmax, s->costs.passes[k].tw,
+                                               s->costs.passes[k].mk, nq));
     }
     for (auto& g : groups) emit(R, seq, recs[g.first], g.second);
   }
@@ -380,7 +382,7 @@ void run(bmpc_plan p, const Seq& seq, const Reloc& r) {
         case RO_FACTOR:
           launch_factor_pass_multi<T>(static_cast<const MultiItem<FactorPassArgs>*>(tab),
                                       rec.nitems, rec.blocks, rec.nmax, rec.first, rec.final,
-                                      rec.fwd, rec.full, rec.lds, r, st);
+                                      rec.fwd, rec.full, rec.kind, rec.lds, r, st);
           break;
         case RO_ROOT_REDUCE:
           launch_root_reduce_multi(static_cast<const MultiItem<RootArgs>*>(tab), rec.nitems,
