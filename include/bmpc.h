@@ -350,7 +350,7 @@ typedef struct {
  * [A, -rho^{-1} I, 0], [G, 0, -rho^{-1} I]], reduced to P + sigma I + rho A^T A +
  * rho G^T G) is this assembly with w = 0, tau = sigma and delta = 1/rho.
  * Asynchronous on stream (NULL = legacy default); allocates nothing.  The root block
- * is summed over the scenarios in scenario order (deterministic). */
+ * is summed over the scenarios in a fixed order (deterministic). */
 bmpc_status bmpc_assemble_qp(const bmpc_qp_dims* dims, const double* Q, const double* A,
                              const double* G, const double* w, double tau, double delta,
                              double* D, double* E, double* C, double* R, double* work,

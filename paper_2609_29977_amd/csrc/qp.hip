@@ -6,23 +6,22 @@
 // on the linear systems of IPM and ADMM).  In branch MPC every cost and constraint
 // term touches two neighbouring blocks, stored per link j of scenario s: link 0 couples
 // (u, v) = (x_0, x_{s,0}), link k couples (x_{s,k-1}, x_{s,k}), link N is the terminal
-// term on u = x_{s,N-1}.  With X_j = [A_j / sqrt(delta); diag(w_j + delta)^{-1/2} G_j]
-// the link's share of K is M_j = Q_j + X_j^T X_j (2n x 2n, quadrants uu, uv, vu, vv):
+// term on u = x_{s,N-1}.  The link's share of K is M_j = Q_j + delta^{-1} A_j^T A_j +
+// G_j^T (w_j + delta)^{-1} G_j (2n x 2n, quadrants uu, uv, vu, vv):
 //   D_{s,k} = tau I + M_{s,k}[vv] + M_{s,k+1}[uu]      E_{s,k} = M_{s,k+1}[vu]
 //   C_s     = M_{s,0}[uv]                             R = tau I + sum_s M_{s,0}[uu]
-// so K has exactly the root-coupled block structure the solver takes.  One workgroup
-// per tail stage stages the scaled rows of its two links in LDS, one link at a time;
-// the root block is a fixed-order sum over the scenarios.
+// so K has exactly the root-coupled block structure the solver takes.
+#include <algorithm>
 #include <mutex>
 
 #include "bmpc.h"
+#include "blockops.h"
 #include "bmpc_internal.h"
+#include "regblock.h"
 
 namespace bmpc {
 
 namespace {
-
-constexpr int QT = 256;
 
 struct QpArgs {
   int S, N, n, me, mi;
@@ -37,83 +36,188 @@ struct QpArgs {
   double* Rpart;  // [S][n][n] link-0 uu parts
 };
 
-// X (rows x 2n, row-major in LDS) of link j of scenario s: A / sqrt(delta), then the
-// G rows divided by sqrt(w + delta).
-__device__ void stage_link(const QpArgs& a, int s, int j, double* X) {
-  const int n2 = 2 * a.n, rows = a.me + a.mi;
-  const size_t link = (size_t)s * (a.N + 1) + j;
-  const double sa = 1.0 / sqrt(a.delta);
-  for (int e = threadIdx.x; e < rows * n2; e += QT) {
-    const int r = e / n2, c = e - r * n2;
-    double v;
-    if (r < a.me) {
-      v = a.A[(link * a.me + r) * n2 + c] * sa;
-    } else {
-      const int i = r - a.me;
-      v = a.G[(link * a.mi + i) * n2 + c] / sqrt(a.w[link * a.mi + i] + a.delta);
+// One wave walks a chunk of consecutive stages of one scenario, a link at a time, so that a
+// link is read once (the first link of a chunk twice, its v columns only): M_j[vv] of a
+// link waits in the accumulators for the next link's uu.  The products X^T diag X are 16 x
+// 16 x 4 FP64 MFMA tiles with the constraint rows as the contraction index: lane 16 g + i
+// holds entry (4 k + g, 16 t + i) of the rows for both operands (one load serves a tile's
+// rows and columns; the weight multiplies one of them, so no square root is taken), and Q
+// is read in the accumulator layout, so nothing is staged in LDS and all loads of a link
+// are in flight together.  Memory-bound: 8 (3 n^2 + (me + mi) 2n + mi) bytes read per link
+// and 16 n^2 written.  S = 256, N = 128, n = 16, 12 + 32 rows: 403 us with one workgroup
+// per stage and scalar products from LDS (every link read twice), 169 us
+// now (4.3 TB/s); S = 64, N = 128, n = 32: 697 -> 200 us.
+template <int NT>  // 16-column tiles of u and of v: ceil(n / 16)
+struct QpLink {
+  typedef Mfma<double>::acc_t acc_t;
+  const QpArgs& a;
+  int g, i;
+
+  // column 16 t + i of the u (off = 0) or v (off = n) part, or out of range
+  __device__ unsigned col(int t, int off) const {
+    const int c = 16 * t + i;
+    return c < a.n ? (unsigned)(off + c) * 8u : kOutOfRange;
+  }
+  // M += sum over the rows r < rows of X of wt(r) X[r][.]^T X[r][.] for the tiles asked for
+  template <bool UU, bool VU, bool UV, typename Wt>
+  __device__ void rows(__amdgpu_buffer_rsrc_t rs, int rows, Wt wt, acc_t (&uu)[NT][NT],
+                       acc_t (&vu)[NT][NT], acc_t (&vv)[NT][NT]) const {
+    constexpr int U = NT == 1 ? 8 : 3;  // steps whose loads go out together
+    constexpr bool NU = UU || VU || UV;
+    const unsigned ld = 2u * (unsigned)a.n * 8u;
+    for (int k0 = 0; 4 * k0 < rows; k0 += U) {
+      double xu[U][NT], xv[U][NT], w[U];
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        const int r = 4 * (k0 + k) + g;
+        w[k] = wt.load(r);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          // rows past the end read as zero: past the range of rs
+          if (NU) xu[k][t] = buf_load_f64(rs, (unsigned)r * ld + col(t, 0));
+          xv[k][t] = buf_load_f64(rs, (unsigned)r * ld + col(t, a.n));
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        if (4 * (k0 + k) >= rows) continue;  // uniform
+        const double s = wt.scale(w[k]);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          const double su = NU ? s * xu[k][t] : 0.0, sv = s * xv[k][t];
+#pragma unroll
+          for (int c = 0; c < NT; ++c) {
+            if (UU) uu[t][c] = Mfma<double>::mma(su, xu[k][c], uu[t][c]);
+            if (VU) vu[t][c] = Mfma<double>::mma(sv, xu[k][c], vu[t][c]);
+            if (UV) vu[t][c] = Mfma<double>::mma(su, xv[k][c], vu[t][c]);
+            vv[t][c] = Mfma<double>::mma(sv, xv[k][c], vv[t][c]);
+          }
+        }
+      }
     }
-    X[e] = v;
+  }
+  // one block (n x n at row offset ro, column offset co of a 2n x 2n array) in accumulator
+  // order; place(t, c, v): its element index, or -1
+  __device__ void quadrant(__amdgpu_buffer_rsrc_t rs, int ro, int co, acc_t (&m)[NT][NT]) const {
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int c = 0; c < NT; ++c)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int r = 16 * t + 4 * v + g, cc = 16 * c + i;
+          m[t][c][v] = buf_load_f64(rs, r < a.n && cc < a.n
+                                            ? (unsigned)((ro + r) * 2 * a.n + co + cc) * 8u
+                                            : kOutOfRange);
+        }
+  }
+  __device__ void store(double* __restrict__ dst, const acc_t (&m)[NT][NT]) const {
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int c = 0; c < NT; ++c)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int r = 16 * t + 4 * v + g, cc = 16 * c + i;
+          if (r < a.n && cc < a.n) dst[r * a.n + cc] = m[t][c][v];
+        }
+  }
+
+  struct ConstWt {
+    double s;
+    __device__ double load(int) const { return 0.0; }
+    __device__ double scale(double) const { return s; }
+  };
+  struct RowWt {
+    __amdgpu_buffer_rsrc_t rs;
+    double delta;
+    __device__ double load(int r) const { return buf_load_f64(rs, (unsigned)r * 8u); }
+    __device__ double scale(double w) const { return 1.0 / (w + delta); }
+  };
+  // the quadrants of M_j: uu (UU), vu (VU) or uv (UV) into m2, vv always
+  template <bool UU, bool VU, bool UV>
+  __device__ void link(size_t lk, acc_t (&uu)[NT][NT], acc_t (&m2)[NT][NT],
+                       acc_t (&vv)[NT][NT]) const {
+    const unsigned n = a.n, n2 = 2 * n;
+    const auto rq = block_rsrc(a.Q + lk * n2 * n2, n2 * n2 * 8u);
+    if (UU) quadrant(rq, 0, 0, uu);
+    if (VU) quadrant(rq, n, 0, m2);
+    if (UV) quadrant(rq, 0, n, m2);
+    quadrant(rq, n, n, vv);
+    if (a.me > 0)
+      rows<UU, VU, UV>(block_rsrc(a.A + lk * a.me * n2, a.me * n2 * 8u), a.me,
+                       ConstWt{1.0 / a.delta}, uu, m2, vv);
+    if (a.mi > 0)
+      rows<UU, VU, UV>(block_rsrc(a.G + lk * a.mi * n2, a.mi * n2 * 8u), a.mi,
+                       RowWt{block_rsrc(a.w + lk * a.mi, a.mi * 8u), a.delta}, uu, m2, vv);
+  }
+};
+
+template <int NT>
+__global__ void __launch_bounds__(256, 2) qp_stage_kernel(QpArgs a, int chunk, int chunks) {
+  typedef Mfma<double>::acc_t acc_t;
+  const unsigned item = blockIdx.x * 4u + (unsigned)wave_id();
+  if (item >= (unsigned)a.S * (unsigned)chunks) return;  // no barrier follows
+  const int s = (int)(item / chunks), k0 = (int)(item - (unsigned)s * chunks) * chunk;
+  const int k1 = min(a.N, k0 + chunk);
+  const int l = threadIdx.x & 63;
+  const QpLink<NT> q{a, l >> 4, l & 15};
+  const int N = a.N;
+  const size_t nn = (size_t)a.n * a.n, lk0 = (size_t)s * (N + 1);
+  acc_t uu[NT][NT], m2[NT][NT], vv[NT][NT], carry[NT][NT];
+  // link k0: its vv waits for the next link; the scenario's first one also gives C and the
+  // root's share
+  if (k0 == 0) {
+    q.template link<true, false, true>(lk0, uu, m2, carry);
+    q.store(a.Rpart + (size_t)s * nn, uu);
+    q.store(a.C + (size_t)s * nn, m2);
+  } else {
+    q.template link<false, false, false>(lk0 + k0, uu, m2, carry);
+  }
+  for (int k = k0; k < k1; ++k) {
+    q.template link<true, true, false>(lk0 + k + 1, uu, m2, vv);
+    // D_{s,k} = tau I + M_k[vv] + M_{k+1}[uu]
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int c = 0; c < NT; ++c)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const double tau = 16 * t + 4 * v + q.g == 16 * c + q.i ? a.tau : 0.0;
+          uu[t][c][v] += tau + carry[t][c][v];
+          carry[t][c][v] = vv[t][c][v];
+        }
+    q.store(a.D + ((size_t)s * N + k) * nn, uu);
+    if (k + 1 < N) q.store(a.E + ((size_t)s * (N - 1) + k) * nn, m2);
   }
 }
 
-// M_j[p][q] for rows p, q of the 2n-sized link variable (X staged in LDS)
-__device__ inline double link_entry(const QpArgs& a, int s, int j, const double* X, int p,
-                                   int q) {
-  const int n2 = 2 * a.n, rows = a.me + a.mi;
-  double acc = a.Q[(((size_t)s * (a.N + 1) + j) * n2 + p) * n2 + q];
-  for (int r = 0; r < rows; ++r) acc += X[r * n2 + p] * X[r * n2 + q];
-  return acc;
-}
-
-__global__ void __launch_bounds__(QT) qp_stage_kernel(QpArgs a) {
-  extern __shared__ double X[];  // (me + mi) x 2n
-  const int s = blockIdx.x / a.N;
-  const int k = blockIdx.x - s * a.N;
-  const int n = a.n, N = a.N;
-  const size_t nn = (size_t)n * n;
-  const size_t blk = (size_t)s * N + k;
-  // link k: its v part is stage k (D's vv share); for k = 0 also C and the root share
-  stage_link(a, s, k, X);
-  __syncthreads();
-  double dacc[(32 * 32 + QT - 1) / QT];
-  int t = 0;
-  for (int e = threadIdx.x; e < n * n; e += QT, ++t) {
-    const int r = e / n, c = e - r * n;
-    dacc[t] = (r == c ? a.tau : 0.0) + link_entry(a, s, k, X, n + r, n + c);
-    if (k == 0) {
-      a.C[(size_t)s * nn + e] = link_entry(a, s, 0, X, r, n + c);
-      a.Rpart[(size_t)s * nn + e] = link_entry(a, s, 0, X, r, c);
-    }
-  }
-  __syncthreads();
-  // link k+1: its u part is stage k (D's uu share) and, below the last stage, its
-  // vu quadrant is E_{s,k}
-  stage_link(a, s, k + 1, X);
-  __syncthreads();
-  t = 0;
-  for (int e = threadIdx.x; e < n * n; e += QT, ++t) {
-    const int r = e / n, c = e - r * n;
-    a.D[blk * nn + e] = dacc[t] + link_entry(a, s, k + 1, X, r, c);
-    if (k + 1 < N) a.E[((size_t)s * (N - 1) + k) * nn + e] = link_entry(a, s, k + 1, X, n + r, c);
-  }
-}
-
-// R = tau I + sum_s Rpart[s], in scenario order (thread per element)
+// R = tau I + sum_s Rpart[s]: 64 entries per workgroup, their scenarios over 16 waves
+// (consecutive groups, each in scenario order, the groups in order)
 __global__ void __launch_bounds__(1024) qp_root_kernel(const double* Rpart, int S, int n,
                                                        double tau, double* R) {
-  const int e = threadIdx.x;
-  if (e >= n * n) return;
-  const size_t nn = (size_t)n * n;
+  __shared__ double part[16][64];
+  const int l = threadIdx.x & 63, g = threadIdx.x >> 6;
+  const int e = blockIdx.x * 64 + l, nn = n * n;
+  const int per = (S + 15) / 16, s0 = g * per, s1 = min(S, s0 + per);
   double acc = 0.0;
-  constexpr int U = 8;
-  for (int s0 = 0; s0 < S; s0 += U) {
-    double v[U];
+  if (e < nn) {
+    constexpr int U = 16;
+    for (int s = s0; s < s1; s += U) {
+      double v[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) v[u] = s0 + u < S ? Rpart[(size_t)(s0 + u) * nn + e] : 0.0;
+      for (int u = 0; u < U; ++u) v[u] = Rpart[(size_t)min(s + u, s1 - 1) * nn + e];
 #pragma unroll
-    for (int u = 0; u < U; ++u) acc += v[u];
+      for (int u = 0; u < U; ++u) acc += s + u < s1 ? v[u] : 0.0;
+    }
   }
-  R[e] = acc + ((e / n) == (e % n) ? tau : 0.0);
+  part[g][l] = acc;
+  __syncthreads();
+  if (g == 0 && e < nn) {
+#pragma unroll
+    for (int w = 1; w < 16; ++w) acc += part[w][l];
+    R[e] = acc + (e / n == e % n ? tau : 0.0);
+  }
 }
 
 }  // namespace
@@ -181,14 +285,17 @@ extern "C" bmpc_status bmpc_assemble_qp(const bmpc_qp_dims* d, const double* Q, 
   a.C = C;
   a.Rpart = work;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  const size_t lds = (size_t)(d->me + d->mi) * 2 * d->n * sizeof(double);
-  if (lds > 64 * 1024 &&
-      hipFuncSetAttribute(reinterpret_cast<const void*>(qp_stage_kernel),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-    return BMPC_ERR_DEVICE;
-  hipLaunchKernelGGL(qp_stage_kernel, dim3((unsigned)(d->S * d->N)), dim3(QT), lds, st, a);
-  hipLaunchKernelGGL(qp_root_kernel, dim3(1), dim3(1024), 0, st, (const double*)work, d->S,
-                     d->n, tau, R);
+  // stages per wave: eight (a link in eight read twice), fewer where that would leave the GPU
+  // with less than four waves on each of its 1024 SIMDs
+  const int chunk = (int)std::min<int64_t>(8, std::max<int64_t>(1, (int64_t)d->S * d->N / 4096));
+  const int chunks = (d->N + chunk - 1) / chunk;
+  const dim3 grid((unsigned)(((int64_t)d->S * chunks + 3) / 4));
+  if (d->n <= 16)
+    hipLaunchKernelGGL(qp_stage_kernel<1>, grid, dim3(256), 0, st, a, chunk, chunks);
+  else
+    hipLaunchKernelGGL(qp_stage_kernel<2>, grid, dim3(256), 0, st, a, chunk, chunks);
+  hipLaunchKernelGGL(qp_root_kernel, dim3((unsigned)((d->n * d->n + 63) / 64)), dim3(1024), 0, st,
+                     (const double*)work, d->S, d->n, tau, R);
   return hipGetLastError() == hipSuccess ? BMPC_OK : BMPC_ERR_DEVICE;
 }
 

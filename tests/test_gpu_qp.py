@@ -87,3 +87,30 @@ def test_admm_system_through_the_ipm_assembly(precision):
     x = x.cpu().numpy()[0]
     assert np.max(np.abs(x - full)) <= 1e-9 * np.max(np.abs(full))
     plan.close()
+
+
+@pytest.mark.parametrize("S,N,n,me,mi", [(1, 1, 1, 0, 0), (3, 9, 3, 1, 0), (2, 17, 16, 0, 5),
+                                         (5, 8, 17, 4, 7), (2, 10, 32, 64, 128),
+                                         (300, 40, 9, 2, 3)])
+def test_assembly_edges_of_tiles_rows_and_chunks(S, N, n, me, mi):
+    """Blocks and constraint rows at the edges of the 16-column tiles and 4-row steps, chains
+    at the edges of a wave's chunk of stages; reference: the link sums in numpy FP64, whose
+    rounding over me + mi rows is below 1e-13 of the largest entry."""
+    import torch
+
+    from paper_2609_29977_amd import bmpc
+    rng = np.random.default_rng(n + N)
+    n2, tau, delta = 2 * n, 1e-3, 1e-2
+    Q = rng.standard_normal((S, N + 1, n2, n2))
+    A = rng.standard_normal((S, N + 1, me, n2))
+    G = rng.standard_normal((S, N + 1, mi, n2))
+    w = 10.0 ** rng.uniform(-3, 1, (S, N + 1, mi))
+    M = Q + np.swapaxes(A, 2, 3) @ A / delta + np.swapaxes(G, 2, 3) @ (G / (w + delta)[..., None])
+    I = np.eye(n)
+    ref = (tau * I + M[:, :N, n:, n:] + M[:, 1:, :n, :n], M[:, 1:N, n:, :n], M[:, 0, :n, n:],
+           tau * I + M[:, 0, :n, :n].sum(0))
+    dev = lambda a: torch.from_numpy(a).to("cuda:0")
+    got = bmpc.assemble_qp(dev(Q), dev(A), dev(G), dev(w), tau, delta)
+    for x, r in zip(got, ref):
+        if r.size:
+            assert np.max(np.abs(x.cpu().numpy() - r)) <= 1e-13 * np.max(np.abs(M)) * max(1, S // 8)
