@@ -76,7 +76,8 @@ typedef struct {
                    dimension) and without the fused forward substitution */
   int32_t nrhs; /* right-hand sides per solve, 1..4096 (Section III-B partitions each
                    right-hand side like the unknowns; their number is free).  The
-                   kernels take them in chunks of 8 (n <= 32) or 4 (n > 32). */
+                   solve kernels take them sixteen at a time, the residual eight (n <= 32)
+                   or four (n > 32). */
 } bmpc_dims;
 
 /* bmpc_options.flags */

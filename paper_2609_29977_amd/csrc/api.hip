@@ -58,7 +58,7 @@ std::vector<int> make_perm(int N) {
   return perm;
 }
 
-Costs make_costs(const bmpc_dims& d, bool fp64, int Tw1, int Tw2, int B, bool no_top_merge) {
+Costs make_costs(const bmpc_dims& d, bool fp64, int Tw1, int Tw2, int B, int flags) {
   Costs c;
   c.Tw = Tw1;
   c.Tw2 = Tw2;
@@ -154,20 +154,19 @@ Costs make_costs(const bmpc_dims& d, bool fp64, int Tw1, int Tw2, int B, bool no
   // symmetric, E and C each acting as themselves and transposed)
   c.pass_flops[KC_RESIDUAL] = q * 2.0 * (double)S * (N * nn + 2.0 * m * nn + nn);
   c.pass_flops[KC_RESIDUAL_ROOT] = q * 2.0 * ((double)S * nn + nn);
-  const int L = chain_levels(m);
   for (int k = 0; k < KC_COUNT; ++k) c.launches[k] = 1;
   if (!level1) c.launches[KC_FACTOR_L1INV] = 0;
   // the solve and residual classes run once per chunk of right-hand sides
-  const int ck = rhs_chunk(nmax_for(n));
-  const int chunks = (d.nrhs + ck - 1) / ck, last = d.nrhs - (chunks - 1) * ck;
-  for (int k : {KC_SOLVE_X_FWD, KC_SOLVE_ROOT, KC_SOLVE_X_BWD, KC_RESIDUAL, KC_RESIDUAL_ROOT})
-    c.launches[k] = chunks;
-  c.launches[KC_SOLVE_FWD] = L * chunks;
-  auto bwd_launches = [&](int q) {
-    const int top = no_top_merge ? L + 1 : bwd_top_level(m, n, q, S, B);
-    return top <= L ? top : L;  // levels below top, plus one for the rest
-  };
-  c.launches[KC_SOLVE_BWD] = (chunks - 1) * bwd_launches(ck) + bwd_launches(last);
+  const int ck = kSolveRhs, rk = residual_chunk(nmax_for(n));
+  const int chunks = (d.nrhs + ck - 1) / ck;
+  for (int k : {KC_SOLVE_X_FWD, KC_SOLVE_ROOT, KC_SOLVE_X_BWD}) c.launches[k] = chunks;
+  for (int k : {KC_RESIDUAL, KC_RESIDUAL_ROOT}) c.launches[k] = (d.nrhs + rk - 1) / rk;
+  const int64_t chains = (int64_t)B * S;
+  const bool one = d.nrhs == 1 && n <= 32;  // x_1 has a launch of its own where
+  const int top = solve_bwd_top(m, n, flags, chains, one);  // the merged levels do without it
+  c.launches[KC_SOLVE_FWD] = (solve_fwd_top(m, n, d.nrhs, flags, chains) - 1) * chunks;
+  c.launches[KC_SOLVE_BWD] =
+      (top - 1 + (!tops_together(n, chains) && top <= chain_levels(m) ? 1 : 0)) * chunks;
   // a batch of B systems does B times the work in the same launches
   for (PassPlan& pp : c.passes) {
     pp.flops *= B;
@@ -199,7 +198,16 @@ bool dims_ok(const bmpc_dims* d, int B) {
 }
 
 int flags_of(const bmpc_options* o) { return o ? o->flags : 0; }
-bool no_top_merge_of(const bmpc_options* o) { return (flags_of(o) & BMPC_FLAG_NO_BWD_TOP_MERGE) != 0; }
+int solve_fwd_top(int m, int n, int nrhs, int flags, int64_t chains) {
+  const bool merged = !(flags & BMPC_FLAG_FWD_ONE_WAVE) && tops_together(n, chains) &&
+                      (fwd_top_one(n, nrhs) || !fwd_one(n, nrhs));
+  return merged ? fwd_top_level(m, n) : chain_levels(m) + 1;
+}
+int solve_bwd_top(int m, int n, int flags, int64_t chains, bool one_vector) {
+  return (flags & BMPC_FLAG_NO_BWD_TOP_MERGE) || !(one_vector || tops_together(n, chains))
+             ? chain_levels(m) + 1
+             : bwd_top_level(m, n);
+}
 
 int systems_of(const bmpc_options* o) { return (o && o->num_systems > 0) ? o->num_systems : 1; }
 
@@ -238,12 +246,12 @@ bool dalloc(bmpc_plan p, void** ptr, size_t bytes) {
 }
 
 // The LDS of a pass includes the right-hand-side slots of the fused forward
-// substitution for one chunk of the plan's right-hand sides, so that path always fits.
+// substitution, so that path always fits.
 int pick_window_depth(bool fp64, int nmax, int nrhs, const bmpc_options* o) {
   if (nmax > 32) return 1;
   int Tw = (o && o->window_depth > 0) ? o->window_depth : default_window_depth(nmax);
   Tw = std::min(Tw, kMaxWindowDepth);
-  const int q = std::min(nrhs, rhs_chunk(nmax));
+  const int q = std::min(nrhs, kMaxRhs);
   while (Tw > 1 && factor_pass_lds_bytes(fp64, nmax, Tw, 1 << Tw, q) > (size_t)kLdsBudget) --Tw;
   return Tw;
 }
@@ -323,13 +331,14 @@ FactorPassArgs factor_pass_args(bmpc_plan p, int k, const double* D, const doubl
 ResidualArgs residual_args(bmpc_plan p, int c, const double* D, const double* E,
                            const double* C, const double* R, const double* b, const double* x,
                            double* r, bool knorm) {
-  const size_t off = (size_t)c * p->chunk * vec_len(p);
+  const int rk = residual_chunk(p->nmax);
+  const size_t off = (size_t)c * rk * vec_len(p);
   ResidualArgs ra{};
   ra.S = p->d.S;
   ra.B = p->B;
   ra.N = p->d.N;
   ra.n = p->d.n;
-  ra.nrhs = chunk_rhs(p, c);
+  ra.nrhs = std::min(rk, p->d.nrhs - c * rk);
   ra.vsys = (size_t)p->d.nrhs * vec_len(p);
   ra.D = D;
   ra.E = E;
@@ -342,7 +351,7 @@ ResidualArgs residual_args(bmpc_plan p, int c, const double* D, const double* E,
   ra.done = p->flags;
   ra.kper = p->kper;
   ra.rpart = p->rpart;
-  ra.rnorm = p->rnorm + c * p->chunk;
+  ra.rnorm = p->rnorm + c * rk;
   ra.seg_sys = p->d.nrhs;
   if (knorm) {
     ra.knorm_part = p->kpart;
@@ -414,56 +423,70 @@ SolveArgs solve_args(bmpc_plan p, const double* b, double* x, int q0, int nq) {
 template <typename T>
 void enqueue_solve_back(bmpc_plan p, const SolveArgs& a) {
   hipStream_t st = p->stream;
-  const int L = chain_levels(p->m);
   timed(p, KC_SOLVE_ROOT, [&] { launch_solve_root(a, st); });
-  timed(p, KC_SOLVE_X_BWD, [&] { launch_solve_x_bwd<T>(a, p->nmax, st); });
-  // the top levels (few positions per chain) in one launch, the others one by one
-  const int top = (p->opt_flags & BMPC_FLAG_NO_BWD_TOP_MERGE)
-                      ? L + 1
-                      : bwd_top_level(p->m, p->d.n, a.nrhs, p->d.S, p->B);
-  if (top <= L) timed(p, KC_SOLVE_BWD, [&] { launch_solve_bwd_top<T>(a, top, st); });
-  for (int l = std::min(L, top - 1); l >= 1; --l)
-    timed(p, KC_SOLVE_BWD, [&] { launch_solve_bwd_level<T>(a, l, p->nmax, st); });
+  // x_1 and the top levels (few positions per chain) in one launch, the others one by one; one
+  // right-hand side merges the top levels also where there are too many chains for that
+  const bool one = a.nrhs == 1 && a.n <= 32;
+  const int64_t chains = (int64_t)p->B * p->d.S;
+  const int L = chain_levels(p->m), top = solve_bwd_top(p->m, a.n, p->opt_flags, chains, one);
+  const bool together = tops_together(a.n, chains);
+  timed(p, KC_SOLVE_X_BWD, [&] {
+    if (one && together)
+      launch_solve_bwd_top<T>(a, top, true, st);
+    else
+      launch_mm_top<T>(a, together ? top : L + 1, false, st);
+  });
+  if (!together && top <= L)
+    timed(p, KC_SOLVE_BWD, [&] { launch_solve_bwd_top<T>(a, top, false, st); });
+  for (int l = top - 1; l >= 1; --l)
+    timed(p, KC_SOLVE_BWD, [&] { launch_solve_bwd_level<T>(a, l, st); });
 }
 
 template <typename T>
 void enqueue_solve_chunk(bmpc_plan p, const SolveArgs& a) {
   hipStream_t st = p->stream;
-  const int L = chain_levels(p->m);
-  for (int l = 1; l <= L; ++l)
-    timed(p, KC_SOLVE_FWD, [&] { launch_solve_fwd_level<T>(a, l, p->nmax, st); });
-  timed(p, KC_SOLVE_X_FWD, [&] { launch_solve_x_fwd<T>(a, p->nmax, st); });
+  const int top = solve_fwd_top(p->m, a.n, a.nrhs, p->opt_flags, (int64_t)p->B * p->d.S);
+  for (int l = 1; l < top; ++l)
+    timed(p, KC_SOLVE_FWD, [&] { launch_solve_fwd_level<T>(a, l, st); });
+  timed(p, KC_SOLVE_X_FWD, [&] {
+    if (fwd_top_one(a.n, a.nrhs) && top <= chain_levels(p->m))
+      launch_solve_fwd_top<T>(a, top, st);
+    else
+      launch_mm_top<T>(a, top, true, st);
+  });
   enqueue_solve_back<T>(p, a);
 }
 
 // Algorithm 2 for every chunk of right-hand sides in turn (the scratch y, w, x0 is
 // sized for one chunk); mod adjusts each chunk's arguments (refinement scaling).
 template <typename T, typename Mod>
-void enqueue_solve(bmpc_plan p, const double* b, double* x, int first_chunk, Mod mod) {
-  for (int c = first_chunk; c < chunks_of(p); ++c) {
+void enqueue_solve(bmpc_plan p, const double* b, double* x, Mod mod) {
+  for (int c = 0; c < chunks_of(p); ++c) {
     SolveArgs a = solve_args(p, b, x, c * p->chunk, chunk_rhs(p, c));
     mod(a, c * p->chunk);
     enqueue_solve_chunk<T>(p, a);
   }
 }
 template <typename T>
-void enqueue_solve(bmpc_plan p, const double* b, double* x, int first_chunk = 0) {
-  enqueue_solve<T>(p, b, x, first_chunk, [](SolveArgs&, int) {});
+void enqueue_solve(bmpc_plan p, const double* b, double* x) {
+  enqueue_solve<T>(p, b, x, [](SolveArgs&, int) {});
 }
 
-// Factor, then the whole solve of b into x with the first chunk's forward substitution
-// inside the factorization.
+// Factor, then the whole solve of b into x, with the forward substitution inside the
+// factorization for up to kMaxRhs right-hand sides.
 template <typename T>
 void enqueue_factor_solve(bmpc_plan p, const double* D, const double* E, const double* C,
                           const double* R, const double* b, double* x) {
-  if (p->nmax > 32) {  // no forward substitution inside the n > 32 factor passes
+  const int nrhs = p->d.nrhs;
+  if (p->nmax > 32 || nrhs > kMaxRhs) {
+    // the n > 32 factor passes take none; more right-hand sides than the passes take go
+    // through the separate forward sweep together, which reads the factor once for sixteen
     enqueue_factor<T>(p, D, E, C, R);
     enqueue_solve<T>(p, b, x);
     return;
   }
-  enqueue_factor<T>(p, D, E, C, R, b, chunk_rhs(p, 0));
-  enqueue_solve_back<T>(p, solve_args(p, b, x, 0, chunk_rhs(p, 0)));
-  enqueue_solve<T>(p, b, x, 1);
+  enqueue_factor<T>(p, D, E, C, R, b, nrhs);
+  enqueue_solve_back<T>(p, solve_args(p, b, x, 0, nrhs));
 }
 
 bmpc_status last_error_status() {
@@ -503,14 +526,14 @@ bmpc_status init_plan(bmpc_plan p, const bmpc_dims* dims, bmpc_precision prec, v
   p->Tw2 = pick_later_depth(p->fp64, p->nmax, dims->N, dims->nrhs, p->Tw, opts);
   p->B = systems_of(opts);
   p->opt_flags = flags_of(opts);
-  p->chunk = rhs_chunk(p->nmax);
+  p->chunk = kSolveRhs;
   p->stream = reinterpret_cast<hipStream_t>(stream);
-  p->costs = make_costs(*dims, p->fp64, p->Tw, p->Tw2, p->B, no_top_merge_of(opts));
+  p->costs = make_costs(*dims, p->fp64, p->Tw, p->Tw2, p->B, flags_of(opts));
   p->perm = make_perm(dims->N);
   p->permpos = make_permpos(dims->N);
   p->groups = std::min(dims->S, 32);
   const int B = p->B, N = dims->N, n = dims->n, nrhs = dims->nrhs;
-  const int cq = std::min(nrhs, p->chunk);  // right-hand sides of one chunk
+  const int cq = std::min(nrhs, p->chunk);  // right-hand sides of one chunk of a solve
   const size_t S = (size_t)B * dims->S;  // chains of the batch
   const size_t nn = (size_t)n * n, tb = p->fp64 ? 8 : 4;
   const size_t len = ((size_t)dims->S * N + 1) * n;
@@ -624,7 +647,7 @@ bmpc_status bmpc_cost_model(const bmpc_dims* dims, bmpc_precision prec,
   const bool fp64 = prec == BMPC_FP64;
   const int Tw = pick_window_depth(fp64, nmax_for(dims->n), dims->nrhs, opts);
   const int Tw2 = pick_later_depth(fp64, nmax_for(dims->n), dims->N, dims->nrhs, Tw, opts);
-  Costs c = make_costs(*dims, fp64, Tw, Tw2, systems_of(opts), no_top_merge_of(opts));
+  Costs c = make_costs(*dims, fp64, Tw, Tw2, systems_of(opts), flags_of(opts));
   std::memset(cost, 0, sizeof(*cost));
   cost->factor_flops = c.factor_flops;
   cost->solve_flops = c.solve_flops;
@@ -697,7 +720,7 @@ bmpc_status bmpc_solve(bmpc_plan p, const double* b, double* x) {
 }
 
 // x = K^{-1} b by refinement (see bmpc_refine); with fused, the factor is issued here
-// and the first solve's forward part (first chunk of right-hand sides) runs inside it.
+// and the first solve's forward part runs inside it (enqueue_factor_solve).
 static bmpc_status refine_impl(bmpc_plan p, const double* D, const double* E, const double* C,
                                const double* R, const double* b, double* x, double tol,
                                int32_t max_iters, bool fused) {
@@ -733,7 +756,8 @@ static bmpc_status refine_impl(bmpc_plan p, const double* D, const double* E, co
   // r = b - K x for every chunk; the first residual of a backward-error loop also takes
   // the row sums of |K|
   auto residual = [&](bool knorm) {
-    for (int c = 0; c < chunks_of(p); ++c) {
+    const int rk = residual_chunk(p->nmax);
+    for (int c = 0; c * rk < nrhs; ++c) {
       const ResidualArgs ra = residual_args(p, c, D, E, C, R, b, x, p->rbuf, knorm && c == 0);
       timed(p, KC_RESIDUAL, [&] { launch_residual(ra, p->nmax, st); });
       timed(p, KC_RESIDUAL_ROOT, [&] { launch_residual_root(ra, st); });
@@ -748,9 +772,9 @@ static bmpc_status refine_impl(bmpc_plan p, const double* D, const double* E, co
       c.accumulate = 1;
     };
     if (p->fp64)
-      enqueue_solve<double>(p, p->rbuf, x, 0, mod);
+      enqueue_solve<double>(p, p->rbuf, x, mod);
     else
-      enqueue_solve<float>(p, p->rbuf, x, 0, mod);
+      enqueue_solve<float>(p, p->rbuf, x, mod);
   };
   bool stopped = false;  // the host saw the stop test hold
   for (int it = 0; it < max_iters; ++it) {

@@ -26,13 +26,16 @@
 namespace bmpc {
 
 constexpr int kFactorThreads = 256;
-constexpr int kSolveThreads = 64;
-// Right-hand sides per kernel launch: the solve, the fused forward substitution and the
-// residual take them in chunks of at most kMaxRhs (kMaxRhs64 at n > 32, where the
-// residual's LDS holds fewer vectors); a plan's nrhs has no such limit.
+// Right-hand sides per kernel launch: a solve takes them in chunks of kSolveRhs (the columns
+// of an MFMA tile), the residual in chunks of kMaxRhs (kMaxRhs64 at n > 32, where its LDS
+// holds fewer vectors), and up to kMaxRhs of them go through the factorization with the
+// forward substitution inside; a plan's nrhs has no such limit.
+constexpr int kSolveRhs = 16;
 constexpr int kMaxRhs = 8;
 constexpr int kMaxRhs64 = 4;
-constexpr __host__ __device__ int rhs_chunk(int nmax) { return nmax > 32 ? kMaxRhs64 : kMaxRhs; }
+constexpr __host__ __device__ int residual_chunk(int nmax) {
+  return nmax > 32 ? kMaxRhs64 : kMaxRhs;
+}
 
 // Blocks per chain in the G_l and G_r arrays: the N-1 blocks of the positions 1..N-1,
 // padded to N so that every factor array (L^{-1} has N) shares one chain stride; the
@@ -49,11 +52,11 @@ enum KernelClass : int {
   KC_FACTOR_FINAL,   // last factor pass + the x_1 step (F, U)
   KC_ROOT_REDUCE,    // partial sums of U over scenario groups
   KC_ROOT_POTRF,     // R~ = R - sum U, L_R = chol(R~)
-  KC_SOLVE_FWD,      // tail forward substitution, one launch per level
-  KC_SOLVE_X_FWD,    // x_1 forward step + F y products
+  KC_SOLVE_FWD,      // tail forward substitution, one launch per level below the top ones
+  KC_SOLVE_X_FWD,    // top forward levels, x_1 forward step + F y products
   KC_SOLVE_ROOT,     // root reduction and root triangular solves
-  KC_SOLVE_X_BWD,    // root propagation and x_1 backward step
-  KC_SOLVE_BWD,      // tail backward substitution, one launch per level
+  KC_SOLVE_X_BWD,    // root propagation, x_1 backward step, top backward levels
+  KC_SOLVE_BWD,      // tail backward substitution, one launch per level below the top ones
   KC_RESIDUAL,       // FP64 tail residual b - K x
   KC_RESIDUAL_ROOT,  // FP64 root residual
   KC_REFINE_MISC,    // refinement bookkeeping (norm reset, stop test)
@@ -95,7 +98,7 @@ struct FactorPassArgs {
   unsigned long long* info;
   // Forward substitution fused into the elimination (null b: factor only).  b is the
   // FP64 right-hand side in the vector layout of the solve ([B][nrhs][len]); y
-  // receives L^{-1} Pi b per chain position ([S][N][nrhs][n], precision T) and w the
+  // receives L^{-1} Pi b per chain position ([S][N][n][nrhs], precision T) and w the
   // FP64 products F_s y_X ([S][nrhs][n]).  The vector accumulators mirror accR /
   // accL / accX per right-hand side ([S][stride][nrhs][n] and [S][npass][nrhs][n]).
   const double* b;       // right-hand side q = 0 of this chunk (b + q0 * len)
@@ -126,7 +129,7 @@ struct SolveArgs {
   const double* LR;
   const double* b;       // [nrhs][len] FP64 input
   double* x;             // [nrhs][len] FP64 output
-  void* y;               // [S][N][nrhs][n] scratch, precision T
+  void* y;               // [S][N][n][nrhs] scratch, precision T
   double* w;             // [S][nrhs][n] FP64 products F_s y_X
   double* x0;            // [nrhs][n]
   const double* rnorm;   // refinement: input scale 1/rnorm, output x += rnorm * d
@@ -200,25 +203,27 @@ void launch_root_potrf(const double* R, const double* part, int B, int groups, i
                        unsigned long long* info, hipStream_t st);
 
 template <typename T>
-void launch_solve_fwd_level(const SolveArgs& a, int level, int nmax, hipStream_t st);
-template <typename T>
-void launch_solve_x_fwd(const SolveArgs& a, int nmax, hipStream_t st);
+void launch_solve_fwd_level(const SolveArgs& a, int level, hipStream_t st);
 void launch_solve_root(const SolveArgs& a, hipStream_t st);
 template <typename T>
-void launch_solve_x_bwd(const SolveArgs& a, int nmax, hipStream_t st);
+void launch_solve_bwd_level(const SolveArgs& a, int level, hipStream_t st);
+// The backward levels from the top down to level_lo in one launch (one workgroup per chain,
+// one wave per position), for one right-hand side and n <= 32; with_x: root propagation and
+// the x_1 backward step before them.  level_lo as bwd_top_level has it or above.
 template <typename T>
-void launch_solve_bwd_level(const SolveArgs& a, int level, int nmax, hipStream_t st);
-// The backward levels from level_lo up to the top, in one launch (one workgroup per
-// chain, one wave per position, top level first); only where bwd_top_level says so.
+void launch_solve_bwd_top(const SolveArgs& a, int level_lo, bool with_x, hipStream_t st);
+// The forward levels from level_lo up to the top and the x_1 forward step in one launch, where
+// fwd_top_one says so.
 template <typename T>
-void launch_solve_bwd_top(const SolveArgs& a, int level_lo, hipStream_t st);
+void launch_solve_fwd_top(const SolveArgs& a, int level_lo, hipStream_t st);
 
-// block sizes 33..64 (solve64.hip): one level of either sweep, the x_1 forward step
-// (fwd) or root propagation + x_1 backward step
+// the same as matrix products over the right-hand sides (solve_rhs.hip): one level of either
+// sweep; the x_1 forward step after the forward levels from level_lo on (fwd), or root
+// propagation and the x_1 backward step before the backward levels down to level_lo
 template <typename T>
-void launch_solve64_level(const SolveArgs& a, int level, bool fwd, hipStream_t st);
+void launch_mm_level(const SolveArgs& a, int level, bool fwd, hipStream_t st);
 template <typename T>
-void launch_solve64_x(const SolveArgs& a, bool fwd, hipStream_t st);
+void launch_mm_top(const SolveArgs& a, int level_lo, bool fwd, hipStream_t st);
 
 // Workgroups of the tail residual per chain of N stages with blocks of n.
 int residual_walks(int N, int n);
@@ -260,18 +265,51 @@ __host__ __device__ inline int chain_levels(int m) {
   return L;  // floor(log2 m) + 1 for m >= 1, 0 for m = 0
 }
 
-// Positions per chain up to which backward levels share one launch.
-constexpr int kBwdTopWaves = 8;
-// Lowest backward level walked by launch_solve_bwd_top: the levels with at most
-// kBwdTopWaves positions per chain, when the plan's backward levels use the one-vector
-// kernels (one right-hand side, n = 8, 16 or 32, S and B within the grid's y and z
-// limits); otherwise chain_levels(m) + 1, i.e. no level.
-inline int bwd_top_level(int m, int n, int nrhs, int S, int B) {
-  const int L = chain_levels(m);
-  if ((n != 8 && n != 16 && n != 32) || nrhs != 1 || S > 65535 || B > 65535) return L + 1;
-  int l = L + 1;
-  while (l > 1 && level_count(m, l - 1) <= kBwdTopWaves) --l;
+// The top levels of a sweep have few positions per chain; they can share one launch with the
+// x_1 step, mm_top_waves waves per chain (solve_rhs.hip).  How many of its waves are there for each of
+// count positions; the pulls that a wave has in flight (as its registers allow: with two at n
+// = 32 in FP64, a solve at S = N = 128 with twelve right-hand sides took 259 us instead of 254,
+// at S = 300, N = 200 with three 652 instead of 633); the waves that the pulls occupy.
+constexpr __host__ __device__ int mm_top_waves(int n) { return n <= 32 ? 8 : 4; }
+constexpr __host__ __device__ int mm_top_share(int n, int count) {
+  return mm_top_waves(n) / (count <= 1 ? 1 : count <= 2 ? 2 : count <= 4 ? 4 : 8);
+}
+constexpr __host__ __device__ int mm_pulls_per_wave(int n, bool fp64) {
+  return n <= 16 || (n <= 32 && !fp64) ? 2 : 1;
+}
+constexpr __host__ __device__ int mm_pull_waves(int n, bool fp64, int pulls, int most) {
+  const int w = mm_pulls_per_wave(n, fp64) == 2 ? (pulls + 1) / 2 : pulls;
+  return w < 1 ? 1 : (w < most ? w : most);
+}
+// Lowest level of either sweep that may go into that launch (chain_levels(m) + 1: none):
+// backward, as many positions per chain as it has waves; forward, half as many.
+inline int bwd_top_level(int m, int n) {
+  int l = chain_levels(m) + 1;
+  while (l > 1 && level_count(m, l - 1) <= mm_top_waves(n)) --l;
   return l;
 }
+__host__ __device__ inline int fwd_top_level(int m, int n) {
+  int l = chain_levels(m) + 1;
+  while (l > 1 && level_count(m, l - 1) <= mm_top_waves(n) / 2) --l;
+  return l;
+}
+// Waves of a forward level's workgroup: as many as its pulls occupy, at most four, or for the levels that may go into that launch as many as they would have there, so
+// that the sums do not depend on whether they do.
+__host__ __device__ inline int mm_fwd_waves(int m, int n, bool fp64, int level) {
+  return mm_pull_waves(n, fp64, 2 * (level - 1), level >= fwd_top_level(m, n)
+                                                     ? mm_top_share(n, level_count(m, level))
+                                                     : 4);
+}
+// One right-hand side with full blocks goes forward through the one-vector kernels; their merged
+// launch exists up to n = 16, the levels of n = 32 stay single.
+constexpr bool fwd_one(int n, int nrhs) { return nrhs == 1 && (n == 8 || n == 16 || n == 32); }
+constexpr bool fwd_top_one(int n, int nrhs) { return fwd_one(n, nrhs) && n <= 16; }
+// Whether they do, for so many chains in the launch: up to what the GPU holds at once (256
+// compute units with one workgroup each for n > 16, two below).  Beyond that the barriers
+// cost more than the launches they replace.  One solve, together / apart: one right-hand side
+// at S = 100, N = 160, n = 16 in FP32 58 / 66 us, at S = 512, N = 64 65 / 68 (96 / 95 at S =
+// 768 with matrix products); four at n = 32, N = 64 in FP32 80 / 95 us at S = 128, 113 / 128
+// at 256, 177 / 171 at 384; at S = 5000, N = 16, n = 16 in FP64 383 / 303.
+constexpr bool tops_together(int n, int64_t chains) { return chains <= (n <= 16 ? 512 : 256); }
 
 }  // namespace bmpc

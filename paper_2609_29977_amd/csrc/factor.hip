@@ -614,7 +614,7 @@ __device__ __attribute__((always_inline)) inline void eliminate(T* Aj, T* Cj, T*
   if constexpr (FWD)  // y_j = L_jj^{-1} V_j (Aj and Vj are not written in this phase)
     block_matvec<T, NMAX>(Aj, Vj, nrhs, [&](int q, int o, T v) {
       Yt[q * NMAX + o] = v;
-      if (o < n) gy[q * n + o] = v;
+      if (o < n) gy[o * nrhs + q] = v;
     });
   __syncthreads();
   if (!have_inverse) slot_store_packed<T, NMAX>(gLinv, Aj, n);
@@ -968,7 +968,7 @@ __device__ __attribute__((always_inline)) inline void factor_pass_body(
       T* Yx = sl.VR();  // the X updates are folded into Vx; VR now holds y_X
       block_matvec<T, NMAX>(Ax, Vx, nr, [&](int q, int o, T v) {
         Yx[q * NMAX + o] = v;
-        if (o < n) yx[q * n + o] = v;
+        if (o < n) yx[o * nr + q] = v;
       });
       __syncthreads();
       const int o = threadIdx.x / TPR, p = threadIdx.x % TPR;

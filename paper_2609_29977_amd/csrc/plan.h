@@ -46,7 +46,7 @@ struct bmpc_plan_s {
   int m = 0, nmax = 8, Tw = 1, Tw2 = 1, groups = 1;
   int B = 1;      // systems in the batch
   int opt_flags = 0;  // BMPC_FLAG_*
-  int chunk = bmpc::kMaxRhs;  // right-hand sides per launch
+  int chunk = bmpc::kSolveRhs;  // right-hand sides per launch of a solve
   int refine_stop = BMPC_STOP_CORRECTION;
   hipStream_t stream = nullptr;
   bmpc::Costs costs;
@@ -106,12 +106,14 @@ namespace bmpc {
 size_t factor_pass_lds_bytes(bool fp64, int nmax, int Tw, int mk, int nrhs_fused);
 int pick_later_depth(bool fp64, int nmax, int N, int nrhs, int Tw, const bmpc_options* o);
 int nmax_for(int n);
-Costs make_costs(const bmpc_dims& d, bool fp64, int Tw, int Tw2, int B, bool no_top_merge);
+Costs make_costs(const bmpc_dims& d, bool fp64, int Tw, int Tw2, int B, int flags);
 std::vector<int> make_permpos(int N);
 std::vector<int> make_perm(int N);
 bool dims_ok(const bmpc_dims* d, int B = 1);
 int flags_of(const bmpc_options* o);
-bool no_top_merge_of(const bmpc_options* o);
+// First levels of the merged launches of each sweep (see fwd_top_level), for so many chains.
+int solve_fwd_top(int m, int n, int nrhs, int flags, int64_t chains);
+int solve_bwd_top(int m, int n, int flags, int64_t chains, bool one_vector);
 int pick_window_depth(bool fp64, int nmax, int nrhs, const bmpc_options* o);
 bool dalloc(bmpc_plan p, void** ptr, size_t bytes);
 void free_plan_memory(bmpc_plan p);

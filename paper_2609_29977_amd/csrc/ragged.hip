@@ -34,7 +34,7 @@ enum RaggedOp {
 
 struct LaunchRec {
   int op = 0, cls = 0;
-  int nmax = 32, kind = 0;
+  int nmax = 32, kind = 0, n = 32;
   bool first = false, final = false, fwd = false, full = false;
   size_t table = 0;  // byte offset of the item table in the device table buffer
   int nitems = 0;
@@ -47,7 +47,8 @@ struct RaggedState {
   std::vector<bmpc_plan> subs;
   std::vector<int> rank;  // position of each system in the item order (largest work first)
   std::vector<size_t> offD, offE, offC, offR, offV, rows;  // element offsets (B + 1 each)
-  int nrhs = 1, chunk = kMaxRhs, chunks = 1;
+  int64_t chains = 0;  // of all systems
+  int nrhs = 1, chunk = kSolveRhs, chunks = 1, rchunks = 1;  // of the solves, of the residual
   char* arena = nullptr;
   char* dtab = nullptr;
   std::vector<unsigned char> htab;
@@ -106,8 +107,11 @@ void emit(RaggedState& R, Seq& seq, LaunchRec rec, std::vector<Pending<Args>> it
 const double* fake(size_t el) { return rel_field<const double>(el); }
 double* fake_w(size_t el) { return rel_field<double>(el); }
 
-// The steps of one solve chunk from the root step on (root step, x_1 backward step,
-// merged top backward levels, backward levels).
+// Systems that share the one-vector kernels of a launch: block bound, full blocks or not.
+int one_class(bmpc_plan s) { return 2 * s->nmax + (s->d.n == s->nmax ? 1 : 0); }
+
+// The steps of one solve chunk from the root step on (root step, x_1 backward step with
+// the top backward levels, the other backward levels).
 void build_back(RaggedState& R, Seq& seq, const std::vector<SolveArgs>& args, int q0) {
   (void)q0;
   const int B = (int)R.subs.size();
@@ -121,98 +125,115 @@ void build_back(RaggedState& R, Seq& seq, const std::vector<SolveArgs>& args, in
     rec.threads = 1024;
     emit(R, seq, rec, items);
   }
-  std::map<int, std::vector<Pending<SolveArgs>>> xb, top;
+  // (kind, class) -> items: x_1 with the top levels, or where there are too many chains for
+  // that x_1, and for one right-hand side the top levels after it
+  std::map<std::tuple<int, int>, std::vector<Pending<SolveArgs>>> x, top;
   int maxL = 0;
-  std::vector<int> topl(B), L(B);
+  std::vector<int> topl(B);
   for (int i = 0; i < B; ++i) {
     bmpc_plan s = R.subs[i];
-    xb[s->nmax].push_back({i, args[i], 0, 0, (unsigned)s->d.S, 1u, 1u});
-    L[i] = chain_levels(s->m);
-    topl[i] = (s->opt_flags & BMPC_FLAG_NO_BWD_TOP_MERGE)
-                  ? L[i] + 1
-                  : bwd_top_level(s->m, s->d.n, args[i].nrhs, s->d.S, 1);
-    if (topl[i] <= L[i]) top[s->nmax].push_back({i, args[i], topl[i], 0, (unsigned)s->d.S, 1u, 1u});
-    maxL = std::max(maxL, L[i]);
+    const bool one = args[i].nrhs == 1, together = tops_together(s->d.n, R.chains);
+    const int L = chain_levels(s->m);
+    topl[i] = solve_bwd_top(s->m, s->d.n, s->opt_flags, R.chains, one);
+    if (one && together)
+      x[std::make_tuple((int)SK_BWD_TOP, one_class(s))].push_back(
+          {i, args[i], topl[i], 1, (unsigned)s->d.S, 1u, 1u});
+    else
+      x[std::make_tuple((int)SK_MM_TOP, mm_class(s->d.n))].push_back(
+          {i, args[i], together ? topl[i] : L + 1, 0, (unsigned)s->d.S, 1u, 1u});
+    if (!together && topl[i] <= L)
+      top[std::make_tuple((int)SK_BWD_TOP, one_class(s))].push_back(
+          {i, args[i], topl[i], 0, (unsigned)s->d.S, 1u, 1u});
+    maxL = std::max(maxL, topl[i] - 1);
   }
-  for (auto& g : xb) {
-    LaunchRec rec;
-    rec.op = RO_SOLVE;
-    rec.cls = KC_SOLVE_X_BWD;
-    rec.kind = SK_X_BWD;
-    rec.nmax = g.first;
-    rec.threads = kSolveThreads;
-    emit(R, seq, rec, g.second);
-  }
-  for (auto& g : top) {
-    LaunchRec rec;
-    rec.op = RO_SOLVE;
-    rec.cls = KC_SOLVE_BWD;
-    rec.kind = SK_BWD_TOP;
-    rec.nmax = g.first;
-    rec.threads = 64 * kBwdTopWaves;
-    emit(R, seq, rec, g.second);
-  }
+  for (auto* groups : {&x, &top})
+    for (auto& g : *groups) {
+      LaunchRec rec;
+      rec.op = RO_SOLVE;
+      rec.cls = groups == &x ? KC_SOLVE_X_BWD : KC_SOLVE_BWD;
+      rec.kind = std::get<0>(g.first);
+      rec.n = g.second[0].a.n;
+      rec.fwd = false;
+      for (const auto& it : g.second)
+        rec.threads = std::max(rec.threads, mm_top_config(it.a, it.p0, false, true).threads);
+      emit(R, seq, rec, g.second);
+    }
   for (int l = maxL; l >= 1; --l) {
-    std::map<std::tuple<int, int, bool>, std::vector<Pending<SolveArgs>>> groups;
-    std::map<std::tuple<int, int, bool>, LaunchRec> recs;
+    std::map<std::tuple<int, int>, std::vector<Pending<SolveArgs>>> groups;
+    std::map<std::tuple<int, int>, LaunchRec> recs;
     for (int i = 0; i < B; ++i) {
       bmpc_plan s = R.subs[i];
-      if (l > L[i] || l >= topl[i]) continue;
+      if (l >= topl[i]) continue;
       const LevelCfg c = solve_level_config(args[i], l, false, s->nmax, s->fp64);
       if (c.count <= 0) continue;
-      const auto key = std::make_tuple(s->nmax, c.kind, c.full);
+      const auto key =
+          std::make_tuple(c.kind, c.kind == SK_LEVEL ? mm_class(s->d.n) : one_class(s));
       groups[key].push_back({i, args[i], l, c.count, c.gx, c.gy, c.gz});
       LaunchRec& rec = recs[key];
       rec.op = RO_SOLVE;
+      rec.n = s->d.n;
       rec.cls = KC_SOLVE_BWD;
       rec.kind = c.kind;
-      rec.nmax = s->nmax;
       rec.fwd = false;
-      rec.full = c.full;
-      rec.threads = c.threads;
+      rec.threads = std::max(rec.threads, c.threads);
       rec.lds = std::max(rec.lds, c.lds);
     }
     for (auto& g : groups) emit(R, seq, recs[g.first], g.second);
   }
 }
 
-// Forward sweep and x_1 forward step of one chunk.
+// Forward sweep of one chunk, its top levels with the x_1 forward step.
 void build_fwd(RaggedState& R, Seq& seq, const std::vector<SolveArgs>& args) {
   const int B = (int)R.subs.size();
   int maxL = 0;
-  for (int i = 0; i < B; ++i) maxL = std::max(maxL, chain_levels(R.subs[i]->m));
+  std::vector<int> topl(B);
+  for (int i = 0; i < B; ++i) {
+    topl[i] = solve_fwd_top(R.subs[i]->m, R.subs[i]->d.n, args[i].nrhs, R.subs[i]->opt_flags,
+                            R.chains);
+    maxL = std::max(maxL, topl[i] - 1);
+  }
   for (int l = 1; l <= maxL; ++l) {
-    std::map<std::tuple<int, int, bool>, std::vector<Pending<SolveArgs>>> groups;
-    std::map<std::tuple<int, int, bool>, LaunchRec> recs;
+    std::map<std::tuple<int, int>, std::vector<Pending<SolveArgs>>> groups;
+    std::map<std::tuple<int, int>, LaunchRec> recs;
     for (int i = 0; i < B; ++i) {
       bmpc_plan s = R.subs[i];
-      if (l > chain_levels(s->m)) continue;
+      if (l >= topl[i]) continue;
       const LevelCfg c = solve_level_config(args[i], l, true, s->nmax, s->fp64);
       if (c.count <= 0) continue;
-      const auto key = std::make_tuple(s->nmax, c.kind, c.full);
+      const auto key =
+          std::make_tuple(c.kind, c.kind == SK_LEVEL ? mm_class(s->d.n) : one_class(s));
       groups[key].push_back({i, args[i], l, c.count, c.gx, c.gy, c.gz});
       LaunchRec& rec = recs[key];
       rec.op = RO_SOLVE;
+      rec.n = s->d.n;
       rec.cls = KC_SOLVE_FWD;
       rec.kind = c.kind;
-      rec.nmax = s->nmax;
       rec.fwd = true;
-      rec.full = c.full;
       rec.threads = std::max(rec.threads, c.threads);
       rec.lds = std::max(rec.lds, c.lds);
     }
     for (auto& g : groups) emit(R, seq, recs[g.first], g.second);
   }
-  std::map<int, std::vector<Pending<SolveArgs>>> xf;
-  for (int i = 0; i < B; ++i)
-    xf[R.subs[i]->nmax].push_back({i, args[i], 0, 0, (unsigned)R.subs[i]->d.S, 1u, 1u});
+  std::map<std::tuple<int, int>, std::vector<Pending<SolveArgs>>> xf;
+  for (int i = 0; i < B; ++i) {
+    bmpc_plan s = R.subs[i];
+    const bool one = fwd_top_one(s->d.n, args[i].nrhs) && topl[i] <= chain_levels(s->m);
+    xf[std::make_tuple((int)(one ? SK_FWD_TOP : SK_MM_TOP),
+                       one ? one_class(s) : mm_class(s->d.n))]
+        .push_back({i, args[i], topl[i], 0, (unsigned)s->d.S, 1u, 1u});
+  }
   for (auto& g : xf) {
     LaunchRec rec;
     rec.op = RO_SOLVE;
     rec.cls = KC_SOLVE_X_FWD;
-    rec.kind = SK_X_FWD;
-    rec.nmax = g.first;
-    rec.threads = kSolveThreads;
+    rec.kind = std::get<0>(g.first);
+    rec.n = g.second[0].a.n;
+    rec.fwd = true;
+    for (const auto& it : g.second) {
+      const MmTopCfg c = mm_top_config(it.a, it.p0, true, R.subs[0]->fp64);
+      rec.threads = std::max(rec.threads, c.threads);
+      rec.lds = std::max(rec.lds, c.lds);
+    }
     emit(R, seq, rec, g.second);
   }
 }
@@ -393,7 +414,7 @@ void run(bmpc_plan p, const Seq& seq, const Reloc& r) {
                                   rec.blocks, rec.nmax, r, st);
           break;
         case RO_SOLVE:
-          launch_solve_multi<T>(rec.kind, rec.fwd, rec.full, rec.nmax,
+          launch_solve_multi<T>(rec.kind, rec.fwd, rec.n,
                                 static_cast<const MultiItem<SolveArgs>*>(tab), rec.nitems,
                                 rec.blocks, rec.threads, rec.lds, r, st);
           break;
@@ -422,9 +443,9 @@ bool ralloc(RaggedState& R, void** ptr, size_t bytes) {
 }
 
 template <typename T>
-void solve_all(bmpc_plan p, const Reloc& r, int first_chunk) {
+void solve_all(bmpc_plan p, const Reloc& r) {
   RaggedState& R = *p->ragged;
-  for (int c = first_chunk; c < R.chunks; ++c) run<T>(p, R.solve[c], r);
+  for (int c = 0; c < R.chunks; ++c) run<T>(p, R.solve[c], r);
 }
 
 }  // namespace
@@ -468,19 +489,22 @@ bmpc_status ragged_factor(bmpc_plan p, const double* D, const double* E, const d
                           const double* R_, const double* b, double* x) {
   RaggedState& R = *p->ragged;
   const Reloc r{D, E, C, R_, b, x, nullptr};
-  const bool fused = b != nullptr;
+  // more right-hand sides than the factor passes take: the separate forward sweep serves them
+  const bool fused = b != nullptr && R.nrhs <= kMaxRhs;
   if (p->fp64)
     run<double>(p, R.factor[fused ? 1 : 0], r);
   else
     run<float>(p, R.factor[fused ? 1 : 0], r);
   if (fused) {
-    if (p->fp64) {
+    if (p->fp64)
       run<double>(p, R.back0, r);
-      solve_all<double>(p, r, 1);
-    } else {
+    else
       run<float>(p, R.back0, r);
-      solve_all<float>(p, r, 1);
-    }
+  } else if (b) {
+    if (p->fp64)
+      solve_all<double>(p, r);
+    else
+      solve_all<float>(p, r);
   }
   const bmpc_status st = last_error_status();
   if (st == BMPC_OK) {
@@ -493,9 +517,9 @@ bmpc_status ragged_factor(bmpc_plan p, const double* D, const double* E, const d
 bmpc_status ragged_solve(bmpc_plan p, const double* b, double* x) {
   const Reloc r{nullptr, nullptr, nullptr, nullptr, b, x, nullptr};
   if (p->fp64)
-    solve_all<double>(p, r, 0);
+    solve_all<double>(p, r);
   else
-    solve_all<float>(p, r, 0);
+    solve_all<float>(p, r);
   return last_error_status();
 }
 
@@ -515,7 +539,7 @@ bmpc_status ragged_refine(bmpc_plan p, const double* D, const double* E, const d
   const Reloc rr{D, E, C, R_, b, x, R.rbuf};        // residual into rbuf
   const Reloc rc{nullptr, nullptr, nullptr, nullptr, R.rbuf, x, R.rbuf};  // correction
   auto residual = [&](bool knorm) {
-    for (int c = 0; c < R.chunks; ++c) {
+    for (int c = 0; c < R.rchunks; ++c) {
       if (p->fp64)
         run<double>(p, R.resid[knorm ? 1 : 0][c], rr);
       else
@@ -617,6 +641,7 @@ bmpc_status bmpc_analyze_ragged(int32_t B, const bmpc_dims* dims, bmpc_precision
     bmpc_plan s = new (std::nothrow) bmpc_plan_s();
     if (!s) return fail(BMPC_ERR_ALLOC);
     R.subs.push_back(s);
+    R.chains += dims[i].S;
     s->parent = p;
     s->measure = true;
     const bmpc_options so = sys_opts(i);
@@ -643,8 +668,9 @@ bmpc_status bmpc_analyze_ragged(int32_t B, const bmpc_dims* dims, bmpc_precision
   R.offR.assign(B + 1, 0);
   R.offV.assign(B + 1, 0);
   R.rows.assign(B + 1, 0);
-  R.chunk = kMaxRhs;
+  R.chunk = kSolveRhs;
   R.chunks = (R.nrhs + R.chunk - 1) / R.chunk;
+  R.rchunks = (R.nrhs + kMaxRhs - 1) / kMaxRhs;
   for (int i = 0; i < B; ++i) {
     const bmpc_dims& d = dims[i];
     const size_t nn = (size_t)d.n * d.n;
@@ -704,11 +730,11 @@ bmpc_status bmpc_analyze_ragged(int32_t B, const bmpc_dims* dims, bmpc_precision
   for (int k = 0; k < B; ++k) R.rank[order[k]] = k;
   // launch tables
   build_factor(p, R.factor[0], false);
-  build_factor(p, R.factor[1], true);
+  if (R.nrhs <= kMaxRhs) build_factor(p, R.factor[1], true);
   R.solve.resize(R.chunks);
   R.corr.resize(R.chunks);
-  R.resid[0].resize(R.chunks);
-  R.resid[1].resize(R.chunks);
+  R.resid[0].resize(R.rchunks);
+  R.resid[1].resize(R.rchunks);
   for (int c = 0; c < R.chunks; ++c) {
     const std::vector<SolveArgs> a = chunk_args(p, c, false);
     build_fwd(R, R.solve[c], a);
@@ -717,6 +743,8 @@ bmpc_status bmpc_analyze_ragged(int32_t B, const bmpc_dims* dims, bmpc_precision
     const std::vector<SolveArgs> ca = chunk_args(p, c, true);
     build_fwd(R, R.corr[c], ca);
     build_back(R, R.corr[c], ca, c * R.chunk);
+  }
+  for (int c = 0; c < R.rchunks; ++c) {
     build_residual(p, R.resid[0][c], c, false);
     build_residual(p, R.resid[1][c], c, true);
   }

@@ -12,6 +12,7 @@
 #include "bmpc_internal.h"
 #include "multi.h"
 #include "regblock.h"
+#include "solve_common.h"
 
 namespace bmpc {
 
@@ -65,7 +66,7 @@ template <int NMAX, bool FULL>
 struct StageFetch {
   static constexpr int RES_T = res_threads<NMAX>();
   static constexpr int PER = (NMAX * NMAX + RES_T - 1) / RES_T;
-  static constexpr int VPER = (rhs_chunk(NMAX) * NMAX + RES_T - 1) / RES_T;
+  static constexpr int VPER = (residual_chunk(NMAX) * NMAX + RES_T - 1) / RES_T;
   double d[PER], e[PER], xv[VPER], bv[VPER];
 
   // Element of the block held in v[u]: with PAIRS, v[2h] and v[2h+1] are two
@@ -355,36 +356,6 @@ __device__ inline double strided_max(const double* p, int cnt, int t0, int step,
     for (int u = 0; u < U; ++u) m = i0 + u * step < cnt ? nan_max(t[u], m) : m;
   }
   return m;
-}
-
-// Sum of v[s][q][i] over the scenarios s = g, g + G, .. < S for the QB right-hand sides
-// q0 .. of nv (n elements each), B scenarios' loads in flight; then over the lanes of the
-// wave that hold element i.
-template <int NMAX, int QB, int B>
-__device__ inline void scenario_sums(const double* __restrict__ v, int S, int n, int nv, int q0,
-                                     double (&acc)[QB]) {
-  constexpr int G = 1024 / NMAX;
-  const int i = threadIdx.x % NMAX, g = threadIdx.x / NMAX;
-#pragma unroll
-  for (int q = 0; q < QB; ++q) acc[q] = 0.0;
-  if (i < n) {
-    for (int s0 = g; s0 < S; s0 += G * B) {
-      double w[QB][B];
-#pragma unroll
-      for (int u = 0; u < B; ++u) {
-        const double* p = v + ((size_t)min(s0 + G * u, S - 1) * nv) * n + i;
-#pragma unroll
-        for (int q = 0; q < QB; ++q) w[q][u] = p[(size_t)min(q0 + q, nv - 1) * n];
-      }
-#pragma unroll
-      for (int q = 0; q < QB; ++q)
-#pragma unroll
-        for (int u = 0; u < B; ++u) acc[q] += s0 + G * u < S ? w[q][u] : 0.0;
-    }
-  }
-#pragma unroll
-  for (int q = 0; q < QB; ++q)
-    for (int off = NMAX; off < 64; off <<= 1) acc[q] += __shfl_xor(acc[q], off);
 }
 
 // One workgroup per system: the root rows of r, and the largest |r| of each right-hand
@@ -834,10 +805,10 @@ static void launch_residual_t(const ResidualArgs& a, dim3 grid, int chunks, hipS
     if (!attr_set) {
       (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&residual_kernel<NMAX, true>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)residual_lds_bytes<NMAX>(rhs_chunk(NMAX)));
+                                (int)residual_lds_bytes<NMAX>(residual_chunk(NMAX)));
       (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&residual_kernel<NMAX, false>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)residual_lds_bytes<NMAX>(rhs_chunk(NMAX)));
+                                (int)residual_lds_bytes<NMAX>(residual_chunk(NMAX)));
       attr_set = true;
     }
   }

@@ -366,7 +366,7 @@ __device__ __attribute__((always_inline)) inline void tree_pass_body(const Facto
         // each right-hand side is read before its place takes y
         wave_matvec<T, NMAX>(Aj, Vj, nr, [&](int q, int o, T v) {
           Vj[q * NMAX + o] = v;
-          if (o < n) yj[q * n + o] = v;
+          if (o < n) yj[o * nr + q] = v;
         });
       }
       wave_lds_fence();
@@ -494,7 +494,7 @@ __device__ __attribute__((always_inline)) inline void tree_pass_body(const Facto
       T* yx = ych + (size_t)(N - 1) * vs;
       wave_matvec<T, NMAX>(AX, Vx, nr, [&](int q, int o, T v) {
         Vx[q * NMAX + o] = v;
-        if (o < n) yx[q * n + o] = v;
+        if (o < n) yx[o * nr + q] = v;
       });
       wave_lds_fence();
       constexpr int TPR = 64 / NMAX, CPT = NMAX / TPR;
