@@ -59,8 +59,8 @@ def _hold_until_freed(ctx, key, plan):
     weakref.finalize(ctx, _release, key, plan)
 
 
-def _refined(plan, D, E, C, R, b, tol, iters, what):
-    x = plan.refine(D, E, C, R, b, tol=tol, max_iters=iters)
+def _refined(solve, plan, D, E, C, R, b, tol, iters, what):
+    x = solve(D, E, C, R, b, tol=tol, max_iters=iters)
     if check_convergence:
         it, rel, ok = plan.stats()
         if not ok:
@@ -89,11 +89,11 @@ class BranchSolve(torch.autograd.Function):
         key, plan = _acquire(S, N, n, nrhs, precision)
         D, C, R, b = D.contiguous(), C.contiguous(), R.contiguous(), b.contiguous()
         E = E.contiguous() if N > 1 else None
-        plan.factor(D, E, C, R)
         if plan.precision == bmpc.FP64:
-            x = plan.solve(b)
+            x = plan.factor_solve(D, E, C, R, b)
         else:
-            x = _refined(plan, D, E, C, R, b, refine_tol, refine_iters, "branch_solve forward")
+            x = _refined(plan.factor_refine, plan, D, E, C, R, b, refine_tol, refine_iters,
+                         "branch_solve forward")
         _hold_until_freed(ctx, key, plan)
         ctx.refine = (refine_tol, refine_iters)
         if plan.precision == bmpc.FP64:
@@ -113,8 +113,8 @@ class BranchSolve(torch.autograd.Function):
             # the adjoint is refined like the forward solve (FP64 residuals)
             x, D, E, C, R = ctx.saved_tensors
             tol, iters = ctx.refine
-            lam = _refined(plan, D, E if ctx.N > 1 else None, C, R, gx.contiguous(), tol, iters,
-                           "branch_solve backward")
+            lam = _refined(plan.refine, plan, D, E if ctx.N > 1 else None, C, R,
+                           gx.contiguous(), tol, iters, "branch_solve backward")
         dD, dE, dC, dR = plan.grad_blocks(x, lam)
         return dD, (dE if ctx.N > 1 else None), dC, dR, lam, None, None, None
 
@@ -136,12 +136,11 @@ class BatchedBranchSolve(torch.autograd.Function):
         key, plan = _acquire(S, N, n, nrhs, precision, num_systems=B)
         D, C, R, b = D.contiguous(), C.contiguous(), R.contiguous(), b.contiguous()
         E = E.contiguous() if N > 1 else None
-        plan.factor(D, E, C, R)
         if plan.precision == bmpc.FP64:
-            x = plan.solve(b)
+            x = plan.factor_solve(D, E, C, R, b)
             ctx.save_for_backward(x)
         else:
-            x = _refined(plan, D, E, C, R, b, refine_tol, refine_iters,
+            x = _refined(plan.factor_refine, plan, D, E, C, R, b, refine_tol, refine_iters,
                          "batched_branch_solve forward")
             ctx.save_for_backward(x, D, E if N > 1 else torch.empty(0, device=D.device), C, R)
         _hold_until_freed(ctx, key, plan)
@@ -159,8 +158,8 @@ class BatchedBranchSolve(torch.autograd.Function):
         else:
             x, D, E, C, R = ctx.saved_tensors
             tol, iters = ctx.refine
-            lam = _refined(plan, D, E if ctx.N > 1 else None, C, R, gx.contiguous(), tol, iters,
-                           "batched_branch_solve backward")
+            lam = _refined(plan.refine, plan, D, E if ctx.N > 1 else None, C, R,
+                           gx.contiguous(), tol, iters, "batched_branch_solve backward")
         dD, dE, dC, dR = plan.grad_blocks(x, lam)
         B, S, N, n = ctx.shapes
         dE = dE.view(B, S, N - 1, n, n) if N > 1 else None
