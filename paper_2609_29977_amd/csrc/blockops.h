@@ -1,7 +1,10 @@
 // Dense n x n block operations on LDS-resident blocks (n <= NMAX <= 32), gfx950.
 //
-// A block lives in LDS row-major with a padded leading dimension LD = NMAX + 1 so
-// that column walks hit distinct banks.  All helpers are called by every thread of
+// A block lives in LDS row-major with a padded leading dimension so that column walks
+// and MFMA operand reads (16 rows by neighbouring columns) hit distinct banks: NMAX + 1,
+// at 32 two more.  (At 33 the operand reads of 32 lanes met in pairs: a third of the FP64
+// first pass's LDS cycles were conflicts; 1716 -> 1664 us at S = 512, N = 256, in FP32 805 ->
+// 788.)  All helpers are called by every thread of
 // the workgroup (NT threads) unless the name says "wave"; helpers that write LDS end
 // with a workgroup barrier.
 #pragma once
@@ -16,7 +19,7 @@ namespace bmpc {
 
 template <int NMAX>
 struct Lay {
-  static constexpr int LD = NMAX + 1;
+  static constexpr int LD = NMAX == 32 ? 34 : NMAX + 1;
   static constexpr int SZ = NMAX * LD;
 };
 
