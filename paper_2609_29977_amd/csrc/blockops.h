@@ -222,51 +222,20 @@ __device__ inline double pivot_rsqrt(double x) {
 
 // In place: A (symmetric NMAX x NMAX, lower triangle read; pad smaller blocks with an
 // identity block) := L with L L^T = A, zeros above the diagonal.  One wave, lane i
-// keeps row i; column k of L is broadcast to the other rows: up to 32 rows as a DPP
-// row-broadcast operand of each multiply-add (as in the inverse leaves), 64 rows with
-// readlane.  Returns (on every lane) the 0-based row of the first non-positive pivot,
+// keeps row i; column k of L is broadcast to the other rows as a DPP row-broadcast operand
+// of each multiply-add (as in the inverse leaves).  Returns (on every lane) the 0-based row of the first non-positive pivot,
 // or -1.
-template <typename T, int NMAX>
+template <typename T, int NMAX, int LD = Lay<NMAX>::LD>
 __device__ __attribute__((always_inline)) inline int wave_potrf(T* A) {
-  constexpr int LD = Lay<NMAX>::LD;
+  static_assert(NMAX <= 32, "larger blocks: block_chol");
   const int lane = threadIdx.x & 63;
   const int row = lane < NMAX ? lane : NMAX - 1;
   T a[NMAX];
 #pragma unroll
   for (int c = 0; c < NMAX; ++c) a[c] = A[row * LD + c];
   int fail = -1;
-  if constexpr (NMAX <= 32) {
-    static_for<NMAX>([&](auto kc) {
-      constexpr int k = decltype(kc)::value;
-      const T piv = wave_bcast(a[k], k);
-      if (fail < 0 && !(piv > T(0))) fail = k;
-      const T inv = pivot_rsqrt(piv);
-      const T lik = (lane == k) ? piv * inv : a[k] * inv;
-      a[k] = lik;
-      if constexpr (k + 1 < NMAX) {
-        // L[c][k] is lik on lane c.  With 32 rows both 16-lane rows get a copy of rows
-        // 0-15 (lo) and of rows 16-31 (hi); entry c of every lane then takes one
-        // multiply-add whose first factor is lane c % 16 of the copy holding row c.
-        T lo = lik, hi = lik;
-        if constexpr (NMAX == 32) rows_both(lik, lo, hi);
-        static_for<NMAX - 1 - k>([&](auto uc) {
-          constexpr int u = decltype(uc)::value, c = k + 1 + u;
-          // the first use of each copy waits for its write
-          if constexpr (c < 16)
-            row_bcast_fms<c, u == 0>(a[c], lo, lik);
-          else
-            row_bcast_fms<c - 16, u == 0 || c == 16>(a[c], hi, lik);
-        });
-      }
-    });
-    if (lane < NMAX) {
-#pragma unroll
-      for (int c = 0; c < NMAX; ++c) A[lane * LD + c] = (c <= lane) ? a[c] : T(0);
-    }
-    return fail;
-  }
-#pragma unroll
-  for (int k = 0; k < NMAX; ++k) {
+  static_for<NMAX>([&](auto kc) {
+    constexpr int k = decltype(kc)::value;
     const T piv = wave_bcast(a[k], k);
     if (fail < 0 && !(piv > T(0))) fail = k;
     // L[k][k] = piv * piv^{-1/2} and L[i][k] = a[i][k] * piv^{-1/2}: one refined
@@ -274,9 +243,22 @@ __device__ __attribute__((always_inline)) inline int wave_potrf(T* A) {
     const T inv = pivot_rsqrt(piv);
     const T lik = (lane == k) ? piv * inv : a[k] * inv;
     a[k] = lik;
-#pragma unroll
-    for (int c = k + 1; c < NMAX; ++c) a[c] -= lik * wave_bcast(lik, c);
-  }
+    if constexpr (k + 1 < NMAX) {
+      // L[c][k] is lik on lane c.  With 32 rows both 16-lane rows get a copy of rows
+      // 0-15 (lo) and of rows 16-31 (hi); entry c of every lane then takes one
+      // multiply-add whose first factor is lane c % 16 of the copy holding row c.
+      T lo = lik, hi = lik;
+      if constexpr (NMAX == 32) rows_both(lik, lo, hi);
+      static_for<NMAX - 1 - k>([&](auto uc) {
+        constexpr int u = decltype(uc)::value, c = k + 1 + u;
+        // the first use of each copy waits for its write
+        if constexpr (c < 16)
+          row_bcast_fms<c, u == 0>(a[c], lo, lik);
+        else
+          row_bcast_fms<c - 16, u == 0 || c == 16>(a[c], hi, lik);
+      });
+    }
+  });
   if (lane < NMAX) {
 #pragma unroll
     for (int c = 0; c < NMAX; ++c) A[lane * LD + c] = (c <= lane) ? a[c] : T(0);

@@ -27,6 +27,7 @@
 #include <type_traits>
 
 #include "bmpc_internal.h"
+#include "blockchol.h"
 #include "blockops.h"
 #include "multi.h"
 #include "regblock.h"
@@ -1149,6 +1150,7 @@ __device__ __attribute__((always_inline)) inline void root_potrf_body(
     unsigned long long* info, unsigned bx) {
   constexpr int LD = NMAX + 1;
   __shared__ double A[NMAX * LD];
+  __shared__ double scratch[16 * 17];
   // one workgroup per system of the batch
   const int sys = bx;
   R += (size_t)sys * n * n;
@@ -1175,14 +1177,11 @@ __device__ __attribute__((always_inline)) inline void root_potrf_body(
     A[r * LD + c] = v;
   }
   __syncthreads();
-  if (threadIdx.x < 64) {
-    const int fail = wave_potrf<double, NMAX>(A);
-    if (fail >= 0 && fail < n && threadIdx.x == 0) atomicMin(info, row_base + fail + 1);
-  }
-  __syncthreads();
+  const int fail = block_chol<double, NMAX / 16, LD, 16, false>(A, scratch);
+  if (fail >= 0 && fail < n && threadIdx.x == 64) atomicMin(info, row_base + fail + 1);
   for (int e = threadIdx.x; e < NMAX * NMAX; e += blockDim.x) {
     const int r = e / NMAX, c = e % NMAX;
-    if (r < n && c < n) LR[r * n + c] = A[r * LD + c];
+    if (r < n && c < n) LR[r * n + c] = c <= r ? A[r * LD + c] : 0.0;
   }
 }
 
@@ -1453,6 +1452,9 @@ void launch_root_potrf(const double* R, const double* part, int B, int groups, i
                        LR, (unsigned long long)sys_rows, (unsigned long long)root_row, info);
   else if (n <= 32)
     hipLaunchKernelGGL(root_potrf_kernel<32>, dim3(B), dim3(1024), 0, st, R, part, groups, n,
+                       LR, (unsigned long long)sys_rows, (unsigned long long)root_row, info);
+  else if (n <= 48)
+    hipLaunchKernelGGL(root_potrf_kernel<48>, dim3(B), dim3(1024), 0, st, R, part, groups, n,
                        LR, (unsigned long long)sys_rows, (unsigned long long)root_row, info);
   else
     hipLaunchKernelGGL(root_potrf_kernel<64>, dim3(B), dim3(1024), 0, st, R, part, groups, n,
