@@ -156,6 +156,8 @@ Costs make_costs(const bmpc_dims& d, bool fp64, int Tw1, int Tw2, int B, int fla
   c.pass_flops[KC_RESIDUAL_ROOT] = q * 2.0 * ((double)S * nn + nn);
   for (int k = 0; k < KC_COUNT; ++k) c.launches[k] = 1;
   if (!level1) c.launches[KC_FACTOR_L1INV] = 0;
+  if (B == 1) c.launches[KC_FACTOR_INIT] = 0;
+  if (S <= 32) c.launches[KC_ROOT_REDUCE] = 0;
   // the solve and residual classes run once per chunk of right-hand sides
   const int ck = kSolveRhs, rk = residual_chunk(nmax_for(n));
   const int chunks = (d.nrhs + ck - 1) / ck;
@@ -310,7 +312,7 @@ FactorPassArgs factor_pass_args(bmpc_plan p, int k, const double* D, const doubl
   a.F = p->F;
   a.U = p->U;
   a.permpos = p->d_permpos;
-  a.info = p->d_info;
+  a.info = p->d_acc;
   if (b) {
     a.b = b;
     a.nrhs = nq;
@@ -361,12 +363,31 @@ ResidualArgs residual_args(bmpc_plan p, int c, const double* D, const double* E,
   return ra;
 }
 
+RootStep root_step(bmpc_plan p, const double* R) {
+  const bmpc_dims& d = p->d;
+  RootStep s{};
+  s.R = R;
+  s.part = p->groups == d.S ? p->U : p->Upart;
+  s.LR = p->LR;
+  s.info = p->d_acc;
+  s.info_out = p->d_acc == p->d_info ? nullptr : p->d_info;
+  s.n = d.n;
+  s.groups = p->groups;
+  s.root_row = (unsigned long long)d.S * d.N * d.n;
+  s.sys_rows = s.root_row + d.n;
+  return s;
+}
+
+// The factorization up to the sums of U over the groups of scenarios (each scenario its own
+// group up to 32, which takes no launch); launch_root_potrf or launch_root_factor_solve
+// completes it.
 template <typename T>
-void enqueue_factor(bmpc_plan p, const double* D, const double* E, const double* C,
-                    const double* R, const double* b = nullptr, int nq = 0) {
+void enqueue_factor_tails(bmpc_plan p, const double* D, const double* E, const double* C,
+                          const double* b, int nq) {
   const bmpc_dims& d = p->d;
   hipStream_t st = p->stream;
-  timed(p, KC_FACTOR_INIT, [&] { launch_factor_init(p->d_info, st); });
+  if (p->d_acc == p->d_info)
+    timed(p, KC_FACTOR_INIT, [&] { launch_factor_init(p->d_info, st); });
   const int npass = (int)p->costs.passes.size();
   if (p->nmax == 32 && d.N > 1) {
     const FactorPassArgs a0 = factor_pass_args(p, 0, D, E, C, nullptr, 0);
@@ -378,14 +399,16 @@ void enqueue_factor(bmpc_plan p, const double* D, const double* E, const double*
     const int cls = pp.is_final ? KC_FACTOR_FINAL : (k == 0 ? KC_FACTOR_FIRST : KC_FACTOR_MID);
     timed(p, cls, [&] { launch_factor_pass<T>(a, p->nmax, st); });
   }
-  timed(p, KC_ROOT_REDUCE,
-        [&] { launch_root_reduce(p->U, p->Upart, p->B, d.S, d.n, p->groups, st); });
-  const int64_t root_row = (int64_t)d.S * d.N * d.n;
-  const int64_t sys_rows = root_row + d.n;
-  timed(p, KC_ROOT_POTRF, [&] {
-    launch_root_potrf(R, p->Upart, p->B, p->groups, d.n, p->LR, sys_rows, root_row, p->d_info,
-                      st);
-  });
+  if (p->groups != d.S)
+    timed(p, KC_ROOT_REDUCE,
+          [&] { launch_root_reduce(p->U, p->Upart, p->B, d.S, d.n, p->groups, st); });
+}
+
+template <typename T>
+void enqueue_factor(bmpc_plan p, const double* D, const double* E, const double* C,
+                    const double* R) {
+  enqueue_factor_tails<T>(p, D, E, C, nullptr, 0);
+  timed(p, KC_ROOT_POTRF, [&] { launch_root_potrf(root_step(p, R), p->B, p->stream); });
 }
 
 size_t vec_len(bmpc_plan p) { return ((size_t)p->d.S * p->d.N + 1) * p->d.n; }
@@ -418,12 +441,10 @@ SolveArgs solve_args(bmpc_plan p, const double* b, double* x, int q0, int nq) {
   return a;
 }
 
-// Root step, root propagation and tail backward substitution (Algorithm 2 from its root
-// step on), given the y and w of the forward part.
+// Root propagation and tail backward substitution (Algorithm 2 after its root step).
 template <typename T>
 void enqueue_solve_back(bmpc_plan p, const SolveArgs& a) {
   hipStream_t st = p->stream;
-  timed(p, KC_SOLVE_ROOT, [&] { launch_solve_root(a, st); });
   // x_1 and the top levels (few positions per chain) in one launch, the others one by one; one
   // right-hand side merges the top levels also where there are too many chains for that
   const bool one = a.nrhs == 1 && a.n <= 32;
@@ -454,6 +475,7 @@ void enqueue_solve_chunk(bmpc_plan p, const SolveArgs& a) {
     else
       launch_mm_top<T>(a, top, true, st);
   });
+  timed(p, KC_SOLVE_ROOT, [&] { launch_solve_root(a, st); });
   enqueue_solve_back<T>(p, a);
 }
 
@@ -473,20 +495,28 @@ void enqueue_solve(bmpc_plan p, const double* b, double* x) {
 }
 
 // Factor, then the whole solve of b into x, with the forward substitution inside the
-// factorization for up to kMaxRhs right-hand sides.
+// factorization for up to kMaxRhs right-hand sides; flags: refinement flags to reset.
 template <typename T>
 void enqueue_factor_solve(bmpc_plan p, const double* D, const double* E, const double* C,
-                          const double* R, const double* b, double* x) {
+                          const double* R, const double* b, double* x, int* flags = nullptr) {
   const int nrhs = p->d.nrhs;
-  if (p->nmax > 32 || nrhs > kMaxRhs) {
+  const bool inside = p->nmax <= 32 && nrhs <= kMaxRhs;
+  RootStep step = root_step(p, R);
+  if (inside && step.info_out)
+    step.flags = flags;
+  else if (flags)
+    timed(p, KC_REFINE_MISC, [&] { launch_refine_reset(flags, p->stream); });
+  if (!inside) {
     // the n > 32 factor passes take none; more right-hand sides than the passes take go
     // through the separate forward sweep together, which reads the factor once for sixteen
     enqueue_factor<T>(p, D, E, C, R);
     enqueue_solve<T>(p, b, x);
     return;
   }
-  enqueue_factor<T>(p, D, E, C, R, b, nrhs);
-  enqueue_solve_back<T>(p, solve_args(p, b, x, 0, nrhs));
+  const SolveArgs a = solve_args(p, b, x, 0, nrhs);
+  enqueue_factor_tails<T>(p, D, E, C, b, nrhs);
+  timed(p, KC_SOLVE_ROOT, [&] { launch_root_factor_solve(step, a, p->stream); });
+  enqueue_solve_back<T>(p, a);
 }
 
 bmpc_status last_error_status() {
@@ -551,8 +581,7 @@ bmpc_status init_plan(bmpc_plan p, const bmpc_dims* dims, bmpc_precision prec, v
             dalloc(p, (void**)&p->LR, (size_t)B * nn * 8) &&
             dalloc(p, &p->accX, S * npass * nn * tb) &&
             dalloc(p, &p->vaccX, S * npass * cq * n * tb) &&
-            dalloc(p, (void**)&p->d_permpos, (size_t)N * sizeof(int)) &&
-            dalloc(p, (void**)&p->d_info, sizeof(unsigned long long)) &&
+            dalloc(p, (void**)&p->d_info, 2 * sizeof(*p->d_info) + (size_t)N * sizeof(int)) &&
             dalloc(p, &p->y, S * N * cq * n * tb) &&
             dalloc(p, (void**)&p->w, S * cq * n * 8) &&
             dalloc(p, (void**)&p->x0, (size_t)B * cq * n * 8) &&
@@ -566,6 +595,10 @@ bmpc_status init_plan(bmpc_plan p, const bmpc_dims* dims, bmpc_precision prec, v
             (p->parent || dalloc(p, (void**)&p->knorm, (size_t)B * 8)) &&
             dalloc(p, (void**)&p->kpart, (size_t)B * p->kper * 8) &&
             dalloc(p, (void**)&p->crow, S * n * 8);
+  // info, its accumulator and the permutation share an allocation and an upload.  A batch's
+  // roots finish in any order: only one system's info can be published by its root
+  if (ok) p->d_permpos = reinterpret_cast<int*>(p->d_info + 2);
+  p->d_acc = ok && B == 1 && !p->parent ? p->d_info + 1 : p->d_info;
   if (ok && !p->parent && !p->measure &&
       hipHostMalloc((void**)&p->hflag, 2 * sizeof(int), hipHostMallocDefault) != hipSuccess) {
     p->hflag = nullptr;
@@ -582,8 +615,11 @@ bmpc_status init_plan(bmpc_plan p, const bmpc_dims* dims, bmpc_precision prec, v
   }
   if (!ok) return BMPC_ERR_ALLOC;
   if (p->measure) return BMPC_OK;
-  if (hipMemcpy(p->d_permpos, p->permpos.data(), (size_t)N * sizeof(int),
-                hipMemcpyHostToDevice) != hipSuccess) {
+  std::vector<int> init(4 + N, -1);
+  std::copy(p->permpos.begin(), p->permpos.end(), init.begin() + 4);
+  static_assert(2 * sizeof(*p->d_info) == 4 * sizeof(int), "info words before the permutation");
+  if (hipMemcpy(p->d_info, init.data(), init.size() * sizeof(int), hipMemcpyHostToDevice) !=
+      hipSuccess) {
     (void)hipGetLastError();  // reported here, not by a later call
     return BMPC_ERR_DEVICE;
   }
@@ -737,15 +773,15 @@ static bmpc_status refine_impl(bmpc_plan p, const double* D, const double* E, co
   const size_t len = vec_len(p);
   const bool be = p->refine_stop == BMPC_STOP_BACKWARD_ERROR;
   double* rnorm = p->rnorm;
-  timed(p, KC_REFINE_MISC, [&] { launch_refine_reset(p->flags, st); });
   if (fused) {
     if (p->fp64)
-      enqueue_factor_solve<double>(p, D, E, C, R, b, x);
+      enqueue_factor_solve<double>(p, D, E, C, R, b, x, p->flags);
     else
-      enqueue_factor_solve<float>(p, D, E, C, R, b, x);
+      enqueue_factor_solve<float>(p, D, E, C, R, b, x, p->flags);
     if (last_error_status() != BMPC_OK) return BMPC_ERR_DEVICE;
     p->factored = true;
   } else {
+    timed(p, KC_REFINE_MISC, [&] { launch_refine_reset(p->flags, st); });
     if (p->fp64)
       enqueue_solve<double>(p, b, x);
     else

@@ -117,6 +117,18 @@ struct FactorPassArgs {
 // its pointers are those of the chunk's first right-hand side in system 0 (offset by
 // q0 * len), nrhs counts the chunk, vsys = (all right-hand sides) * len is the stride
 // between systems and seg_sys the stride of the per-(system, right-hand side) norms.
+// Root factorization of every system of a batch: L_R = chol(R - sum of the groups' partials).
+struct RootStep {
+  const double* R;
+  const double* part;  // [B][groups][n][n]
+  double* LR;
+  unsigned long long* info;      // smallest failing row so far (permuted), ~0: none
+  unsigned long long* info_out;  // one system: where the finished info goes (else null)
+  int* flags;                    // refinement flags to reset (or null)
+  int n, groups;
+  unsigned long long sys_rows, root_row;
+};
+
 struct SolveArgs {
   int S, N, n, m, nrhs;  // S = scenarios per system, nrhs of this chunk
   int B;                 // systems in the batch
@@ -198,13 +210,13 @@ void launch_root_reduce(const double* U, double* part, int B, int S, int n, int 
                         hipStream_t st);
 // LR[sys] = chol(R[sys] - sum_g part[sys][g]) for every system; row numbers of system
 // sys start at sys * sys_rows, its root rows at root_row within it
-void launch_root_potrf(const double* R, const double* part, int B, int groups, int n,
-                       double* LR, int64_t sys_rows, int64_t root_row,
-                       unsigned long long* info, hipStream_t st);
+void launch_root_potrf(const RootStep& s, int B, hipStream_t st);
 
 template <typename T>
 void launch_solve_fwd_level(const SolveArgs& a, int level, hipStream_t st);
 void launch_solve_root(const SolveArgs& a, hipStream_t st);
+// root factorization and the root step of a solve in one launch, n <= 32
+void launch_root_factor_solve(const RootStep& s, const SolveArgs& a, hipStream_t st);
 template <typename T>
 void launch_solve_bwd_level(const SolveArgs& a, int level, hipStream_t st);
 // The backward levels from the top down to level_lo in one launch (one workgroup per chain,

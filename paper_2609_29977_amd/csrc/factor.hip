@@ -27,10 +27,10 @@
 #include <type_traits>
 
 #include "bmpc_internal.h"
-#include "blockchol.h"
 #include "blockops.h"
 #include "multi.h"
 #include "regblock.h"
+#include "root.h"
 
 namespace bmpc {
 
@@ -1140,59 +1140,21 @@ __global__ void __launch_bounds__(1024) root_reduce_kernel(const double* __restr
 }
 
 // R~ = R - sum_g part[g] (group order), L_R = chol(R~) in FP64 (Algorithm 1, root
-// reduction and root factorization).
-// 1024 threads: thread e owns element e of the NMAX x NMAX block (identity padded
-// beyond n) and loads all group partials at once.
+// reduction and root factorization), one workgroup of 1024 threads per system.
 template <int NMAX>
-__device__ __attribute__((always_inline)) inline void root_potrf_body(
-    const double* __restrict__ R, const double* __restrict__ part, int groups, int n,
-    double* LR, unsigned long long sys_rows, unsigned long long root_row,
-    unsigned long long* info, unsigned bx) {
+__device__ __attribute__((always_inline)) inline void root_potrf_body(const RootStep& s, int sys) {
   constexpr int LD = NMAX + 1;
   __shared__ double A[NMAX * LD];
   __shared__ double scratch[16 * 17];
-  // one workgroup per system of the batch
-  const int sys = bx;
-  R += (size_t)sys * n * n;
-  part += (size_t)sys * groups * n * n;
-  LR += (size_t)sys * n * n;
-  const unsigned long long row_base = sys * sys_rows + root_row;
-  for (int e = threadIdx.x; e < NMAX * NMAX; e += blockDim.x) {
-    const int r = e / NMAX, c = e % NMAX;
-    double v = (r == c) ? 1.0 : 0.0;  // identity padding
-    if (r < n && c < n) {
-      constexpr int B = 32;
-      double acc = 0.0;
-      for (int g0 = 0; g0 < groups; g0 += B) {
-        double t[B];
-#pragma unroll
-        for (int u = 0; u < B; ++u)
-          t[u] = part[(size_t)min(g0 + u, groups - 1) * n * n + r * n + c];
-#pragma unroll
-        for (int u = 0; u < B; ++u) acc = (g0 + u < groups) ? acc + t[u] : acc;
-      }
-      const double rv = (r >= c) ? R[r * n + c] : R[c * n + r];
-      v = rv - acc;
-    }
-    A[r * LD + c] = v;
-  }
+  root_matrix<NMAX, LD>(A, s, sys);
   __syncthreads();
   const int fail = block_chol<double, NMAX / 16, LD, 16, false>(A, scratch);
-  if (fail >= 0 && fail < n && threadIdx.x == 64) atomicMin(info, row_base + fail + 1);
-  for (int e = threadIdx.x; e < NMAX * NMAX; e += blockDim.x) {
-    const int r = e / NMAX, c = e % NMAX;
-    if (r < n && c < n) LR[r * n + c] = c <= r ? A[r * LD + c] : 0.0;
-  }
+  root_store<NMAX, LD>(A, s, sys, fail);
 }
 
 template <int NMAX>
-__global__ void __launch_bounds__(1024) root_potrf_kernel(const double* __restrict__ R,
-                                                          const double* __restrict__ part,
-                                                          int groups, int n, double* LR,
-                                                          unsigned long long sys_rows,
-                                                          unsigned long long root_row,
-                                                          unsigned long long* info) {
-  root_potrf_body<NMAX>(R, part, groups, n, LR, sys_rows, root_row, info, blockIdx.x);
+__global__ void __launch_bounds__(1024) root_potrf_kernel(RootStep s) {
+  root_potrf_body<NMAX>(s, blockIdx.x);
 }
 
 // ---- one launch over the systems of a ragged batch (see multi.h) ----
@@ -1231,8 +1193,16 @@ template <int NMAX>
 __global__ void __launch_bounds__(1024) root_potrf_multi(const MultiItem<RootArgs>* items,
                                                          int nitems, Reloc r) {
   const MultiItem<RootArgs>& it = items[multi_find(items, nitems, blockIdx.x)];
-  root_potrf_body<NMAX>(rel(r.R, it.a.R), it.a.part, it.a.groups, it.a.n, it.a.LR,
-                        it.a.sys_rows, it.a.root_row, it.a.info, multi_local(it).x);
+  RootStep s{};
+  s.R = rel(r.R, it.a.R);
+  s.part = it.a.part;
+  s.LR = it.a.LR;
+  s.info = it.a.info;
+  s.n = it.a.n;
+  s.groups = it.a.groups;
+  s.sys_rows = it.a.sys_rows;
+  s.root_row = it.a.root_row;
+  root_potrf_body<NMAX>(s, multi_local(it).x);
 }
 
 __global__ void info_reset_kernel(unsigned long long* info, int count) {
@@ -1444,21 +1414,15 @@ void launch_root_reduce(const double* U, double* part, int B, int S, int n, int 
                      groups);
 }
 
-void launch_root_potrf(const double* R, const double* part, int B, int groups, int n,
-                       double* LR, int64_t sys_rows, int64_t root_row,
-                       unsigned long long* info, hipStream_t st) {
-  if (n <= 16)
-    hipLaunchKernelGGL(root_potrf_kernel<16>, dim3(B), dim3(1024), 0, st, R, part, groups, n,
-                       LR, (unsigned long long)sys_rows, (unsigned long long)root_row, info);
-  else if (n <= 32)
-    hipLaunchKernelGGL(root_potrf_kernel<32>, dim3(B), dim3(1024), 0, st, R, part, groups, n,
-                       LR, (unsigned long long)sys_rows, (unsigned long long)root_row, info);
-  else if (n <= 48)
-    hipLaunchKernelGGL(root_potrf_kernel<48>, dim3(B), dim3(1024), 0, st, R, part, groups, n,
-                       LR, (unsigned long long)sys_rows, (unsigned long long)root_row, info);
+void launch_root_potrf(const RootStep& s, int B, hipStream_t st) {
+  if (s.n <= 16)
+    hipLaunchKernelGGL(root_potrf_kernel<16>, dim3(B), dim3(1024), 0, st, s);
+  else if (s.n <= 32)
+    hipLaunchKernelGGL(root_potrf_kernel<32>, dim3(B), dim3(1024), 0, st, s);
+  else if (s.n <= 48)
+    hipLaunchKernelGGL(root_potrf_kernel<48>, dim3(B), dim3(1024), 0, st, s);
   else
-    hipLaunchKernelGGL(root_potrf_kernel<64>, dim3(B), dim3(1024), 0, st, R, part, groups, n,
-                       LR, (unsigned long long)sys_rows, (unsigned long long)root_row, info);
+    hipLaunchKernelGGL(root_potrf_kernel<64>, dim3(B), dim3(1024), 0, st, s);
 }
 
 }  // namespace bmpc

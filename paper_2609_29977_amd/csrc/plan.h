@@ -65,7 +65,9 @@ struct bmpc_plan_s {
   void* vacc[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};  // fused forward: R, L
   void* vaccX = nullptr;
   int* d_permpos = nullptr;
-  unsigned long long* d_info = nullptr;
+  unsigned long long* d_info = nullptr;  // of the last factorization
+  unsigned long long* d_acc = nullptr;   // of the one under way: d_info's neighbour for one
+                                         // system (~0 between factorizations), else d_info
   void* y = nullptr;
   double* w = nullptr;
   double* x0 = nullptr;

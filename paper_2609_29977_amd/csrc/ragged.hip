@@ -339,7 +339,10 @@ void build_factor(bmpc_plan p, Seq& seq, bool fused) {
     ra.groups = s->groups;
     ra.root_row = (unsigned long long)s->d.S * s->d.N * s->d.n;
     ra.sys_rows = ra.root_row + s->d.n;
-    red.push_back({i, ra, 0, 0, (unsigned)s->groups, 1u, 1u});
+    if (s->groups == s->d.S)
+      ra.part = s->U;  // each scenario is a group
+    else
+      red.push_back({i, ra, 0, 0, (unsigned)s->groups, 1u, 1u});
     pot[s->d.n <= 16 ? 16 : 32].push_back({i, ra, 0, 0, 1u, 1u, 1u});
   }
   LaunchRec rr;
@@ -714,7 +717,7 @@ bmpc_status bmpc_analyze_ragged(int32_t B, const bmpc_dims* dims, bmpc_precision
     bmpc_plan s = R.subs[i];
     s->flags = p->flags;
     s->rbuf = R.rbuf + R.offV[i];
-    s->d_info = R.info + i;
+    s->d_info = s->d_acc = R.info + i;
     s->rnorm = R.rnorm + (size_t)i * R.nrhs;
     s->knorm = R.knorm + i;
     s->stream = p->stream;

@@ -23,6 +23,7 @@
 #include "blockops.h"
 #include "multi.h"
 #include "regblock.h"
+#include "root.h"
 #include "solve_common.h"
 #include "solve_mm.h"
 
@@ -431,8 +432,13 @@ __global__ void __launch_bounds__(64 * kFwdTopWaves) solve_fwd_top_kernel(SolveA
 // threads, up to eight right-hand sides at a time, the waves' sums combined in order); then
 // the two triangular solves with L_R in LDS, one wave per right-hand side, lane i
 // owning row i.
-template <int NMAX>
+// FACTOR: L_R is factored here first (step), its 32 x 32 or smaller matrix read together with
+// the w_s; one launch, and its latency, fewer where a factorization has the forward
+// substitution inside (with the group sums and the info reset, which one system up to 32
+// scenarios needs no launch for, S = 4, N = 16, n = 8 in FP64: 29.7 -> 25.6 us).
+template <int NMAX, bool FACTOR>
 __device__ __attribute__((always_inline)) inline void solve_root_body(const SolveArgs& a,
+                                                                      const RootStep& step,
                                                                       unsigned bx) {
   if (a.done && *a.done) return;
   constexpr int W = 16, LD = NMAX + 1, QB = NMAX == 64 ? 2 : 8;
@@ -446,10 +452,14 @@ __device__ __attribute__((always_inline)) inline void solve_root_body(const Solv
   const int seg0 = sys * a.seg_sys;
   const double* w = a.w + (size_t)sys * S * nrhs * n;  // this system's chains
   const int t = threadIdx.x, i = t % NMAX, q = t / NMAX;
-  for (int e = t; e < NMAX * NMAX; e += 1024) {
-    const int r = e / NMAX, c = e % NMAX;
-    L[r * LD + c] = (r < n && c < n) ? a.LR[(size_t)sys * n * n + r * n + c]
-                                     : (r == c ? 1.0 : 0.0);  // identity padding
+  if constexpr (FACTOR) {
+    root_matrix<NMAX, LD>(L, step, sys);
+  } else {
+    for (int e = t; e < NMAX * NMAX; e += 1024) {
+      const int r = e / NMAX, c = e % NMAX;
+      L[r * LD + c] = (r < n && c < n) ? a.LR[(size_t)sys * n * n + r * n + c]
+                                       : (r == c ? 1.0 : 0.0);  // identity padding
+    }
   }
   const bool mine = q < nrhs && i < n;  // this thread's row and right-hand side
   double bv = mine ? a.b[(size_t)q * len + root_off + i] : 0.0;
@@ -485,6 +495,12 @@ __device__ __attribute__((always_inline)) inline void solve_root_body(const Solv
   }
   if (q < nrhs) r0[q][i] = bv - sum;
   __syncthreads();
+  if constexpr (FACTOR) {
+    double* const scratch = &part[0][0][0];  // the sums are taken
+    const int fail = n <= 16 ? block_chol<double, 1, LD, W, false>(L, scratch)
+                             : block_chol<double, NMAX / 16, LD, W, false>(L, scratch);
+    root_store<NMAX, LD>(L, step, sys, fail);
+  }
   // L_R y = r, then L_R^T x = y: wave q handles right-hand side q, lane k row k.  L is
   // identity padded to NMAX x NMAX, so both sweeps run NMAX unrolled steps (the padded
   // unknowns stay 0); each lane holds the row (forward) or column (backward) of L it
@@ -521,7 +537,10 @@ __device__ __attribute__((always_inline)) inline void solve_root_body(const Solv
 
 template <int NMAX>
 __global__ void __launch_bounds__(1024) solve_root_kernel(SolveArgs a) {
-  solve_root_body<NMAX>(a, blockIdx.x);
+  solve_root_body<NMAX, false>(a, RootStep{}, blockIdx.x);
+}
+__global__ void __launch_bounds__(1024) root_factor_solve_kernel(RootStep s, SolveArgs a) {
+  solve_root_body<32, true>(a, s, blockIdx.x);
 }
 
 // ---- one launch over the systems of a ragged batch (see multi.h) ----
@@ -570,7 +589,7 @@ template <int NMAX>
 __global__ void __launch_bounds__(1024) solve_root_multi(const MultiItem<SolveArgs>* items,
                                                          int nitems, Reloc r) {
   const MultiItem<SolveArgs>& it = items[multi_find(items, nitems, blockIdx.x)];
-  solve_root_body<NMAX>(relocate_solve(it.a, r), multi_local(it).x);
+  solve_root_body<NMAX, false>(relocate_solve(it.a, r), RootStep{}, multi_local(it).x);
 }
 
 template <typename T, int NMAX, bool FULL>
@@ -716,6 +735,10 @@ void launch_solve_root(const SolveArgs& a, hipStream_t st) {
     hipLaunchKernelGGL(solve_root_kernel<64>, dim3(a.B), dim3(1024), 0, st, a);
   else
     hipLaunchKernelGGL(solve_root_kernel<32>, dim3(a.B), dim3(1024), 0, st, a);
+}
+
+void launch_root_factor_solve(const RootStep& s, const SolveArgs& a, hipStream_t st) {
+  hipLaunchKernelGGL(root_factor_solve_kernel, dim3(a.B), dim3(1024), 0, st, s, a);
 }
 
 size_t solve_level_lds(bool fp64, int nmax, int waves) {
