@@ -502,30 +502,38 @@ __device__ __attribute__((always_inline)) inline void solve_root_body(const Solv
     root_store<NMAX, LD>(L, step, sys, fail);
   }
   // L_R y = r, then L_R^T x = y: wave q handles right-hand side q, lane k row k.  L is
-  // identity padded to NMAX x NMAX, so both sweeps run NMAX unrolled steps (the padded
-  // unknowns stay 0); each lane holds the row (forward) or column (backward) of L it
-  // updates with, and 1 / L[k][k] is formed once per lane and broadcast with x_k.
+  // identity padded to NMAX x NMAX, so both sweeps run K (NMAX, or 16 for n <= 16) unrolled
+  // steps (the padded unknowns stay 0); each lane holds the row (forward) or column
+  // (backward) of L it updates with, and 1 / L[k][k] is formed once per lane and
+  // broadcast with x_k.
   const int wv = t >> 6, lane = t & 63;
-  if (wv < nrhs) {
-    const int row = lane < NMAX ? lane : NMAX - 1;
+  auto sweeps = [&](auto steps) {
+    constexpr int K = decltype(steps)::value;
+    const int row = lane < K ? lane : K - 1;
     double v = (lane < n) ? r0[wv][lane] : 0.0;
     const double rd = 1.0 / L[row * LD + row];
-    double lk[NMAX];
+    double lk[K];
 #pragma unroll
-    for (int k = 0; k < NMAX; ++k) lk[k] = L[row * LD + k];
+    for (int k = 0; k < K; ++k) lk[k] = L[row * LD + k];
 #pragma unroll
-    for (int k = 0; k < NMAX; ++k) {
+    for (int k = 0; k < K; ++k) {
       const double xk = wave_bcast(v, k) * wave_bcast(rd, k);
       v = (lane == k) ? xk : (lane > k ? v - lk[k] * xk : v);
     }
 #pragma unroll
-    for (int k = 0; k < NMAX; ++k) lk[k] = L[k * LD + row];
+    for (int k = 0; k < K; ++k) lk[k] = L[k * LD + row];
 #pragma unroll
-    for (int k = NMAX - 1; k >= 0; --k) {
+    for (int k = K - 1; k >= 0; --k) {
       const double xk = wave_bcast(v, k) * wave_bcast(rd, k);
       v = (lane == k) ? xk : (lane < k ? v - lk[k] * xk : v);
     }
     if (lane < n) r0[wv][lane] = v;
+  };
+  if (wv < nrhs) {
+    if (NMAX == 32 && n <= 16)
+      sweeps(std::integral_constant<int, 16>{});
+    else
+      sweeps(std::integral_constant<int, NMAX>{});
   }
   __syncthreads();
   for (int idx = t; idx < n * nrhs; idx += 1024) {
