@@ -23,54 +23,6 @@ struct Lay {
   static constexpr int SZ = NMAX * LD;
 };
 
-// ---- global <-> LDS ----------------------------------------------------------
-
-// dst = the symmetric matrix whose lower triangle is src (row-major n x n, FP64).
-// Only the lower triangle of src is read.
-template <typename T, int NMAX, int NT>
-__device__ inline void lds_load_sym_lower(T* dst, const double* __restrict__ src, int n) {
-  constexpr int LD = Lay<NMAX>::LD;
-  for (int e = threadIdx.x; e < n * n; e += NT) {
-    const int r = e / n, c = e - (e / n) * n;
-    if (r >= c) {
-      const T v = static_cast<T>(src[e]);
-      dst[r * LD + c] = v;
-      dst[c * LD + r] = v;
-    }
-  }
-}
-
-// dst (+)= src or src^T; src is a row-major n x n block of type S.
-template <typename T, int NMAX, int NT, typename S>
-__device__ inline void lds_load(T* dst, const S* __restrict__ src, int n, bool transpose,
-                                bool add = false) {
-  constexpr int LD = Lay<NMAX>::LD;
-  for (int e = threadIdx.x; e < n * n; e += NT) {
-    const int r = e / n, c = e - (e / n) * n;
-    const T v = static_cast<T>(src[e]);
-    const int o = transpose ? c * LD + r : r * LD + c;
-    dst[o] = add ? dst[o] + v : v;
-  }
-}
-
-template <typename T, int NMAX, int NT>
-__device__ inline void lds_zero(T* dst, int n) {
-  constexpr int LD = Lay<NMAX>::LD;
-  for (int e = threadIdx.x; e < n * n; e += NT) {
-    const int r = e / n, c = e - (e / n) * n;
-    dst[r * LD + c] = T(0);
-  }
-}
-
-template <typename T, int NMAX, int NT>
-__device__ inline void lds_store(T* __restrict__ dst, const T* src, int n) {
-  constexpr int LD = Lay<NMAX>::LD;
-  for (int e = threadIdx.x; e < n * n; e += NT) {
-    const int r = e / n, c = e - (e / n) * n;
-    dst[e] = src[r * LD + c];
-  }
-}
-
 // ---- wave-uniform broadcast and reciprocal square root ---------------------------
 
 // This wave's index in the workgroup, in a scalar register (the compiler cannot tell

@@ -1,10 +1,8 @@
-// Register-resident n x n blocks for matrix-vector products on one or more waves
-// (gfx950).
+// Register-resident n x n blocks for matrix-vector products on one wave (gfx950).
 //
-// A block is split over the lanes of WAVES waves: wave w owns the RPW = NMAX/WAVES
-// output indices starting at w*RPW; within a wave LPR = 64/RPW lanes share one output
-// index o and each holds EPL = NMAX/LPR consecutive elements of the contraction index,
-// starting at base = (lane % LPR) * EPL.  In the normal mapping a
+// A block is split over the lanes: LPR = 64/NMAX lanes share one output index o and each
+// holds EPL = NMAX/LPR consecutive elements of the contraction index, starting at
+// base = (lane % LPR) * EPL.  In the normal mapping a
 // lane holds part of row o (products M v); in the transposed mapping part of column o
 // (products M^T v).  Both load coalesced from a row-major block and share the same
 // dot-product / reduction code.  Rows and columns >= n read as zero.
@@ -35,37 +33,17 @@ __device__ inline float buf_load_f32(__amdgpu_buffer_rsrc_t r, unsigned off) {
   return f;
 }
 
-template <typename T, int NMAX, int WAVES = 1>
+template <typename T, int NMAX>
 struct RegBlock {
-  static_assert(NMAX == 8 || NMAX == 16 || NMAX == 32 || NMAX == 64, "block size bound");
-  static_assert(WAVES == 1 || WAVES == 2 || WAVES == 4, "waves per block");
-  static constexpr int RPW = NMAX / WAVES;
-  static constexpr int LPR = 64 / RPW;
+  static_assert(NMAX == 8 || NMAX == 16 || NMAX == 32, "block size bound");
+  static constexpr int LPR = 64 / NMAX;
   static constexpr int EPL = NMAX / LPR;
   T v[EPL];
 
   __device__ static int out_index() {
-    return (WAVES > 1 ? (int)(threadIdx.x >> 6) * RPW : 0) + (threadIdx.x & 63) / LPR;
+    return (int)(threadIdx.x & 63) / LPR;
   }
   __device__ static int base() { return ((threadIdx.x & 63) % LPR) * EPL; }
-
-  template <bool TRANS>
-  __device__ void load(const T* __restrict__ g, int n) {
-    const int o = out_index(), b = base();
-    if (n == NMAX) {
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) v[e] = TRANS ? g[(b + e) * NMAX + o] : g[o * NMAX + b + e];
-    } else {
-      // branch-free: out-of-range elements load element 0 and are replaced by zero
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) {
-        const int r = TRANS ? b + e : o, c = TRANS ? o : b + e;
-        const bool ok = r < n && c < n;
-        const T t = g[ok ? r * n + c : 0];
-        v[e] = ok ? t : T(0);
-      }
-    }
-  }
 
   // FULL (n == NMAX known at compile time): every element of the lane sits at a fixed
   // offset from one lane base address.  Otherwise the block is read through a buffer
@@ -82,7 +60,7 @@ struct RegBlock {
     }
   }
 
-  // Same as load, through a buffer resource covering the n x n block (out-of-range
+  // Through a buffer resource covering the n x n block (out-of-range
   // elements read as zero without a branch or a select).
   template <bool TRANS>
   __device__ void load_buf(__amdgpu_buffer_rsrc_t rs, int n) {
@@ -157,18 +135,11 @@ struct RegBlock {
   }
 };
 
-// Sum over the LPR lanes that share an output index (all of them get the sum).
-template <int LPR, typename T>
-__device__ inline T lane_group_sum(T p) {
-#pragma unroll
-  for (int off = 1; off < LPR; off <<= 1) p += __shfl_xor(p, off);
-  return p;
-}
-
-// The same sum through DPP lane permutations (xor 1 and xor 2 within quads, then the
+// Sum over the LPR lanes that share an output index (all of them get the sum)
+// through DPP lane permutations (xor 1 and xor 2 within quads, then the
 // mirrored quad and the mirrored half row, which pair each partial sum with one that
 // does not overlap it).  Additions are commutative, so all lanes of a group end up with
-// bit-identical sums, in the same pairwise order as lane_group_sum.
+// bit-identical sums, pairs first.
 template <int CTRL>
 __device__ inline float dpp_perm(float x) {
   return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xF, 0xF, false));
