@@ -72,8 +72,8 @@ typedef struct {
   int32_t S;    /* scenarios, >= 1 */
   int32_t N;    /* stages per tail, >= 1 */
   int32_t n;    /* block size n_b (Assumption 1, uniform), 1..64.  Blocks of 33..64
-                   are factored one level per pass (two 32 x 32 quadrants per block
-                   dimension) and without the fused forward substitution */
+                   are factored one level per pass (in tiles of 16 x 16) and without
+                   the fused forward substitution */
   int32_t nrhs; /* right-hand sides per solve, 1..4096 (Section III-B partitions each
                    right-hand side like the unknowns; their number is free).  The
                    solve kernels take them sixteen at a time, the residual eight (n <= 32)
@@ -85,7 +85,7 @@ typedef struct {
                                           per position) even where the top levels could
                                           share one launch (one workgroup per chain) */
 #define BMPC_FLAG_FWD_ONE_WAVE 0x2     /* forward sweep: one wave per position instead of
-                                          up to four sharing its pulls */
+                                          several sharing its pulls, one launch per level */
 
 typedef struct {
   int32_t window_depth; /* 0 = automatic; else levels eliminated per factor pass
@@ -169,7 +169,7 @@ bmpc_status bmpc_ragged_layout(bmpc_plan plan, int32_t i, bmpc_dims* dims, int64
  * window_depth from 1 to the largest the shared memory allows, crossed with
  * BMPC_FLAG_NO_BWD_TOP_MERGE (the backward sweep's top levels in one launch, one
  * workgroup per chain, or one launch per level, one wave per position) and
- * BMPC_FLAG_FWD_ONE_WAVE (forward positions on up to four waves or on one) -- times the
+ * BMPC_FLAG_FWD_ONE_WAVE (forward positions on several waves or on one) -- times the
  * plan's step (FP64: bmpc_factor_solve; FP32: bmpc_factor_refine with one correction) on
  * synthetic SPD data in device memory (allocated here and freed), the median of reps
  * runs (1..100) after one warm-up, and writes the fastest configuration to *best
