@@ -47,13 +47,11 @@ struct Slots {
   __device__ T* AL() const { return base + (2 * Tw) * SZ; }
   __device__ T* CL() const { return base + (2 * Tw + 1) * SZ; }
   __device__ T* AR() const { return base + (2 * Tw + 2) * SZ; }
-  // right-hand sides of the live nodes (by level), the boundaries, y_j and the pushes
+  // right-hand sides of the live nodes (by level), the boundaries, and y_j
   __device__ T* V(int t) const { return base + (2 * Tw + 3) * SZ + t * VS; }
   __device__ T* VL() const { return V(Tw); }
   __device__ T* VR() const { return V(Tw + 1); }
   __device__ T* Y() const { return V(Tw + 2); }
-  __device__ T* Pr() const { return V(Tw + 3); }  // pushes of an elimination
-  __device__ T* Pl() const { return V(Tw + 4); }
 };
 
 // Per-thread share of an NMAX x NMAX block: element e = threadIdx.x + j*NT.
@@ -225,14 +223,13 @@ __device__ inline void block_matvec(const T* M, const T* v, int nrhs, Put put) {
   }
 }
 
-// Both pushes of an elimination, V_r -= G_r y and (with a left neighbour)
-// V_l -= G_l y, in two steps so that each overlaps other work of the elimination:
-// push_products forms the reduced sums (G and y read from LDS, same thread split as
-// block_matvec) into the LDS vectors Pr, Pl; push_apply subtracts them later, one
-// element per thread.
+// Both pushes of an elimination, V_r -= G_r y and (with a left neighbour) V_l -= G_l y, from
+// LDS with the thread split of block_matvec.  Nothing else touches V_r and V_l between
+// the barriers around the update products, so the thread with a sum subtracts it
+// there.  (Staging the sums for the next phase: first pass 1660 us against 1648 in FP64, 788
+// against 782 in FP32 at S = 512, N = 256.)
 template <typename T, int NMAX>
-__device__ inline void push_products(const T* Gr, const T* Gl, const T* y, T* Pr, T* Pl,
-                                     int nrhs) {
+__device__ inline void push(const T* Gr, const T* Gl, const T* y, T* Vr, T* Vl, int nrhs) {
   constexpr int NT = TileCfg<NMAX>::NT;
   constexpr int LD = Lay<NMAX>::LD;
   constexpr int TPR = NT / NMAX;
@@ -245,6 +242,7 @@ __device__ inline void push_products(const T* Gr, const T* Gl, const T* y, T* Pr
     gl[u] = Gl ? Gl[o * LD + p * CPT + u] : T(0);
   }
   for (int q = 0; q < nrhs; ++q) {
+    const T vr = Vr[q * NMAX + o], vl = Gl ? Vl[q * NMAX + o] : T(0);
     T r = T(0), l = T(0);
 #pragma unroll
     for (int u = 0; u < CPT; ++u) {
@@ -255,16 +253,9 @@ __device__ inline void push_products(const T* Gr, const T* Gl, const T* y, T* Pr
     r = lane_group_sum_dpp<TPR>(r);
     if (Gl) l = lane_group_sum_dpp<TPR>(l);
     if (p == 0) {
-      Pr[q * NMAX + o] = r;
-      if (Gl) Pl[q * NMAX + o] = l;
+      Vr[q * NMAX + o] = vr - r;
+      if (Gl) Vl[q * NMAX + o] = vl - l;
     }
-  }
-}
-template <typename T, int NMAX>
-__device__ inline void push_apply(T* Vr, T* Vl, const T* Pr, const T* Pl, int nrhs) {
-  for (int idx = threadIdx.x; idx < nrhs * NMAX; idx += TileCfg<NMAX>::NT) {
-    Vr[idx] -= Pr[idx];
-    if (Vl) Vl[idx] -= Pl[idx];
   }
 }
 
@@ -592,7 +583,7 @@ template <typename T, int NMAX, bool FWD>
 __device__ __attribute__((always_inline)) inline void eliminate(T* Aj, T* Cj, T* Al, T* Cl, T* Ar, int n, T* gLinv,
                                  T* gGl, T* gGr, unsigned long long perm_row0,
                                  unsigned long long* info, bool have_inverse, T* Vj,
-                                 T* Vl, T* Vr, T* Yt, T* Pr, T* Pl, T* gy, int nrhs) {
+                                 T* Vl, T* Vr, T* Yt, T* gy, int nrhs) {
   typedef typename Mfma<T>::acc_t acc_t;
   if (!have_inverse) factor_diag<T, NMAX>(Aj, perm_row0, n, info);
   const bool left = Cl != nullptr;
@@ -632,14 +623,13 @@ __device__ __attribute__((always_inline)) inline void eliminate(T* Aj, T* Cj, T*
     uf = mfma_tile_nt<T, NMAX, false>(Cj, Cl);
   }
   if constexpr (FWD)  // G_l is still in Cl
-    push_products<T, NMAX>(Cj, left ? Cl : nullptr, Yt, Pr, Pl, nrhs);
+    push<T, NMAX>(Cj, left ? Cl : nullptr, Yt, Vr, Vl, nrhs);
   __syncthreads();
   if (!upper) mfma_tile_store<T, NMAX, true>(Ar, ur, T(-1));
   if (left) {
     if (!upper) mfma_tile_store<T, NMAX, true>(Al, ul, T(-1));
     mfma_tile_store<T, NMAX, false>(Cl, uf, T(-1));
   }
-  if constexpr (FWD) push_apply<T, NMAX>(Vr, left ? Vl : nullptr, Pr, Pl, nrhs);
   __syncthreads();
 }
 
@@ -866,7 +856,7 @@ __device__ __attribute__((always_inline)) inline void factor_pass_body(
       const unsigned long long prow = chain_row0 + (unsigned long long)a.permpos[j - 1] * n;
       eliminate<T, NMAX, FWD>(sl.A(t), sl.Cp(t), Al, Cl, Ar, n, Linv + (size_t)(j - 1) * nn,
                          Gl + (size_t)(j - 1) * nn, Gr + (size_t)(j - 1) * nn, prow, a.info,
-                         (pos & 1) != 0, sl.V(t), Vl, Vr, sl.Y(), sl.Pr(), sl.Pl(),
+                         (pos & 1) != 0, sl.V(t), Vl, Vr, sl.Y(),
                          ych ? ych + (size_t)(j - 1) * a.nrhs * n : nullptr, a.nrhs);
       live &= ~(1u << t);
     }
@@ -1250,10 +1240,10 @@ void launch_multi_pass_t(const MultiItem<FactorPassArgs>* items, int nitems, uns
 #undef BMPC_MULTI_KF
 }
 
-// Block slots, plus (fused forward substitution) Tw + 5 right-hand-side slots.
+// Block slots, plus (fused forward substitution) Tw + 3 right-hand-side slots.
 template <typename T, int NMAX>
 size_t pass_lds_bytes(int Tw, int nrhs_fused) {
-  return ((size_t)(2 * Tw + 3) * Lay<NMAX>::SZ + (size_t)(Tw + 5) * nrhs_fused * NMAX) *
+  return ((size_t)(2 * Tw + 3) * Lay<NMAX>::SZ + (size_t)(Tw + 3) * nrhs_fused * NMAX) *
          sizeof(T);
 }
 
