@@ -1,4 +1,4 @@
-// Vector indexing shared by the solve kernels (solve.hip, solve64.hip).
+// Vector indexing and scenario sums shared by the solve and residual kernels.
 #pragma once
 
 #include "bmpc_internal.h"
