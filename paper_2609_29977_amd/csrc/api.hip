@@ -248,13 +248,16 @@ bool dalloc(bmpc_plan p, void** ptr, size_t bytes) {
 }
 
 // The LDS of a pass includes the right-hand-side slots of the fused forward
-// substitution, so that path always fits.
+// substitution, so that path always fits, and is that of a last pass over as many
+// positions as a window holds, the most that a pass of this depth takes (x_1 and C on top
+// of a full window at n <= 16).
 int pick_window_depth(bool fp64, int nmax, int nrhs, const bmpc_options* o) {
   if (nmax > 32) return 1;
   int Tw = (o && o->window_depth > 0) ? o->window_depth : default_window_depth(nmax);
   Tw = std::min(Tw, kMaxWindowDepth);
   const int q = std::min(nrhs, kMaxRhs);
-  while (Tw > 1 && factor_pass_lds_bytes(fp64, nmax, Tw, 1 << Tw, q) > (size_t)kLdsBudget) --Tw;
+  while (Tw > 1 && factor_pass_lds_bytes(fp64, nmax, Tw, (1 << Tw) - 1, q) > (size_t)kLdsBudget)
+    --Tw;
   return Tw;
 }
 
