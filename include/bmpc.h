@@ -177,8 +177,9 @@ bmpc_status bmpc_ragged_layout(bmpc_plan plan, int32_t i, bmpc_dims* dims, int64
  * that fills the GPU measures throughput, the right criterion for a system that shares
  * the GPU with many others (a ragged batch).  times (cap entries, may be NULL with
  * cap = 0) receives each candidate's median in the order tried, *count the number
- * tried.  Synchronizes the stream; not capturable.  BMPC_ERR_ALLOC if no candidate
- * fits in device memory. */
+ * tried; a candidate that does not fit in device memory or whose step fails is left out.
+ * Synchronizes the stream; not capturable.  BMPC_ERR_ALLOC if no candidate fits in device
+ * memory, the step's error if none of those that fit runs. */
 bmpc_status bmpc_autotune(const bmpc_dims* dims, int32_t num_systems, bmpc_precision prec,
                           void* stream, int32_t reps, bmpc_options* best, double* best_ms,
                           double* times, int32_t cap, int32_t* count);

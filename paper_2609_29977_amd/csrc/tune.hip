@@ -101,7 +101,7 @@ extern "C" bmpc_status bmpc_autotune(const bmpc_dims* dims, int32_t num_systems,
   (void)hipEventCreate(&e1);
   double best_t = -1.0;
   int tried = 0;
-  bmpc_status status = BMPC_OK;
+  bmpc_status status = BMPC_OK, failed = BMPC_ERR_ALLOC;
   for (const bmpc_options& o : cands) {
     bmpc_plan p = nullptr;
     const bmpc_status a = bmpc_analyze_ex(dims, prec, stream, &o, &p);
@@ -111,21 +111,24 @@ extern "C" bmpc_status bmpc_autotune(const bmpc_dims* dims, int32_t num_systems,
       break;
     }
     auto step = [&] {
-      if (fp64)
-        (void)bmpc_factor_solve(p, D, E, C, R, b, x);
-      else
-        (void)bmpc_factor_refine(p, D, E, C, R, b, x, 0.0, 1);
+      return fp64 ? bmpc_factor_solve(p, D, E, C, R, b, x)
+                  : bmpc_factor_refine(p, D, E, C, R, b, x, 0.0, 1);
     };
-    step();  // warm-up
+    bmpc_status ran = step();  // warm-up
     std::vector<double> ms;
-    for (int r = 0; r < reps; ++r) {
+    for (int r = 0; r < reps && ran == BMPC_OK; ++r) {
       (void)hipEventRecord(e0, st);
-      step();
+      ran = step();
       (void)hipEventRecord(e1, st);
       float t = 0.f;
       (void)hipEventSynchronize(e1);
       (void)hipEventElapsedTime(&t, e0, e1);
       ms.push_back(t);
+    }
+    if (ran != BMPC_OK) {  // a launch was refused: what was timed is not the step
+      failed = ran;
+      (void)bmpc_destroy(p);
+      continue;
     }
     std::sort(ms.begin(), ms.end());
     const double med = ms[ms.size() / 2];
@@ -149,6 +152,6 @@ extern "C" bmpc_status bmpc_autotune(const bmpc_dims* dims, int32_t num_systems,
   release();
   if (count) *count = tried;
   if (best_ms) *best_ms = best_t;
-  if (status == BMPC_OK && tried == 0) status = BMPC_ERR_ALLOC;
+  if (status == BMPC_OK && tried == 0) status = failed;
   return status;
 }
