@@ -81,7 +81,8 @@ struct QpLink {
 #pragma unroll
       for (int k = 0; k < U; ++k) {
         if (4 * (k0 + k) >= rows) continue;  // uniform
-        const double s = wt.scale(w[k]);
+        // rows past the end are zero; so is their weight (1 / delta may be infinite)
+        const double s = 4 * (k0 + k) + g < rows ? wt.scale(w[k]) : 0.0;
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
           const double su = NU ? s * xu[k][t] : 0.0, sv = s * xv[k][t];
