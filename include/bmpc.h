@@ -346,8 +346,8 @@ typedef struct {
  *   Q [S][N+1][2n][2n]   link cost Hessians (P = sum of links), variables (u, v)
  *   A [S][N+1][me][2n]   equality rows,  G [S][N+1][mi][2n] inequality rows
  *   w [S][N+1][mi]       diagonal of W (nonnegative; the IPM weights are positive)
- * Outputs (device, overwritten): D [S][N][n][n] (both triangles), E [S][N-1][n][n],
- * C [S][n][n], R [n][n]; work: device scratch of S*n*n doubles.  tau >= 0, delta > 0.
+ * Outputs (device, overwritten): D [S][N][n][n] (both triangles; D and R are exactly
+ * symmetric where Q is), E [S][N-1][n][n], C [S][n][n], R [n][n]; work: device scratch of S*n*n doubles.  tau >= 0, delta > 0.
  * The ADMM system of the same appendix (the OSQP form [[P + sigma I, A^T, G^T],
  * [A, -rho^{-1} I, 0], [G, 0, -rho^{-1} I]], reduced to P + sigma I + rho A^T A +
  * rho G^T G) is this assembly with w = 0, tau = sigma and delta = 1/rho.

@@ -41,7 +41,8 @@ struct QpArgs {
 // link waits in the accumulators for the next link's uu.  The products X^T diag X are 16 x
 // 16 x 4 FP64 MFMA tiles with the constraint rows as the contraction index: lane 16 g + i
 // holds entry (4 k + g, 16 t + i) of the rows for both operands (one load serves a tile's
-// rows and columns; the weight multiplies one of them, so no square root is taken), and Q
+// rows and columns; both carry the square root of the weight, so that entries (p, q) and
+// (q, p) are sums of the same products and D and R are exactly symmetric where Q is), and Q
 // is read in the accumulator layout, so nothing is staged in LDS and all loads of a link
 // are in flight together.  Memory-bound: 8 (3 n^2 + (me + mi) 2n + mi) bytes read per link
 // and 16 n^2 written.  S = 256, N = 128, n = 16, 12 + 32 rows: 403 us with one workgroup
@@ -58,7 +59,8 @@ struct QpLink {
     const int c = 16 * t + i;
     return c < a.n ? (unsigned)(off + c) * 8u : kOutOfRange;
   }
-  // M += sum over the rows r < rows of X of wt(r) X[r][.]^T X[r][.] for the tiles asked for
+  // M += sum over the rows r < rows of X of (wt(r) X[r][.])^T (wt(r) X[r][.]) for the tiles
+  // asked for
   template <bool UU, bool VU, bool UV, typename Wt>
   __device__ void rows(__amdgpu_buffer_rsrc_t rs, int rows, Wt wt, acc_t (&uu)[NT][NT],
                        acc_t (&vu)[NT][NT], acc_t (&vv)[NT][NT]) const {
@@ -81,17 +83,21 @@ struct QpLink {
 #pragma unroll
       for (int k = 0; k < U; ++k) {
         if (4 * (k0 + k) >= rows) continue;  // uniform
-        // rows past the end are zero; so is their weight (1 / delta may be infinite)
+        // rows past the end are zero; so is their weight
         const double s = 4 * (k0 + k) + g < rows ? wt.scale(w[k]) : 0.0;
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-          const double su = NU ? s * xu[k][t] : 0.0, sv = s * xv[k][t];
+          if (NU) xu[k][t] *= s;
+          xv[k][t] *= s;
+        }
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
 #pragma unroll
           for (int c = 0; c < NT; ++c) {
-            if (UU) uu[t][c] = Mfma<double>::mma(su, xu[k][c], uu[t][c]);
-            if (VU) vu[t][c] = Mfma<double>::mma(sv, xu[k][c], vu[t][c]);
-            if (UV) vu[t][c] = Mfma<double>::mma(su, xv[k][c], vu[t][c]);
-            vv[t][c] = Mfma<double>::mma(sv, xv[k][c], vv[t][c]);
+            if (UU) uu[t][c] = Mfma<double>::mma(xu[k][t], xu[k][c], uu[t][c]);
+            if (VU) vu[t][c] = Mfma<double>::mma(xv[k][t], xu[k][c], vu[t][c]);
+            if (UV) vu[t][c] = Mfma<double>::mma(xu[k][t], xv[k][c], vu[t][c]);
+            vv[t][c] = Mfma<double>::mma(xv[k][t], xv[k][c], vv[t][c]);
           }
         }
       }
@@ -133,7 +139,7 @@ struct QpLink {
     __amdgpu_buffer_rsrc_t rs;
     double delta;
     __device__ double load(int r) const { return buf_load_f64(rs, (unsigned)r * 8u); }
-    __device__ double scale(double w) const { return 1.0 / (w + delta); }
+    __device__ double scale(double w) const { return 1.0 / sqrt(w + delta); }
   };
   // the quadrants of M_j: uu (UU), vu (VU) or uv (UV) into m2, vv always
   template <bool UU, bool VU, bool UV>
@@ -147,7 +153,7 @@ struct QpLink {
     quadrant(rq, n, n, vv);
     if (a.me > 0)
       rows<UU, VU, UV>(block_rsrc(a.A + lk * a.me * n2, a.me * n2 * 8u), a.me,
-                       ConstWt{1.0 / a.delta}, uu, m2, vv);
+                       ConstWt{1.0 / sqrt(a.delta)}, uu, m2, vv);
     if (a.mi > 0)
       rows<UU, VU, UV>(block_rsrc(a.G + lk * a.mi * n2, a.mi * n2 * 8u), a.mi,
                        RowWt{block_rsrc(a.w + lk * a.mi, a.mi * 8u), a.delta}, uu, m2, vv);
