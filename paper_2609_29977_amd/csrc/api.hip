@@ -414,6 +414,9 @@ void enqueue_factor(bmpc_plan p, const double* D, const double* E, const double*
   timed(p, KC_ROOT_POTRF, [&] { launch_root_potrf(root_step(p, R), p->B, p->stream); });
 }
 
+// Right-hand sides of the forward substitution inside the factorization: all of them, or none
+// at n > 32 and beyond what the factor passes take.
+int fused_rhs(bmpc_plan p) { return p->nmax <= 32 && p->d.nrhs <= kMaxRhs ? p->d.nrhs : 0; }
 size_t vec_len(bmpc_plan p) { return ((size_t)p->d.S * p->d.N + 1) * p->d.n; }
 int chunks_of(bmpc_plan p) { return (p->d.nrhs + p->chunk - 1) / p->chunk; }
 int chunk_rhs(bmpc_plan p, int c) { return std::min(p->chunk, p->d.nrhs - c * p->chunk); }
@@ -503,7 +506,7 @@ template <typename T>
 void enqueue_factor_solve(bmpc_plan p, const double* D, const double* E, const double* C,
                           const double* R, const double* b, double* x, int* flags = nullptr) {
   const int nrhs = p->d.nrhs;
-  const bool inside = p->nmax <= 32 && nrhs <= kMaxRhs;
+  const bool inside = fused_rhs(p) > 0;
   RootStep step = root_step(p, R);
   if (inside && step.info_out)
     step.flags = flags;
@@ -567,6 +570,7 @@ bmpc_status init_plan(bmpc_plan p, const bmpc_dims* dims, bmpc_precision prec, v
   p->groups = std::min(dims->S, 32);
   const int B = p->B, N = dims->N, n = dims->n, nrhs = dims->nrhs;
   const int cq = std::min(nrhs, p->chunk);  // right-hand sides of one chunk of a solve
+  const int fq = fused_rhs(p);              // of those inside the factorization
   const size_t S = (size_t)B * dims->S;  // chains of the batch
   const size_t nn = (size_t)n * n, tb = p->fp64 ? 8 : 4;
   const size_t len = ((size_t)dims->S * N + 1) * n;
@@ -583,7 +587,7 @@ bmpc_status init_plan(bmpc_plan p, const bmpc_dims* dims, bmpc_precision prec, v
             dalloc(p, (void**)&p->Upart, (size_t)B * p->groups * nn * 8) &&
             dalloc(p, (void**)&p->LR, (size_t)B * nn * 8) &&
             dalloc(p, &p->accX, S * npass * nn * tb) &&
-            dalloc(p, &p->vaccX, S * npass * cq * n * tb) &&
+            dalloc(p, &p->vaccX, S * npass * fq * n * tb) &&
             dalloc(p, (void**)&p->d_info, 2 * sizeof(*p->d_info) + (size_t)N * sizeof(int)) &&
             dalloc(p, &p->y, S * N * cq * n * tb) &&
             dalloc(p, (void**)&p->w, S * cq * n * 8) &&
@@ -613,7 +617,7 @@ bmpc_status init_plan(bmpc_plan p, const bmpc_dims* dims, bmpc_precision prec, v
       for (int b = 0; b < 3 && ok; ++b)
         ok = dalloc(p, &p->acc[set][b], S * p->stride * nn * tb);
       for (int b = 0; b < 2 && ok; ++b)
-        ok = dalloc(p, &p->vacc[set][b], S * p->stride * cq * n * tb);
+        ok = dalloc(p, &p->vacc[set][b], S * p->stride * fq * n * tb);
     }
   }
   if (!ok) return BMPC_ERR_ALLOC;

@@ -120,6 +120,7 @@ int pick_window_depth(bool fp64, int nmax, int nrhs, const bmpc_options* o);
 bool dalloc(bmpc_plan p, void** ptr, size_t bytes);
 void free_plan_memory(bmpc_plan p);
 bmpc_status last_error_status();
+int fused_rhs(bmpc_plan p);
 size_t vec_len(bmpc_plan p);
 int chunks_of(bmpc_plan p);
 int chunk_rhs(bmpc_plan p, int c);

@@ -301,7 +301,7 @@ void build_factor(bmpc_plan p, Seq& seq, bool fused) {
       bmpc_plan s = R.subs[i];
       const int np = (int)s->costs.passes.size();
       if (k >= np) continue;
-      const int nq = fused ? chunk_rhs(s, 0) : 0;
+      const int nq = fused ? fused_rhs(s) : 0;
       const FactorPassArgs a = factor_pass_args(s, k, fake(R.offD[i]), fake(R.offE[i]),
                                                 fake(R.offC[i]), fused ? fake(R.offV[i]) : nullptr,
                                                 nq);
