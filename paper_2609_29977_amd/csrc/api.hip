@@ -28,9 +28,10 @@ double gemm_flops(double n) { return 2.0 * n * n * n; }
 // Levels of the first factor pass.  n > 16 (the serial walk of factor.hip): three, so that
 // four workgroups (FP32) share a CU; deeper windows save passes and boundary traffic but
 // lengthen the walk.  n <= 16 (tree.hip): deeper windows save passes, but leave more waves
-// idle at their upper levels once the GPU is full and take more LDS.  16 x 16: three (FP64,
-// 8192 chains of 64 stages: factor 1475 us with three, 1787 with four; 100 chains of 160:
-// 91 and 85).  8 x 8: four (FP64 / FP32, 8192 chains of 136: 1126 / 615 us with four, 1117 /
+// idle at their upper levels once the GPU is full and take more LDS.  16 x 16: three for any
+// number of chains, which costs few of them little (FP64, 100 chains of 160 stages: factor
+// 91 us with three, 85 with four) and saves many of them much (8192 of 64: 1475 and
+// 1787).  8 x 8: four (FP64 / FP32, 8192 chains of 136: 1126 / 615 us with four, 1117 /
 // 617 with three and one wave; 4 chains of 16: 15 us, 19 with three).
 int default_window_depth(int nmax) {
   if (nmax > 32) return 1;  // blocks of 33..64: one level per pass (factor64.hip)
@@ -262,14 +263,22 @@ int pick_window_depth(bool fp64, int nmax, int nrhs, const bmpc_options* o) {
 }
 
 // Levels of the passes after the first: the option, else the first pass's depth, or four at
-// 16 x 16 where that makes the second pass the last one (256 chains of 128 stages, FP32:
-// 84 us instead of 91).
-int pick_later_depth(bool fp64, int nmax, int N, int nrhs, int Tw, const bmpc_options* o) {
+// 9..16 where that makes the second pass the last one and the system has up to 512
+// scenarios, whose windows (up to 72 KB of LDS in FP64) fit on the card together, or the
+// window has only eight positions.  factor_solve with three / four, n = 16 in FP64 at N = 100:
+// S = 32 79 / 75 us, 512 275 / 263, 1024 487 / 515, 2048 892 / 946; in FP32 512 176 / 165,
+// 1024 307 / 314; eight positions (N = 65) S = 1024 348 / 337 and in FP32 228 / 204, n = 9 at S
+// = 4096 1078 / 1040, nine positions there (N = 80) 1234 / 1262.  The number of systems of a
+// batch does not count: the depth decides the order of the sums, and a batch gives the
+// bits of its systems' own plans.
+int pick_later_depth(bool fp64, int nmax, int S, int N, int nrhs, int Tw, const bmpc_options* o) {
   if (nmax > 32) return 1;
   bmpc_options lo{};
   if (o) lo = *o;
   const int mk = (N - 1) >> Tw;
-  const int dflt = nmax == 16 && !(o && o->window_depth > 0) && mk >= 8 && mk < 16 ? 4 : Tw;
+  const bool four = nmax == 16 && !(o && o->window_depth > 0) && mk >= 8 && mk < 16 &&
+                    (S <= 512 || mk == 8);
+  const int dflt = four ? 4 : Tw;
   lo.window_depth = std::min((o && o->later_depth > 0) ? o->later_depth : dflt, kMaxWindowDepth);
   return pick_window_depth(fp64, nmax, nrhs, &lo);
 }
@@ -559,7 +568,7 @@ bmpc_status init_plan(bmpc_plan p, const bmpc_dims* dims, bmpc_precision prec, v
   p->m = dims->N - 1;
   p->nmax = nmax_for(dims->n);
   p->Tw = pick_window_depth(p->fp64, p->nmax, dims->nrhs, opts);
-  p->Tw2 = pick_later_depth(p->fp64, p->nmax, dims->N, dims->nrhs, p->Tw, opts);
+  p->Tw2 = pick_later_depth(p->fp64, p->nmax, dims->S, dims->N, dims->nrhs, p->Tw, opts);
   p->B = systems_of(opts);
   p->opt_flags = flags_of(opts);
   p->chunk = kSolveRhs;
@@ -689,7 +698,8 @@ bmpc_status bmpc_cost_model(const bmpc_dims* dims, bmpc_precision prec,
     return BMPC_ERR_INVALID;
   const bool fp64 = prec == BMPC_FP64;
   const int Tw = pick_window_depth(fp64, nmax_for(dims->n), dims->nrhs, opts);
-  const int Tw2 = pick_later_depth(fp64, nmax_for(dims->n), dims->N, dims->nrhs, Tw, opts);
+  const int Tw2 =
+      pick_later_depth(fp64, nmax_for(dims->n), dims->S, dims->N, dims->nrhs, Tw, opts);
   Costs c = make_costs(*dims, fp64, Tw, Tw2, systems_of(opts), flags_of(opts));
   std::memset(cost, 0, sizeof(*cost));
   cost->factor_flops = c.factor_flops;
