@@ -161,15 +161,19 @@ Costs make_costs(const bmpc_dims& d, bool fp64, int Tw1, int Tw2, int B, int fla
   if (S <= 32) c.launches[KC_ROOT_REDUCE] = 0;
   // the solve and residual classes run once per chunk of right-hand sides
   const int ck = kSolveRhs, rk = residual_chunk(nmax_for(n));
-  const int chunks = (d.nrhs + ck - 1) / ck;
-  for (int k : {KC_SOLVE_X_FWD, KC_SOLVE_ROOT, KC_SOLVE_X_BWD}) c.launches[k] = chunks;
+  for (int k : {KC_SOLVE_X_FWD, KC_SOLVE_ROOT, KC_SOLVE_X_BWD})
+    c.launches[k] = (d.nrhs + ck - 1) / ck;
   for (int k : {KC_RESIDUAL, KC_RESIDUAL_ROOT}) c.launches[k] = (d.nrhs + rk - 1) / rk;
   const int64_t chains = (int64_t)B * S;
-  const bool one = d.nrhs == 1 && n <= 32;  // x_1 has a launch of its own where
-  const int top = solve_bwd_top(m, n, flags, chains, one);  // the merged levels do without it
-  c.launches[KC_SOLVE_FWD] = (solve_fwd_top(m, n, d.nrhs, flags, chains) - 1) * chunks;
-  c.launches[KC_SOLVE_BWD] =
-      (top - 1 + (!tops_together(n, chains) && top <= chain_levels(m) ? 1 : 0)) * chunks;
+  c.launches[KC_SOLVE_FWD] = c.launches[KC_SOLVE_BWD] = 0;
+  for (int q0 = 0; q0 < d.nrhs; q0 += ck) {
+    const int q = std::min(ck, d.nrhs - q0);
+    // x_1 has a launch of its own where the merged levels do without it
+    const int top = solve_bwd_top(m, n, q, flags, chains);
+    c.launches[KC_SOLVE_FWD] += solve_fwd_top(m, n, q, flags, chains) - 1;
+    c.launches[KC_SOLVE_BWD] +=
+        top - 1 + (!tops_together(n, chains) && top <= chain_levels(m) ? 1 : 0);
+  }
   // a batch of B systems does B times the work in the same launches
   for (PassPlan& pp : c.passes) {
     pp.flops *= B;
@@ -203,11 +207,13 @@ bool dims_ok(const bmpc_dims* d, int B) {
 int flags_of(const bmpc_options* o) { return o ? o->flags : 0; }
 int solve_fwd_top(int m, int n, int nrhs, int flags, int64_t chains) {
   const bool merged = !(flags & BMPC_FLAG_FWD_ONE_WAVE) && tops_together(n, chains) &&
-                      (fwd_top_one(n, nrhs) || !fwd_one(n, nrhs));
+                      (fwd_top_one(n, nrhs) || !fwd_one(n, nrhs)) && !few_rhs64(n, nrhs);
   return merged ? fwd_top_level(m, n) : chain_levels(m) + 1;
 }
-int solve_bwd_top(int m, int n, int flags, int64_t chains, bool one_vector) {
-  return (flags & BMPC_FLAG_NO_BWD_TOP_MERGE) || !(one_vector || tops_together(n, chains))
+int solve_bwd_top(int m, int n, int nrhs, int flags, int64_t chains) {
+  const bool one_vector = nrhs == 1 && n <= 32;
+  return (flags & BMPC_FLAG_NO_BWD_TOP_MERGE) || few_rhs64(n, nrhs) ||
+                 !(one_vector || tops_together(n, chains))
              ? chain_levels(m) + 1
              : bwd_top_level(m, n);
 }
@@ -464,11 +470,13 @@ void enqueue_solve_back(bmpc_plan p, const SolveArgs& a) {
   // right-hand side merges the top levels also where there are too many chains for that
   const bool one = a.nrhs == 1 && a.n <= 32;
   const int64_t chains = (int64_t)p->B * p->d.S;
-  const int L = chain_levels(p->m), top = solve_bwd_top(p->m, a.n, p->opt_flags, chains, one);
+  const int L = chain_levels(p->m), top = solve_bwd_top(p->m, a.n, a.nrhs, p->opt_flags, chains);
   const bool together = tops_together(a.n, chains);
   timed(p, KC_SOLVE_X_BWD, [&] {
     if (one && together)
       launch_solve_bwd_top<T>(a, top, true, st);
+    else if (few_rhs64(a.n, a.nrhs))
+      launch_solve64_x<T>(a, false, st);
     else
       launch_mm_top<T>(a, together ? top : L + 1, false, st);
   });
@@ -487,6 +495,8 @@ void enqueue_solve_chunk(bmpc_plan p, const SolveArgs& a) {
   timed(p, KC_SOLVE_X_FWD, [&] {
     if (fwd_top_one(a.n, a.nrhs) && top <= chain_levels(p->m))
       launch_solve_fwd_top<T>(a, top, st);
+    else if (few_rhs64(a.n, a.nrhs))
+      launch_solve64_x<T>(a, true, st);
     else
       launch_mm_top<T>(a, top, true, st);
   });

@@ -33,6 +33,10 @@ constexpr int kFactorThreads = 256;
 constexpr int kSolveRhs = 16;
 constexpr int kMaxRhs = 8;
 constexpr int kMaxRhs64 = 4;
+// Solves of so few right-hand sides at n > 48 go level by level through solve64.hip.
+constexpr __host__ __device__ bool few_rhs64(int n, int nrhs) {
+  return n > 48 && nrhs <= kMaxRhs64;
+}
 constexpr __host__ __device__ int residual_chunk(int nmax) {
   return nmax > 32 ? kMaxRhs64 : kMaxRhs;
 }
@@ -236,6 +240,12 @@ template <typename T>
 void launch_mm_level(const SolveArgs& a, int level, bool fwd, hipStream_t st);
 template <typename T>
 void launch_mm_top(const SolveArgs& a, int level_lo, bool fwd, hipStream_t st);
+
+// the same one level, or one x_1 step, at a time, where few_rhs64 (solve64.hip)
+template <typename T>
+void launch_solve64_level(const SolveArgs& a, int level, bool fwd, hipStream_t st);
+template <typename T>
+void launch_solve64_x(const SolveArgs& a, bool fwd, hipStream_t st);
 
 // Workgroups of the tail residual per chain of N stages with blocks of n.
 int residual_walks(int N, int n);

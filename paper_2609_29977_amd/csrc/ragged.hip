@@ -134,7 +134,7 @@ void build_back(RaggedState& R, Seq& seq, const std::vector<SolveArgs>& args, in
     bmpc_plan s = R.subs[i];
     const bool one = args[i].nrhs == 1, together = tops_together(s->d.n, R.chains);
     const int L = chain_levels(s->m);
-    topl[i] = solve_bwd_top(s->m, s->d.n, s->opt_flags, R.chains, one);
+    topl[i] = solve_bwd_top(s->m, s->d.n, args[i].nrhs, s->opt_flags, R.chains);
     if (one && together)
       x[std::make_tuple((int)SK_BWD_TOP, one_class(s))].push_back(
           {i, args[i], topl[i], 1, (unsigned)s->d.S, 1u, 1u});

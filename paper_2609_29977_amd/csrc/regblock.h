@@ -1,8 +1,10 @@
-// Register-resident n x n blocks for matrix-vector products on one wave (gfx950).
+// Register-resident n x n blocks for matrix-vector products on one or more waves
+// (gfx950).
 //
-// A block is split over the lanes: LPR = 64/NMAX lanes share one output index o and each
-// holds EPL = NMAX/LPR consecutive elements of the contraction index, starting at
-// base = (lane % LPR) * EPL.  In the normal mapping a
+// A block is split over the lanes of WAVES waves: wave w owns the RPW = NMAX/WAVES
+// output indices starting at w*RPW; within a wave LPR = 64/RPW lanes share one output
+// index o and each holds EPL = NMAX/LPR consecutive elements of the contraction index,
+// starting at base = (lane % LPR) * EPL.  In the normal mapping a
 // lane holds part of row o (products M v); in the transposed mapping part of column o
 // (products M^T v).  Both load coalesced from a row-major block and share the same
 // dot-product / reduction code.  Rows and columns >= n read as zero.
@@ -33,17 +35,39 @@ __device__ inline float buf_load_f32(__amdgpu_buffer_rsrc_t r, unsigned off) {
   return f;
 }
 
-template <typename T, int NMAX>
+template <typename T, int NMAX, int WAVES = 1>
 struct RegBlock {
-  static_assert(NMAX == 8 || NMAX == 16 || NMAX == 32, "block size bound");
-  static constexpr int LPR = 64 / NMAX;
+  static_assert((WAVES == 1 && (NMAX == 8 || NMAX == 16 || NMAX == 32)) ||
+                    (WAVES == 4 && NMAX == 64),
+                "block size bound, waves per block");
+  static constexpr int RPW = NMAX / WAVES;
+  static constexpr int LPR = 64 / RPW;
   static constexpr int EPL = NMAX / LPR;
   T v[EPL];
 
   __device__ static int out_index() {
-    return (int)(threadIdx.x & 63) / LPR;
+    return (WAVES > 1 ? (int)(threadIdx.x >> 6) * RPW : 0) + (int)(threadIdx.x & 63) / LPR;
   }
   __device__ static int base() { return ((threadIdx.x & 63) % LPR) * EPL; }
+
+  // For n known at run time: a full block from one lane base address, a smaller one with
+  // its out-of-range elements replaced by zero (they load element 0).
+  template <bool TRANS>
+  __device__ void load(const T* __restrict__ g, int n) {
+    const int o = out_index(), b = base();
+    if (n == NMAX) {
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) v[e] = TRANS ? g[(b + e) * NMAX + o] : g[o * NMAX + b + e];
+    } else {
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) {
+        const int r = TRANS ? b + e : o, c = TRANS ? o : b + e;
+        const bool ok = r < n && c < n;
+        const T t = g[ok ? r * n + c : 0];
+        v[e] = ok ? t : T(0);
+      }
+    }
+  }
 
   // FULL (n == NMAX known at compile time): every element of the lane sits at a fixed
   // offset from one lane base address.  Otherwise the block is read through a buffer

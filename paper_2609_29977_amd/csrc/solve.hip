@@ -707,6 +707,7 @@ LevelCfg solve_level_config(const SolveArgs& a, int level, bool fwd, int nmax, b
 
 template <typename T>
 static void launch_level(const SolveArgs& a, int level, bool fwd, hipStream_t st) {
+  if (few_rhs64(a.n, a.nrhs)) return launch_solve64_level<T>(a, level, fwd, st);
   if (a.n > 32) return launch_mm_level<T>(a, level, fwd, st);
   by_size(a.n, [&](auto nmax, auto full) {
     level_t<T, decltype(nmax)::value, decltype(full)::value>(a, level, fwd, st);
