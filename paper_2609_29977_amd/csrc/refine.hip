@@ -8,6 +8,7 @@
 // (per-block partial maxima, then one block), so they are deterministic and need no
 // atomics.
 #include <algorithm>
+#include <type_traits>
 
 #include "bmpc_internal.h"
 #include "multi.h"
@@ -389,21 +390,27 @@ __device__ __attribute__((always_inline)) inline void residual_root_body(const R
   }
   const double* w = a.w + (size_t)sys * S * nrhs * n;
   double sum = 0.0;
-  for (int q0 = 0; q0 < nrhs; q0 += QB) {
+  for (int q0 = 0, taken; q0 < nrhs; q0 += taken) {
     if (q0) __syncthreads();
-    if (nrhs == 1) {
-      double acc[1];
-      scenario_sums<NMAX, 1, 16>(w, S, n, 1, 0, acc);
-      if ((t & 63) < NMAX) part[0][wv][i] = acc[0];
-    } else {
-      double acc[QB];
-      scenario_sums<NMAX, QB, 4>(w, S, n, nrhs, q0, acc);
+    auto partials = [&](auto qb, auto in_flight) {
+      constexpr int Q = decltype(qb)::value;
+      double acc[Q];
+      scenario_sums<NMAX, Q, decltype(in_flight)::value>(w, S, n, nrhs, q0, acc);
       if ((t & 63) < NMAX)
 #pragma unroll
-        for (int u = 0; u < QB; ++u) part[u][wv][i] = acc[u];
-    }
+        for (int u = 0; u < Q; ++u) part[u][wv][i] = acc[u];
+      return Q;
+    };
+    // with few scenarios (some rounds of loads) four for three, the last one read again for the
+    // one that is not there; beyond, as many as there are, a power of two
+    if (nrhs - q0 >= (S <= 16 * (1024 / NMAX) ? 3 : QB))
+      taken = partials(std::integral_constant<int, QB>{}, std::integral_constant<int, 4>{});
+    else if (nrhs - q0 >= 2)
+      taken = partials(std::integral_constant<int, 2>{}, std::integral_constant<int, 8>{});
+    else
+      taken = partials(std::integral_constant<int, 1>{}, std::integral_constant<int, 16>{});
     __syncthreads();
-    if (mine && q >= q0 && q < q0 + QB) {
+    if (mine && q >= q0 && q < q0 + taken) {
 #pragma unroll
       for (int v = 0; v < W; ++v) sum += part[q - q0][v][i];
     }

@@ -468,7 +468,7 @@ __device__ __attribute__((always_inline)) inline void solve_root_body(const Solv
     bv = rn > 0.0 ? bv / rn : 0.0;
   }
   double sum = 0.0;
-  for (int q0 = 0; q0 < nrhs; q0 += QB) {
+  for (int q0 = 0, taken; q0 < nrhs; q0 += taken) {
     if (q0) __syncthreads();
     auto partials = [&](auto qb, auto in_flight) {
       constexpr int Q = decltype(qb)::value;
@@ -477,18 +477,28 @@ __device__ __attribute__((always_inline)) inline void solve_root_body(const Solv
       if ((t & 63) < NMAX)
 #pragma unroll
         for (int u = 0; u < Q; ++u) part[u][t >> 6][i] = acc[u];
+      return Q;
     };
-    // sixteen loads in flight per thread, or as many as there are scenarios for
-    if (nrhs == 1 && S <= 4 * (1024 / NMAX))
-      partials(std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{});
-    else if (nrhs == 1)
-      partials(std::integral_constant<int, 1>{}, std::integral_constant<int, 16>{});
-    else if (nrhs - q0 <= QB / 2)
-      partials(std::integral_constant<int, QB / 2>{}, std::integral_constant<int, 4>{});
+    // with few scenarios (a round or some of loads) all right-hand sides at once, the last one
+    // read again for those that are not there; beyond, as many as there are, a power of two,
+    // with at least sixteen loads in flight per thread: S = 20000, n = 8 in FP64, two
+    // right-hand sides, one solve 584 -> 441 us, five 858 -> 671
+    const int left = nrhs - q0;
+    const bool spare = S <= 4 * (1024 / NMAX);
+    if (QB >= 8 && left >= (spare ? 5 : 8))
+      taken = partials(std::integral_constant<int, QB < 8 ? QB : 8>{}, std::integral_constant<int, 4>{});
+    else if (QB >= 4 && left >= (S <= 16 * (1024 / NMAX) ? 3 : 4))
+      taken = partials(std::integral_constant<int, QB < 4 ? QB : 4>{}, std::integral_constant<int, 4>{});
+    else if (left >= 2 && spare)
+      taken = partials(std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});
+    else if (left >= 2)
+      taken = partials(std::integral_constant<int, 2>{}, std::integral_constant<int, 8>{});
+    else if (spare)
+      taken = partials(std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{});
     else
-      partials(std::integral_constant<int, QB>{}, std::integral_constant<int, 4>{});
+      taken = partials(std::integral_constant<int, 1>{}, std::integral_constant<int, 16>{});
     __syncthreads();
-    if (mine && q >= q0 && q < q0 + QB) {
+    if (mine && q >= q0 && q < q0 + taken) {
 #pragma unroll
       for (int v = 0; v < W; ++v) sum += part[q - q0][v][i];
     }

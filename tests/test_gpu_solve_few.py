@@ -1,8 +1,8 @@
-"""Solves of few right-hand sides with the kernels that hold a block in the registers of one or
-four waves: block sizes at the edges of their classes (full and padded), chains of 0 to 8
-levels, the launch flags, a last chunk of few right-hand sides behind sixteen, more
-scenarios than a grid dimension holds.  Reference: the FP64 oracle with the parity suite's
-tolerances (1e-11 FP64, 1e-10 FP32 with refinement)."""
+"""Solves of few right-hand sides with the kernels that hold a block in the registers of four
+waves: block sizes at the edges of their classes (full and padded), chains of 0 to 8
+levels, the launch flags, a last chunk of few right-hand sides behind sixteen; the root
+step either side of its scenario counts.  Reference: the FP64 oracle with the parity
+suite's tolerances (1e-11 FP64, 1e-10 FP32 with refinement)."""
 import numpy as np
 import pytest
 
@@ -31,6 +31,15 @@ def _check(S, N, n, nrhs, precision, flags=0):
     err = float(np.max(np.abs(x.cpu().numpy() - ref)) / np.max(np.abs(ref)))
     assert err <= (1e-11 if precision == "fp64" else 1e-10), (N, err)
     p.close()
+
+
+# either side of the chains whose top levels share a launch (512, 256 above n = 16), and of the
+# scenarios that the root step reads in one go (128, 512)
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("S", [127, 129, 255, 257, 511, 514])
+@pytest.mark.parametrize("n,nrhs", [(8, 2), (8, 3), (16, 1), (12, 5), (21, 2), (32, 3), (32, 6)])
+def test_chain_counts(n, nrhs, S, precision):
+    _check(S, 12, n, nrhs, precision)
 
 
 SIZES64 = [(49, 1), (49, 4), (50, 3), (63, 2), (64, 1), (64, 4), (64, 5), (57, 18)]
