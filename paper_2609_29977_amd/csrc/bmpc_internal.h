@@ -224,12 +224,13 @@ void launch_root_factor_solve(const RootStep& s, const SolveArgs& a, hipStream_t
 template <typename T>
 void launch_solve_bwd_level(const SolveArgs& a, int level, hipStream_t st);
 // The backward levels from the top down to level_lo in one launch (one workgroup per chain,
-// one wave per position), for one right-hand side and n <= 32; with_x: root propagation and
-// the x_1 backward step before them.  level_lo as bwd_top_level has it or above.
+// one wave per position), for few right-hand sides; with_x: root propagation and
+// the x_1 backward step before them (alone if level_lo is above the top).  level_lo as
+// bwd_top_level has it or above.
 template <typename T>
 void launch_solve_bwd_top(const SolveArgs& a, int level_lo, bool with_x, hipStream_t st);
-// The forward levels from level_lo up to the top and the x_1 forward step in one launch, where
-// fwd_top_one says so.
+// The forward levels from level_lo up to the top (where fwd_top_few says so; else none, level_lo
+// above the top) and the x_1 forward step in one launch, for few right-hand sides.
 template <typename T>
 void launch_solve_fwd_top(const SolveArgs& a, int level_lo, hipStream_t st);
 
@@ -322,10 +323,25 @@ __host__ __device__ inline int mm_fwd_waves(int m, int n, bool fp64, int level) 
                                                      ? mm_top_share(n, level_count(m, level))
                                                      : 4);
 }
-// One right-hand side with full blocks goes forward through the one-vector kernels; their merged
-// launch exists up to n = 16, the levels of n = 32 stay single.
-constexpr bool fwd_one(int n, int nrhs) { return nrhs == 1 && (n == 8 || n == 16 || n == 32); }
-constexpr bool fwd_top_one(int n, int nrhs) { return fwd_one(n, nrhs) && n <= 16; }
+// Few right-hand sides at n <= 32 go through the kernels that hold a block in a wave's registers
+// (solve.hip), the others through matrix products, which read a block once for up to
+// sixteen columns but cost the same for one of them, and pad n to 16 or 32 rows.  By n, nrhs
+// and precision alone: a system's sums do not depend on the others of its launch.  One
+// solve, products / registers: two right-hand sides in FP64 at S = 60, N = 250 n = 8 82 / 59 us, n =
+// 32 212 / 178, at S = 1500, N = 16 85 / 63 and 248 / 214, at S = 4, N = 16 24 / 20 and 46 / 41,
+// n = 12 24.9 / 25.6; in FP32 at S = 4, N = 16 n = 12 22 / 24, n = 16 21.8 / 21.4; three at S = 4, N
+// = 16 n = 8 23.5 / 23 in FP64 and 22.5 / 23.5 in FP32, n = 16 25.5 / 27.5 in FP64, n = 32 at S = 1500,
+// N = 16 in FP64 265 / 242.
+constexpr int kFewRhs = 3;
+constexpr bool few_rhs(int n, int nrhs, bool fp64) {
+  return n <= 32 && (nrhs == 1 || (nrhs == 2 && (fp64 || n <= 8 || n >= 16)) ||
+                     (nrhs == kFewRhs && (n == 32 || (fp64 && n <= 8))));
+}
+// Their merged forward launch, of sixteen waves, exists where a wave does with the 128
+// registers that it then has.
+constexpr bool fwd_top_few(int n, int nrhs, bool fp64) {
+  return few_rhs(n, nrhs, fp64) && n <= (fp64 ? 16 : 32);
+}
 // Whether they do, for so many chains in the launch: up to what the GPU holds at once (256
 // compute units with one workgroup each for n > 16, two below).  Beyond that the barriers
 // cost more than the launches they replace.  One solve, together / apart: one right-hand side

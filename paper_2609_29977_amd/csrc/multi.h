@@ -130,16 +130,19 @@ void launch_info_reset(unsigned long long* info, int count, hipStream_t st);
 
 enum SolveKind {
   SK_LEVEL = 0,   // matrix products (solve_rhs.hip)
-  SK_LEVEL_ONE,   // solve_level_one_kernel (one right-hand side, n == NMAX)
-  SK_BWD_ROWS,    // solve_bwd_rows_kernel (backward level, n = 32, one right-hand side)
+  SK_LEVEL_ONE,   // solve_level_one_kernel (few right-hand sides)
+  SK_BWD_ROWS,    // solve_bwd_rows_kernel (few right-hand sides, backward level, n > 16)
   SK_BWD_TOP,     // solve_bwd_top_kernel (x_1 step and top backward levels)
   SK_FWD_TOP,     // solve_fwd_top_kernel (top forward levels and x_1 step)
+  SK_X_FWD,       // solve_x_fwd_kernel, solve_x_bwd_kernel: x_1 alone
+  SK_X_BWD,
   SK_MM_TOP,      // the same as matrix products, either sweep
   SK_ROOT
 };
 struct LevelCfg {
   int kind;        // SolveKind
   int count;       // positions of the level per chain
+  int flat;        // register kernels: count where the grid is flat, else 0
   unsigned gx, gy, gz, threads;
   size_t lds;
 };
@@ -149,11 +152,12 @@ struct MmTopCfg {
   unsigned threads;
   size_t lds;
 };
+MmTopCfg x_fwd_config(const SolveArgs& a, int nmax, bool fp64);
 MmTopCfg mm_top_config(const SolveArgs& a, int level_lo, bool fwd, bool fp64);
 
 // n: the items' block size, or for the matrix products any with their mm_class
 template <typename T>
-void launch_solve_multi(int kind, bool fwd, int n, const MultiItem<SolveArgs>* items, int nitems,
+void launch_solve_multi(int kind, bool fwd, int n, int nrhs, const MultiItem<SolveArgs>* items, int nitems,
                         unsigned blocks, unsigned threads, size_t lds, const Reloc& r,
                         hipStream_t st);
 template <typename T>
@@ -163,9 +167,9 @@ void launch_mm_multi(int kind, bool fwd, int n, const MultiItem<SolveArgs>* item
 // Block sizes that share the matrix-product kernels of a launch: row tiles, n % 4 == 0.
 constexpr int mm_class(int n) { return (n + 15) / 16 * 2 + (n % 4 == 0 ? 1 : 0); }
 
-// Dynamic LDS of a one-vector level launch (waves per position), of a residual launch
-// (right-hand sides of the chunk).
-size_t solve_level_lds(bool fp64, int nmax, int waves);
+// Dynamic LDS of a level launch of few right-hand sides (waves per position), of a residual
+// launch (right-hand sides of the chunk).
+size_t solve_level_lds(bool fp64, int nmax, int waves, int nrhs);
 size_t residual_lds(int nmax, int nrhs);
 
 void launch_residual_multi(int nmax, bool full, const MultiItem<ResidualArgs>* items,

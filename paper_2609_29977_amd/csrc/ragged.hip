@@ -34,7 +34,7 @@ enum RaggedOp {
 
 struct LaunchRec {
   int op = 0, cls = 0;
-  int nmax = 32, kind = 0, n = 32;
+  int nmax = 32, kind = 0, n = 32, nrhs = 1;
   bool first = false, final = false, fwd = false, full = false;
   size_t table = 0;  // byte offset of the item table in the device table buffer
   int nitems = 0;
@@ -132,12 +132,13 @@ void build_back(RaggedState& R, Seq& seq, const std::vector<SolveArgs>& args, in
   std::vector<int> topl(B);
   for (int i = 0; i < B; ++i) {
     bmpc_plan s = R.subs[i];
-    const bool one = args[i].nrhs == 1, together = tops_together(s->d.n, R.chains);
+    const bool few = few_rhs(s->d.n, args[i].nrhs, s->fp64);
+    const bool together = tops_together(s->d.n, R.chains);
     const int L = chain_levels(s->m);
     topl[i] = solve_bwd_top(s->m, s->d.n, args[i].nrhs, s->opt_flags, R.chains);
-    if (one && together)
-      x[std::make_tuple((int)SK_BWD_TOP, one_class(s))].push_back(
-          {i, args[i], topl[i], 1, (unsigned)s->d.S, 1u, 1u});
+    if (few)
+      x[std::make_tuple((int)(together && topl[i] <= L ? SK_BWD_TOP : SK_X_BWD), one_class(s))]
+          .push_back({i, args[i], topl[i], 1, (unsigned)s->d.S, 1u, 1u});
     else
       x[std::make_tuple((int)SK_MM_TOP, mm_class(s->d.n))].push_back(
           {i, args[i], together ? topl[i] : L + 1, 0, (unsigned)s->d.S, 1u, 1u});
@@ -153,6 +154,7 @@ void build_back(RaggedState& R, Seq& seq, const std::vector<SolveArgs>& args, in
       rec.cls = groups == &x ? KC_SOLVE_X_BWD : KC_SOLVE_BWD;
       rec.kind = std::get<0>(g.first);
       rec.n = g.second[0].a.n;
+      rec.nrhs = g.second[0].a.nrhs;
       rec.fwd = false;
       for (const auto& it : g.second)
         rec.threads = std::max(rec.threads, mm_top_config(it.a, it.p0, false, true).threads);
@@ -168,10 +170,12 @@ void build_back(RaggedState& R, Seq& seq, const std::vector<SolveArgs>& args, in
       if (c.count <= 0) continue;
       const auto key =
           std::make_tuple(c.kind, c.kind == SK_LEVEL ? mm_class(s->d.n) : one_class(s));
-      groups[key].push_back({i, args[i], l, c.count, c.gx, c.gy, c.gz});
+      groups[key].push_back(
+          {i, args[i], l, c.kind == SK_LEVEL ? c.count : c.flat, c.gx, c.gy, c.gz});
       LaunchRec& rec = recs[key];
       rec.op = RO_SOLVE;
       rec.n = s->d.n;
+      rec.nrhs = args[i].nrhs;
       rec.cls = KC_SOLVE_BWD;
       rec.kind = c.kind;
       rec.fwd = false;
@@ -188,8 +192,8 @@ void build_fwd(RaggedState& R, Seq& seq, const std::vector<SolveArgs>& args) {
   int maxL = 0;
   std::vector<int> topl(B);
   for (int i = 0; i < B; ++i) {
-    topl[i] = solve_fwd_top(R.subs[i]->m, R.subs[i]->d.n, args[i].nrhs, R.subs[i]->opt_flags,
-                            R.chains);
+    topl[i] = solve_fwd_top(R.subs[i]->m, R.subs[i]->d.n, args[i].nrhs, R.subs[i]->fp64,
+                            R.subs[i]->opt_flags, R.chains);
     maxL = std::max(maxL, topl[i] - 1);
   }
   for (int l = 1; l <= maxL; ++l) {
@@ -202,10 +206,12 @@ void build_fwd(RaggedState& R, Seq& seq, const std::vector<SolveArgs>& args) {
       if (c.count <= 0) continue;
       const auto key =
           std::make_tuple(c.kind, c.kind == SK_LEVEL ? mm_class(s->d.n) : one_class(s));
-      groups[key].push_back({i, args[i], l, c.count, c.gx, c.gy, c.gz});
+      groups[key].push_back(
+          {i, args[i], l, c.kind == SK_LEVEL ? c.count : c.flat, c.gx, c.gy, c.gz});
       LaunchRec& rec = recs[key];
       rec.op = RO_SOLVE;
       rec.n = s->d.n;
+      rec.nrhs = args[i].nrhs;
       rec.cls = KC_SOLVE_FWD;
       rec.kind = c.kind;
       rec.fwd = true;
@@ -217,9 +223,9 @@ void build_fwd(RaggedState& R, Seq& seq, const std::vector<SolveArgs>& args) {
   std::map<std::tuple<int, int>, std::vector<Pending<SolveArgs>>> xf;
   for (int i = 0; i < B; ++i) {
     bmpc_plan s = R.subs[i];
-    const bool one = fwd_top_one(s->d.n, args[i].nrhs) && topl[i] <= chain_levels(s->m);
-    xf[std::make_tuple((int)(one ? SK_FWD_TOP : SK_MM_TOP),
-                       one ? one_class(s) : mm_class(s->d.n))]
+    const bool few = few_rhs(s->d.n, args[i].nrhs, s->fp64), alone = topl[i] > chain_levels(s->m);
+    xf[std::make_tuple((int)(!few ? SK_MM_TOP : alone ? SK_X_FWD : SK_FWD_TOP),
+                       few ? one_class(s) : mm_class(s->d.n))]
         .push_back({i, args[i], topl[i], 0, (unsigned)s->d.S, 1u, 1u});
   }
   for (auto& g : xf) {
@@ -228,9 +234,12 @@ void build_fwd(RaggedState& R, Seq& seq, const std::vector<SolveArgs>& args) {
     rec.cls = KC_SOLVE_X_FWD;
     rec.kind = std::get<0>(g.first);
     rec.n = g.second[0].a.n;
+    rec.nrhs = g.second[0].a.nrhs;
     rec.fwd = true;
     for (const auto& it : g.second) {
-      const MmTopCfg c = mm_top_config(it.a, it.p0, true, R.subs[0]->fp64);
+      const MmTopCfg c = rec.kind == SK_X_FWD
+                             ? x_fwd_config(it.a, nmax_for(it.a.n), R.subs[0]->fp64)
+                             : mm_top_config(it.a, it.p0, true, R.subs[0]->fp64);
       rec.threads = std::max(rec.threads, c.threads);
       rec.lds = std::max(rec.lds, c.lds);
     }
@@ -417,7 +426,7 @@ void run(bmpc_plan p, const Seq& seq, const Reloc& r) {
                                   rec.blocks, rec.nmax, r, st);
           break;
         case RO_SOLVE:
-          launch_solve_multi<T>(rec.kind, rec.fwd, rec.n,
+          launch_solve_multi<T>(rec.kind, rec.fwd, rec.n, rec.nrhs,
                                 static_cast<const MultiItem<SolveArgs>*>(tab), rec.nitems,
                                 rec.blocks, rec.threads, rec.lds, r, st);
           break;

@@ -11,10 +11,10 @@
 // The permutation Pi_i (Algorithm 2, gather and scatter) is applied as an index map:
 // chain position j reads and writes stage N-j of the natural-order vectors.
 //
-// This file: the level kernels of one right-hand side with full blocks, and the root step.
-// Factor blocks are held in registers (RegBlock); every block a position needs is loaded at
-// once, spread over up to four waves.  Several right-hand sides, padded blocks, blocks of
-// 33..64 and the x_1 steps: solve_rhs.hip.
+// This file: the sweeps of few right-hand sides at n <= 32 (few_rhs), and the root step.
+// Factor blocks are held in registers (RegBlock) and read once for all right-hand sides;
+// every block a position needs is loaded at once, spread over up to four waves.  More
+// right-hand sides and blocks of 33..64: solve_rhs.hip, solve64.hip.
 #include <algorithm>
 
 #include <type_traits>
@@ -25,7 +25,6 @@
 #include "regblock.h"
 #include "root.h"
 #include "solve_common.h"
-#include "solve_mm.h"
 
 namespace bmpc {
 
@@ -42,53 +41,62 @@ namespace {
 constexpr int kPullsPerWave = 2;
 constexpr int kLevelMaxWaves = 4;
 
-// waves of a forward position
+// waves of a forward position, and of the x_1 forward step of a chain of L levels
 __host__ __device__ inline int fwd_one_waves(int level) {
   return level < 2 ? 1 : level - 1 < kLevelMaxWaves ? level - 1 : kLevelMaxWaves;
 }
-
-// Dynamic LDS of a level workgroup with W waves:
-// vbuf[W][kPullsPerWave][NMAX], partial[W][NMAX], rhs[NMAX].
-template <typename T, int NMAX>
-inline size_t level_smem_bytes(int waves) {
-  return (size_t)(waves * kPullsPerWave + waves + 1) * NMAX * sizeof(T);
+__host__ __device__ inline int x_fwd_waves(int L) {
+  return L < 3 ? 1 : L < 2 * kLevelMaxWaves ? (L + 1) / 2 : kLevelMaxWaves;
 }
 
-// Level kernel for one right-hand side; FULL: n == NMAX (smaller n: backward only, padding
-// read as zero).  Lane l holds element l % NMAX of each vector it stages; the chain comes
-// from the grid (position index, scenario, system), and each wave keeps its partial sums
-// in a register across rounds.  One position (index i of the level, scenario sl, system sys) served by W waves, this
-// thread's wave being wv; smem holds (W * kPullsPerWave + W + 1) * NMAX elements.
+// Dynamic LDS of a level workgroup with W waves:
+// vbuf[W][kPullsPerWave][NR][NMAX], partial[W][NR][NMAX], rhs[NR][NMAX].
+template <typename T, int NMAX>
+inline size_t level_smem_bytes(int waves, int nrhs) {
+  return (size_t)(waves * kPullsPerWave + waves + 1) * nrhs * NMAX * sizeof(T);
+}
+
+// What a wave or several do for NR right-hand sides: a position of a forward or backward level,
+// or the x_1 forward step, whose pulls are the G_r of the last position of every level with
+// an odd chain length and which also forms w_s = F_s y_X.
+enum FewKind { FEW_FWD, FEW_BWD, FEW_X };
+
+// One position (index i of the level, scenario sl, system sys) served by W waves, this
+// thread's wave being wv; smem holds (W * kPullsPerWave + W + 1) * NR * NMAX elements.  FULL:
+// n == NMAX (smaller n: padding read as zero).  Lane l holds element l % NMAX of each vector
+// it stages, and each wave keeps its partial sums in registers across rounds.
 // TOGETHER: the workgroup holds several positions, so that every wave goes through the
 // barrier, the ones without a position (not active) too.
-template <typename T, int NMAX, bool FWD, bool FULL, bool TOGETHER = false>
-__device__ __attribute__((always_inline)) inline void level_one_position(
-    const SolveArgs& a, int level, int i, int sl, int sys, int W, int wv,
-    unsigned char* smem, bool active = true) {
+template <typename T, int NMAX, int KIND, bool FULL, int NR, bool TOGETHER = false>
+__device__ __attribute__((always_inline)) inline void few_position(
+    const SolveArgs& a, int level, int i, int sl, int sys, int W, int wv, unsigned char* smem,
+    bool active = true) {
   if (TOGETHER && !active) {
     __syncthreads();
     return;
   }
   typedef RegBlock<T, NMAX> RB;
+  constexpr bool BWD = KIND == FEW_BWD;
   constexpr int P = kPullsPerWave;
   const int n = FULL ? NMAX : a.n;
   const size_t nn = (size_t)n * n;
   const int N = a.N, m = a.m;
   const int lane = threadIdx.x & 63;
   typedef T Vec[NMAX];
-  Vec* vbuf = reinterpret_cast<Vec*>(smem);  // [w * P + u]
-  Vec* partial = vbuf + W * P;               // [w]
-  T* t = partial[W];                         // right-hand side, then residual
+  Vec* vbuf = reinterpret_cast<Vec*>(smem);  // [(w * P + u) * NR + q]
+  Vec* partial = vbuf + W * P * NR;          // [w * NR + q]
+  Vec* t = partial + W * NR;                 // [q]: right-hand side, then residual
   const size_t s = (size_t)sys * a.S + sl;
-  const int j = (2 * i + 1) << (level - 1);
+  const int j = KIND == FEW_X ? N : (2 * i + 1) << (level - 1);
   const size_t gstride = g_chain_blocks(N);
   const T* Gl = reinterpret_cast<const T*>(a.Gl) + s * gstride * nn;
   const T* Gr = reinterpret_cast<const T*>(a.Gr) + s * gstride * nn;
   const T* Linv = reinterpret_cast<const T*>(a.Linv) + s * N * nn;
-  T* y = reinterpret_cast<T*>(a.y) + s * N * n;
-  T* yj = y + (size_t)(j - 1) * n;
-  const int half = 1 << (level - 1);
-  const int npull = FWD ? 2 * (level - 1) : 2;
+  T* y = reinterpret_cast<T*>(a.y) + s * N * n * NR;
+  T* yj = y + (size_t)(j - 1) * n * NR;
+  const int half = BWD ? 1 << (level - 1) : 0;
+  const int npull = KIND == FEW_FWD ? 2 * (level - 1) : BWD ? 2 : chain_levels(m);
+  const size_t len = vec_len(a);
   const size_t off = (size_t)sys * a.vsys + ((size_t)sl * N + (N - j)) * n;
   const int seg = sys * a.seg_sys;
   const int o = RB::out_index();
@@ -97,45 +105,54 @@ __device__ __attribute__((always_inline)) inline void level_one_position(
   const bool vin = FULL || vl < n;
 
   auto pull = [&](int p, const T*& blk, const T*& vec) -> bool {
-    if constexpr (FWD) {
+    int c;
+    if constexpr (KIND == FEW_FWD) {
       const int tt = p >> 1;
-      const int c = (p & 1) ? j + (1 << tt) : j - (1 << tt);
+      c = (p & 1) ? j + (1 << tt) : j - (1 << tt);
       if (c > m) return false;
       blk = ((p & 1) ? Gl : Gr) + (size_t)(c - 1) * nn;
-      vec = y + (size_t)(c - 1) * n;
-    } else {
+    } else if constexpr (BWD) {
       if (p == 0) {
         if (j - half < 1) return false;
         blk = Gl + (size_t)(j - 1) * nn;
-        vec = y + (size_t)(j - half - 1) * n;
+        c = j - half;
       } else {
-        const int ir = j + half <= m ? j + half - 1 : N - 1;
+        c = j + half <= m ? j + half : N;
         blk = Gr + (size_t)(j - 1) * nn;
-        vec = y + (size_t)ir * n;
       }
+    } else {
+      if (((m >> p) & 1) == 0) return false;
+      c = (m >> p) << p;
+      blk = Gr + (size_t)(c - 1) * nn;
     }
+    vec = y + (size_t)(c - 1) * n * NR;
     return true;
   };
 
   // All loads of the first round are issued before the first wait.
-  RB lin;
-  T rv = T(0);
-  double rb = 0.0, xo = 0.0;
+  RB lin, fb;
+  T rv[NR] = {};
+  double rb[NR] = {}, xo[NR] = {};
   if (wv == 0) {
     if constexpr (FULL)
-      lin.template load_packed_raw<!FWD>(Linv + (size_t)(j - 1) * nn);
+      lin.template load_packed_raw<BWD>(Linv + (size_t)(j - 1) * nn);
     else
-      lin.template load_packed<!FWD>(Linv + (size_t)(j - 1) * nn, n);
-    if constexpr (FWD)
-      rb = vin ? a.b[off + vl] : 0.0;
-    else
-      rv = vin ? yj[vl] : T(0);
-    if (!FWD && a.accumulate && (FULL || o < n)) xo = a.x[off + o];
+      lin.template load_packed<BWD>(Linv + (size_t)(j - 1) * nn, n);
+    if constexpr (KIND == FEW_X)
+      fb.template load_fixed<false, FULL>(reinterpret_cast<const T*>(a.F) + s * nn, n);
+#pragma unroll
+    for (int q = 0; q < NR; ++q) {
+      if constexpr (BWD)
+        rv[q] = vin ? yj[vl * NR + q] : T(0);
+      else
+        rb[q] = vin ? a.b[(size_t)q * len + off + vl] : 0.0;
+      if (BWD && a.accumulate && (FULL || o < n)) xo[q] = a.x[(size_t)q * len + off + o];
+    }
   }
-  T tot = T(0);
+  T tot[NR];
   auto round = [&](int base, bool first) {
     RB blk[P];
-    T vv[P];
+    T vv[P][NR];
     bool has[P];
 #pragma unroll
     for (int u = 0; u < P; ++u) {
@@ -144,55 +161,162 @@ __device__ __attribute__((always_inline)) inline void level_one_position(
       const T* vp = nullptr;
       has[u] = p < npull && pull(p, bp, vp);
       if (has[u]) {
-        blk[u].template load_fixed<!FWD, FULL>(bp, n);
-        vv[u] = vin ? vp[vl] : T(0);
+        blk[u].template load_fixed<BWD, FULL>(bp, n);
+#pragma unroll
+        for (int q = 0; q < NR; ++q) vv[u][q] = vin ? vp[vl * NR + q] : T(0);
       }
     }
     if (first && wv == 0 && lane < NMAX) {
-      if constexpr (FWD) {
-        const double rn = a.rnorm ? a.rnorm[seg] : 1.0;
-        t[lane] = static_cast<T>(rn > 0.0 ? rb / rn : 0.0);
-      } else {
-        t[lane] = rv;
+#pragma unroll
+      for (int q = 0; q < NR; ++q) {
+        if constexpr (BWD) {
+          t[q][lane] = rv[q];
+        } else {
+          const double rn = a.rnorm ? a.rnorm[seg + q] : 1.0;
+          t[q][lane] = static_cast<T>(rn > 0.0 ? rb[q] / rn : 0.0);
+        }
       }
     }
 #pragma unroll
     for (int u = 0; u < P; ++u)
-      if (has[u] && lane < NMAX) vbuf[wv * P + u][lane] = vv[u];
-    wave_lds_fence();
-    T acc = T(0);
 #pragma unroll
-    for (int u = 0; u < P; ++u)
-      if (has[u]) acc += blk[u].dot(vbuf[wv * P + u]);
-    acc = lane_group_sum_dpp<RB::LPR>(acc);
-    tot = first ? acc : tot + acc;
+      for (int q = 0; q < NR; ++q)
+        if (has[u] && lane < NMAX) vbuf[(wv * P + u) * NR + q][lane] = vv[u][q];
+    wave_lds_fence();
+#pragma unroll
+    for (int q = 0; q < NR; ++q) {
+      T acc = T(0);
+#pragma unroll
+      for (int u = 0; u < P; ++u)
+        if (has[u]) acc += blk[u].dot(vbuf[(wv * P + u) * NR + q]);
+      acc = lane_group_sum_dpp<RB::LPR>(acc);
+      tot[q] = first ? acc : tot[q] + acc;
+    }
     wave_lds_fence();
   };
   round(0, true);
   for (int base = W * P; base < npull; base += W * P) round(base, false);
   if (TOGETHER || W > 1) {
-    if (writer) partial[wv][o] = tot;
+    if (writer)
+#pragma unroll
+      for (int q = 0; q < NR; ++q) partial[wv * NR + q][o] = tot[q];
     __syncthreads();
     if (wv != 0) return;
-    T sum = partial[0][o];
-    for (int w = 1; w < W; ++w) sum += partial[w][o];
-    tot = sum;
+#pragma unroll
+    for (int q = 0; q < NR; ++q) {
+      T sum = partial[q][o];
+      for (int w = 1; w < W; ++w) sum += partial[w * NR + q][o];
+      tot[q] = sum;
+    }
   }
   // residual of the position, then L_jj^{-1} (forward) or L_jj^{-T} (backward) on it
-  const T r = t[o] - tot;
+#pragma unroll
+  for (int q = 0; q < NR; ++q) tot[q] = t[q][o] - tot[q];
   wave_lds_fence();
-  if (writer) t[o] = r;
+  if (writer)
+#pragma unroll
+    for (int q = 0; q < NR; ++q) t[q][o] = tot[q];
   wave_lds_fence();
-  if constexpr (FULL) lin.template mask_packed<!FWD>();
-  const T v = lane_group_sum_dpp<RB::LPR>(lin.dot(t));
+  if constexpr (FULL) lin.template mask_packed<BWD>();
+  T v[NR];
+#pragma unroll
+  for (int q = 0; q < NR; ++q) v[q] = lane_group_sum_dpp<RB::LPR>(lin.dot(t[q]));
   if (out) {
-    yj[o] = v;
-    if constexpr (!FWD) {
-      const size_t idx = off + o;
+#pragma unroll
+    for (int q = 0; q < NR; ++q) {
+      yj[o * NR + q] = v[q];
+      if constexpr (BWD) {
+        const size_t idx = (size_t)q * len + off + o;
+        const double d = static_cast<double>(v[q]);
+        if (a.accumulate) {
+          const double dd = a.rnorm[seg + q] * d;
+          a.x[idx] = xo[q] + dd;
+          a.dstore[idx] = dd;
+        } else {
+          a.x[idx] = d;
+        }
+      }
+    }
+  }
+  if constexpr (KIND == FEW_X) {
+    // w_s = F_s y_X in FP64 (the root reduction input of Algorithm 2)
+    if (writer)
+#pragma unroll
+      for (int q = 0; q < NR; ++q) vbuf[q][o] = v[q];
+    wave_lds_fence();
+#pragma unroll
+    for (int q = 0; q < NR; ++q) {
+      double p = 0.0;
+#pragma unroll
+      for (int e = 0; e < RB::EPL; ++e)
+        p += static_cast<double>(fb.v[e]) * static_cast<double>(vbuf[q][RB::base() + e]);
+      p = lane_group_sum_dpp<RB::LPR>(p);
+      if (out) a.w[(s * NR + q) * n + o] = p;
+    }
+  }
+}
+
+// Root propagation and the x_1 backward step on one wave: dy_X -= F^T x_0 (FP64), x_X = L_X^{-T}
+// dy_X.  smem: NR * NMAX doubles, then as many T.
+template <typename T, int NMAX, bool FULL, int NR>
+__device__ __attribute__((always_inline)) inline void few_x_bwd(const SolveArgs& a, int sl,
+                                                                int sys, unsigned char* smem) {
+  typedef RegBlock<T, NMAX> RB;
+  const int n = FULL ? NMAX : a.n, N = a.N;
+  const size_t nn = (size_t)n * n, s = (size_t)sys * a.S + sl;
+  double(*x0s)[NMAX] = reinterpret_cast<double(*)[NMAX]>(smem);
+  T(*rhs)[NMAX] = reinterpret_cast<T(*)[NMAX]>(smem + NR * NMAX * sizeof(double));
+  const int vl = threadIdx.x & (NMAX - 1), o = RB::out_index();
+  const bool vin = FULL || vl < n, writer = RB::base() == 0, out = writer && (FULL || o < n);
+  T* yx = reinterpret_cast<T*>(a.y) + (s * N + (N - 1)) * n * NR;
+  const size_t len = vec_len(a), off = (size_t)sys * a.vsys + (size_t)sl * N * n;
+  RB lin, fb;
+  fb.template load_fixed<true, FULL>(reinterpret_cast<const T*>(a.F) + s * nn, n);
+  if constexpr (FULL)
+    lin.template load_packed_raw<true>(reinterpret_cast<const T*>(a.Linv) + (s * N + (N - 1)) * nn);
+  else
+    lin.template load_packed<true>(reinterpret_cast<const T*>(a.Linv) + (s * N + (N - 1)) * nn, n);
+  double x0[NR], xo[NR] = {};
+  T yv[NR];
+#pragma unroll
+  for (int q = 0; q < NR; ++q) {
+    x0[q] = vin ? a.x0[((size_t)sys * NR + q) * n + vl] : 0.0;
+    yv[q] = vin ? yx[vl * NR + q] : T(0);
+    if (a.accumulate && (FULL || o < n)) xo[q] = a.x[(size_t)q * len + off + o];
+  }
+  if ((threadIdx.x & 63) < NMAX)
+#pragma unroll
+    for (int q = 0; q < NR; ++q) {
+      x0s[q][vl] = x0[q];
+      rhs[q][vl] = yv[q];
+    }
+  wave_lds_fence();
+  T r[NR];
+#pragma unroll
+  for (int q = 0; q < NR; ++q) {
+    double p = 0.0;
+#pragma unroll
+    for (int e = 0; e < RB::EPL; ++e)
+      p += static_cast<double>(fb.v[e]) * x0s[q][RB::base() + e];
+    p = lane_group_sum_dpp<RB::LPR>(p);
+    r[q] = static_cast<T>(static_cast<double>(rhs[q][o]) - p);
+  }
+  wave_lds_fence();
+  if (writer)
+#pragma unroll
+    for (int q = 0; q < NR; ++q) rhs[q][o] = r[q];
+  wave_lds_fence();
+  if constexpr (FULL) lin.template mask_packed<true>();
+#pragma unroll
+  for (int q = 0; q < NR; ++q) {
+    const T v = lane_group_sum_dpp<RB::LPR>(lin.dot(rhs[q]));
+    if (out) {
+      yx[o * NR + q] = v;
+      const size_t idx = (size_t)q * len + off + o;
       const double d = static_cast<double>(v);
       if (a.accumulate) {
-        const double dd = a.rnorm[seg] * d;
-        a.x[idx] = xo + dd;
+        const double dd = a.rnorm[sys * a.seg_sys + q] * d;
+        a.x[idx] = xo[q] + dd;
         a.dstore[idx] = dd;
       } else {
         a.x[idx] = d;
@@ -201,16 +325,61 @@ __device__ __attribute__((always_inline)) inline void level_one_position(
   }
 }
 
-template <typename T, int NMAX, bool FWD, bool FULL>
-__global__ void __launch_bounds__(64 * kLevelMaxWaves) solve_level_one_kernel(SolveArgs a,
-                                                                             int level) {
+template <typename T, int NMAX, bool FULL, int NR>
+__device__ __attribute__((always_inline)) inline void few_x_bwd_body(const SolveArgs& a, int s) {
   if (a.done && *a.done) return;
-  extern __shared__ __align__(16) unsigned char level_smem[];
-  level_one_position<T, NMAX, FWD, FULL>(a, level, blockIdx.x, blockIdx.y, blockIdx.z,
-                                   (int)(blockDim.x >> 6), (int)(threadIdx.x >> 6), level_smem);
+  __shared__ __align__(16) unsigned char sm[NR * NMAX * (sizeof(double) + sizeof(T))];
+  const int sys = s / a.S;
+  few_x_bwd<T, NMAX, FULL, NR>(a, s - sys * a.S, sys, sm);
+}
+template <typename T, int NMAX, bool FULL, int NR>
+__global__ void __launch_bounds__(64) solve_x_bwd_kernel(SolveArgs a) {
+  few_x_bwd_body<T, NMAX, FULL, NR>(a, blockIdx.x);
 }
 
-// Backward level kernel for one right-hand side and n of 17..32 (FULL: 32) that reads every block by
+// The place of a workgroup in a level's grid: (position, scenario, system), or flat (count
+// positions per chain) beyond the y and z launch limits.
+struct FewPlace {
+  int i, sl, sys;
+};
+__device__ inline FewPlace few_place(const SolveArgs& a, int count, unsigned x, unsigned y,
+                                     unsigned z) {
+  if (count == 0) return {(int)x, (int)y, (int)z};
+  const unsigned s = x / (unsigned)count, sys = s / (unsigned)a.S;
+  return {(int)(x - s * count), (int)(s - sys * a.S), (int)sys};
+}
+
+template <typename T, int NMAX, bool FWD, bool FULL, int NR>
+__device__ __attribute__((always_inline)) inline void few_level_body(const SolveArgs& a, int level,
+                                                                     const FewPlace& w) {
+  if (a.done && *a.done) return;
+  extern __shared__ __align__(16) unsigned char level_smem[];
+  few_position<T, NMAX, FWD ? FEW_FWD : FEW_BWD, FULL, NR>(
+      a, level, w.i, w.sl, w.sys, (int)(blockDim.x >> 6), wave_id(), level_smem);
+}
+template <typename T, int NMAX, bool FWD, bool FULL, int NR>
+__global__ void __launch_bounds__(64 * kLevelMaxWaves) solve_level_one_kernel(SolveArgs a,
+                                                                             int level, int count) {
+  few_level_body<T, NMAX, FWD, FULL, NR>(
+      a, level, few_place(a, count, blockIdx.x, blockIdx.y, blockIdx.z));
+}
+
+// The x_1 forward step of every chain, a wave for two pulls.
+template <typename T, int NMAX, bool FULL, int NR>
+__device__ __attribute__((always_inline)) inline void few_x_fwd_body(const SolveArgs& a, int s,
+                                                                     int W) {
+  if (a.done && *a.done) return;
+  extern __shared__ __align__(16) unsigned char level_smem[];
+  const int sys = s / a.S, wv = wave_id();
+  few_position<T, NMAX, FEW_X, FULL, NR, true>(a, 0, 0, s - sys * a.S, sys, W, wv, level_smem,
+                                               wv < W);
+}
+template <typename T, int NMAX, bool FULL, int NR>
+__global__ void __launch_bounds__(64 * kLevelMaxWaves) solve_x_fwd_kernel(SolveArgs a) {
+  few_x_fwd_body<T, NMAX, FULL, NR>(a, blockIdx.x, (int)(blockDim.x >> 6));
+}
+
+// Backward position for n of 17..32 (FULL: 32) that reads every block by
 // rows: lane l holds the 16-byte piece (VEC elements) at columns VEC*q of rows
 // mrow + RPI*k (q = l % QPR, mrow = l / QPR, k < K), so one load instruction covers RPI
 // whole rows of a block, as in the forward sweep, instead of reading columns with
@@ -222,7 +391,7 @@ __global__ void __launch_bounds__(64 * kLevelMaxWaves) solve_level_one_kernel(So
 // are dropped.  (At n = 24, S = 73, N = 100 in FP64 the seven levels took 59.5 us with the
 // columns read by dwords, 65 us as matrix products with fifteen of sixteen columns empty,
 // 40 us so with the top levels in one launch.)
-template <typename T, bool FULL>
+template <typename T, bool FULL, int NR>
 __device__ __attribute__((always_inline)) inline void bwd_rows_position(
     const SolveArgs& a, int level, int i, int sl, int sys, T (*xs)[32]) {
   constexpr int NMAX = 32;
@@ -233,7 +402,10 @@ __device__ __attribute__((always_inline)) inline void bwd_rows_position(
   const int n = FULL ? NMAX : a.n;
   const size_t nn = (size_t)n * n;
   typedef T vt __attribute__((ext_vector_type(VEC)));
-  // xs[3][NMAX] (this wave's LDS): x of the left and right neighbours, y_j; then r by rows
+  // xs[3][NR][NMAX] (this wave's LDS): x of the left and right neighbours, y_j; then r by rows
+  T(*const xl)[32] = xs;
+  T(*const xr)[32] = xs + NR;
+  T(*const yr)[32] = xs + 2 * NR;
   const int lane = threadIdx.x & 63, q = lane % QPR, mrow = lane / QPR;
   const int N = a.N, m = a.m;
   const size_t s = (size_t)sys * a.S + sl;
@@ -243,10 +415,11 @@ __device__ __attribute__((always_inline)) inline void bwd_rows_position(
   const T* Glb = reinterpret_cast<const T*>(a.Gl) + (s * gstride + (j - 1)) * nn;
   const T* Grb = reinterpret_cast<const T*>(a.Gr) + (s * gstride + (j - 1)) * nn;
   const T* Lb = reinterpret_cast<const T*>(a.Linv) + (s * N + (j - 1)) * nn;
-  T* y = reinterpret_cast<T*>(a.y) + s * N * n;
-  T* yj = y + (size_t)(j - 1) * n;
+  T* y = reinterpret_cast<T*>(a.y) + s * N * n * NR;
+  T* yj = y + (size_t)(j - 1) * n * NR;
   const bool has_left = j - half >= 1;
   const int ir = j + half <= m ? j + half - 1 : N - 1;
+  const size_t len = vec_len(a);
   const size_t off = (size_t)sys * a.vsys + ((size_t)sl * N + (N - j)) * n;
   vt gl[K], gr[K];
   T li[K][VEC];
@@ -258,7 +431,8 @@ __device__ __attribute__((always_inline)) inline void bwd_rows_position(
       gr[k] = *reinterpret_cast<const vt*>(Grb + R * NMAX + VEC * q);
       gl[k] = *reinterpret_cast<const vt*>(Glb + R * NMAX + VEC * q);
     } else {
-      const unsigned o = R < n && VEC * q < n ? (unsigned)(R * n + VEC * q) * sizeof(T) : kOutOfRange;
+      const unsigned o =
+          R < n && VEC * q < n ? (unsigned)(R * n + VEC * q) * sizeof(T) : kOutOfRange;
       const auto wr = __builtin_amdgcn_raw_buffer_load_b128(
           block_rsrc(Grb, (unsigned)nn * (unsigned)sizeof(T)), o, 0, 0);
       const auto wl = __builtin_amdgcn_raw_buffer_load_b128(
@@ -277,154 +451,174 @@ __device__ __attribute__((always_inline)) inline void bwd_rows_position(
   }
   const int vl = lane & (NMAX - 1);
   const bool vin = FULL || vl < n;
-  const T v0 = vin ? y[(size_t)(has_left ? j - half - 1 : j - 1) * n + vl] : T(0);
-  const T v1 = vin ? y[(size_t)ir * n + vl] : T(0);
-  const T v2 = vin ? yj[vl] : T(0);
-  double xo[VEC];
-  if (a.accumulate) {  // wave-uniform; the x being updated, at the output lanes' columns
+  T v0[NR], v1[NR], v2[NR];
+  double xo[NR][VEC];
 #pragma unroll
-    for (int e = 0; e < VEC; ++e)
-      xo[e] = FULL || VEC * q + e < n ? a.x[off + VEC * q + e] : 0.0;
+  for (int k = 0; k < NR; ++k) {
+    v0[k] = vin ? y[((size_t)(has_left ? j - half - 1 : j - 1) * n + vl) * NR + k] : T(0);
+    v1[k] = vin ? y[((size_t)ir * n + vl) * NR + k] : T(0);
+    v2[k] = vin ? yj[vl * NR + k] : T(0);
+    if (a.accumulate) {  // wave-uniform; the x being updated, at the output lanes' columns
+#pragma unroll
+      for (int e = 0; e < VEC; ++e)
+        xo[k][e] = FULL || VEC * q + e < n ? a.x[(size_t)k * len + off + VEC * q + e] : 0.0;
+    }
   }
   if (lane < NMAX) {
-    xs[0][lane] = has_left ? v0 : T(0);
-    xs[1][lane] = v1;
-    xs[2][lane] = v2;
+#pragma unroll
+    for (int k = 0; k < NR; ++k) {
+      xl[k][lane] = has_left ? v0[k] : T(0);
+      xr[k][lane] = v1[k];
+      yr[k][lane] = v2[k];
+    }
   }
   wave_lds_fence();
   // r = y_j - G_l^T x_l - G_r^T x_r, by columns c = VEC*q + e
-  T p[VEC];
+  T r[NR][VEC];
 #pragma unroll
-  for (int e = 0; e < VEC; ++e) p[e] = T(0);
+  for (int u = 0; u < NR; ++u) {
+    T p[VEC];
 #pragma unroll
-  for (int k = 0; k < K; ++k) {
-    const int R = mrow + RPI * k;
-    const T al = xs[0][R], ar = xs[1][R];
+    for (int e = 0; e < VEC; ++e) p[e] = T(0);
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) {
-      if (has_left) p[e] += gl[k][e] * al;
-      p[e] += gr[k][e] * ar;
+    for (int k = 0; k < K; ++k) {
+      const int R = mrow + RPI * k;
+      const T al = xl[u][R], ar = xr[u][R];
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) {
+        if (has_left) p[e] += gl[k][e] * al;
+        p[e] += gr[k][e] * ar;
+      }
     }
-  }
-  T r[VEC];
 #pragma unroll
-  for (int e = 0; e < VEC; ++e) r[e] = xs[2][VEC * q + e] - column_group_sum<QPR>(p[e]);
+    for (int e = 0; e < VEC; ++e) r[u][e] = yr[u][VEC * q + e] - column_group_sum<QPR>(p[e]);
+  }
   wave_lds_fence();
   if (mrow == 0) {
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) xs[0][VEC * q + e] = FULL || VEC * q + e < n ? r[e] : T(0);
+    for (int u = 0; u < NR; ++u)
+#pragma unroll
+      for (int e = 0; e < VEC; ++e)
+        xl[u][VEC * q + e] = FULL || VEC * q + e < n ? r[u][e] : T(0);
   }
   wave_lds_fence();
-  // x_j = L_jj^{-T} r: sum over rows R >= c of L^{-1}[R][c] r[R]
-  T x[VEC];
 #pragma unroll
-  for (int e = 0; e < VEC; ++e) x[e] = T(0);
+  for (int u = 0; u < NR; ++u) {
+    // x_j = L_jj^{-T} r: sum over rows R >= c of L^{-1}[R][c] r[R]
+    T x[VEC];
 #pragma unroll
-  for (int k = 0; k < K; ++k) {
-    const int R = mrow + RPI * k;
-    const T rr = xs[0][R];
+    for (int e = 0; e < VEC; ++e) x[e] = T(0);
 #pragma unroll
-    for (int e = 0; e < VEC; ++e)
-      if (VEC * q + e <= R) x[e] += li[k][e] * rr;
-  }
+    for (int k = 0; k < K; ++k) {
+      const int R = mrow + RPI * k;
+      const T rr = xl[u][R];
 #pragma unroll
-  for (int e = 0; e < VEC; ++e) x[e] = column_group_sum<QPR>(x[e]);
-  if (mrow == 0) {
+      for (int e = 0; e < VEC; ++e)
+        if (VEC * q + e <= R) x[e] += li[k][e] * rr;
+    }
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) {
-      const int c = VEC * q + e;
-      if (!FULL && c >= n) break;
-      yj[c] = x[e];
-      const size_t idx = off + c;
-      const double d = static_cast<double>(x[e]);
-      if (a.accumulate) {
-        const double dd = a.rnorm[sys * a.seg_sys] * d;
-        a.x[idx] = xo[e] + dd;
-        a.dstore[idx] = dd;
-      } else {
-        a.x[idx] = d;
+    for (int e = 0; e < VEC; ++e) x[e] = column_group_sum<QPR>(x[e]);
+    if (mrow == 0) {
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) {
+        const int c = VEC * q + e;
+        if (!FULL && c >= n) break;
+        yj[c * NR + u] = x[e];
+        const size_t idx = (size_t)u * len + off + c;
+        const double d = static_cast<double>(x[e]);
+        if (a.accumulate) {
+          const double dd = a.rnorm[sys * a.seg_sys + u] * d;
+          a.x[idx] = xo[u][e] + dd;
+          a.dstore[idx] = dd;
+        } else {
+          a.x[idx] = d;
+        }
       }
     }
   }
 }
 
-template <typename T, bool FULL>
-__global__ void __launch_bounds__(64) solve_bwd_rows_kernel(SolveArgs a, int level) {
+template <typename T, bool FULL, int NR>
+__device__ __attribute__((always_inline)) inline void bwd_rows_body(const SolveArgs& a, int level,
+                                                                    const FewPlace& w) {
   if (a.done && *a.done) return;
-  __shared__ T xs[3][32];
-  bwd_rows_position<T, FULL>(a, level, blockIdx.x, blockIdx.y, blockIdx.z, xs);
+  __shared__ T xs[3 * NR][32];
+  bwd_rows_position<T, FULL, NR>(a, level, w.i, w.sl, w.sys, xs);
+}
+template <typename T, bool FULL, int NR>
+__global__ void __launch_bounds__(64) solve_bwd_rows_kernel(SolveArgs a, int level, int count) {
+  bwd_rows_body<T, FULL, NR>(a, level, few_place(a, count, blockIdx.x, blockIdx.y, blockIdx.z));
 }
 
 // The top backward levels of every chain in one launch, with_x after root propagation and the
-// x_1 backward step, one workgroup per chain: wave 0 solves x_1 (solve_mm.h), then wave w
+// x_1 backward step, one workgroup per chain: wave 0 solves x_1, then wave w
 // position w of each level from the top level down to level_lo (at most one per wave), with a
 // barrier between levels.  A position reads the x of its neighbours from y, written by
 // other waves of the workgroup at higher levels; the barrier orders those stores before
 // the reads (the waves of a workgroup share one CU and its vector cache).  Each position
-// runs the code of the single-level kernel (row reads at n > 16, one wave of the general
-// one-vector kernel otherwise), so the results are bitwise those of the launches level by
-// level.
-template <typename T, int NMAX, bool FULL>
+// runs the code of the single-level kernel (row reads at n > 16, one wave of the level
+// kernel otherwise), so the results are bitwise those of the launches level by level.
+template <typename T, int NMAX, bool FULL, int NR>
 __device__ __attribute__((always_inline)) inline void solve_bwd_top_body(const SolveArgs& a,
                                                                          int level_lo,
                                                                          bool with_x, int s) {
   if (a.done && *a.done) return;
-  constexpr int PER = NMAX == 32 ? 3 * NMAX : (kPullsPerWave + 2) * NMAX;  // per wave
+  constexpr int PER = (NMAX == 32 ? 3 : kPullsPerWave + 2) * NR * NMAX;  // per wave
+  static_assert(PER * sizeof(T) >= NR * NMAX * (sizeof(double) + sizeof(T)), "x_1 fits too");
   constexpr int W = mm_top_waves(NMAX);
   __shared__ __align__(16) T sm[W * PER];
   const int w = threadIdx.x >> 6, sys = s / a.S, sl = s - sys * a.S;
-  if (with_x && w == 0) mm_x_bwd_body<T, NMAX == 32 ? 2 : 1, FULL>(a, s);
+  if (with_x && w == 0)
+    few_x_bwd<T, NMAX, FULL, NR>(a, sl, sys, reinterpret_cast<unsigned char*>(sm));
   for (int level = chain_levels(a.m); level >= level_lo; --level) {
     __syncthreads();
     if (w < level_count(a.m, level)) {
       if constexpr (NMAX == 32)
-        bwd_rows_position<T, FULL>(a, level, w, sl, sys,
-                                   reinterpret_cast<T(*)[NMAX]>(sm + w * PER));
+        bwd_rows_position<T, FULL, NR>(a, level, w, sl, sys,
+                                       reinterpret_cast<T(*)[NMAX]>(sm + w * PER));
       else
-        level_one_position<T, NMAX, false, FULL>(a, level, w, sl, sys, 1, 0,
+        few_position<T, NMAX, FEW_BWD, FULL, NR>(a, level, w, sl, sys, 1, 0,
                                                  reinterpret_cast<unsigned char*>(sm + w * PER));
     }
   }
 }
 
-template <typename T, int NMAX, bool FULL>
+template <typename T, int NMAX, bool FULL, int NR>
 __global__ void __launch_bounds__(64 * mm_top_waves(NMAX)) solve_bwd_top_kernel(
     SolveArgs a, int level_lo, bool with_x) {
-  solve_bwd_top_body<T, NMAX, FULL>(a, level_lo, with_x, blockIdx.x);
+  solve_bwd_top_body<T, NMAX, FULL, NR>(a, level_lo, with_x, blockIdx.x);
 }
 
 // The top forward levels (at most four positions) and the x_1 forward step of every chain in
 // one launch, one workgroup of sixteen waves per chain: four waves for each position,
 // of which as many take part as in the single-level kernel, so the results are bitwise
-// those of the launches level by level.  For n <= 16; at n = 32 it would cost what the
-// launches do (S = 128, N = 64 in FP64: 96 us for the solve against 92).
+// those of the launches level by level.  In FP64 for n <= 16: at n = 32 a wave would spill (S
+// = 128, N = 64: 96 us for the solve against 92 level by level).  In FP32 at n = 24, S = 4, N =
+// 16, two right-hand sides, 42 us level by level, 36 so.
 constexpr int kFwdTopWaves = 16;
-template <typename T, int NMAX>
+template <typename T, int NMAX, bool FULL, int NR>
 __device__ __attribute__((always_inline)) inline void solve_fwd_top_body(const SolveArgs& a,
                                                                          int level_lo, int s) {
   if (a.done && *a.done) return;
-  typedef typename Mfma<T>::acc_t acc_t;
-  constexpr size_t kPos = (size_t)(kLevelMaxWaves * (kPullsPerWave + 1) + 1) * NMAX * sizeof(T);
-  constexpr size_t kPart = (size_t)mm_top_waves(NMAX) * 64 * sizeof(acc_t);
-  constexpr size_t kAll = kFwdTopWaves / kLevelMaxWaves * kPos;
-  __shared__ __align__(16) unsigned char sm[kAll > kPart ? kAll : kPart];
+  constexpr size_t kPos =
+      (size_t)(kLevelMaxWaves * (kPullsPerWave + 1) + 1) * NR * NMAX * sizeof(T);
+  __shared__ __align__(16) unsigned char sm[kFwdTopWaves / kLevelMaxWaves * kPos];
   const int wv = wave_id(), sys = s / a.S, sl = s - sys * a.S, L = chain_levels(a.m);
   const int i = wv / kLevelMaxWaves, w = wv % kLevelMaxWaves;
   for (int level = level_lo; level <= L; ++level) {
     const int W = fwd_one_waves(level);
-    level_one_position<T, NMAX, true, true, true>(a, level, i, sl, sys, W, w, sm + i * kPos,
-                                                  i < level_count(a.m, level) && w < W);
+    few_position<T, NMAX, FEW_FWD, FULL, NR, true>(a, level, i, sl, sys, W, w, sm + i * kPos,
+                                                   i < level_count(a.m, level) && w < W);
     __syncthreads();
   }
-  const int W = mm_pull_waves(NMAX, sizeof(T) == 8, L, mm_top_waves(NMAX));
-  mm_position_body<T, 1, MM_X, true, true>(a, 0, s, a.N, W, wv, reinterpret_cast<acc_t*>(sm),
-                                           wv < W);
+  const int W = x_fwd_waves(L);
+  few_position<T, NMAX, FEW_X, FULL, NR, true>(a, 0, 0, sl, sys, W, wv, sm, wv < W);
 }
 
-template <typename T, int NMAX>
+template <typename T, int NMAX, bool FULL, int NR>
 __global__ void __launch_bounds__(64 * kFwdTopWaves) solve_fwd_top_kernel(SolveArgs a,
                                                                           int level_lo) {
-  solve_fwd_top_body<T, NMAX>(a, level_lo, blockIdx.x);
+  solve_fwd_top_body<T, NMAX, FULL, NR>(a, level_lo, blockIdx.x);
 }
 
 // Root step in FP64 (Algorithm 2, root step).  One workgroup of 1024 threads per
@@ -486,9 +680,11 @@ __device__ __attribute__((always_inline)) inline void solve_root_body(const Solv
     const int left = nrhs - q0;
     const bool spare = S <= 4 * (1024 / NMAX);
     if (QB >= 8 && left >= (spare ? 5 : 8))
-      taken = partials(std::integral_constant<int, QB < 8 ? QB : 8>{}, std::integral_constant<int, 4>{});
+      taken = partials(std::integral_constant<int, QB < 8 ? QB : 8>{},
+                       std::integral_constant<int, 4>{});
     else if (QB >= 4 && left >= (S <= 16 * (1024 / NMAX) ? 3 : 4))
-      taken = partials(std::integral_constant<int, QB < 4 ? QB : 4>{}, std::integral_constant<int, 4>{});
+      taken = partials(std::integral_constant<int, QB < 4 ? QB : 4>{},
+                       std::integral_constant<int, 4>{});
     else if (left >= 2 && spare)
       taken = partials(std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});
     else if (left >= 2)
@@ -562,45 +758,55 @@ __global__ void __launch_bounds__(1024) root_factor_solve_kernel(RootStep s, Sol
 }
 
 // ---- one launch over the systems of a ragged batch (see multi.h) ----
-// Items of the level kinds carry (level, count) in p0, p1; the merged backward top
-// levels carry (level_lo, with_x).
+// Items of the level kinds carry (level, positions per chain of a flat grid or 0) in p0, p1; the
+// merged backward top levels carry (level_lo, with_x).
 
-template <typename T, int NMAX, bool FWD, bool FULL>
+template <typename T, int NMAX, bool FWD, bool FULL, int NR>
 __global__ void __launch_bounds__(64 * kLevelMaxWaves) solve_level_one_multi(
     const MultiItem<SolveArgs>* items, int nitems, Reloc r) {
   const MultiItem<SolveArgs>& it = items[multi_find(items, nitems, blockIdx.x)];
-  const SolveArgs a = relocate_solve(it.a, r);
-  if (a.done && *a.done) return;
-  extern __shared__ __align__(16) unsigned char level_smem[];
   const LocalBlock lb = multi_local(it);
-  level_one_position<T, NMAX, FWD, FULL>(a, it.p0, lb.x, lb.y, lb.z, (int)(blockDim.x >> 6),
-                                   (int)(threadIdx.x >> 6), level_smem);
+  const SolveArgs a = relocate_solve(it.a, r);
+  few_level_body<T, NMAX, FWD, FULL, NR>(a, it.p0, few_place(a, it.p1, lb.x, lb.y, lb.z));
 }
 
-template <typename T, bool FULL>
+template <typename T, bool FULL, int NR>
 __global__ void __launch_bounds__(64) solve_bwd_rows_multi(const MultiItem<SolveArgs>* items,
                                                            int nitems, Reloc r) {
   const MultiItem<SolveArgs>& it = items[multi_find(items, nitems, blockIdx.x)];
-  const SolveArgs a = relocate_solve(it.a, r);
-  if (a.done && *a.done) return;
-  __shared__ T xs[3][32];
   const LocalBlock lb = multi_local(it);
-  bwd_rows_position<T, FULL>(a, it.p0, lb.x, lb.y, lb.z, xs);
+  const SolveArgs a = relocate_solve(it.a, r);
+  bwd_rows_body<T, FULL, NR>(a, it.p0, few_place(a, it.p1, lb.x, lb.y, lb.z));
 }
 
-template <typename T, int NMAX, bool FULL>
+template <typename T, int NMAX, bool FULL, int NR>
 __global__ void __launch_bounds__(64 * mm_top_waves(NMAX)) solve_bwd_top_multi(
     const MultiItem<SolveArgs>* items, int nitems, Reloc r) {
   const MultiItem<SolveArgs>& it = items[multi_find(items, nitems, blockIdx.x)];
   const SolveArgs a = relocate_solve(it.a, r);
-  solve_bwd_top_body<T, NMAX, FULL>(a, it.p0, it.p1 != 0, multi_local(it).x);
+  solve_bwd_top_body<T, NMAX, FULL, NR>(a, it.p0, it.p1 != 0, multi_local(it).x);
 }
 
-template <typename T, int NMAX>
+template <typename T, int NMAX, bool FULL, int NR>
 __global__ void __launch_bounds__(64 * kFwdTopWaves) solve_fwd_top_multi(
     const MultiItem<SolveArgs>* items, int nitems, Reloc r) {
   const MultiItem<SolveArgs>& it = items[multi_find(items, nitems, blockIdx.x)];
-  solve_fwd_top_body<T, NMAX>(relocate_solve(it.a, r), it.p0, multi_local(it).x);
+  solve_fwd_top_body<T, NMAX, FULL, NR>(relocate_solve(it.a, r), it.p0, multi_local(it).x);
+}
+
+template <typename T, int NMAX, bool FULL, int NR>
+__global__ void __launch_bounds__(64 * kLevelMaxWaves) solve_x_fwd_multi(
+    const MultiItem<SolveArgs>* items, int nitems, Reloc r) {
+  const MultiItem<SolveArgs>& it = items[multi_find(items, nitems, blockIdx.x)];
+  few_x_fwd_body<T, NMAX, FULL, NR>(relocate_solve(it.a, r), multi_local(it).x,
+                                    x_fwd_waves(chain_levels(it.a.m)));
+}
+
+template <typename T, int NMAX, bool FULL, int NR>
+__global__ void __launch_bounds__(64) solve_x_bwd_multi(const MultiItem<SolveArgs>* items,
+                                                        int nitems, Reloc r) {
+  const MultiItem<SolveArgs>& it = items[multi_find(items, nitems, blockIdx.x)];
+  few_x_bwd_body<T, NMAX, FULL, NR>(relocate_solve(it.a, r), multi_local(it).x);
 }
 
 template <int NMAX>
@@ -610,72 +816,76 @@ __global__ void __launch_bounds__(1024) solve_root_multi(const MultiItem<SolveAr
   solve_root_body<NMAX, false>(relocate_solve(it.a, r), RootStep{}, multi_local(it).x);
 }
 
-template <typename T, int NMAX, bool FULL>
+template <typename T, int NMAX, bool FULL, int NR>
 void solve_multi_t(int kind, bool fwd, const MultiItem<SolveArgs>* items, int nitems,
                    unsigned blocks, unsigned threads, size_t lds, const Reloc& r, hipStream_t st) {
   const dim3 g(blocks), b(threads);
   switch (kind) {
     case SK_LEVEL_ONE:
-      if (!fwd) {
-        if constexpr (NMAX < 32)
-          hipLaunchKernelGGL((solve_level_one_multi<T, NMAX, false, FULL>), g, b, lds, st, items,
-                             nitems, r);
-      } else if constexpr (FULL) {
-        hipLaunchKernelGGL((solve_level_one_multi<T, NMAX, true, true>), g, b, lds, st, items,
+      if (fwd)
+        hipLaunchKernelGGL((solve_level_one_multi<T, NMAX, true, FULL, NR>), g, b, lds, st, items,
                            nitems, r);
-      }
+      else if constexpr (NMAX < 32)
+        hipLaunchKernelGGL((solve_level_one_multi<T, NMAX, false, FULL, NR>), g, b, lds, st, items,
+                           nitems, r);
       break;
     case SK_BWD_ROWS:
       if constexpr (NMAX == 32)
-        hipLaunchKernelGGL((solve_bwd_rows_multi<T, FULL>), g, b, 0, st, items, nitems, r);
+        hipLaunchKernelGGL((solve_bwd_rows_multi<T, FULL, NR>), g, b, 0, st, items, nitems, r);
       break;
     case SK_BWD_TOP:
-      hipLaunchKernelGGL((solve_bwd_top_multi<T, NMAX, FULL>), g, b, 0, st, items, nitems, r);
+      hipLaunchKernelGGL((solve_bwd_top_multi<T, NMAX, FULL, NR>), g, b, 0, st, items, nitems, r);
       break;
     case SK_FWD_TOP:
-      if constexpr (NMAX < 32 && FULL)
-        hipLaunchKernelGGL((solve_fwd_top_multi<T, NMAX>), g, dim3(64 * kFwdTopWaves), 0, st,
-                           items, nitems, r);
+      if constexpr (fwd_top_few(NMAX, NR, sizeof(T) == 8))
+        hipLaunchKernelGGL((solve_fwd_top_multi<T, NMAX, FULL, NR>), g, dim3(64 * kFwdTopWaves), 0,
+                           st, items, nitems, r);
       break;
-    case SK_ROOT:
-      hipLaunchKernelGGL((solve_root_multi<32>), g, b, 0, st, items, nitems, r);
+    case SK_X_BWD:
+      hipLaunchKernelGGL((solve_x_bwd_multi<T, NMAX, FULL, NR>), g, dim3(64), 0, st, items, nitems,
+                         r);
+      break;
+    case SK_X_FWD:
+      hipLaunchKernelGGL((solve_x_fwd_multi<T, NMAX, FULL, NR>), g, b, lds, st, items, nitems, r);
       break;
   }
 }
 
-template <typename T, int NMAX, bool FULL>
+template <typename T, int NMAX, bool FULL, int NR>
 void level_t(const SolveArgs& a, int level, bool fwd, hipStream_t st) {
   const LevelCfg c = solve_level_config(a, level, fwd, NMAX, sizeof(T) == 8);
   if (c.count <= 0) return;
   const dim3 g(c.gx, c.gy, c.gz), b(c.threads);
-  switch (c.kind) {
-    case SK_BWD_ROWS:
-      if constexpr (NMAX == 32)
-        hipLaunchKernelGGL((solve_bwd_rows_kernel<T, FULL>), g, b, 0, st, a, level);
-      break;
-    case SK_LEVEL_ONE:
-      if (!fwd) {
-        if constexpr (NMAX < 32)
-          hipLaunchKernelGGL((solve_level_one_kernel<T, NMAX, false, FULL>), g, b, c.lds, st, a,
-                             level);
-      } else if constexpr (FULL) {
-        hipLaunchKernelGGL((solve_level_one_kernel<T, NMAX, true, true>), g, b, c.lds, st, a,
-                           level);
-      }
-      break;
-    default:
-      launch_mm_level<T>(a, level, fwd, st);
+  if (c.kind == SK_BWD_ROWS) {
+    if constexpr (NMAX == 32)
+      hipLaunchKernelGGL((solve_bwd_rows_kernel<T, FULL, NR>), g, b, 0, st, a, level, c.flat);
+  } else if (fwd) {
+    hipLaunchKernelGGL((solve_level_one_kernel<T, NMAX, true, FULL, NR>), g, b, c.lds, st, a, level,
+                       c.flat);
+  } else if constexpr (NMAX < 32) {
+    hipLaunchKernelGGL((solve_level_one_kernel<T, NMAX, false, FULL, NR>), g, b, c.lds, st, a,
+                       level, c.flat);
   }
 }
 
-// f(NMAX, FULL as std::integral_constant) for a block size of at most 32
+// f(NMAX, FULL, NR as std::integral_constant) for a block size of at most 32 and few
+// right-hand sides
 template <typename F>
-void by_size(int n, F&& f) {
+void by_size(int n, int nrhs, F&& f) {
+  auto rhs = [&](auto nmax, auto full) {
+    constexpr int NMAX = decltype(nmax)::value;
+    if (nrhs == 1)
+      f(nmax, full, std::integral_constant<int, 1>{});
+    else if (nrhs == 2)
+      f(nmax, full, std::integral_constant<int, 2>{});
+    else if constexpr (NMAX == 8 || (NMAX == 32 && decltype(full)::value))
+      f(nmax, full, std::integral_constant<int, kFewRhs>{});
+  };
   auto full = [&](auto nmax) {
     if (n == decltype(nmax)::value)
-      f(nmax, std::true_type{});
+      rhs(nmax, std::true_type{});
     else
-      f(nmax, std::false_type{});
+      rhs(nmax, std::false_type{});
   };
   if (n <= 8)
     full(std::integral_constant<int, 8>{});
@@ -687,40 +897,42 @@ void by_size(int n, F&& f) {
 
 }  // namespace
 
-// Kernel, grid and LDS of one level of a sweep.  One right-hand side with blocks up to 32
-// and a grid of (positions, scenarios, systems) within the y and z launch limits takes the
-// one-vector kernels backward (row reads for n > 16), and forward for full blocks (n = 8, 16
-// or 32): they read whole rows where the matrix products read columns for one column of
-// sixteen (figures at bwd_rows_position; forward, where both read rows, the products are
-// the faster for padded blocks: 68 us against 71 at n = 24, S = 73, N = 100 in FP64).
-// Everything else goes as matrix products (solve_rhs.hip) on a flat grid.  Forward
-// positions of level l pull 2 (l - 1) blocks, kPullsPerWave per wave, on up to
+// Kernel, grid and LDS of one level of a sweep: register blocks for few right-hand sides
+// (few_rhs; row reads backward for n > 16), matrix products (solve_rhs.hip) otherwise.
+// Forward positions of level l pull 2 (l - 1) blocks, kPullsPerWave per wave, on up to
 // kLevelMaxWaves waves (or a.fwd_waves: one wave per position when the plan asks for it).
 LevelCfg solve_level_config(const SolveArgs& a, int level, bool fwd, int nmax, bool fp64) {
+  if (!few_rhs(a.n, a.nrhs, fp64)) return mm_level_config(a, level, fwd, fp64);
   LevelCfg c{};
   c.count = level_count(a.m, level);
-  const bool one = a.nrhs == 1 && nmax <= 32 && a.S <= 65535 && a.B <= 65535 &&
-                   (!fwd || a.n == nmax);
-  if (one) {
-    const int waves = fwd && a.fwd_waves != 1 ? fwd_one_waves(level) : 1;
-    c.threads = 64 * waves;
-    c.kind = (!fwd && nmax == 32) ? SK_BWD_ROWS : SK_LEVEL_ONE;
-    c.lds = c.kind == SK_BWD_ROWS ? 0 : solve_level_lds(fp64, nmax, waves);
+  const int waves = fwd && a.fwd_waves != 1 ? fwd_one_waves(level) : 1;
+  c.threads = 64 * waves;
+  c.kind = (!fwd && nmax == 32) ? SK_BWD_ROWS : SK_LEVEL_ONE;
+  c.lds = c.kind == SK_BWD_ROWS ? 0 : solve_level_lds(fp64, nmax, waves, a.nrhs);
+  if (a.S <= 65535 && a.B <= 65535) {
     c.gx = (unsigned)c.count;
     c.gy = (unsigned)a.S;
     c.gz = (unsigned)a.B;
   } else {
-    return mm_level_config(a, level, fwd, fp64);
+    c.flat = c.count;
+    c.gx = (unsigned)(a.B * a.S) * (unsigned)std::max(c.count, 0);
+    c.gy = c.gz = 1;
   }
   return c;
+}
+// Threads and LDS of the x_1 forward step alone.
+MmTopCfg x_fwd_config(const SolveArgs& a, int nmax, bool fp64) {
+  const int waves = x_fwd_waves(chain_levels(a.m));
+  return {64u * waves, solve_level_lds(fp64, nmax, waves, a.nrhs)};
 }
 
 template <typename T>
 static void launch_level(const SolveArgs& a, int level, bool fwd, hipStream_t st) {
   if (few_rhs64(a.n, a.nrhs)) return launch_solve64_level<T>(a, level, fwd, st);
-  if (a.n > 32) return launch_mm_level<T>(a, level, fwd, st);
-  by_size(a.n, [&](auto nmax, auto full) {
-    level_t<T, decltype(nmax)::value, decltype(full)::value>(a, level, fwd, st);
+  if (!few_rhs(a.n, a.nrhs, sizeof(T) == 8)) return launch_mm_level<T>(a, level, fwd, st);
+  by_size(a.n, a.nrhs, [&](auto nmax, auto full, auto nr) {
+    level_t<T, decltype(nmax)::value, decltype(full)::value, decltype(nr)::value>(a, level, fwd,
+                                                                                 st);
   });
 }
 template <typename T>
@@ -733,21 +945,34 @@ void launch_solve_bwd_level(const SolveArgs& a, int level, hipStream_t st) {
 }
 template <typename T>
 void launch_solve_bwd_top(const SolveArgs& a, int level_lo, bool with_x, hipStream_t st) {
-  const int waves = level_lo > chain_levels(a.m) ? 1 : level_count(a.m, level_lo);
-  const dim3 grid((unsigned)(a.B * a.S)), block(64 * waves);
-  by_size(a.n, [&](auto nmax, auto full) {
-    hipLaunchKernelGGL(
-        (solve_bwd_top_kernel<T, decltype(nmax)::value, decltype(full)::value>), grid, block, 0,
-        st, a, level_lo, with_x);
+  const dim3 grid((unsigned)(a.B * a.S));
+  by_size(a.n, a.nrhs, [&](auto nmax, auto full, auto nr) {
+    constexpr int NMAX = decltype(nmax)::value, NR = decltype(nr)::value;
+    constexpr bool FULL = decltype(full)::value;
+    if (level_lo > chain_levels(a.m)) {  // x_1 alone
+      if (with_x)
+        hipLaunchKernelGGL((solve_x_bwd_kernel<T, NMAX, FULL, NR>), grid, dim3(64), 0, st, a);
+    } else {
+      hipLaunchKernelGGL((solve_bwd_top_kernel<T, NMAX, FULL, NR>), grid,
+                         dim3(64 * level_count(a.m, level_lo)), 0, st, a, level_lo, with_x);
+    }
   });
 }
 template <typename T>
 void launch_solve_fwd_top(const SolveArgs& a, int level_lo, hipStream_t st) {
-  const dim3 grid((unsigned)(a.B * a.S)), block(64 * kFwdTopWaves);
-  if (a.n == 8)
-    hipLaunchKernelGGL((solve_fwd_top_kernel<T, 8>), grid, block, 0, st, a, level_lo);
-  else if (a.n == 16)
-    hipLaunchKernelGGL((solve_fwd_top_kernel<T, 16>), grid, block, 0, st, a, level_lo);
+  const dim3 grid((unsigned)(a.B * a.S));
+  by_size(a.n, a.nrhs, [&](auto nmax, auto full, auto nr) {
+    constexpr int NMAX = decltype(nmax)::value, NR = decltype(nr)::value;
+    constexpr bool FULL = decltype(full)::value;
+    if (level_lo > chain_levels(a.m)) {  // x_1 alone
+      const MmTopCfg c = x_fwd_config(a, NMAX, sizeof(T) == 8);
+      hipLaunchKernelGGL((solve_x_fwd_kernel<T, NMAX, FULL, NR>), grid, dim3(c.threads), c.lds, st,
+                         a);
+    } else if constexpr (fwd_top_few(NMAX, NR, sizeof(T) == 8)) {
+      hipLaunchKernelGGL((solve_fwd_top_kernel<T, NMAX, FULL, NR>), grid, dim3(64 * kFwdTopWaves),
+                         0, st, a, level_lo);
+    }
+  });
 }
 void launch_solve_root(const SolveArgs& a, hipStream_t st) {
   if (a.n > 32)
@@ -760,31 +985,34 @@ void launch_root_factor_solve(const RootStep& s, const SolveArgs& a, hipStream_t
   hipLaunchKernelGGL(root_factor_solve_kernel, dim3(a.B), dim3(1024), 0, st, s, a);
 }
 
-size_t solve_level_lds(bool fp64, int nmax, int waves) {
-  return fp64 ? (nmax <= 8 ? level_smem_bytes<double, 8>(waves)
-                          : nmax <= 16 ? level_smem_bytes<double, 16>(waves)
-                                       : level_smem_bytes<double, 32>(waves))
-              : (nmax <= 8 ? level_smem_bytes<float, 8>(waves)
-                           : nmax <= 16 ? level_smem_bytes<float, 16>(waves)
-                                        : level_smem_bytes<float, 32>(waves));
+size_t solve_level_lds(bool fp64, int nmax, int waves, int nrhs) {
+  return fp64 ? (nmax <= 8 ? level_smem_bytes<double, 8>(waves, nrhs)
+                          : nmax <= 16 ? level_smem_bytes<double, 16>(waves, nrhs)
+                                       : level_smem_bytes<double, 32>(waves, nrhs))
+              : (nmax <= 8 ? level_smem_bytes<float, 8>(waves, nrhs)
+                           : nmax <= 16 ? level_smem_bytes<float, 16>(waves, nrhs)
+                                        : level_smem_bytes<float, 32>(waves, nrhs));
 }
 
 template <typename T>
-void launch_solve_multi(int kind, bool fwd, int n, const MultiItem<SolveArgs>* items, int nitems,
-                        unsigned blocks, unsigned threads, size_t lds, const Reloc& r,
+void launch_solve_multi(int kind, bool fwd, int n, int nrhs, const MultiItem<SolveArgs>* items,
+                        int nitems, unsigned blocks, unsigned threads, size_t lds, const Reloc& r,
                         hipStream_t st) {
-  if (kind == SK_LEVEL || kind == SK_MM_TOP)
+  if (kind == SK_ROOT)
+    hipLaunchKernelGGL((solve_root_multi<32>), dim3(blocks), dim3(threads), 0, st, items, nitems,
+                       r);
+  else if (kind == SK_LEVEL || kind == SK_MM_TOP)
     launch_mm_multi<T>(kind, fwd, n, items, nitems, blocks, threads, lds, r, st);
   else
-    by_size(n, [&](auto nmax, auto full) {
-      solve_multi_t<T, decltype(nmax)::value, decltype(full)::value>(
+    by_size(n, nrhs, [&](auto nmax, auto full, auto nr) {
+      solve_multi_t<T, decltype(nmax)::value, decltype(full)::value, decltype(nr)::value>(
           kind, fwd, items, nitems, blocks, threads, lds, r, st);
     });
 }
-template void launch_solve_multi<double>(int, bool, int, const MultiItem<SolveArgs>*, int,
+template void launch_solve_multi<double>(int, bool, int, int, const MultiItem<SolveArgs>*, int,
                                          unsigned, unsigned, size_t, const Reloc&, hipStream_t);
-template void launch_solve_multi<float>(int, bool, int, const MultiItem<SolveArgs>*, int, unsigned,
-                                        unsigned, size_t, const Reloc&, hipStream_t);
+template void launch_solve_multi<float>(int, bool, int, int, const MultiItem<SolveArgs>*, int,
+                                        unsigned, unsigned, size_t, const Reloc&, hipStream_t);
 
 template void launch_solve_fwd_level<double>(const SolveArgs&, int, hipStream_t);
 template void launch_solve_fwd_level<float>(const SolveArgs&, int, hipStream_t);

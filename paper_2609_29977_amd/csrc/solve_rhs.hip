@@ -1,15 +1,12 @@
-// Solve steps (Algorithm 2) as matrix products, for several right-hand sides, padded blocks
-// and blocks of 33..64 (gfx950): the level kernel of both sweeps, and the x_1 steps together
-// with the levels next to them.  (One right-hand side: solve.hip's level kernels, forward
-// with full 8 x 8, 16 x 16 or 32 x 32 blocks.)  Layouts: solve_mm.h.
+// Solve steps (Algorithm 2) as matrix products, for several right-hand sides and blocks of
+// 33..64 (gfx950): the level kernel of both sweeps, and the x_1 steps together with the levels
+// next to them.  (Few right-hand sides: solve.hip, solve64.hip.)  Layouts: solve_mm.h.
 //
 // Against scalar products per right-hand side with the vectors in LDS, in chunks of eight
 // (four for n > 32), one solve: FP64 n = 32, S = N = 128, twelve right-hand sides 556 -> 272
 // us (level 1 backward moves its blocks at 5.1 TB/s); FP32 n = 16, S = 100, N = 160, four
 // 115 -> 85 us; FP64 n = 48, S = N = 64, one 215 -> 160 us; FP32 n = 64, S = N = 64, sixteen
-// 678 -> 208 us.  FP64 n = 32, S = 300, N = 200, three: 638 -> 633 us, both near the copy
-// rate; S = 60, N = 250, two: 204 -> 214 us, the matrix cores' latency on two of sixteen
-// columns.  Tried: tiles interleaved so that the transposed blocks come in 16-byte pieces (the
+// 678 -> 208 us.  Tried: tiles interleaved so that the transposed blocks come in 16-byte pieces (the
 // backward levels above: 132 -> 149 us, the triangle's zeros are no longer whole tiles); one
 // pull in flight and three waves per SIMD instead of two backward (132 -> 136 us).
 //
