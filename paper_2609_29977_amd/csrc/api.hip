@@ -168,6 +168,11 @@ Costs make_costs(const bmpc_dims& d, bool fp64, int Tw1, int Tw2, int B, int fla
   c.launches[KC_SOLVE_FWD] = c.launches[KC_SOLVE_BWD] = 0;
   for (int q0 = 0; q0 < d.nrhs; q0 += ck) {
     const int q = std::min(ck, d.nrhs - q0);
+    if (few_rhs64(S, d.N, n, q, fp64)) {  // every step on its own
+      c.launches[KC_SOLVE_FWD] += chain_levels(m);
+      c.launches[KC_SOLVE_BWD] += chain_levels(m);
+      continue;
+    }
     // x_1 has a launch of its own where the merged levels do without it
     const int top = solve_bwd_top(m, n, q, flags, chains);
     c.launches[KC_SOLVE_FWD] += solve_fwd_top(m, n, q, fp64, flags, chains) - 1;
@@ -207,12 +212,11 @@ bool dims_ok(const bmpc_dims* d, int B) {
 int flags_of(const bmpc_options* o) { return o ? o->flags : 0; }
 int solve_fwd_top(int m, int n, int nrhs, bool fp64, int flags, int64_t chains) {
   const bool merged = !(flags & BMPC_FLAG_FWD_ONE_WAVE) && tops_together(n, chains) &&
-                      (fwd_top_few(n, nrhs, fp64) || !few_rhs(n, nrhs, fp64)) &&
-                      !few_rhs64(n, nrhs);
+                      (fwd_top_few(n, nrhs, fp64) || !few_rhs(n, nrhs, fp64));
   return merged ? fwd_top_level(m, n) : chain_levels(m) + 1;
 }
 int solve_bwd_top(int m, int n, int nrhs, int flags, int64_t chains) {
-  return (flags & BMPC_FLAG_NO_BWD_TOP_MERGE) || few_rhs64(n, nrhs) ||
+  return (flags & BMPC_FLAG_NO_BWD_TOP_MERGE) ||
                  !((nrhs == 1 && n <= 32) || tops_together(n, chains))
              ? chain_levels(m) + 1
              : bwd_top_level(m, n);
@@ -475,8 +479,6 @@ void enqueue_solve_back(bmpc_plan p, const SolveArgs& a) {
   timed(p, KC_SOLVE_X_BWD, [&] {
     if (few)
       launch_solve_bwd_top<T>(a, together ? top : L + 1, true, st);
-    else if (few_rhs64(a.n, a.nrhs))
-      launch_solve64_x<T>(a, false, st);
     else
       launch_mm_top<T>(a, together ? top : L + 1, false, st);
   });
@@ -486,8 +488,23 @@ void enqueue_solve_back(bmpc_plan p, const SolveArgs& a) {
     timed(p, KC_SOLVE_BWD, [&] { launch_solve_bwd_level<T>(a, l, st); });
 }
 
+// One chunk where few_rhs64, every step on its own.
+template <typename T>
+void enqueue_solve64(bmpc_plan p, const SolveArgs& a) {
+  hipStream_t st = p->stream;
+  const int L = chain_levels(p->m);
+  for (int l = 1; l <= L; ++l)
+    timed(p, KC_SOLVE_FWD, [&] { launch_solve64_level<T>(a, l, true, st); });
+  timed(p, KC_SOLVE_X_FWD, [&] { launch_solve64_x<T>(a, true, st); });
+  timed(p, KC_SOLVE_ROOT, [&] { launch_solve_root(a, st); });
+  timed(p, KC_SOLVE_X_BWD, [&] { launch_solve64_x<T>(a, false, st); });
+  for (int l = L; l >= 1; --l)
+    timed(p, KC_SOLVE_BWD, [&] { launch_solve64_level<T>(a, l, false, st); });
+}
+
 template <typename T>
 void enqueue_solve_chunk(bmpc_plan p, const SolveArgs& a) {
+  if (few_rhs64(a.S, a.N, a.n, a.nrhs, sizeof(T) == 8)) return enqueue_solve64<T>(p, a);
   hipStream_t st = p->stream;
   const int top =
       solve_fwd_top(p->m, a.n, a.nrhs, p->fp64, p->opt_flags, (int64_t)p->B * p->d.S);
@@ -496,8 +513,6 @@ void enqueue_solve_chunk(bmpc_plan p, const SolveArgs& a) {
   timed(p, KC_SOLVE_X_FWD, [&] {
     if (few_rhs(a.n, a.nrhs, sizeof(T) == 8))
       launch_solve_fwd_top<T>(a, top, st);
-    else if (few_rhs64(a.n, a.nrhs))
-      launch_solve64_x<T>(a, true, st);
     else
       launch_mm_top<T>(a, top, true, st);
   });

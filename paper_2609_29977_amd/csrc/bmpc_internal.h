@@ -33,9 +33,15 @@ constexpr int kFactorThreads = 256;
 constexpr int kSolveRhs = 16;
 constexpr int kMaxRhs = 8;
 constexpr int kMaxRhs64 = 4;
-// Solves of so few right-hand sides at n > 48 go level by level through solve64.hip.
-constexpr __host__ __device__ bool few_rhs64(int n, int nrhs) {
-  return n > 48 && nrhs <= kMaxRhs64;
+// Solves of few right-hand sides at n > 32 that go level by level through solve64.hip (figures
+// there): at n > 48, and of chains of one or two stages, where nothing hides the latency of
+// the products' one wave per position, unless there are scenarios enough for that (in FP32
+// with short runs of loads, n % 4, there hardly are).
+constexpr bool few_rhs64(int S, int N, int n, int nrhs, bool fp64) {
+  const bool runs = n % 4 == 0;
+  return (n > 48 && nrhs <= kMaxRhs64) ||
+         (n > 32 && N <= 2 && (nrhs == 1 || (nrhs == 2 && (N == 1 || !runs))) &&
+          S <= (fp64 || runs ? 512 : 2048));
 }
 constexpr __host__ __device__ int residual_chunk(int nmax) {
   return nmax > 32 ? kMaxRhs64 : kMaxRhs;

@@ -928,7 +928,6 @@ MmTopCfg x_fwd_config(const SolveArgs& a, int nmax, bool fp64) {
 
 template <typename T>
 static void launch_level(const SolveArgs& a, int level, bool fwd, hipStream_t st) {
-  if (few_rhs64(a.n, a.nrhs)) return launch_solve64_level<T>(a, level, fwd, st);
   if (!few_rhs(a.n, a.nrhs, sizeof(T) == 8)) return launch_mm_level<T>(a, level, fwd, st);
   by_size(a.n, a.nrhs, [&](auto nmax, auto full, auto nr) {
     level_t<T, decltype(nmax)::value, decltype(full)::value, decltype(nr)::value>(a, level, fwd,

@@ -142,3 +142,10 @@ def test_blocks_over_48(n, nrhs, precision):
         _check(3, N, n, nrhs, precision)
     for flags in (1, 2, 3):
         _check(2, 21, n, nrhs, precision, flags)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("n,nrhs", [(33, 1), (40, 2), (47, 1), (48, 2), (48, 3)])
+def test_short_chains_of_blocks_over_32(n, nrhs, precision):
+    for S, N in ((1, 1), (3, 2), (512, 2), (513, 2), (3, 3)):
+        _check(S, N, n, nrhs, precision)
