@@ -678,19 +678,15 @@ __device__ __attribute__((always_inline)) inline void solve_root_body(const Solv
     // with at least sixteen loads in flight per thread: S = 20000, n = 8 in FP64, two
     // right-hand sides, one solve 584 -> 441 us, five 858 -> 671
     const int left = nrhs - q0;
-    const bool spare = S <= 4 * (1024 / NMAX);
-    if (QB >= 8 && left >= (spare ? 5 : 8))
+    if (QB >= 8 && left >= (S <= 4 * (1024 / NMAX) ? 5 : 8))
       taken = partials(std::integral_constant<int, QB < 8 ? QB : 8>{},
                        std::integral_constant<int, 4>{});
     else if (QB >= 4 && left >= (S <= 16 * (1024 / NMAX) ? 3 : 4))
       taken = partials(std::integral_constant<int, QB < 4 ? QB : 4>{},
                        std::integral_constant<int, 4>{});
-    else if (left >= 2 && spare)
-      taken = partials(std::integral_constant<int, 2>{}, std::integral_constant<int, 4>{});
     else if (left >= 2)
-      taken = partials(std::integral_constant<int, 2>{}, std::integral_constant<int, 8>{});
-    else if (spare)
-      taken = partials(std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{});
+      taken = partials(std::integral_constant<int, 2>{},
+                       std::integral_constant<int, QB < 8 ? 4 : 8>{});
     else
       taken = partials(std::integral_constant<int, 1>{}, std::integral_constant<int, 16>{});
     __syncthreads();
