@@ -175,7 +175,7 @@ Costs make_costs(const bmpc_dims& d, bool fp64, int Tw1, int Tw2, int B, int fla
     }
     // x_1 has a launch of its own where the merged levels do without it
     const int top = solve_bwd_top(m, n, q, flags, chains);
-    c.launches[KC_SOLVE_FWD] += solve_fwd_top(m, n, q, fp64, flags, chains) - 1;
+    c.launches[KC_SOLVE_FWD] += solve_fwd_top(d, q, fp64, flags, chains) - 1;
     c.launches[KC_SOLVE_BWD] +=
         top - 1 + (!tops_together(n, chains) && top <= chain_levels(m) ? 1 : 0);
   }
@@ -210,9 +210,10 @@ bool dims_ok(const bmpc_dims* d, int B) {
 }
 
 int flags_of(const bmpc_options* o) { return o ? o->flags : 0; }
-int solve_fwd_top(int m, int n, int nrhs, bool fp64, int flags, int64_t chains) {
+int solve_fwd_top(const bmpc_dims& d, int nrhs, bool fp64, int flags, int64_t chains) {
+  const int m = d.N - 1, n = d.n;
   const bool merged = !(flags & BMPC_FLAG_FWD_ONE_WAVE) && tops_together(n, chains) &&
-                      (fwd_top_few(n, nrhs, fp64) || !few_rhs(n, nrhs, fp64));
+                      (few_fwd_top(n, fp64) || !few_rhs(d.S, d.N, n, nrhs, fp64));
   return merged ? fwd_top_level(m, n) : chain_levels(m) + 1;
 }
 int solve_bwd_top(int m, int n, int nrhs, int flags, int64_t chains) {
@@ -472,7 +473,7 @@ void enqueue_solve_back(bmpc_plan p, const SolveArgs& a) {
   hipStream_t st = p->stream;
   // x_1 and the top levels (few positions per chain) in one launch, the others one by one; one
   // right-hand side merges the top levels also where there are too many chains for that
-  const bool few = few_rhs(a.n, a.nrhs, sizeof(T) == 8);
+  const bool few = few_rhs(a.S, a.N, a.n, a.nrhs, sizeof(T) == 8);
   const int64_t chains = (int64_t)p->B * p->d.S;
   const int L = chain_levels(p->m), top = solve_bwd_top(p->m, a.n, a.nrhs, p->opt_flags, chains);
   const bool together = tops_together(a.n, chains);
@@ -507,11 +508,11 @@ void enqueue_solve_chunk(bmpc_plan p, const SolveArgs& a) {
   if (few_rhs64(a.S, a.N, a.n, a.nrhs, sizeof(T) == 8)) return enqueue_solve64<T>(p, a);
   hipStream_t st = p->stream;
   const int top =
-      solve_fwd_top(p->m, a.n, a.nrhs, p->fp64, p->opt_flags, (int64_t)p->B * p->d.S);
+      solve_fwd_top(p->d, a.nrhs, p->fp64, p->opt_flags, (int64_t)p->B * p->d.S);
   for (int l = 1; l < top; ++l)
     timed(p, KC_SOLVE_FWD, [&] { launch_solve_fwd_level<T>(a, l, st); });
   timed(p, KC_SOLVE_X_FWD, [&] {
-    if (few_rhs(a.n, a.nrhs, sizeof(T) == 8))
+    if (few_rhs(a.S, a.N, a.n, a.nrhs, sizeof(T) == 8))
       launch_solve_fwd_top<T>(a, top, st);
     else
       launch_mm_top<T>(a, top, true, st);

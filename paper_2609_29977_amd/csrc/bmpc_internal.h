@@ -235,7 +235,7 @@ void launch_solve_bwd_level(const SolveArgs& a, int level, hipStream_t st);
 // bwd_top_level has it or above.
 template <typename T>
 void launch_solve_bwd_top(const SolveArgs& a, int level_lo, bool with_x, hipStream_t st);
-// The forward levels from level_lo up to the top (where fwd_top_few says so; else none, level_lo
+// The forward levels from level_lo up to the top (where few_fwd_top says so; else none, level_lo
 // above the top) and the x_1 forward step in one launch, for few right-hand sides.
 template <typename T>
 void launch_solve_fwd_top(const SolveArgs& a, int level_lo, hipStream_t st);
@@ -322,8 +322,9 @@ __host__ __device__ inline int fwd_top_level(int m, int n) {
   while (l > 1 && level_count(m, l - 1) <= mm_top_waves(n) / 2) --l;
   return l;
 }
-// Waves of a forward level's workgroup: as many as its pulls occupy, at most four, or for the levels that may go into that launch as many as they would have there, so
-// that the sums do not depend on whether they do.
+// Waves of a forward level's workgroup: as many as its pulls occupy, at most four, or for the
+// levels that may go into that launch as many as they would have there, so that the sums do
+// not depend on whether they do.
 __host__ __device__ inline int mm_fwd_waves(int m, int n, bool fp64, int level) {
   return mm_pull_waves(n, fp64, 2 * (level - 1), level >= fwd_top_level(m, n)
                                                      ? mm_top_share(n, level_count(m, level))
@@ -331,24 +332,30 @@ __host__ __device__ inline int mm_fwd_waves(int m, int n, bool fp64, int level) 
 }
 // Few right-hand sides at n <= 32 go through the kernels that hold a block in a wave's registers
 // (solve.hip), the others through matrix products, which read a block once for up to
-// sixteen columns but cost the same for one of them, and pad n to 16 or 32 rows.  By n, nrhs
-// and precision alone: a system's sums do not depend on the others of its launch.  One
-// solve, products / registers: two right-hand sides in FP64 at S = 60, N = 250 n = 8 82 / 59 us, n =
-// 32 212 / 178, at S = 1500, N = 16 85 / 63 and 248 / 214, at S = 4, N = 16 24 / 20 and 46 / 41,
-// n = 12 24.9 / 25.6; in FP32 at S = 4, N = 16 n = 12 22 / 24, n = 16 21.8 / 21.4; three at S = 4, N
-// = 16 n = 8 23.5 / 23 in FP64 and 22.5 / 23.5 in FP32, n = 16 25.5 / 27.5 in FP64, n = 32 at S = 1500,
-// N = 16 in FP64 265 / 242.
+// sixteen columns but cost the same for one of them, and pad n to 16 or 32 rows.  By a
+// system's own sizes alone: its sums do not depend on the other systems of a launch.  One
+// solve, products / registers, us:
+//   two right-hand sides in FP64 at S = 60, N = 250 n = 8 82 / 59, n = 32 212 / 178, at S =
+//   1500, N = 16 85 / 63 and 248 / 214; in FP32 at S = 20, N = 30 n = 12 31 / 34, n = 16 31 / 29, n =
+//   24 46 / 47.5, at S = 60, N = 250 n = 24 121 / 116;
+//   three at S = 4, N = 16 n = 8 23.5 / 23 in FP64 and 22.5 / 23.5 in FP32, n = 16 25.5 / 27.5 in
+//   FP64, at S = 400, N = 20 n = 16 50 / 55.5, at S = 1500, N = 16 n = 12 in FP64 97 / 92, n = 20 195 / 150
+//   and in FP32 134 / 122, n = 12 84 / 83, n = 32 in FP64 265 / 242;
+//   up to nine stages, where all forward levels are one launch of the products, two at S =
+//   5, N = 9 in FP64 n = 24 34 / 40, n = 32 36 / 36, at S = 5000, N = 8 n = 24 304 / 245.
 constexpr int kFewRhs = 3;
-constexpr bool few_rhs(int n, int nrhs, bool fp64) {
-  return n <= 32 && (nrhs == 1 || (nrhs == 2 && (fp64 || n <= 8 || n >= 16)) ||
-                     (nrhs == kFewRhs && (n == 32 || (fp64 && n <= 8))));
+constexpr bool few_rhs(int S, int N, int n, int nrhs, bool fp64) {
+  const bool one_launch = N <= 9 && S <= 256;
+  if (n > 32 || nrhs > kFewRhs) return false;
+  if (nrhs == 1 || (nrhs == 2 && (n <= 8 || n == 16 || n == 32))) return true;
+  if (one_launch) return false;
+  if (nrhs == 2) return fp64 || (n > 16 && (n % 4 != 0 || S > 32));
+  return n == 32 || (fp64 && n <= 8) || (n > 16 ? S > 256 : fp64 && S > 512);
 }
-// Their merged forward launch, of sixteen waves, exists where a wave does with the 128
-// registers that it then has.
-constexpr bool fwd_top_few(int n, int nrhs, bool fp64) {
-  return few_rhs(n, nrhs, fp64) && n <= (fp64 ? 16 : 32);
-}
-// Whether they do, for so many chains in the launch: up to what the GPU holds at once (256
+// The merged forward launch of these kernels, of sixteen waves, exists where a wave does with
+// the 128 registers that it then has.
+constexpr bool few_fwd_top(int n, bool fp64) { return n <= (fp64 ? 16 : 32); }
+// Whether the top levels go into a launch with x_1, for so many chains in it: up to what the GPU holds at once (256
 // compute units with one workgroup each for n > 16, two below).  Beyond that the barriers
 // cost more than the launches they replace.  One solve, together / apart: one right-hand side
 // at S = 100, N = 160, n = 16 in FP32 58 / 66 us, at S = 512, N = 64 65 / 68 (96 / 95 at S =

@@ -114,7 +114,7 @@ std::vector<int> make_perm(int N);
 bool dims_ok(const bmpc_dims* d, int B = 1);
 int flags_of(const bmpc_options* o);
 // First levels of the merged launches of each sweep (see fwd_top_level), for so many chains.
-int solve_fwd_top(int m, int n, int nrhs, bool fp64, int flags, int64_t chains);
+int solve_fwd_top(const bmpc_dims& d, int nrhs, bool fp64, int flags, int64_t chains);
 int solve_bwd_top(int m, int n, int nrhs, int flags, int64_t chains);
 int pick_window_depth(bool fp64, int nmax, int nrhs, const bmpc_options* o);
 bool dalloc(bmpc_plan p, void** ptr, size_t bytes);

@@ -132,7 +132,7 @@ void build_back(RaggedState& R, Seq& seq, const std::vector<SolveArgs>& args, in
   std::vector<int> topl(B);
   for (int i = 0; i < B; ++i) {
     bmpc_plan s = R.subs[i];
-    const bool few = few_rhs(s->d.n, args[i].nrhs, s->fp64);
+    const bool few = few_rhs(s->d.S, s->d.N, s->d.n, args[i].nrhs, s->fp64);
     const bool together = tops_together(s->d.n, R.chains);
     const int L = chain_levels(s->m);
     topl[i] = solve_bwd_top(s->m, s->d.n, args[i].nrhs, s->opt_flags, R.chains);
@@ -192,8 +192,8 @@ void build_fwd(RaggedState& R, Seq& seq, const std::vector<SolveArgs>& args) {
   int maxL = 0;
   std::vector<int> topl(B);
   for (int i = 0; i < B; ++i) {
-    topl[i] = solve_fwd_top(R.subs[i]->m, R.subs[i]->d.n, args[i].nrhs, R.subs[i]->fp64,
-                            R.subs[i]->opt_flags, R.chains);
+    topl[i] = solve_fwd_top(R.subs[i]->d, args[i].nrhs, R.subs[i]->fp64, R.subs[i]->opt_flags,
+                            R.chains);
     maxL = std::max(maxL, topl[i] - 1);
   }
   for (int l = 1; l <= maxL; ++l) {
@@ -223,7 +223,8 @@ void build_fwd(RaggedState& R, Seq& seq, const std::vector<SolveArgs>& args) {
   std::map<std::tuple<int, int>, std::vector<Pending<SolveArgs>>> xf;
   for (int i = 0; i < B; ++i) {
     bmpc_plan s = R.subs[i];
-    const bool few = few_rhs(s->d.n, args[i].nrhs, s->fp64), alone = topl[i] > chain_levels(s->m);
+    const bool few = few_rhs(s->d.S, s->d.N, s->d.n, args[i].nrhs, s->fp64);
+    const bool alone = topl[i] > chain_levels(s->m);
     xf[std::make_tuple((int)(!few ? SK_MM_TOP : alone ? SK_X_FWD : SK_FWD_TOP),
                        few ? one_class(s) : mm_class(s->d.n))]
         .push_back({i, args[i], topl[i], 0, (unsigned)s->d.S, 1u, 1u});

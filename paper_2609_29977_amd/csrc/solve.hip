@@ -833,7 +833,7 @@ void solve_multi_t(int kind, bool fwd, const MultiItem<SolveArgs>* items, int ni
       hipLaunchKernelGGL((solve_bwd_top_multi<T, NMAX, FULL, NR>), g, b, 0, st, items, nitems, r);
       break;
     case SK_FWD_TOP:
-      if constexpr (fwd_top_few(NMAX, NR, sizeof(T) == 8))
+      if constexpr (few_fwd_top(NMAX, sizeof(T) == 8))
         hipLaunchKernelGGL((solve_fwd_top_multi<T, NMAX, FULL, NR>), g, dim3(64 * kFwdTopWaves), 0,
                            st, items, nitems, r);
       break;
@@ -869,12 +869,11 @@ void level_t(const SolveArgs& a, int level, bool fwd, hipStream_t st) {
 template <typename F>
 void by_size(int n, int nrhs, F&& f) {
   auto rhs = [&](auto nmax, auto full) {
-    constexpr int NMAX = decltype(nmax)::value;
     if (nrhs == 1)
       f(nmax, full, std::integral_constant<int, 1>{});
     else if (nrhs == 2)
       f(nmax, full, std::integral_constant<int, 2>{});
-    else if constexpr (NMAX == 8 || (NMAX == 32 && decltype(full)::value))
+    else
       f(nmax, full, std::integral_constant<int, kFewRhs>{});
   };
   auto full = [&](auto nmax) {
@@ -898,7 +897,7 @@ void by_size(int n, int nrhs, F&& f) {
 // Forward positions of level l pull 2 (l - 1) blocks, kPullsPerWave per wave, on up to
 // kLevelMaxWaves waves (or a.fwd_waves: one wave per position when the plan asks for it).
 LevelCfg solve_level_config(const SolveArgs& a, int level, bool fwd, int nmax, bool fp64) {
-  if (!few_rhs(a.n, a.nrhs, fp64)) return mm_level_config(a, level, fwd, fp64);
+  if (!few_rhs(a.S, a.N, a.n, a.nrhs, fp64)) return mm_level_config(a, level, fwd, fp64);
   LevelCfg c{};
   c.count = level_count(a.m, level);
   const int waves = fwd && a.fwd_waves != 1 ? fwd_one_waves(level) : 1;
@@ -924,7 +923,8 @@ MmTopCfg x_fwd_config(const SolveArgs& a, int nmax, bool fp64) {
 
 template <typename T>
 static void launch_level(const SolveArgs& a, int level, bool fwd, hipStream_t st) {
-  if (!few_rhs(a.n, a.nrhs, sizeof(T) == 8)) return launch_mm_level<T>(a, level, fwd, st);
+  if (!few_rhs(a.S, a.N, a.n, a.nrhs, sizeof(T) == 8))
+    return launch_mm_level<T>(a, level, fwd, st);
   by_size(a.n, a.nrhs, [&](auto nmax, auto full, auto nr) {
     level_t<T, decltype(nmax)::value, decltype(full)::value, decltype(nr)::value>(a, level, fwd,
                                                                                  st);
@@ -963,7 +963,7 @@ void launch_solve_fwd_top(const SolveArgs& a, int level_lo, hipStream_t st) {
       const MmTopCfg c = x_fwd_config(a, NMAX, sizeof(T) == 8);
       hipLaunchKernelGGL((solve_x_fwd_kernel<T, NMAX, FULL, NR>), grid, dim3(c.threads), c.lds, st,
                          a);
-    } else if constexpr (fwd_top_few(NMAX, NR, sizeof(T) == 8)) {
+    } else if constexpr (few_fwd_top(NMAX, sizeof(T) == 8)) {
       hipLaunchKernelGGL((solve_fwd_top_kernel<T, NMAX, FULL, NR>), grid, dim3(64 * kFwdTopWaves),
                          0, st, a, level_lo);
     }

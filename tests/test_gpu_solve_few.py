@@ -48,13 +48,16 @@ def test_blocks_up_to_32(n, nrhs, precision):
         _check(2, 40, n, nrhs, precision, flags)
 
 
-# either side of the chains whose top levels share a launch (512, 256 above n = 16), and of the
-# scenarios that the root step reads in one go (128, 512)
+# either side of the chains whose top levels share a launch (512, 256 above n = 16), of the
+# scenarios that the root step reads in one go (128, 512) and of those that decide which
+# kernels take two or three right-hand sides (32, 256)
 @pytest.mark.parametrize("precision", ["fp64", "fp32"])
-@pytest.mark.parametrize("S", [127, 129, 255, 257, 511, 514])
-@pytest.mark.parametrize("n,nrhs", [(8, 2), (8, 3), (16, 1), (12, 5), (21, 2), (32, 3), (32, 6)])
+@pytest.mark.parametrize("S", [32, 33, 127, 129, 255, 257, 511, 514])
+@pytest.mark.parametrize("n,nrhs", [(8, 2), (8, 3), (16, 1), (12, 5), (12, 3), (21, 2), (19, 3), (32, 3),
+                                    (32, 6)])
 def test_chain_counts(n, nrhs, S, precision):
-    _check(S, 12, n, nrhs, precision)
+    for N in (12, 6):
+        _check(S, N, n, nrhs, precision)
 
 
 @pytest.mark.parametrize("precision", ["fp64", "fp32"])
