@@ -12,6 +12,7 @@
 //   C_s     = M_{s,0}[uv]                             R = tau I + sum_s M_{s,0}[uu]
 // so K has exactly the root-coupled block structure the solver takes.
 #include <algorithm>
+#include <cmath>
 #include <mutex>
 
 #include "bmpc.h"
@@ -29,7 +30,7 @@ struct QpArgs {
   const double* A;
   const double* G;
   const double* w;
-  double tau, delta;
+  double tau, delta, sdelta;  // sdelta: 1 / sqrt(delta)
   double* D;
   double* E;
   double* C;
@@ -45,9 +46,9 @@ struct QpArgs {
 // (q, p) are sums of the same products and D and R are exactly symmetric where Q is), and Q
 // is read in the accumulator layout, so nothing is staged in LDS and all loads of a link
 // are in flight together.  Memory-bound: 8 (3 n^2 + (me + mi) 2n + mi) bytes read per link
-// and 16 n^2 written.  S = 256, N = 128, n = 16, 12 + 32 rows: 403 us with one workgroup
+// and 16 n^2 written.  S = 256, N = 128, n = 16, 12 + 32 rows: 349 us with one workgroup
 // per stage and scalar products from LDS (every link read twice), 169 us
-// now (4.3 TB/s); S = 64, N = 128, n = 32: 697 -> 200 us.
+// now (4.3 TB/s); S = 64, N = 128, n = 32, 24 + 64 rows: 690 -> 193 us.
 template <int NT>  // 16-column tiles of u and of v: ceil(n / 16)
 struct QpLink {
   typedef Mfma<double>::acc_t acc_t;
@@ -83,8 +84,8 @@ struct QpLink {
 #pragma unroll
       for (int k = 0; k < U; ++k) {
         if (4 * (k0 + k) >= rows) continue;  // uniform
-        // rows past the end are zero; so is their weight
-        const double s = 4 * (k0 + k) + g < rows ? wt.scale(w[k]) : 0.0;
+        // rows past the end are zero, and their weight is finite: 1 / sqrt(delta) at most
+        const double s = wt.scale(w[k]);
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
           if (NU) xu[k][t] *= s;
@@ -139,7 +140,7 @@ struct QpLink {
     __amdgpu_buffer_rsrc_t rs;
     double delta;
     __device__ double load(int r) const { return buf_load_f64(rs, (unsigned)r * 8u); }
-    __device__ double scale(double w) const { return 1.0 / sqrt(w + delta); }
+    __device__ double scale(double w) const { return rsqrt(w + delta); }
   };
   // the quadrants of M_j: uu (UU), vu (VU) or uv (UV) into m2, vv always
   template <bool UU, bool VU, bool UV>
@@ -153,7 +154,7 @@ struct QpLink {
     quadrant(rq, n, n, vv);
     if (a.me > 0)
       rows<UU, VU, UV>(block_rsrc(a.A + lk * a.me * n2, a.me * n2 * 8u), a.me,
-                       ConstWt{1.0 / sqrt(a.delta)}, uu, m2, vv);
+                       ConstWt{a.sdelta}, uu, m2, vv);
     if (a.mi > 0)
       rows<UU, VU, UV>(block_rsrc(a.G + lk * a.mi * n2, a.mi * n2 * 8u), a.mi,
                        RowWt{block_rsrc(a.w + lk * a.mi, a.mi * 8u), a.delta}, uu, m2, vv);
@@ -287,6 +288,7 @@ extern "C" bmpc_status bmpc_assemble_qp(const bmpc_qp_dims* d, const double* Q, 
   a.w = w;
   a.tau = tau;
   a.delta = delta;
+  a.sdelta = 1.0 / std::sqrt(delta);
   a.D = D;
   a.E = E;
   a.C = C;
