@@ -62,18 +62,16 @@ __device__ inline T buf_load(__amdgpu_buffer_rsrc_t rs, unsigned off) {
   else
     return buf_load_f32(rs, off);
 }
-// K neighbouring values from byte offset off (8, 16 or 32 bytes in all)
+// K neighbouring values from byte offset off (16 or 32 bytes in all).  The whole offset goes
+// through the range check: an offset on the side is taken off the range first, which a block
+// of one entry (8 bytes) is shorter than.
 template <typename T, int K>
 __device__ inline void buf_load_run(__amdgpu_buffer_rsrc_t rs, unsigned off, T (&out)[K]) {
-  if constexpr (K * sizeof(T) == 8) {
-    const auto w = __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0);
-    __builtin_memcpy(out, &w, 8);
-  } else {
+  static_assert(K * sizeof(T) % 16 == 0, "whole 16-byte pieces");
 #pragma unroll
-    for (int h = 0; h < (int)(K * sizeof(T)) / 16; ++h) {
-      const auto w = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 16 * h, 0);
-      __builtin_memcpy(&out[h * (16 / (int)sizeof(T))], &w, 16);
-    }
+  for (int h = 0; h < (int)(K * sizeof(T)) / 16; ++h) {
+    const auto w = __builtin_amdgcn_raw_buffer_load_b128(rs, off + 16u * h, 0, 0);
+    __builtin_memcpy(&out[h * (16 / (int)sizeof(T))], &w, 16);
   }
 }
 

@@ -35,7 +35,7 @@ def _check(S, N, n, nrhs, precision, flags=0):
     p.close()
 
 
-SIZES = [(1, 1), (1, 3), (5, 2), (8, 1), (8, 2), (8, 3), (9, 2), (12, 1), (15, 2), (16, 1), (16, 2),
+SIZES = [(1, 1), (1, 3), (1, 6), (2, 17), (5, 2), (8, 1), (8, 2), (8, 3), (9, 2), (12, 1), (15, 2), (16, 1), (16, 2),
          (17, 1), (17, 2), (24, 2), (31, 1), (31, 2), (32, 1), (32, 2), (32, 3), (13, 17), (32, 18)]
 
 
