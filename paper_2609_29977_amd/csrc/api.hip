@@ -414,7 +414,7 @@ void enqueue_factor_tails(bmpc_plan p, const double* D, const double* E, const d
   const int npass = (int)p->costs.passes.size();
   if (p->nmax == 32 && d.N > 1) {
     const FactorPassArgs a0 = factor_pass_args(p, 0, D, E, C, nullptr, 0);
-    timed(p, KC_FACTOR_L1INV, [&] { launch_level1_inverse<T>(a0, p->nmax, st); });
+    timed(p, KC_FACTOR_L1INV, [&] { launch_level1_inverse<T>(a0, st); });
   }
   for (int k = 0; k < npass; ++k) {
     const PassPlan& pp = p->costs.passes[k];

@@ -6,8 +6,8 @@ namespace bmpc {
 
 // In place: A (NT x NT tiles of 16 in LDS, rows of LD entries, lower tiles read, identity padded)
 // := L^{-1} (INV) or L, with L L^T = A.  W waves call it, at least NT; the tiles above the
-// diagonal are left as they were.  scratch: 16 x 17 entries (INV: not used).  Returns the row of the
-// first non-positive pivot, or -1 (INV: on wave 0, else on wave 1).
+// diagonal are left as they were.  scratch: 16 x 17 entries (INV: not used).  Returns the row
+// of the first non-positive pivot, or -1 (INV: on wave 0, else on wave 1).
 //
 // The chain is the NT diagonal tiles, one wave each (their 16 columns take 1.9 us in FP64);
 // everything else is one or a few MFMA tile products per wave between them.  While a

@@ -175,8 +175,8 @@ __device__ inline double pivot_rsqrt(double x) {
 // In place: A (symmetric NMAX x NMAX, lower triangle read; pad smaller blocks with an
 // identity block) := L with L L^T = A, zeros above the diagonal.  One wave, lane i
 // keeps row i; column k of L is broadcast to the other rows as a DPP row-broadcast operand
-// of each multiply-add (as in the inverse leaves).  Returns (on every lane) the 0-based row of the first non-positive pivot,
-// or -1.
+// of each multiply-add (as in the inverse leaves).  Returns (on every lane) the 0-based row
+// of the first non-positive pivot, or -1.
 template <typename T, int NMAX, int LD = Lay<NMAX>::LD>
 __device__ __attribute__((always_inline)) inline int wave_potrf(T* A) {
   static_assert(NMAX <= 32, "larger blocks: block_chol");

@@ -204,7 +204,7 @@ void launch_factor_pass(const FactorPassArgs& a, int nmax, hipStream_t st);
 // L^{-1} of the odd chain positions' diagonal blocks (D only), before the first pass
 // (whose arguments a are); block sizes 17..32 only.
 template <typename T>
-void launch_level1_inverse(const FactorPassArgs& a, int nmax, hipStream_t st);
+void launch_level1_inverse(const FactorPassArgs& a, hipStream_t st);
 // block sizes up to 16 (tree.hip): window LDS and threads of a pass of Tw levels
 template <typename T>
 void launch_tree_pass(const FactorPassArgs& a, int nmax, hipStream_t st);
@@ -295,10 +295,10 @@ __host__ __device__ inline int chain_levels(int m) {
 }
 
 // The top levels of a sweep have few positions per chain; they can share one launch with the
-// x_1 step, mm_top_waves waves per chain (solve_rhs.hip).  How many of its waves are there for each of
-// count positions; the pulls that a wave has in flight (as its registers allow: with two at n
-// = 32 in FP64, a solve at S = N = 128 with twelve right-hand sides took 259 us instead of 254,
-// at S = 300, N = 200 with three 652 instead of 633); the waves that the pulls occupy.
+// x_1 step, mm_top_waves waves per chain (solve_rhs.hip).  How many of its waves are there for
+// each of count positions; the pulls that a wave has in flight (as its registers allow: with two
+// at n = 32 in FP64, a solve at S = N = 128 with twelve right-hand sides took 259 us instead of
+// 254, at S = 300, N = 200 with three 652 instead of 633); the waves that the pulls occupy.
 constexpr __host__ __device__ int mm_top_waves(int n) { return n <= 32 ? 8 : 4; }
 constexpr __host__ __device__ int mm_top_share(int n, int count) {
   return mm_top_waves(n) / (count <= 1 ? 1 : count <= 2 ? 2 : count <= 4 ? 4 : 8);
@@ -336,11 +336,11 @@ __host__ __device__ inline int mm_fwd_waves(int m, int n, bool fp64, int level) 
 // system's own sizes alone: its sums do not depend on the other systems of a launch.  One
 // solve, products / registers, us:
 //   two right-hand sides in FP64 at S = 60, N = 250 n = 8 82 / 59, n = 32 212 / 178, at S =
-//   1500, N = 16 85 / 63 and 248 / 214; in FP32 at S = 20, N = 30 n = 12 31 / 34, n = 16 31 / 29, n =
-//   24 46 / 47.5, at S = 60, N = 250 n = 24 121 / 116;
+//   1500, N = 16 85 / 63 and 248 / 214; in FP32 at S = 20, N = 30 n = 12 31 / 34, n = 16 31 / 29, n
+//   = 24 46 / 47.5, at S = 60, N = 250 n = 24 121 / 116;
 //   three at S = 4, N = 16 n = 8 23.5 / 23 in FP64 and 22.5 / 23.5 in FP32, n = 16 25.5 / 27.5 in
-//   FP64, at S = 400, N = 20 n = 16 50 / 55.5, at S = 1500, N = 16 n = 12 in FP64 97 / 92, n = 20 195 / 150
-//   and in FP32 134 / 122, n = 12 84 / 83, n = 32 in FP64 265 / 242;
+//   FP64, at S = 400, N = 20 n = 16 50 / 55.5, at S = 1500, N = 16 n = 12 in FP64 97 / 92, n = 20
+//   195 / 150 and in FP32 134 / 122, n = 12 84 / 83, n = 32 in FP64 265 / 242;
 //   up to nine stages, where all forward levels are one launch of the products, two at S =
 //   5, N = 9 in FP64 n = 24 34 / 40, n = 32 36 / 36, at S = 5000, N = 8 n = 24 304 / 245.
 constexpr int kFewRhs = 3;
@@ -355,12 +355,12 @@ constexpr bool few_rhs(int S, int N, int n, int nrhs, bool fp64) {
 // The merged forward launch of these kernels, of sixteen waves, exists where a wave does with
 // the 128 registers that it then has.
 constexpr bool few_fwd_top(int n, bool fp64) { return n <= (fp64 ? 16 : 32); }
-// Whether the top levels go into a launch with x_1, for so many chains in it: up to what the GPU holds at once (256
-// compute units with one workgroup each for n > 16, two below).  Beyond that the barriers
-// cost more than the launches they replace.  One solve, together / apart: one right-hand side
-// at S = 100, N = 160, n = 16 in FP32 58 / 66 us, at S = 512, N = 64 65 / 68 (96 / 95 at S =
-// 768 with matrix products); four at n = 32, N = 64 in FP32 80 / 95 us at S = 128, 113 / 128
-// at 256, 177 / 171 at 384; at S = 5000, N = 16, n = 16 in FP64 383 / 303.
+// Whether the top levels go into a launch with x_1, for so many chains in it: up to what the
+// GPU holds at once (256 compute units with one workgroup each for n > 16, two below).
+// Beyond that the barriers cost more than the launches they replace.  One solve, together /
+// apart: one right-hand side at S = 100, N = 160, n = 16 in FP32 56 / 63 us, at S = 512, N = 64
+// 62 / 65, at S = 768 81 / 81; four at n = 32, N = 64 in FP32 107 / 126 us at S = 256, 166 / 170
+// at 384, in FP64 288 / 284; one at S = 5000, N = 16, n = 16 in FP64 277 / 205.
 constexpr bool tops_together(int n, int64_t chains) { return chains <= (n <= 16 ? 512 : 256); }
 
 }  // namespace bmpc

@@ -1313,55 +1313,39 @@ void launch_factor_pass(const FactorPassArgs& a, int nmax, hipStream_t st) {
 template void launch_factor_pass<double>(const FactorPassArgs&, int, hipStream_t);
 template void launch_factor_pass<float>(const FactorPassArgs&, int, hipStream_t);
 
-namespace {
-template <typename T, int NMAX>
-void launch_l1inv_t(const FactorPassArgs& a, hipStream_t st) {
+template <typename T>
+void launch_level1_inverse(const FactorPassArgs& a, hipStream_t st) {
   const int nodd = (a.m + 1) / 2;
   const unsigned total = (unsigned)a.S * (unsigned)nodd;
   if (total == 0) return;
   constexpr unsigned PER_WG = 4 * level1_blocks_per_wave(sizeof(T) == 8);
   const size_t lds = PER_WG * (size_t)kPacked32 * sizeof(T);
   const dim3 grid((total + PER_WG - 1) / PER_WG);
-  if (a.n == NMAX)
-    hipLaunchKernelGGL((level1_inverse_kernel<T, NMAX, true>), grid, dim3(256), lds, st, a, nodd,
+  if (a.n == 32)
+    hipLaunchKernelGGL((level1_inverse_kernel<T, 32, true>), grid, dim3(256), lds, st, a, nodd,
                        total);
   else
-    hipLaunchKernelGGL((level1_inverse_kernel<T, NMAX, false>), grid, dim3(256), lds, st, a,
-                       nodd, total);
+    hipLaunchKernelGGL((level1_inverse_kernel<T, 32, false>), grid, dim3(256), lds, st, a, nodd,
+                       total);
 }
-template <typename T, int NMAX>
-void launch_l1inv_multi_t(const MultiItem<FactorPassArgs>* items, int nitems, unsigned blocks,
-                          bool full, const Reloc& r, hipStream_t st) {
-  const size_t lds =
-      4 * (size_t)level1_blocks_per_wave(sizeof(T) == 8) * kPacked32 *
-      sizeof(T);
-  if (full)
-    hipLaunchKernelGGL((level1_inverse_multi<T, NMAX, true>), dim3(blocks), dim3(256), lds, st,
-                       items, nitems, r);
-  else
-    hipLaunchKernelGGL((level1_inverse_multi<T, NMAX, false>), dim3(blocks), dim3(256), lds, st,
-                       items, nitems, r);
-}
-}  // namespace
-
-template <typename T>
-void launch_level1_inverse(const FactorPassArgs& a, int nmax, hipStream_t st) {
-  if (nmax == 32) launch_l1inv_t<T, 32>(a, st);
-}
-template void launch_level1_inverse<double>(const FactorPassArgs&, int, hipStream_t);
-template void launch_level1_inverse<float>(const FactorPassArgs&, int, hipStream_t);
+template void launch_level1_inverse<double>(const FactorPassArgs&, hipStream_t);
+template void launch_level1_inverse<float>(const FactorPassArgs&, hipStream_t);
 
 template <typename T>
 void launch_level1_inverse_multi(const MultiItem<FactorPassArgs>* items, int nitems,
-                                 unsigned blocks, int nmax, bool full, const Reloc& r,
-                                 hipStream_t st) {
-  if (nmax == 32) launch_l1inv_multi_t<T, 32>(items, nitems, blocks, full, r, st);
+                                 unsigned blocks, bool full, const Reloc& r, hipStream_t st) {
+  const size_t lds = 4 * (size_t)level1_blocks_per_wave(sizeof(T) == 8) * kPacked32 * sizeof(T);
+  if (full)
+    hipLaunchKernelGGL((level1_inverse_multi<T, 32, true>), dim3(blocks), dim3(256), lds, st,
+                       items, nitems, r);
+  else
+    hipLaunchKernelGGL((level1_inverse_multi<T, 32, false>), dim3(blocks), dim3(256), lds, st,
+                       items, nitems, r);
 }
-template void launch_level1_inverse_multi<double>(const MultiItem<FactorPassArgs>*, int,
-                                                  unsigned, int, bool, const Reloc&,
-                                                  hipStream_t);
+template void launch_level1_inverse_multi<double>(const MultiItem<FactorPassArgs>*, int, unsigned,
+                                                  bool, const Reloc&, hipStream_t);
 template void launch_level1_inverse_multi<float>(const MultiItem<FactorPassArgs>*, int, unsigned,
-                                                 int, bool, const Reloc&, hipStream_t);
+                                                 bool, const Reloc&, hipStream_t);
 
 template <typename T>
 void launch_factor_pass_multi(const MultiItem<FactorPassArgs>* items, int nitems,

@@ -120,8 +120,7 @@ constexpr int level1_blocks_per_wave(bool fp64) { return fp64 ? 2 : 1; }
 // (level1_blocks_per_wave per wave, four waves per workgroup) of the system.
 template <typename T>
 void launch_level1_inverse_multi(const MultiItem<FactorPassArgs>* items, int nitems,
-                                 unsigned blocks, int nmax, bool full, const Reloc& r,
-                                 hipStream_t st);
+                                 unsigned blocks, bool full, const Reloc& r, hipStream_t st);
 void launch_root_reduce_multi(const MultiItem<RootArgs>* items, int nitems, unsigned blocks,
                               hipStream_t st);
 void launch_root_potrf_multi(const MultiItem<RootArgs>* items, int nitems, unsigned blocks,
@@ -157,8 +156,8 @@ MmTopCfg mm_top_config(const SolveArgs& a, int level_lo, bool fwd, bool fp64);
 
 // n: the items' block size, or for the matrix products any with their mm_class
 template <typename T>
-void launch_solve_multi(int kind, bool fwd, int n, int nrhs, const MultiItem<SolveArgs>* items, int nitems,
-                        unsigned blocks, unsigned threads, size_t lds, const Reloc& r,
+void launch_solve_multi(int kind, bool fwd, int n, int nrhs, const MultiItem<SolveArgs>* items,
+                        int nitems, unsigned blocks, unsigned threads, size_t lds, const Reloc& r,
                         hipStream_t st);
 template <typename T>
 void launch_mm_multi(int kind, bool fwd, int n, const MultiItem<SolveArgs>* items, int nitems,

@@ -112,8 +112,7 @@ int one_class(bmpc_plan s) { return 2 * s->nmax + (s->d.n == s->nmax ? 1 : 0); }
 
 // The steps of one solve chunk from the root step on (root step, x_1 backward step with
 // the top backward levels, the other backward levels).
-void build_back(RaggedState& R, Seq& seq, const std::vector<SolveArgs>& args, int q0) {
-  (void)q0;
+void build_back(RaggedState& R, Seq& seq, const std::vector<SolveArgs>& args) {
   const int B = (int)R.subs.size();
   {
     std::vector<Pending<SolveArgs>> items;
@@ -278,9 +277,9 @@ void build_factor(bmpc_plan p, Seq& seq, bool fused) {
     seq.push_back(rec);
   }
   {
-    // level-1 inverses of every system's first pass, one launch per tile size and
-    // n == NMAX (level1_blocks_per_wave blocks per wave, four waves per workgroup)
-    std::map<std::tuple<int, bool>, std::vector<Pending<FactorPassArgs>>> groups;
+    // level-1 inverses of every system's first pass (n of 17..32), one launch for n == 32 and
+    // one for the others (level1_blocks_per_wave blocks per wave, four waves per workgroup)
+    std::map<bool, std::vector<Pending<FactorPassArgs>>> groups;
     for (int i = 0; i < B; ++i) {
       bmpc_plan s = R.subs[i];
       const int nodd = s->d.N / 2;  // odd positions 1, 3, .. of the N - 1 chain positions
@@ -290,15 +289,14 @@ void build_factor(bmpc_plan p, Seq& seq, bool fused) {
       const unsigned total = (unsigned)(s->B * s->d.S) * (unsigned)nodd;
       const unsigned per_wg =
           4u * (unsigned)level1_blocks_per_wave(p->prec == BMPC_FP64);
-      groups[std::make_tuple(s->nmax, s->d.n == s->nmax)].push_back(
+      groups[s->d.n == s->nmax].push_back(
           {i, a, nodd, (int)total, (total + per_wg - 1) / per_wg, 1u, 1u});
     }
     for (auto& g : groups) {
       LaunchRec rec;
       rec.op = RO_L1INV;
       rec.cls = KC_FACTOR_L1INV;
-      rec.nmax = std::get<0>(g.first);
-      rec.full = std::get<1>(g.first);
+      rec.full = g.first;
       emit(R, seq, rec, g.second);
     }
   }
@@ -411,7 +409,7 @@ void run(bmpc_plan p, const Seq& seq, const Reloc& r) {
           break;
         case RO_L1INV:
           launch_level1_inverse_multi<T>(static_cast<const MultiItem<FactorPassArgs>*>(tab),
-                                         rec.nitems, rec.blocks, rec.nmax, rec.full, r, st);
+                                         rec.nitems, rec.blocks, rec.full, r, st);
           break;
         case RO_FACTOR:
           launch_factor_pass_multi<T>(static_cast<const MultiItem<FactorPassArgs>*>(tab),
@@ -751,11 +749,11 @@ bmpc_status bmpc_analyze_ragged(int32_t B, const bmpc_dims* dims, bmpc_precision
   for (int c = 0; c < R.chunks; ++c) {
     const std::vector<SolveArgs> a = chunk_args(p, c, false);
     build_fwd(R, R.solve[c], a);
-    build_back(R, R.solve[c], a, c * R.chunk);
-    if (c == 0) build_back(R, R.back0, a, 0);
+    build_back(R, R.solve[c], a);
+    if (c == 0) build_back(R, R.back0, a);
     const std::vector<SolveArgs> ca = chunk_args(p, c, true);
     build_fwd(R, R.corr[c], ca);
-    build_back(R, R.corr[c], ca, c * R.chunk);
+    build_back(R, R.corr[c], ca);
   }
   for (int c = 0; c < R.rchunks; ++c) {
     build_residual(p, R.resid[0][c], c, false);

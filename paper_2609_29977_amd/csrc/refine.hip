@@ -30,15 +30,14 @@ __device__ inline double wave_max(double v) {
 // One workgroup walks res_stages consecutive stages of one tail: four waves for blocks of
 // more than 16 rows, one wave for smaller ones, whose stages are too little work for four
 // (a stage of a 16 x 16 block has one entry per thread there, and both barriers of a step
-// are between waves).  The
-// blocks of a stage (the lower triangle of D, all of E) are read with coalesced 8-byte
-// loads into registers two stages ahead, together with the x of the next stage and the
-// b of the stage, then staged in double-buffered LDS, where the symmetric product with
-// D and the product with E^T read them transposed; so each E block leaves HBM once and
-// serves both rows it touches.  Nothing fetched ahead is used before the step that
-// needs it, so the loads of two stages stay in flight while a stage is applied.  Row o
-// of the stage's result is summed by RT = RES_T / NMAX threads, each over
-// NMAX / RT columns.
+// are between waves).  The blocks of a stage (the lower triangle of D, all of E) are read
+// with coalesced loads (16 bytes where the block is full) into registers two stages
+// ahead, together with the x of the next stage and the b of the stage, then staged in
+// double-buffered LDS, where the symmetric product with D and the product with E^T read
+// them transposed; so each E block leaves HBM once and serves both rows it touches.
+// Nothing fetched ahead is used before the step that needs it, so the loads of two stages
+// stay in flight while a stage is applied.  Row o of the stage's result is summed by RT =
+// RES_T / NMAX threads, each over NMAX / RT columns.
 // On 64 systems of 2 K to 65 K stages: n = 8 405 -> 144 us, n = 16 584 -> 471 us
 // (n = 32 keeps four waves); S = 256, N = 128, n = 16, one right-hand side 36 -> 31 us.
 // Eight stages per walk there: four right-hand sides 58 -> 48 us against sixteen.
@@ -242,8 +241,14 @@ __device__ __attribute__((always_inline)) inline void residual_body(const Residu
       // This thread's entries of the row, the same for every right-hand side: D, E_{k-1}
       // (or C^T at k = 0), E_k^T.  Blocks up to 16 keep them in registers (four right-hand
       // sides 54 -> 48 us, one as fast); at 32 the registers cost a wave per SIMD (5%).
-      auto ld = [&](int u) { const int c = p * CPT + u; return c <= o ? D[o * LD + c] : D[c * LD + o]; };
-      auto lp = [&](int u) { const int c = p * CPT + u; return has_prev ? Ep[o * LD + c] : Ep[c * LD + o]; };
+      auto ld = [&](int u) {
+        const int c = p * CPT + u;
+        return c <= o ? D[o * LD + c] : D[c * LD + o];
+      };
+      auto lp = [&](int u) {
+        const int c = p * CPT + u;
+        return has_prev ? Ep[o * LD + c] : Ep[c * LD + o];
+      };
       auto ln = [&](int u) { return has_next ? Ek[(p * CPT + u) * LD + o] : 0.0; };
       constexpr bool KEEP = NMAX <= 16;
       double md[KEEP ? CPT : 1], mp[KEEP ? CPT : 1], mn[KEEP ? CPT : 1];
@@ -362,7 +367,7 @@ __device__ inline double strided_max(const double* p, int cnt, int t0, int step,
 // One workgroup per system: the root rows of r, and the largest |r| of each right-hand
 // side (rnorm), from the tail workgroups' maxima and the root rows.  Thread (g, i) sums
 // element i of the products C_s x_{s,0} over the scenarios s = g mod G (G = 1024 / NMAX
-// groups), four right-hand sides at a time; the lanes of a wave are added by shuffles, the
+// groups), up to four right-hand sides at a time; the lanes of a wave are added by shuffles, the
 // waves in order from LDS.  Latency-bound (one workgroup per system).
 template <int NMAX>
 __device__ __attribute__((always_inline)) inline void residual_root_body(const ResidualArgs& a,
@@ -820,9 +825,11 @@ static void launch_residual_t(const ResidualArgs& a, dim3 grid, int chunks, hipS
     }
   }
   if (a.n == NMAX)
-    hipLaunchKernelGGL((residual_kernel<NMAX, true>), grid, dim3(res_threads<NMAX>()), lds, st, a, chunks);
+    hipLaunchKernelGGL((residual_kernel<NMAX, true>), grid, dim3(res_threads<NMAX>()), lds, st, a,
+                       chunks);
   else
-    hipLaunchKernelGGL((residual_kernel<NMAX, false>), grid, dim3(res_threads<NMAX>()), lds, st, a, chunks);
+    hipLaunchKernelGGL((residual_kernel<NMAX, false>), grid, dim3(res_threads<NMAX>()), lds, st, a,
+                       chunks);
 }
 
 void launch_residual(const ResidualArgs& a, int nmax, hipStream_t st) {

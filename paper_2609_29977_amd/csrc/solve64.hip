@@ -12,13 +12,13 @@
 //
 // Bound: the latency of a position's blocks at the upper levels, their bytes at the lower
 // ones.  As matrix products (solve_rhs.hip), one wave issues all loads of a position and
-// fifteen of sixteen columns are empty: n = 64, one right-hand side, products -> here, S = 4, N
-// = 16 in FP64 108 -> 82 us, S = 28, N = 70 221 -> 189, S = N = 128 727 -> 681; in FP32 79 -> 60,
-// 149 -> 123, 431 -> 377; four right-hand sides 110 -> 105, 226 -> 232, 787 -> 793 in FP64.  At
-// 33..48 the products take nine tiles of sixteen, not sixteen, and are faster but for chains of
-// one or two stages: n = 33, N = 2, one right-hand side in FP64 at S = 2 28.6 -> 25.2 us, S =
-// 200 31.3 -> 28.5, S = 2000 78 -> 80; n = 48 at S = 2 27.6 -> 27, S = 2000 84 -> 99; n = 47 in FP32 at
-// S = 600 41.8 -> 37.9.
+// fifteen of sixteen columns are empty: n = 64, one right-hand side, products -> here, S =
+// 4, N = 16 in FP64 108 -> 82 us, S = 28, N = 70 221 -> 189, S = N = 128 727 -> 681; in FP32
+// 79 -> 60, 149 -> 123, 431 -> 377; four right-hand sides 110 -> 105, 226 -> 232, 787 -> 793
+// in FP64.  At 33..48 the products take nine tiles of sixteen, not sixteen, and are faster
+// but for chains of one or two stages: n = 33, N = 2, one right-hand side in FP64 at S = 2
+// 28.6 -> 25.2 us, S = 200 31.3 -> 28.5, S = 2000 78 -> 80; n = 48 at S = 2 27.6 -> 27, S =
+// 2000 84 -> 99; n = 47 in FP32 at S = 600 41.8 -> 37.9.
 #include "bmpc_internal.h"
 #include "regblock.h"
 #include "solve_common.h"

@@ -3,20 +3,21 @@
 // next to them.  (Few right-hand sides: solve.hip, solve64.hip.)  Layouts: solve_mm.h.
 //
 // Against scalar products per right-hand side with the vectors in LDS, in chunks of eight
-// (four for n > 32), one solve: FP64 n = 32, S = N = 128, twelve right-hand sides 556 -> 272
+// (four for n > 32), one solve: FP64 n = 32, S = N = 128, twelve right-hand sides 554 -> 254
 // us (level 1 backward moves its blocks at 5.1 TB/s); FP32 n = 16, S = 100, N = 160, four
-// 115 -> 85 us; FP64 n = 48, S = N = 64, one 215 -> 160 us; FP32 n = 64, S = N = 64, sixteen
-// 678 -> 208 us.  Tried: tiles interleaved so that the transposed blocks come in 16-byte pieces (the
-// backward levels above: 132 -> 149 us, the triangle's zeros are no longer whole tiles); one
-// pull in flight and three waves per SIMD instead of two backward (132 -> 136 us).
+// 114 -> 72 us; FP64 n = 48, S = N = 64, one 213 -> 159 us; FP32 n = 64, S = N = 64, sixteen
+// 676 -> 199 us.  Tried: tiles interleaved so that the transposed blocks come in 16-byte
+// pieces (the backward levels above: 132 -> 149 us, the triangle's zeros are no longer whole
+// tiles); one pull in flight and three waves per SIMD instead of two backward (132 -> 136
+// us).
 //
 // The top levels have a few positions per chain and cost a launch's latency each (4.2 to 5
 // us).  They share one launch with the x_1 step: a workgroup of eight waves (four for n > 32,
 // where a wave takes more than half of a SIMD's registers) per chain, a barrier between
 // levels.  Forward the waves divide among the positions of a level, which therefore have
 // at most half as many, and share their pulls; backward every position (two pulls) has one
-// wave.  One solve at S = 28, N = 214: FP32 n = 16 with four right-hand sides 75 -> 63 us, FP64
-// n = 32 with eight 154 -> 145 us.
+// wave.  One solve at S = 28, N = 214: FP32 n = 16 with four right-hand sides 77 -> 61 us, FP64
+// n = 32 with twelve 158 -> 155 us.
 #include <type_traits>
 
 #include "bmpc_internal.h"
@@ -35,7 +36,9 @@ __device__ __attribute__((always_inline)) inline void mm_level_body(const SolveA
   extern __shared__ __align__(16) unsigned char mm_smem[];
   if (a.done && *a.done) return;
   const int s = bx / count, i = (int)(bx - (unsigned)s * count), wv = wave_id();
-  const int W = KIND == MM_BWD || a.fwd_waves == 1 ? 1 : mm_fwd_waves(a.m, a.n, sizeof(T) == 8, level);
+  const int W = KIND == MM_BWD || a.fwd_waves == 1
+                    ? 1
+                    : mm_fwd_waves(a.m, a.n, sizeof(T) == 8, level);
   mm_position_body<T, NT, KIND, VEC, TOGETHER>(
       a, level, s, (2 * i + 1) << (level - 1), W, wv,
       reinterpret_cast<typename Mfma<T>::acc_t*>(mm_smem), wv < W);
@@ -96,7 +99,8 @@ template <typename T, int NT, int KIND, bool VEC>
 __global__ void __launch_bounds__(KIND == MM_BWD ? 64 : 64 * mm_top_waves(16 * NT))
     mm_level_multi(const MultiItem<SolveArgs>* items, int nitems, Reloc r) {
   const MultiItem<SolveArgs>& it = items[multi_find(items, nitems, blockIdx.x)];
-  mm_level_body<T, NT, KIND, VEC, KIND == MM_FWD>(relocate_solve(it.a, r), it.p0, it.p1, multi_local(it).x);
+  mm_level_body<T, NT, KIND, VEC, KIND == MM_FWD>(relocate_solve(it.a, r), it.p0, it.p1,
+                                                  multi_local(it).x);
 }
 template <typename T, int NT, bool FWD, bool VEC>
 __global__ void __launch_bounds__(64 * mm_top_waves(16 * NT))

@@ -3,7 +3,7 @@
 // For one shape (S, N, n, nrhs), a batch count and a precision it builds a plan for every candidate
 // configuration -- levels per factor pass (window depth), the backward sweep's top
 // levels in one launch with one workgroup per chain or one launch per level with one
-// wave per position, the forward sweep's positions on up to four waves or on one --
+// wave per position, the forward sweep's positions on several waves or on one --
 // and times the plan's own step (FP64: factor + solve; FP32: factor + one refinement
 // correction) on synthetic data in HBM with HIP events, the median of a few runs.  One
 // system of a small shape leaves most of the GPU idle and is timed for its latency; a

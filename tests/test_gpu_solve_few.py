@@ -35,8 +35,9 @@ def _check(S, N, n, nrhs, precision, flags=0):
     p.close()
 
 
-SIZES = [(1, 1), (1, 3), (1, 6), (2, 17), (5, 2), (8, 1), (8, 2), (8, 3), (9, 2), (12, 1), (15, 2), (16, 1), (16, 2),
-         (17, 1), (17, 2), (24, 2), (31, 1), (31, 2), (32, 1), (32, 2), (32, 3), (13, 17), (32, 18)]
+SIZES = [(1, 1), (1, 3), (1, 6), (2, 17), (5, 2), (8, 1), (8, 2), (8, 3), (9, 2), (12, 1), (15, 2),
+         (16, 1), (16, 2), (17, 1), (17, 2), (24, 2), (31, 1), (31, 2), (32, 1), (32, 2), (32, 3),
+         (13, 17), (32, 18)]
 
 
 @pytest.mark.parametrize("precision", ["fp64", "fp32"])
@@ -53,8 +54,8 @@ def test_blocks_up_to_32(n, nrhs, precision):
 # kernels take two or three right-hand sides (32, 256)
 @pytest.mark.parametrize("precision", ["fp64", "fp32"])
 @pytest.mark.parametrize("S", [32, 33, 127, 129, 255, 257, 511, 514])
-@pytest.mark.parametrize("n,nrhs", [(8, 2), (8, 3), (16, 1), (12, 5), (12, 3), (21, 2), (19, 3), (32, 3),
-                                    (32, 6)])
+@pytest.mark.parametrize("n,nrhs", [(8, 2), (8, 3), (16, 1), (12, 5), (12, 3), (21, 2), (19, 3),
+                                    (32, 3), (32, 6)])
 def test_chain_counts(n, nrhs, S, precision):
     for N in (12, 6):
         _check(S, N, n, nrhs, precision)
@@ -68,8 +69,8 @@ def test_more_scenarios_than_a_grid_dimension(n, nrhs, precision):
 
 # the sums do not depend on which levels share a launch
 @pytest.mark.parametrize("precision", ["fp64", "fp32"])
-@pytest.mark.parametrize("n,nrhs", [(8, 2), (8, 3), (13, 1), (13, 2), (16, 4), (20, 1), (24, 2), (31, 6),
-                                    (32, 3), (32, 9), (40, 1), (48, 16), (64, 2), (64, 7)])
+@pytest.mark.parametrize("n,nrhs", [(8, 2), (8, 3), (13, 1), (13, 2), (16, 4), (20, 1), (24, 2),
+                                    (31, 6), (32, 3), (32, 9), (40, 1), (48, 16), (64, 2), (64, 7)])
 def test_merged_top_levels_are_bitwise_the_level_launches(n, nrhs, precision):
     from paper_2609_29977_amd import bmpc
     S, N = 3, 45
@@ -92,9 +93,9 @@ def test_ragged_beyond_the_merged_launches_is_bitwise_its_plans(nrhs, precision)
     import torch
 
     from paper_2609_29977_amd import bmpc
-    shapes = [(40, N, n) for N, n in ((9, 8), (20, 8), (33, 5), (12, 12), (40, 16), (7, 15), (21, 20),
-                                      (16, 32), (35, 24), (10, 31), (3, 9), (5, 16), (1, 8), (2, 32),
-                                      (18, 27), (24, 11))]
+    shapes = [(40, N, n) for N, n in ((9, 8), (20, 8), (33, 5), (12, 12), (40, 16), (7, 15),
+                                      (21, 20), (16, 32), (35, 24), (10, 31), (3, 9), (5, 16),
+                                      (1, 8), (2, 32), (18, 27), (24, 11))]
     systems = [make_system(S, N, n, nrhs, 1e-2, 170 + i) for i, (S, N, n) in enumerate(shapes)]
     rp = bmpc.RaggedPlan([(S, N, n, nrhs) for S, N, n in shapes], precision)
     parts = lambda name: [_dev(getattr(s, name)) for s in systems]
@@ -111,8 +112,8 @@ def test_ragged_beyond_the_merged_launches_is_bitwise_its_plans(nrhs, precision)
 
 # a batch beyond them and beyond a grid dimension
 @pytest.mark.parametrize("precision", ["fp64", "fp32"])
-@pytest.mark.parametrize("B,S,N,n,nrhs", [(20, 40, 21, 16, 2), (20, 40, 21, 24, 1), (6, 60, 10, 48, 1),
-                                          (66000, 1, 3, 4, 2)])
+@pytest.mark.parametrize("B,S,N,n,nrhs", [(20, 40, 21, 16, 2), (20, 40, 21, 24, 1),
+                                          (6, 60, 10, 48, 1), (66000, 1, 3, 4, 2)])
 def test_batch_is_bitwise_its_plans(B, S, N, n, nrhs, precision):
     import torch
 
