@@ -30,6 +30,14 @@ namespace {
 
 // TOGETHER: a workgroup of a ragged launch, with as many waves as the launch's largest item
 // asks for.
+// Waves per SIMD that the registers of a level kernel leave room for.  FP64 at n <= 16 and the
+// forward levels at n 33..48 come out just above such a limit when the compiler is left to
+// itself: one wave instead of two costs the solve of 300 chains of 100 at n = 40 with four
+// right-hand sides 19 %, four instead of five that of n = 8 2 %.  No bound makes a kernel spill.
+constexpr int mm_level_waves_per_simd(bool fp64, int nt, bool bwd) {
+  return !fp64 ? 1 : nt == 1 ? (bwd ? 6 : 5) : nt == 3 && !bwd ? 2 : 1;
+}
+
 template <typename T, int NT, int KIND, bool VEC, bool TOGETHER>
 __device__ __attribute__((always_inline)) inline void mm_level_body(const SolveArgs& a, int level,
                                                                     int count, unsigned bx) {
@@ -80,7 +88,8 @@ __device__ __attribute__((always_inline)) inline void mm_bwd_top_body(const Solv
 }
 
 template <typename T, int NT, int KIND, bool VEC>
-__global__ void __launch_bounds__(KIND == MM_BWD ? 64 : 64 * mm_top_waves(16 * NT))
+__global__ void __launch_bounds__(KIND == MM_BWD ? 64 : 64 * mm_top_waves(16 * NT),
+                                  mm_level_waves_per_simd(sizeof(T) == 8, NT, KIND == MM_BWD))
     mm_level_kernel(SolveArgs a, int level, int count) {
   mm_level_body<T, NT, KIND, VEC, false>(a, level, count, blockIdx.x);
 }
@@ -96,7 +105,8 @@ __global__ void __launch_bounds__(64 * mm_top_waves(16 * NT))
 // one launch over the systems of a ragged batch (see multi.h); items carry (level, count) or
 // level_lo in p0, p1
 template <typename T, int NT, int KIND, bool VEC>
-__global__ void __launch_bounds__(KIND == MM_BWD ? 64 : 64 * mm_top_waves(16 * NT))
+__global__ void __launch_bounds__(KIND == MM_BWD ? 64 : 64 * mm_top_waves(16 * NT),
+                                  mm_level_waves_per_simd(sizeof(T) == 8, NT, KIND == MM_BWD))
     mm_level_multi(const MultiItem<SolveArgs>* items, int nitems, Reloc r) {
   const MultiItem<SolveArgs>& it = items[multi_find(items, nitems, blockIdx.x)];
   mm_level_body<T, NT, KIND, VEC, KIND == MM_FWD>(relocate_solve(it.a, r), it.p0, it.p1,
