@@ -676,7 +676,8 @@ __device__ __attribute__((always_inline)) inline void solve_root_body(const Solv
     // with few scenarios (a round or some of loads) all right-hand sides at once, the last one
     // read again for those that are not there; beyond, as many as there are, a power of two,
     // with at least sixteen loads in flight per thread: S = 20000, n = 8 in FP64, two
-    // right-hand sides, one solve 584 -> 441 us, five 858 -> 671
+    // right-hand sides, one solve 584 -> 441 us, five 858 -> 671; one right-hand side with a
+    // round or some needs four (one solve at S = 40, N = 30, n = 8 3 % longer with sixteen)
     const int left = nrhs - q0;
     if (QB >= 8 && left >= (S <= 4 * (1024 / NMAX) ? 5 : 8))
       taken = partials(std::integral_constant<int, QB < 8 ? QB : 8>{},
@@ -687,6 +688,8 @@ __device__ __attribute__((always_inline)) inline void solve_root_body(const Solv
     else if (left >= 2)
       taken = partials(std::integral_constant<int, 2>{},
                        std::integral_constant<int, QB < 8 ? 4 : 8>{});
+    else if (S <= 4 * (1024 / NMAX))
+      taken = partials(std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{});
     else
       taken = partials(std::integral_constant<int, 1>{}, std::integral_constant<int, 16>{});
     __syncthreads();
