@@ -473,7 +473,7 @@ void enqueue_solve_back(bmpc_plan p, const SolveArgs& a) {
   hipStream_t st = p->stream;
   // x_1 and the top levels (few positions per chain) in one launch, the others one by one; one
   // right-hand side merges the top levels also where there are too many chains for that
-  const bool few = few_rhs(a.S, a.N, a.n, a.nrhs, sizeof(T) == 8);
+  const bool few = few_bwd(a.S, a.N, a.n, a.nrhs, sizeof(T) == 8);
   const int64_t chains = (int64_t)p->B * p->d.S;
   const int L = chain_levels(p->m), top = solve_bwd_top(p->m, a.n, a.nrhs, p->opt_flags, chains);
   const bool together = tops_together(a.n, chains);

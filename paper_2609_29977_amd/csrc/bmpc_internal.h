@@ -337,7 +337,8 @@ __host__ __device__ inline int mm_fwd_waves(int m, int n, bool fp64, int level) 
 // solve, products / registers, us:
 //   two right-hand sides in FP64 at S = 60, N = 250 n = 8 82 / 59, n = 32 212 / 178, at S =
 //   1500, N = 16 85 / 63 and 248 / 214; in FP32 at S = 20, N = 30 n = 12 31 / 34, n = 16 31 / 29, n
-//   = 24 46 / 47.5, at S = 60, N = 250 n = 24 121 / 116;
+//   = 24 46 / 47.5, at S = 100, N = 20 44 / 46.5, at S = 60, N = 250 121 / 116, at S = 512, N = 32
+//   107 / 92, n = 28 at S = 128, N = 200 154 / 159, at S = 512, N = 32 112 / 103;
 //   three at S = 4, N = 16 n = 8 23.5 / 23 in FP64 and 22.5 / 23.5 in FP32, n = 16 25.5 / 27.5 in
 //   FP64, at S = 400, N = 20 n = 16 50 / 55.5, at S = 1500, N = 16 n = 12 in FP64 97 / 92, n = 20
 //   195 / 150 and in FP32 134 / 122, n = 12 84 / 83, n = 32 in FP64 265 / 242;
@@ -349,8 +350,15 @@ constexpr bool few_rhs(int S, int N, int n, int nrhs, bool fp64) {
   if (n > 32 || nrhs > kFewRhs) return false;
   if (nrhs == 1 || (nrhs == 2 && (n <= 8 || n == 16 || n == 32))) return true;
   if (one_launch) return false;
-  if (nrhs == 2) return fp64 || (n > 16 && (n % 4 != 0 || S > 32));
+  if (nrhs == 2)
+    return fp64 || (n > 16 && (n % 4 != 0 || S > 256 || (n <= 24 && S > 32 && N > 32)));
   return n == 32 || (fp64 && n <= 8) || (n > 16 ? S > 256 : fp64 && S > 512);
+}
+// Backward, two right-hand sides of full 16 x 16 blocks in FP64 stay with the products, which
+// need no padding there: both sweeps / the forward one in registers, one solve at S = 60, N = 100
+// 55 / 53 us, at S = 256, N = 128 102 / 96, factor_solve at S = 4, N = 16 44.5 / 43.
+constexpr bool few_bwd(int S, int N, int n, int nrhs, bool fp64) {
+  return few_rhs(S, N, n, nrhs, fp64) && !(fp64 && nrhs == 2 && n == 16);
 }
 // The merged forward launch of these kernels, of sixteen waves, exists where a wave does with
 // the 128 registers that it then has.

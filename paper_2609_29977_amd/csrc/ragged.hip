@@ -131,7 +131,7 @@ void build_back(RaggedState& R, Seq& seq, const std::vector<SolveArgs>& args) {
   std::vector<int> topl(B);
   for (int i = 0; i < B; ++i) {
     bmpc_plan s = R.subs[i];
-    const bool few = few_rhs(s->d.S, s->d.N, s->d.n, args[i].nrhs, s->fp64);
+    const bool few = few_bwd(s->d.S, s->d.N, s->d.n, args[i].nrhs, s->fp64);
     const bool together = tops_together(s->d.n, R.chains);
     const int L = chain_levels(s->m);
     topl[i] = solve_bwd_top(s->m, s->d.n, args[i].nrhs, s->opt_flags, R.chains);

@@ -900,7 +900,8 @@ void by_size(int n, int nrhs, F&& f) {
 // Forward positions of level l pull 2 (l - 1) blocks, kPullsPerWave per wave, on up to
 // kLevelMaxWaves waves (or a.fwd_waves: one wave per position when the plan asks for it).
 LevelCfg solve_level_config(const SolveArgs& a, int level, bool fwd, int nmax, bool fp64) {
-  if (!few_rhs(a.S, a.N, a.n, a.nrhs, fp64)) return mm_level_config(a, level, fwd, fp64);
+  if (!(fwd ? few_rhs : few_bwd)(a.S, a.N, a.n, a.nrhs, fp64))
+    return mm_level_config(a, level, fwd, fp64);
   LevelCfg c{};
   c.count = level_count(a.m, level);
   const int waves = fwd && a.fwd_waves != 1 ? fwd_one_waves(level) : 1;
@@ -926,7 +927,7 @@ MmTopCfg x_fwd_config(const SolveArgs& a, int nmax, bool fp64) {
 
 template <typename T>
 static void launch_level(const SolveArgs& a, int level, bool fwd, hipStream_t st) {
-  if (!few_rhs(a.S, a.N, a.n, a.nrhs, sizeof(T) == 8))
+  if (!(fwd ? few_rhs : few_bwd)(a.S, a.N, a.n, a.nrhs, sizeof(T) == 8))
     return launch_mm_level<T>(a, level, fwd, st);
   by_size(a.n, a.nrhs, [&](auto nmax, auto full, auto nr) {
     level_t<T, decltype(nmax)::value, decltype(full)::value, decltype(nr)::value>(a, level, fwd,

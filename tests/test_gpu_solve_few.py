@@ -55,9 +55,9 @@ def test_blocks_up_to_32(n, nrhs, precision):
 @pytest.mark.parametrize("precision", ["fp64", "fp32"])
 @pytest.mark.parametrize("S", [32, 33, 127, 129, 255, 257, 511, 514])
 @pytest.mark.parametrize("n,nrhs", [(8, 2), (8, 3), (16, 1), (12, 5), (12, 3), (21, 2), (19, 3),
-                                    (32, 3), (32, 6)])
+                                    (24, 2), (28, 2), (32, 3), (32, 6)])
 def test_chain_counts(n, nrhs, S, precision):
-    for N in (12, 6):
+    for N in (12, 6, 36):
         _check(S, N, n, nrhs, precision)
 
 
@@ -69,8 +69,9 @@ def test_more_scenarios_than_a_grid_dimension(n, nrhs, precision):
 
 # the sums do not depend on which levels share a launch
 @pytest.mark.parametrize("precision", ["fp64", "fp32"])
-@pytest.mark.parametrize("n,nrhs", [(8, 2), (8, 3), (13, 1), (13, 2), (16, 4), (20, 1), (24, 2),
-                                    (31, 6), (32, 3), (32, 9), (40, 1), (48, 16), (64, 2), (64, 7)])
+@pytest.mark.parametrize("n,nrhs", [(8, 2), (8, 3), (13, 1), (13, 2), (16, 2), (16, 4), (20, 1),
+                                    (24, 2), (31, 6), (32, 3), (32, 9), (40, 1), (48, 16),
+                                    (64, 2), (64, 7)])
 def test_merged_top_levels_are_bitwise_the_level_launches(n, nrhs, precision):
     from paper_2609_29977_amd import bmpc
     S, N = 3, 45
